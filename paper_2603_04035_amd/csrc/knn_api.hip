@@ -58,7 +58,8 @@ unsigned long long* pinned_counters()
 {
     // one small pinned block per host thread, held until the process ends
     static thread_local unsigned long long* p = nullptr;
-    if (!p && hipHostMalloc((void**)&p, 64, hipHostMallocDefault) != hipSuccess) p = nullptr;
+    const size_t bytes = (size_t)kCounterBanks * kCounterWords * sizeof(unsigned long long);
+    if (!p && hipHostMalloc((void**)&p, bytes, hipHostMallocDefault) != hipSuccess) p = nullptr;
     return p;
 }
 

@@ -6,7 +6,7 @@
 //
 // State: per point a list of K_b (index, squared distance, new-flag)
 // entries sorted by (distance, index).  One iteration is two kernels with
-// no host round trip except a 64-byte counter read:
+// no host round trip except an 8 KiB counter read:
 //
 //  join     one wave per point v: the new list new_f(v) + reverse-new and the
 //           old list old_f(v) + reverse-old are deduplicated (at most 64
@@ -811,11 +811,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void nn
         coll += shfl_u64(coll, lane ^ o);
     }
     if (lane == 0) {
-        atomicAdd(&counters[1], emitted);
-        atomicAdd(&counters[2], tally[0]);
-        atomicAdd(&counters[3], coll);
-        atomicAdd(&counters[4], tally[2]);
-        atomicAdd(&counters[5], tally[1]);
+        unsigned long long* bank = counters + (blockIdx.x % kCounterBanks) * kCounterWords;
+        if (emitted) atomicAdd(&bank[1], emitted);
+        if (tally[0]) atomicAdd(&bank[2], tally[0]);
+        if (coll) atomicAdd(&bank[3], coll);
+        if (tally[2]) atomicAdd(&bank[4], tally[2]);
+        if (tally[1]) atomicAdd(&bank[5], tally[1]);
     }
 }
 
@@ -983,7 +984,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void n
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
     }
-    if (lane == 0 && upd) atomicAdd(&counters[0], upd);
+    if (lane == 0 && upd) atomicAdd(&counters[(blockIdx.x % kCounterBanks) * kCounterWords], upd);
 }
 
 // --------------------------------------------------------------- finalize
@@ -1169,7 +1170,8 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         sampold = revold;
     }
     if ((r = ws.alloc(&cand, (size_t)n * cfg.C)) != KNN_OK) return r;
-    if ((r = ws.alloc(&counters, 8)) != KNN_OK) return r;
+    const size_t cnt_bytes = (size_t)kCounterBanks * kCounterWords * 8;
+    if ((r = ws.alloc(&counters, (size_t)kCounterBanks * kCounterWords)) != KNN_OK) return r;
     KNN_HIP(hipMemsetAsync(revnew, 0xFF, (size_t)n * T * 4, st));
     KNN_HIP(hipMemsetAsync(revold, 0xFF, (size_t)n * T * 4, st));
 
@@ -1240,7 +1242,7 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     Timer tj, tm, ts;
     for (int it = 0; it < p->max_iters; ++it) {
         const int iter = iter_offset + it;
-        KNN_HIP(hipMemsetAsync(counters, 0, 64, st));
+        KNN_HIP(hipMemsetAsync(counters, 0, cnt_bytes, st));
         // iteration `iter` was sampled by the init kernel or the previous merge
         (void)hipEventRecord(ts.a, st);
         if (!cfg.reset)
@@ -1273,8 +1275,11 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
                                                                         counters, worst, wstride, sa);
         KNN_HIP(hipGetLastError());
         (void)hipEventRecord(tm.b, st);
-        KNN_HIP(hipMemcpyAsync(host_cnt, counters, 64, hipMemcpyDeviceToHost, st));
+        KNN_HIP(hipMemcpyAsync(host_cnt, counters, cnt_bytes, hipMemcpyDeviceToHost, st));
         KNN_HIP(hipStreamSynchronize(st));
+        unsigned long long cnt[6] = {};   // the banks' sums
+        for (int b = 0; b < kCounterBanks; ++b)
+            for (int i = 0; i < 6; ++i) cnt[i] += host_cnt[b * kCounterWords + i];
         float ms = 0;
         (void)hipEventElapsedTime(&ms, tj.a, tj.b);
         ms_join += ms;
@@ -1283,16 +1288,16 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         ms_merge += ms;
         (void)hipEventElapsedTime(&ms, ts.a, ts.b);
         ms_sample += ms;
-        gathered += host_cnt[2];
-        pairs_joined += host_cnt[5];
+        gathered += cnt[2];
+        pairs_joined += cnt[5];
         if (stats && it < KNN_MAX_ITERS_LOGGED) {
-            stats->updates[it] = (int64_t)host_cnt[0];
-            stats->emitted[it] = (int64_t)host_cnt[1];
-            stats->slot_collisions[it] = (int64_t)host_cnt[3];
-            stats->list_dropped[it] = (int64_t)host_cnt[4];
+            stats->updates[it] = (int64_t)cnt[0];
+            stats->emitted[it] = (int64_t)cnt[1];
+            stats->slot_collisions[it] = (int64_t)cnt[3];
+            stats->list_dropped[it] = (int64_t)cnt[4];
         }
         ++iters;
-        if ((double)host_cnt[0] < stop) {
+        if ((double)cnt[0] < stop) {
             // the flags are seen only through the returned state
             if (smp && state_flags) {
                 nnd_unsample_kernel<<<(unsigned)ceil_div(n, 8), 256, 0, st>>>(n, K, s, gidx, gflag, newf);
