@@ -943,33 +943,81 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
 
 // --------------------------------------------------------------- fallback
 
-// Exhaustive direct-difference k-NN for the rows listed in fb_rows (one
-// workgroup of 4 waves per row; each wave scans a quarter of the references
-// 64 at a time and merges them into its list; the 4 lists are merged last).
+// Exhaustive direct-difference k-NN for the rows listed in fb_rows.  The
+// work is one canonical distance per (listed row, reference): reading the
+// references bounds it, so how many workgroups share a row decides the time.
+// The count is known only here: with cnt rows, each row's references are cut
+// into P parts so that cnt * P workgroups run (P = 1 when the rows alone fill
+// the grid); a part is at least the 256 references of one batch.  With P > 1
+// every part's 32 best keys go to `lists` (room for `slots` lists; the split
+// lists, already merged, are reused) and the workgroup that finishes last
+// (counted in *done, zeroed beforehand) merges each row's parts.  One
+// workgroup per row, whatever their count, had left one uncertified row of
+// the 70,000 x 784 pixel set to a single workgroup: 64 ms of a 179 ms quality
+// call, which now takes 116 ms, as without such a row.
+// A wave takes 64 references per batch, four per 16-lane group in flight.
 template <int DT>
 __global__ __launch_bounds__(256) void exact_fallback_kernel(
     const int32_t* __restrict__ fb_rows, const int* __restrict__ fb_count,
     const void* __restrict__ Q, int64_t ldq, const void* __restrict__ R, int64_t ldr, int64_t nr,
     int d, const int32_t* __restrict__ q_self, int self_mode, int64_t self_base, int k, int out_kind,
-    int32_t* __restrict__ out_idx, float* __restrict__ out_dist)
+    int32_t* __restrict__ out_idx, float* __restrict__ out_dist, uint64_t* lists, int64_t slots,
+    unsigned* __restrict__ done)
 {
     __shared__ uint64_t sl[4][64];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ unsigned order_;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane & 15;
     const int cnt = *fb_count;
-    for (int f = blockIdx.x; f < cnt; f += gridDim.x) {
-        const int64_t row = fb_rows[f];
+    if (cnt == 0) return;
+    int64_t P = (slots < (int64_t)gridDim.x ? slots : (int64_t)gridDim.x) / cnt;
+    const int64_t batches = ceil_div(nr, 256);
+    P = P > batches ? batches : (P < 1 ? 1 : P);
+    const int64_t jobs = (int64_t)cnt * P, per = ceil_div(batches, P) * 256;
+    auto write_row = [&](int64_t row, uint64_t key) {
+        if (lane < k) {
+            const float d2 = key_d2(key);
+            out_idx[row * k + lane] = (int32_t)key_idx(key);
+            out_dist[row * k + lane] = out_kind == KNN_OUT_L2 ? sqrtf(d2) : d2;
+        }
+    };
+    for (int64_t job = blockIdx.x; job < jobs; job += gridDim.x) {
+        const int64_t row = fb_rows[job / P], c = job % P;
         const int64_t self = self_mode == 1 ? self_base + row : (self_mode == 2 ? (int64_t)q_self[row] : -1);
+        const int64_t rbeg = c * per, rend = rbeg + per < nr ? rbeg + per : nr;
         uint64_t list = kEmptyList;
-        for (int64_t base = (int64_t)wv * 64; base < nr; base += 256) {
+        for (int64_t base = rbeg + wv * 64; base < rend; base += 256) {
             uint64_t cand = kEmptyCand;
-            for (int p = 0; p < 16; ++p) {
-                const int64_t j = base + p * 4 + (lane >> 4);
-                const bool act = j < nr && j != self;
-                const float v = dist_g16<DT>(Q, row * ldq, R, j * ldr, d, act);
-                const float got = shfl_f32(v, ((lane - p * 4) & 3) * 16);
-                const int64_t jj = base + lane;
-                if (lane >= p * 4 && lane < p * 4 + 4 && jj < nr && jj != self)
-                    cand = make_key(got, (uint32_t)jj);
+            for (int p0 = 0; p0 < 16; p0 += 4) {
+                // pass p0 + u: references base + 4 (p0 + u) + group; their
+                // loads of a coordinate step are issued together, each sum
+                // in the order dist_g16 forms it
+                float s[4];
+                int64_t off[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t j = base + (p0 + u) * 4 + (lane >> 4);
+                    off[u] = (j < rend ? j : rend - 1) * ldr;
+                    s[u] = 0.0f;
+                }
+                for (int t = g; t < d; t += 16) {
+                    const float xq = elem<DT>::ld(Q, row * ldq + t);
+                    float xr[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) xr[u] = elem<DT>::ld(R, off[u] + t);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float e = xq - xr[u];
+                        s[u] = fmaf(e, e, s[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int p = p0 + u;
+                    const float got = shfl_f32(wave_sum16(s[u]), ((lane - p * 4) & 3) * 16);
+                    const int64_t jj = base + lane;
+                    if (lane >= p * 4 && lane < p * 4 + 4 && jj < rend && jj != self)
+                        cand = make_key(got, (uint32_t)jj);
+                }
             }
             cand = seg_sort<64>(cand);
             list = seg_merge_sorted<64>(list, cand);
@@ -979,13 +1027,27 @@ __global__ __launch_bounds__(256) void exact_fallback_kernel(
         if (wv == 0) {
             uint64_t a = sl[0][lane];
             for (int o = 1; o < 4; ++o) a = seg_merge_sorted<64>(a, sl[o][lane]);
-            if (lane < k) {
-                const float d2 = key_d2(a);
-                out_idx[row * k + lane] = (int32_t)key_idx(a);
-                out_dist[row * k + lane] = out_kind == KNN_OUT_L2 ? sqrtf(d2) : d2;
-            }
+            if (P == 1) write_row(row, a);
+            else if (lane < kListW) lists[job * kListW + lane] = a;
         }
         __syncthreads();
+    }
+    if (P == 1 || (int64_t)blockIdx.x >= jobs) return;
+    // P > 1: one job per workgroup; the last one merges (k <= kListW)
+    if (threadIdx.x < 64) __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) order_ = atomicAdd(done, 1u);
+    __syncthreads();
+    if ((int64_t)order_ != jobs - 1) return;
+    __threadfence();
+    for (int64_t f = wv; f < cnt; f += 4) {
+        // even parts in lanes 0..31, odd ones in lanes 32..63
+        const int h = lane >> 5;
+        uint64_t a = kEmptyList;
+        for (int64_t c = 0; c < P; c += 2)
+            a = seg_merge_sorted<32>(a, c + h < P ? lists[(f * P + c + h) * kListW + (lane & 31)] : kEmptyCand);
+        const uint64_t rv = shfl_xor_u64(a, 31);
+        write_row(fb_rows[f], seg_bitonic_merge<64>(h ? rv : a));
     }
 }
 
@@ -1199,7 +1261,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     }
 
     knn_status r;
-    unsigned* small = nullptr;   // [0] = max ref norm bits, [1] = fallback count
+    unsigned* small = nullptr;   // [0] = max ref norm bits, [1] = fallback count, [2] = fallback parts done
     r = ws.alloc(&small, 4);
     if (r != KNN_OK) return r;
     zero_words_kernel<<<1, 64, 0, st>>>(small, 4);
@@ -1247,7 +1309,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
             qn = qnb;
         }
         const int32_t* qself = self_mode == 2 ? q_self + q0 : nullptr;
-        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(small + 1, 1);
+        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(small + 1, 2);
         dim3 tgrid((unsigned)ceil_div(nq, kTileRows), (unsigned)S);
 #define KNN_TILE(BFV, AR)                                                                        \
     exact_tile_kernel<BFV, AR><<<tgrid, 256, 0, st>>>(Qs, qn, nq, Rs, rn, R.n, ldp, qself,       \
@@ -1283,7 +1345,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
 #define KNN_FB(DT)                                                                              \
     exact_fallback_kernel<DT><<<fgrid, 256, 0, st>>>(fb_rows, fb_count, Qd, Q.ld, R.data, R.ld, \
                                                      R.n, R.d, qself, self_mode, q0, k,         \
-                                                     out_kind, oi, od)
+                                                     out_kind, oi, od, part, nq * S, small + 2)
             if (Q.dtype == KNN_F32) KNN_FB(KNN_F32);
             else if (Q.dtype == KNN_BF16) KNN_FB(KNN_BF16);
             else KNN_FB(KNN_F16);
@@ -1501,15 +1563,16 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
         int32_t* fb_rows = nullptr;
         int* fb_count = nullptr;
         if ((r = ws.alloc(&fb_rows, (size_t)n)) != KNN_OK) return r;
-        if ((r = ws.alloc(&fb_count, 1)) != KNN_OK) return r;
-        zero_words_kernel<<<1, 64, 0, st>>>((unsigned*)fb_count, 1);
+        if ((r = ws.alloc(&fb_count, 2)) != KNN_OK) return r;   // [1]: fallback parts done
+        zero_words_kernel<<<1, 64, 0, st>>>((unsigned*)fb_count, 2);
         const float err_coef = (float)(X.d + 3) * u * 1.01f, edir = (float)(X.d / 16 + 8) * u;
         const dim3 mgrid((unsigned)ceil_div(n, 4));
 #define KNN_QMR(DT)                                                                                            \
     merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, S, n, kp, k, X.data, X.ld, X.data, X.ld, X.d, xn, small, \
                                                    err_coef, edir, 1, KNN_OUT_SQL2, Hn, Hd, fb_rows, fb_count);    \
     exact_fallback_kernel<DT><<<1024, 256, 0, st>>>(fb_rows, fb_count, X.data, X.ld, X.data, X.ld, n, X.d, nullptr,  \
-                                                    1, 0, k, KNN_OUT_SQL2, Hn, Hd)
+                                                    1, 0, k, KNN_OUT_SQL2, Hn, Hd, part, n * S,                    \
+                                                    (unsigned*)fb_count + 1)
         if (X.dtype == KNN_F32) {
             KNN_QMR(KNN_F32);
         } else if (X.dtype == KNN_BF16) {

@@ -25,3 +25,49 @@ def test_update_count_over_counter_banks(n, precision):
     new = ~(states[1][:, :, None] == states[0][:, None, :]).any(2) & (states[1] >= 0)
     assert st["iters"] == 1 and st["updates"][0] == int(new.sum())
     assert st["emitted"][0] >= st["updates"][0] and st["pairs_joined"] > 0
+
+
+def _with_shells(n, d, shells, seed):
+    """A mixture plus `shells` groups of 2d + 1 integer points: a centre and
+    its 2d axis neighbours at distance 1.  Every row of a group has more than
+    2k equidistant nearest rows, so none is certified by the GEMM lists."""
+    X = datagen.gmm_isotropic(n=n, d=d, seed=seed)
+    E = np.concatenate([np.zeros((1, d)), np.eye(d), -np.eye(d)]).astype(np.float32)
+    C = np.zeros((shells, d), np.float32)
+    C[:, 0] = 40.0
+    C[:, 1] = 8.0 * np.arange(shells)
+    return np.ascontiguousarray(np.concatenate([X, (C[:, None, :] + E[None]).reshape(-1, d)]))
+
+
+@pytest.mark.parametrize("shells", [1, 13, 30])
+def test_fallback_rows_shared_by_workgroups(orc, shells):
+    """Uncertified rows searched exhaustively: 41 rows (24 workgroups each),
+    533 (one each) and 1,230 (more rows than workgroups)."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    n, d, k = 20_003, 20, 6
+    X = _with_shells(n, d, shells, 4)
+    idx, dist = knn.knn_exact(torch.from_numpy(X).cuda(), k)
+    rows = np.concatenate([np.arange(0, n, 997), np.arange(n, len(X))])
+    O, _ = orc.exact_knn(X, k, rows=rows)
+    res = exact_parity(X, rows, idx.cpu().numpy()[rows], dist.cpu().numpy()[rows], O)
+    assert parity_ok(res), res
+    # integer distances: the order among equals is the index order
+    assert np.array_equal(idx.cpu().numpy()[n], np.sort(idx.cpu().numpy()[n]))
+
+
+@pytest.mark.parametrize("nq", [1, 2, 300])
+def test_fallback_one_row_many_parts(orc, nq):
+    """One uncertified query: as many workgroups as the lists' room allows (4
+    and 8 parts) or as the references have batches (79 parts, the last of 3
+    rows)."""
+    import paper_2603_04035_amd as knn
+    d, k = 20, 6
+    X = _with_shells(20_000 - 41 + 227, d, 1, 5)     # 20,227 = 79 * 256 + 3 rows
+    Q = np.ascontiguousarray(np.concatenate([X[-41:-40], X[:nq - 1]]))
+    self_rows = np.concatenate([[len(X) - 41], np.arange(nq - 1)]).astype(np.int32)
+    idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda(), k,
+                                    q_self=torch.from_numpy(self_rows))
+    O, O2 = orc.exact_query(X, Q, k, q_self=self_rows.astype(np.int64))
+    assert np.array_equal(idx.cpu().numpy()[0], O[0])
+    assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5, atol=1e-6)
