@@ -2,17 +2,16 @@
 // with a triplet loss on k-NN graphs the library builds, and sorted
 // projections of its embedding that give every point initial candidates.
 //
-// Training kernels (all FP32, deterministic):
-//   triplets   anchor / positive (one of the anchor's k neighbours) / negative
-//              drawn from the counter-based hash;
-//   forward    one thread per batch row: h = relu(b1 + x W1), z = b2 + h W2;
-//   loss       one thread per triplet: max(0, m + |za-zp|^2 - |za-zn|^2) and
-//              dL/dz for the three rows; the loss is summed by a fixed tree;
-//   backward   dh = (dz W2^T) masked by h > 0; every weight gradient is a sum
-//              over batch rows, taken in two stages (per-chunk partial sums
-//              in row order, then a sum over chunks in order), never with
-//              floating-point atomics, so results are bitwise reproducible;
-//   adam       elementwise update with bias correction.
+// Training kernels (FP32 sums, deterministic), three per step:
+//   batch      triplets (anchor / one of the anchor's k neighbours / negative)
+//              drawn from the counter-based hash; h = relu(b1 + x W1),
+//              z = b2 + h W2; max(0, m + |za-zp|^2 - |za-zn|^2) and dL/dz;
+//              dh = (dz W2^T) masked by h > 0;
+//   gradient   every weight gradient is a sum over batch rows, taken in two
+//              stages (per-chunk partial sums in row order, then a sum over
+//              chunks in order), never with floating-point atomics, so
+//              results are bitwise reproducible;
+//   update     the sum over chunks, the loss, and Adam with bias correction.
 // Seeding: keys z . r_p for P seeded unit directions, mapped to order-
 // preserving u32 and sorted with a stable LSD radix sort (4 x 8-bit passes,
 // index payload, so equal keys stay in index order); each point then takes
@@ -179,98 +178,261 @@ __global__ __launch_bounds__(64) void mlp_forward_bf16_kernel(const void* __rest
 
 // ------------------------------------------------------------------- loss
 
+// Training runs three kernels per step.  A step's arithmetic is small (0.24
+// GFLOP at 4,096 triplets x 50: 2 us of FP32 FMAs), so its time is latency:
+// launches, dependent loads and the waves in flight.  At that size the step
+// took 154 us as eight kernels with a thread per row, per triplet or per
+// parameter; the three below take 44 us (16.7 + 17.6 + 6.0 and gaps).  Every sum keeps its terms and
+// their order, so weights and losses are those of the eight kernels bit for
+// bit.
+
+// Rows, forward pass, loss and dL/dh of 32 triplets per workgroup (rows p * 32
+// + c of the workgroup: anchors, positives and negatives p = 0, 1, 2 of
+// triplet b0 + c), everything between X and dH in LDS.  rows_in (nullable)
+// gives the 3B rows; without it they are drawn (triplet_row) and kept in
+// rows_out for the gradient kernel.  H gets the hidden layer, dZ and dH the
+// gradients, lterm the loss terms.
+//   BF16 mode: wave (p, half) forms hidden columns 32 half .. + 31 of part p
+//     on 32x32x16 MFMA as mlp_forward_bf16_kernel does (six waves instead of
+//     three share the conversions of X and W1), waves (p, 0) the embedding.
+//   FP32 mode: lane = hidden unit, 16 rows per wave; the rows' inputs come
+//     from LDS as broadcasts, so each weight is loaded once per wave and
+//     serves 16 FMAs.
+constexpr int kTb = 32;   // triplets per workgroup
+
+__device__ inline int32_t triplet_row(int p, int b, int64_t n, const int32_t* knn_idx, int k, uint64_t seed, int step)
+{
+    const uint64_t s = seed ^ kTagTriplet;
+    if (p == 2) return (int32_t)bounded(hash4(s, (uint64_t)step, (uint64_t)b, 2), (uint32_t)n);
+    const uint32_t a = bounded(hash4(s, (uint64_t)step, (uint64_t)b, 0), (uint32_t)n);
+    if (p == 0) return (int32_t)a;
+    const uint32_t pj = bounded(hash4(s, (uint64_t)step, (uint64_t)b, 1), (uint32_t)k);
+    const int32_t q = knn_idx[(int64_t)a * k + pj];
+    return q < 0 || q >= n ? (int32_t)a : q;
+}
+
+// The triplets alone (knn_encoder_triplets); training draws them inside
+// triplet_batch_kernel.
 __global__ __launch_bounds__(256) void triplet_sample_kernel(int64_t n, const int32_t* __restrict__ knn_idx,
                                                              int k, int B, uint64_t seed, int step,
                                                              int32_t* __restrict__ rows)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
-    const uint64_t s = seed ^ kTagTriplet;
-    const uint32_t a = bounded(hash4(s, (uint64_t)step, (uint64_t)b, 0), (uint32_t)n);
-    const uint32_t pj = bounded(hash4(s, (uint64_t)step, (uint64_t)b, 1), (uint32_t)k);
-    int32_t p = knn_idx[(int64_t)a * k + pj];
-    if (p < 0 || p >= n) p = (int32_t)a;
-    const uint32_t q = bounded(hash4(s, (uint64_t)step, (uint64_t)b, 2), (uint32_t)n);
-    rows[b] = (int32_t)a;
-    rows[B + b] = p;
-    rows[2 * B + b] = (int32_t)q;
+    for (int p = 0; p < 3; ++p) rows[(int64_t)p * B + b] = triplet_row(p, b, n, knn_idx, k, seed, step);
 }
 
-// One thread per triplet; Z rows are [anchors; positives; negatives].
-__global__ __launch_bounds__(256) void triplet_loss_kernel(const float* __restrict__ Z, int B, float margin,
-                                                           float* __restrict__ dZ, float* __restrict__ lterm)
+template <int DT, bool BF>
+__global__ __launch_bounds__(384) void triplet_batch_kernel(
+    const void* __restrict__ X, int64_t ld, int d, int64_t n, const int32_t* __restrict__ rows_in,
+    const int32_t* __restrict__ knn_idx, int k, uint64_t seed, int step, int B, float margin,
+    const float* __restrict__ prm, int32_t* __restrict__ rows_out, float* __restrict__ H, float* __restrict__ dZ,
+    float* __restrict__ dH, float* __restrict__ lterm)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const float* za = Z + (int64_t)b * H2;
-    const float* zp = Z + (int64_t)(B + b) * H2;
-    const float* zn = Z + (int64_t)(2 * B + b) * H2;
-    float dp = 0.0f, dn = 0.0f;
+    constexpr int XC = 32;   // coordinates per staged chunk (FP32 mode)
+    __shared__ int32_t srow[3 * kTb];
+    __shared__ __attribute__((aligned(16))) float hs[3 * kTb][H1 + 4];   // FP32; BF16 mode: bf16 rows in the same bytes
+    __shared__ __attribute__((aligned(16))) float zs[3 * kTb][H2 + 4];
+    __shared__ __attribute__((aligned(16))) float xs[3 * kTb][XC + 4];   // staged inputs, then dZ
+    __shared__ int sact[kTb];
+    static_assert(XC == H2, "dZ reuses the staged inputs' rows");
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 31, h = lane >> 5;
+    const Off o(d);
+    const int b0 = blockIdx.x * kTb;
+    // the second layer's weights, used after three barriers, are requested
+    // first: row `lane` for dH, and in the BF16 mode the embedding's operand
+    float w2[H2], wz[BF ? 4 : 1][8];
 #pragma unroll
-    for (int q = 0; q < H2; ++q) {
-        const float ep = za[q] - zp[q], en = za[q] - zn[q];
-        dp = fmaf(ep, ep, dp);
-        dn = fmaf(en, en, dn);
+    for (int q = 0; q < H2; q += 4) {
+        const float4 v = *(const float4*)(prm + o.W2 + lane * H2 + q);
+        w2[q] = v.x;
+        w2[q + 1] = v.y;
+        w2[q + 2] = v.z;
+        w2[q + 3] = v.w;
     }
-    const float g = margin + dp - dn;
-    const bool act = g > 0.0f;
-    lterm[b] = act ? g : 0.0f;
-    const float sc = 2.0f / (float)B;
+    if (BF && (w & 1) == 0) {
 #pragma unroll
-    for (int q = 0; q < H2; ++q) {
-        dZ[(int64_t)b * H2 + q] = act ? sc * (zn[q] - zp[q]) : 0.0f;
-        dZ[(int64_t)(B + b) * H2 + q] = act ? sc * (zp[q] - za[q]) : 0.0f;
-        dZ[(int64_t)(2 * B + b) * H2 + q] = act ? sc * (za[q] - zn[q]) : 0.0f;
+        for (int kk = 0; kk < (BF ? 4 : 0); ++kk)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wz[kk][e] = prm[o.W2 + (16 * kk + 8 * h + e) * H2 + c];
     }
-}
-
-// Fixed-order sum of m values by one workgroup: each thread sums a strided
-// slice in order, then a tree over threads.  out[0] = sum * scale.
-__global__ __launch_bounds__(256) void ordered_sum_kernel(const float* __restrict__ v, int64_t m,
-                                                          float scale, float* __restrict__ out)
-{
-    __shared__ float s[256];
-    float a = 0.0f;
-    for (int64_t i = threadIdx.x; i < m; i += 256) a += v[i];
-    s[threadIdx.x] = a;
+    if (tid < 3 * kTb) {
+        const int p = tid / kTb, b = b0 + tid % kTb;
+        int32_t r = 0;
+        if (b < B) {
+            r = rows_in ? rows_in[(int64_t)p * B + b] : triplet_row(p, b, n, knn_idx, k, seed, step);
+            if (!rows_in) rows_out[(int64_t)p * B + b] = r;
+        }
+        srow[tid] = r;
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+    if constexpr (BF) {
+        typedef uint16_t (*HsT)[2 * (H1 + 4)];
+        HsT hb = (HsT)hs;   // row stride 136 bf16 values (272 bytes, 16-byte aligned)
+        const int part = w >> 1, half = w & 1;
+        const bool valid = b0 + c < B;
+        const int64_t src = valid ? (int64_t)srow[part * kTb + c] : 0;
+        f32x16_t acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+        // four steps' inputs and weights (64 columns) are loaded together: a
+        // round of loads is a memory round trip, a step's conversions and
+        // MFMA a small part of it
+        for (int kb = 0; kb < d; kb += 64) {
+            float xv[4][8], wv[4][8];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int t = kb + 16 * u + 8 * h + e;
+                    const bool in = t < d;
+                    wv[u][e] = in ? prm[o.W1 + t * H1 + 32 * half + c] : 0.0f;
+                    xv[u][e] = valid && in ? elem<DT>::ld(X, src * ld + t) : 0.0f;
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (kb + 16 * u < d)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack_bf16x8(xv[u]), pack_bf16x8(wv[u]), acc, 0, 0, 0);
+        }
+        const float bj = prm[o.b1 + 32 * half + c];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+            const float hv = bf16_round(fmaxf(acc[v] + bj, 0.0f));
+            hb[part * kTb + r][32 * half + c] = (uint16_t)(__float_as_uint(hv) >> 16);
+            if (b0 + r < B) H[((int64_t)part * B + b0 + r) * H1 + 32 * half + c] = hv;
+        }
         __syncthreads();
+        if (half == 0) {
+            f32x16_t az;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) az[v] = 0.0f;
+#pragma unroll
+            for (int kk = 0; kk < H1 / 16; ++kk) {
+                const bf16x8_t ha = __builtin_bit_cast(bf16x8_t, *(const uint4*)&hb[part * kTb + c][16 * kk + 8 * h]);
+                az = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ha, pack_bf16x8(wz[kk]), az, 0, 0, 0);
+            }
+            const float bq = prm[o.b2 + c];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) zs[part * kTb + 8 * (v >> 2) + 4 * h + (v & 3)][c] = az[v] + bq;
+        }
+    } else {
+        float acc[16];   // rows 16 w .. + 15, hidden unit `lane`
+        const float bj = prm[o.b1 + lane];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = bj;
+        for (int k0 = 0; k0 < d; k0 += XC) {
+            __syncthreads();
+            for (int e = tid; e < 3 * kTb * XC; e += 384) {
+                const int r = e / XC, t = k0 + e % XC;
+                xs[r][e % XC] = t < d ? elem<DT>::ld(X, (int64_t)srow[r] * ld + t) : 0.0f;
+            }
+            __syncthreads();
+            const int tn = d - k0 < XC ? d - k0 : XC;
+            for (int t = 0; t < tn; t += 4) {
+                float wt[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) wt[e] = t + e < tn ? prm[o.W1 + (k0 + t + e) * H1 + lane] : 0.0f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float4 x = *(const float4*)&xs[16 * w + r][t];
+                    // a coordinate past d multiplies 0 by 0: the sum keeps its bits
+                    acc[r] = fmaf(x.w, wt[3], fmaf(x.z, wt[2], fmaf(x.y, wt[1], fmaf(x.x, wt[0], acc[r]))));
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rr = 16 * w + r, b = b0 + rr % kTb;
+            const float hv = acc[r] > 0.0f ? acc[r] : 0.0f;
+            hs[rr][lane] = hv;
+            if (b < B) H[((int64_t)(rr / kTb) * B + b) * H1 + lane] = hv;
+        }
+        __syncthreads();
+        // embedding: lane (half h, output c) takes rows 16 w + 8 h .. + 7
+        float z[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) z[r] = prm[o.b2 + c];
+        for (int j = 0; j < H1; j += 4) {
+            float wt[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wt[e] = prm[o.W2 + (j + e) * H2 + c];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const float4 x = *(const float4*)&hs[16 * w + 8 * h + r][j];
+                z[r] = fmaf(x.w, wt[3], fmaf(x.z, wt[2], fmaf(x.y, wt[1], fmaf(x.x, wt[0], z[r]))));
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) zs[16 * w + 8 * h + r][c] = z[r];
     }
-    if (threadIdx.x == 0) out[0] = s[0] * scale;
+    __syncthreads();
+    // loss terms: max(0, margin + |za - zp|^2 - |za - zn|^2)
+    if (tid < kTb) {
+        float dp = 0.0f, dn = 0.0f;
+#pragma unroll
+        for (int q = 0; q < H2; ++q) {
+            const float za = zs[tid][q], ep = za - zs[kTb + tid][q], en = za - zs[2 * kTb + tid][q];
+            dp = fmaf(ep, ep, dp);
+            dn = fmaf(en, en, dn);
+        }
+        const float g = margin + dp - dn;
+        const bool act = g > 0.0f;
+        sact[tid] = act ? 1 : 0;
+        if (b0 + tid < B) lterm[b0 + tid] = act ? g : 0.0f;
+    }
+    __syncthreads();
+    const float sc = 2.0f / (float)B;
+    for (int e = tid; e < kTb * H2; e += 384) {
+        const int t = e / H2, q = e % H2;
+        const float za = zs[t][q], zp = zs[kTb + t][q], zn = zs[2 * kTb + t][q];
+        const bool act = sact[t] != 0;
+        const float g[3] = {act ? sc * (zn - zp) : 0.0f, act ? sc * (zp - za) : 0.0f, act ? sc * (za - zn) : 0.0f};
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            xs[p * kTb + t][q] = BF ? bf16_round(g[p]) : g[p];
+            if (b0 + t < B) dZ[((int64_t)p * B + b0 + t) * H2 + q] = g[p];
+        }
+    }
+    __syncthreads();
+    // dH[i][j] = (sum_q dZ[i][q] W2[j][q]) if H[i][j] > 0 else 0; in the BF16
+    // mode the factors dZ and W2 are rounded to BF16 first.  lane = j.
+    if (BF) {
+#pragma unroll
+        for (int q = 0; q < H2; ++q) w2[q] = bf16_round(w2[q]);
+    }
+    for (int r = 0; r < 16; ++r) {
+        const int rr = 16 * w + r, b = b0 + rr % kTb;
+        float a = 0.0f;
+#pragma unroll
+        for (int q = 0; q < H2; q += 4) {
+            const float4 x = *(const float4*)&xs[rr][q];
+            a = fmaf(x.w, w2[q + 3], fmaf(x.z, w2[q + 2], fmaf(x.y, w2[q + 1], fmaf(x.x, w2[q], a))));
+        }
+        const bool on = BF ? __uint_as_float((uint32_t)((const uint16_t*)hs[rr])[lane] << 16) > 0.0f : hs[rr][lane] > 0.0f;
+        if (b < B) dH[((int64_t)(rr / kTb) * B + b) * H1 + lane] = on ? a : 0.0f;
+    }
 }
 
 // --------------------------------------------------------------- backward
 
-// dH[i][j] = (sum_q dZ[i][q] W2[j][q]) if H[i][j] > 0 else 0.  In the BF16
-// mode (BF) the product operands dZ and W2 are rounded to BF16 first.
-template <bool BF>
-__global__ __launch_bounds__(256) void mlp_dh_kernel(int64_t m, int d, const float* __restrict__ prm,
-                                                     const float* __restrict__ H, const float* __restrict__ dZ,
-                                                     float* __restrict__ dH)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const Off o(d);
-    float dz[H2];
-#pragma unroll
-    for (int q = 0; q < H2; ++q) dz[q] = BF ? bf16_round(dZ[i * H2 + q]) : dZ[i * H2 + q];
-    for (int j = 0; j < H1; ++j) {
-        const float* w = prm + o.W2 + j * H2;
-        float a = 0.0f;
-#pragma unroll
-        for (int q = 0; q < H2; ++q) a = fmaf(dz[q], BF ? bf16_round(w[q]) : w[q], a);
-        dH[i * H1 + j] = H[i * H1 + j] > 0.0f ? a : 0.0f;
-    }
-}
-
 constexpr int kGradChunk = 256;   // batch rows per partial sum
+constexpr int kGradT = 32;        // inputs per tile of gW1
 
 // partial[c][p] = sum over the rows of chunk c (in order) of the product that
 // defines gradient p: gW1[t][j] = x_t dh_j, gb1[j] = dh_j, gW2[j][q] = h_j dz_q,
 // gb2[q] = dz_q.  In the BF16 mode (BF) the factors of the weight-gradient
 // products are rounded to BF16 (the bias gradients are plain FP32 sums).
+// Workgroup (c, y): the 32 x 64 tile of gW1 for inputs 32 y .. + 31, or (y =
+// nt) gW2 as the 32 x 64 tile (output q, hidden j), or (y = nt + 1) the
+// biases.  A tile's rows pass through LDS 128 at a time, the next 128 loaded
+// meanwhile: a chunk costs two memory round trips, which bound the kernel
+// (its FMAs are 2 us).  Thread (ty, tx) sums entries (2 ty + {0, 1}, 4 tx ..
+// + 3), so two LDS reads serve eight FMAs.  At 4,096 triplets x 50 (MI355X):
+// a thread per parameter, both factors read from memory for each FMA 69 us;
+// tiles of 32 rows 40 us; this 17.6 us.
+constexpr int kGradRows = 128;    // rows per staged tile
+
 template <int DT, bool BF>
 __global__ __launch_bounds__(256) void mlp_grad_partial_kernel(const void* __restrict__ X, int64_t ld, int d,
                                                                const int32_t* __restrict__ rows, int64_t m,
@@ -279,52 +441,142 @@ __global__ __launch_bounds__(256) void mlp_grad_partial_kernel(const void* __res
                                                                const float* __restrict__ dH,
                                                                float* __restrict__ partial)
 {
+    __shared__ __attribute__((aligned(16))) float sx[kGradRows][kGradT + 4];
+    __shared__ __attribute__((aligned(16))) float sg[kGradRows][H1 + 4];
+    __shared__ int32_t srow[kGradChunk];
     const Off o(d);
-    const int p = blockIdx.y * blockDim.x + threadIdx.x;
-    if (p >= o.P) return;
-    const int c = blockIdx.x;
-    const int64_t i0 = (int64_t)c * kGradChunk;
-    const int64_t i1 = i0 + kGradChunk < m ? i0 + kGradChunk : m;
-    float a = 0.0f;
-    if (p < o.b1) {
-        const int t = p / H1, j = p % H1;
-        for (int64_t i = i0; i < i1; ++i) {
-            const int64_t r = rows ? (int64_t)rows[i] : i;
-            const float x = elem<DT>::ld(X, r * ld + t), g = dH[i * H1 + j];
-            a = BF ? fmaf(bf16_round(x), bf16_round(g), a) : fmaf(x, g, a);
+    const int tid = threadIdx.x, nt = (d + kGradT - 1) / kGradT, y = blockIdx.y;
+    const int64_t i0 = (int64_t)blockIdx.x * kGradChunk, i1 = i0 + kGradChunk < m ? i0 + kGradChunk : m;
+    float* out = partial + (int64_t)blockIdx.x * o.P;
+    if (y == nt + 1) {
+        if (tid < H1 + H2) {
+            const bool one = tid < H1;
+            const float* src = one ? dH + tid : dZ + (tid - H1);
+            const int64_t st = one ? H1 : H2;
+            float a = 0.0f;
+            for (int64_t ib = i0; ib < i1; ib += 64) {
+                float v[64];   // 64 rows in flight; rows past the end add zero
+#pragma unroll
+                for (int e = 0; e < 64; ++e) v[e] = ib + e < i1 ? src[(ib + e) * st] : 0.0f;
+#pragma unroll
+                for (int e = 0; e < 64; ++e) a += v[e];
+            }
+            out[one ? o.b1 + tid : o.b2 + tid - H1] = a;
         }
-    } else if (p < o.W2) {
-        const int j = p - o.b1;
-        for (int64_t i = i0; i < i1; ++i) a += dH[i * H1 + j];
-    } else if (p < o.b2) {
-        const int j = (p - o.W2) / H2, q = (p - o.W2) % H2;
-        for (int64_t i = i0; i < i1; ++i)
-            a = BF ? fmaf(bf16_round(H[i * H1 + j]), bf16_round(dZ[i * H2 + q]), a)
-                   : fmaf(H[i * H1 + j], dZ[i * H2 + q], a);
-    } else {
-        const int q = p - o.b2;
-        for (int64_t i = i0; i < i1; ++i) a += dZ[i * H2 + q];
+        return;
     }
-    partial[(int64_t)c * o.P + p] = a;
+    const bool w2 = y == nt;
+    const int t0 = y * kGradT;
+    static_assert(kGradChunk == 256 && kGradT == 32 && H2 == 32, "staging layout");
+    srow[tid] = i0 + tid < i1 ? (w2 ? (int32_t)0 : rows[i0 + tid]) : -1;
+    __syncthreads();
+    // staging: pass u, thread: column tid % 32 of row 8 u + tid / 32 (inputs),
+    // columns 4 (tid % 16) .. + 3 of row 16 u + tid / 16 (hidden gradients)
+    float px[16];
+    float4 pg[8];
+    auto fetch = [&](int ib) {
+        const int xc = tid & 31, t = t0 + xc;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int i = ib + 8 * u + (tid >> 5);
+            const int32_t r = srow[i];
+            float v = 0.0f;
+            if (w2) {
+                if (r >= 0) v = dZ[(i0 + i) * H2 + xc];
+            } else if (r >= 0 && t < d) {
+                v = elem<DT>::ld(X, (int64_t)r * ld + t);
+            }
+            px[u] = v;
+        }
+        const float* g = w2 ? H : dH;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = ib + 16 * u + (tid >> 4);
+            pg[u] = srow[i] >= 0 ? *(const float4*)(g + (i0 + i) * H1 + 4 * (tid & 15)) : make_float4(0, 0, 0, 0);
+        }
+    };
+    float acc[2][4] = {};
+    const int ty = tid >> 4, tx = tid & 15;
+    const int nrow = (int)(i1 - i0);
+    fetch(0);
+    for (int ib = 0; ib < nrow; ib += kGradRows) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sx[8 * u + (tid >> 5)][tid & 31] = BF ? bf16_round(px[u]) : px[u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            float4 v = pg[u];
+            if (BF) v = make_float4(bf16_round(v.x), bf16_round(v.y), bf16_round(v.z), bf16_round(v.w));
+            *(float4*)&sg[16 * u + (tid >> 4)][4 * (tid & 15)] = v;
+        }
+        __syncthreads();
+        if (ib + kGradRows < nrow) fetch(ib + kGradRows);
+        // rows past the chunk hold zeros: their products leave the sums as they are
+#pragma unroll 8
+        for (int r = 0; r < kGradRows; ++r) {
+            const float2 x = *(const float2*)&sx[r][2 * ty];
+            const float4 g = *(const float4*)&sg[r][4 * tx];
+            acc[0][0] = fmaf(x.x, g.x, acc[0][0]);
+            acc[0][1] = fmaf(x.x, g.y, acc[0][1]);
+            acc[0][2] = fmaf(x.x, g.z, acc[0][2]);
+            acc[0][3] = fmaf(x.x, g.w, acc[0][3]);
+            acc[1][0] = fmaf(x.y, g.x, acc[1][0]);
+            acc[1][1] = fmaf(x.y, g.y, acc[1][1]);
+            acc[1][2] = fmaf(x.y, g.z, acc[1][2]);
+            acc[1][3] = fmaf(x.y, g.w, acc[1][3]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = 2 * ty + a, j = 4 * tx + e;
+            if (w2) out[o.W2 + j * H2 + t] = acc[a][e];
+            else if (t0 + t < d) out[(t0 + t) * H1 + j] = acc[a][e];
+        }
 }
 
-__global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ partial, int nch, int P,
-                                                          float* __restrict__ g)
+// The chunks' partial gradients summed in chunk order to g, and (w not null)
+// an Adam update of w with that gradient.  The last workgroup sums the B
+// loss terms instead: each thread a strided slice in order, then a tree over
+// the threads; loss[0] = sum / B.
+constexpr int kReduceThreads = 64;
+
+__global__ __launch_bounds__(256) void grad_reduce_adam_kernel(const float* __restrict__ partial, int nch, int P,
+                                                               float* __restrict__ g, const float* __restrict__ lterm,
+                                                               int B, float* __restrict__ loss, float* __restrict__ w,
+                                                               float* __restrict__ mo, float* __restrict__ ve,
+                                                               float lr, float b1, float b2, float eps, float c1,
+                                                               float c2)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+    __shared__ float s[256];
+    if (blockIdx.x == gridDim.x - 1) {
+        float a = 0.0f;
+        for (int64_t i = threadIdx.x; i < B; i += 256) a += lterm[i];
+        s[threadIdx.x] = a;
+        __syncthreads();
+        for (int o = 128; o > 0; o >>= 1) {
+            if ((int)threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) loss[0] = s[0] * (1.0f / (float)B);
+        return;
+    }
+    // one wave's worth of parameters per workgroup: a few thousand
+    // parameters then run on as many CUs as there are
+    const int p = blockIdx.x * kReduceThreads + threadIdx.x;
+    if (threadIdx.x >= kReduceThreads || p >= P) return;
     float a = 0.0f;
-    for (int c = 0; c < nch; ++c) a += partial[(int64_t)c * P + p];
+    for (int c0 = 0; c0 < nch; c0 += 32) {
+        float v[32];   // 32 chunks in flight; chunks past the end add zero
+#pragma unroll
+        for (int e = 0; e < 32; ++e) v[e] = c0 + e < nch ? partial[(int64_t)(c0 + e) * P + p] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) a += v[e];
+    }
     g[p] = a;
-}
-
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ w, const float* __restrict__ g,
-                                                   float* __restrict__ mo, float* __restrict__ ve, int P,
-                                                   float lr, float b1, float b2, float eps, float c1, float c2)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const float gg = g[p];
+    if (!w) return;
+    const float gg = a;
     const float mm = b1 * mo[p] + (1.0f - b1) * gg;
     const float vv = b2 * ve[p] + (1.0f - b2) * gg * gg;
     mo[p] = mm;
@@ -1018,47 +1270,65 @@ knn_status encoder_seed(const knn_encoder* enc, const knn_matrix& X, const knn_m
     return proj_seed_impl(Xd, Z, H2, dirs, P, D, w, 0, nullptr, nullptr, ws, st, seed_idx, seed_d2);
 }
 
-// Forward + loss + backward of one batch (rows: 3B device ints).  Leaves the
-// loss sum in loss_dev[0] (already divided by B) and the gradient in grad.
-static knn_status batch_grads(const knn_encoder* enc, const knn_matrix& X, const int32_t* rows, int B,
-                              float margin, int precision, float* H, float* Z, float* dZ, float* dH,
-                              float* lterm, float* partial, float* grad, float* loss_dev, hipStream_t st)
+// Scratch of one training batch of B triplets (rows: drawn triplets).
+struct BatchBuf {
+    int32_t* rows;
+    float *H, *dZ, *dH, *lterm, *partial, *grad;
+};
+
+static knn_status batch_alloc(ScratchAlloc& ws, const Off& o, int B, bool draws, float* grads, BatchBuf* b)
+{
+    const int64_t m = 3 * (int64_t)B;
+    knn_status r;
+    b->rows = nullptr;
+    b->grad = grads;
+    if (draws && (r = ws.alloc(&b->rows, (size_t)m)) != KNN_OK) return r;
+    if ((r = ws.alloc(&b->H, (size_t)m * H1)) != KNN_OK) return r;
+    if ((r = ws.alloc(&b->dZ, (size_t)m * H2)) != KNN_OK) return r;
+    if ((r = ws.alloc(&b->dH, (size_t)m * H1)) != KNN_OK) return r;
+    if ((r = ws.alloc(&b->lterm, (size_t)B)) != KNN_OK) return r;
+    if ((r = ws.alloc(&b->partial, (size_t)ceil_div(m, kGradChunk) * o.P)) != KNN_OK) return r;
+    if (!grads && (r = ws.alloc(&b->grad, (size_t)o.P)) != KNN_OK) return r;
+    return KNN_OK;
+}
+
+// One batch: rows (given, or drawn from knn_idx for step `step` with `seed`),
+// forward, loss, backward; the loss (divided by B) in loss_dev[0], the
+// gradient in b.grad.  With tp, also Adam step number t (1-based) on the
+// encoder's FP32 weights: the bias corrections 1 - beta^t are computed on the
+// host in double (in FP32, 1 - 0.999^t loses about 2^-24 / (1 - 0.999^t)
+// relative to the cancellation: 3e-5 at t = 2) and rounded once.
+static knn_status batch_step(knn_encoder* enc, const knn_matrix& X, const int32_t* rows, const int32_t* knn_idx,
+                             int k, uint64_t seed, int step, int B, float margin, int precision, const BatchBuf& b,
+                             float* loss_dev, const knn_train_params* tp, int t, hipStream_t st)
 {
     const int64_t m = 3 * (int64_t)B;
     const Off o(enc->d);
     const bool bf = precision == KNN_PREC_BF16;
-    knn_status r = forward_impl(enc, X, rows, m, precision, H, Z, st);
-    if (r != KNN_OK) return r;
-    triplet_loss_kernel<<<(unsigned)ceil_div(B, 256), 256, 0, st>>>(Z, B, margin, dZ, lterm);
-    ordered_sum_kernel<<<1, 256, 0, st>>>(lterm, B, 1.0f / (float)B, loss_dev);
-    if (bf) mlp_dh_kernel<true><<<(unsigned)ceil_div(m, 256), 256, 0, st>>>(m, enc->d, enc->params, H, dZ, dH);
-    else mlp_dh_kernel<false><<<(unsigned)ceil_div(m, 256), 256, 0, st>>>(m, enc->d, enc->params, H, dZ, dH);
     const int nch = (int)ceil_div(m, kGradChunk);
-    dim3 g((unsigned)nch, (unsigned)ceil_div(o.P, 256));
+    const dim3 g((unsigned)nch, (unsigned)(ceil_div(enc->d, kGradT) + 2));
+    const unsigned bg = (unsigned)ceil_div(B, kTb);
+    const int32_t* used = rows ? rows : b.rows;
     by_dtype(X.dtype, [&](auto dt) {
-        if (bf)
-            mlp_grad_partial_kernel<decltype(dt)::value, true><<<g, 256, 0, st>>>(X.data, X.ld, X.d, rows, m, H,
-                                                                                  dZ, dH, partial);
-        else
-            mlp_grad_partial_kernel<decltype(dt)::value, false><<<g, 256, 0, st>>>(X.data, X.ld, X.d, rows, m, H,
-                                                                                   dZ, dH, partial);
+        constexpr int DT = decltype(dt)::value;
+        if (bf) {
+            triplet_batch_kernel<DT, true><<<bg, 384, 0, st>>>(X.data, X.ld, X.d, X.n, rows, knn_idx, k, seed, step, B,
+                                                               margin, enc->params, b.rows, b.H, b.dZ, b.dH, b.lterm);
+            mlp_grad_partial_kernel<DT, true><<<g, 256, 0, st>>>(X.data, X.ld, X.d, used, m, b.H, b.dZ, b.dH,
+                                                                 b.partial);
+        } else {
+            triplet_batch_kernel<DT, false><<<bg, 384, 0, st>>>(X.data, X.ld, X.d, X.n, rows, knn_idx, k, seed, step,
+                                                                B, margin, enc->params, b.rows, b.H, b.dZ, b.dH,
+                                                                b.lterm);
+            mlp_grad_partial_kernel<DT, false><<<g, 256, 0, st>>>(X.data, X.ld, X.d, used, m, b.H, b.dZ, b.dH,
+                                                                  b.partial);
+        }
     });
-    grad_reduce_kernel<<<(unsigned)ceil_div(o.P, 256), 256, 0, st>>>(partial, nch, o.P, grad);
-    KNN_HIP(hipGetLastError());
-    return KNN_OK;
-}
-
-// Adam step number t (1-based) on the encoder's FP32 weights with gradient
-// grad: the bias corrections 1 - beta^t are computed on the host in double
-// (in FP32, 1 - 0.999^t loses about 2^-24 / (1 - 0.999^t) relative to the
-// cancellation: 3e-5 at t = 2) and rounded once.
-static knn_status adam_apply(knn_encoder* enc, const float* grad, const knn_train_params& tp, int t,
-                             hipStream_t st)
-{
-    const float c1 = (float)(1.0 - pow((double)tp.beta1, (double)t));
-    const float c2 = (float)(1.0 - pow((double)tp.beta2, (double)t));
-    adam_kernel<<<(unsigned)ceil_div(enc->P, 256), 256, 0, st>>>(enc->params, grad, enc->mom, enc->vel, enc->P,
-                                                                 tp.lr, tp.beta1, tp.beta2, tp.eps, c1, c2);
+    const float c1 = tp ? (float)(1.0 - pow((double)tp->beta1, (double)t)) : 1.0f;
+    const float c2 = tp ? (float)(1.0 - pow((double)tp->beta2, (double)t)) : 1.0f;
+    grad_reduce_adam_kernel<<<(unsigned)ceil_div(o.P, kReduceThreads) + 1, 256, 0, st>>>(
+        b.partial, nch, o.P, b.grad, b.lterm, B, loss_dev, tp ? enc->params : nullptr, enc->mom, enc->vel,
+        tp ? tp->lr : 0.0f, tp ? tp->beta1 : 0.0f, tp ? tp->beta2 : 0.0f, tp ? tp->eps : 0.0f, c1, c2);
     KNN_HIP(hipGetLastError());
     return KNN_OK;
 }
@@ -1169,19 +1439,11 @@ extern "C" knn_status knn_encoder_grads(knn_encoder* enc, knn_matrix X, const in
         if (B < 1) return fail(KNN_EINVAL, "B must be >= 1");
         hipStream_t st = (hipStream_t)stream;
         Workspace ws(st, 0);
-        const int64_t m = 3 * (int64_t)B;
-        const Off o(enc->d);
-        float *H, *Z, *dZ, *dH, *lterm, *partial, *grad, *loss_dev;
-        if ((r = ws.alloc(&H, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&Z, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dZ, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dH, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&lterm, (size_t)B)) != KNN_OK) return r;
-        if ((r = ws.alloc(&partial, (size_t)ceil_div(m, kGradChunk) * o.P)) != KNN_OK) return r;
-        grad = grads;
-        if (!grad && (r = ws.alloc(&grad, (size_t)o.P)) != KNN_OK) return r;
+        BatchBuf b;
+        float* loss_dev;
+        if ((r = batch_alloc(ws, Off(enc->d), B, false, grads, &b)) != KNN_OK) return r;
         if ((r = ws.alloc(&loss_dev, 1)) != KNN_OK) return r;
-        r = batch_grads(enc, X, rows, B, margin, precision, H, Z, dZ, dH, lterm, partial, grad, loss_dev, st);
+        r = batch_step(enc, X, rows, nullptr, 0, 0, 0, B, margin, precision, b, loss_dev, nullptr, 0, st);
         if (r != KNN_OK) return r;
         KNN_HIP(hipMemcpyAsync(loss_out, loss_dev, 4, hipMemcpyDeviceToHost, st));
         KNN_HIP(hipStreamSynchronize(st));
@@ -1219,26 +1481,14 @@ extern "C" knn_status knn_encoder_train(knn_encoder* enc, knn_matrix X, const in
         hipStream_t st = (hipStream_t)stream;
         Workspace ws(st, 0);
         const int B = tp->batch;
-        const int64_t m = 3 * (int64_t)B;
-        const Off o(enc->d);
-        int32_t* rows;
-        float *H, *Z, *dZ, *dH, *lterm, *partial, *grad, *losses;
-        if ((r = ws.alloc(&rows, (size_t)m)) != KNN_OK) return r;
-        if ((r = ws.alloc(&H, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&Z, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dZ, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dH, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&lterm, (size_t)B)) != KNN_OK) return r;
-        if ((r = ws.alloc(&partial, (size_t)ceil_div(m, kGradChunk) * o.P)) != KNN_OK) return r;
-        if ((r = ws.alloc(&grad, (size_t)o.P)) != KNN_OK) return r;
+        BatchBuf b;
+        float* losses;
+        if ((r = batch_alloc(ws, Off(enc->d), B, true, nullptr, &b)) != KNN_OK) return r;
         if ((r = ws.alloc(&losses, (size_t)(tp->steps > 0 ? tp->steps : 1))) != KNN_OK) return r;
         for (int s = 0; s < tp->steps; ++s) {
-            triplet_sample_kernel<<<(unsigned)ceil_div(B, 256), 256, 0, st>>>(X.n, knn_idx, k, B, tp->seed,
-                                                                              enc->t + s, rows);
-            r = batch_grads(enc, X, rows, B, tp->margin, tp->precision, H, Z, dZ, dH, lterm, partial, grad,
-                            losses + s, st);
+            r = batch_step(enc, X, nullptr, knn_idx, k, tp->seed, enc->t + s, B, tp->margin, tp->precision, b,
+                           losses + s, tp, enc->t + s + 1, st);
             if (r != KNN_OK) return r;
-            if ((r = adam_apply(enc, grad, *tp, enc->t + s + 1, st)) != KNN_OK) return r;
         }
         enc->t += tp->steps;
         if (loss_log && tp->steps > 0)
@@ -1280,20 +1530,12 @@ extern "C" knn_status knn_encoder_step(knn_encoder* enc, knn_matrix X, const int
             return fail(KNN_EINVAL, "unknown precision");
         hipStream_t st = (hipStream_t)stream;
         Workspace ws(st, 0);
-        const int64_t m = 3 * (int64_t)B;
-        const Off o(enc->d);
-        float *H, *Z, *dZ, *dH, *lterm, *partial, *grad, *loss_dev;
-        if ((r = ws.alloc(&H, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&Z, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dZ, (size_t)m * H2)) != KNN_OK) return r;
-        if ((r = ws.alloc(&dH, (size_t)m * H1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&lterm, (size_t)B)) != KNN_OK) return r;
-        if ((r = ws.alloc(&partial, (size_t)ceil_div(m, kGradChunk) * o.P)) != KNN_OK) return r;
-        if ((r = ws.alloc(&grad, (size_t)o.P)) != KNN_OK) return r;
+        BatchBuf b;
+        float* loss_dev;
+        if ((r = batch_alloc(ws, Off(enc->d), B, false, nullptr, &b)) != KNN_OK) return r;
         if ((r = ws.alloc(&loss_dev, 1)) != KNN_OK) return r;
-        r = batch_grads(enc, X, rows, B, tp->margin, tp->precision, H, Z, dZ, dH, lterm, partial, grad, loss_dev, st);
+        r = batch_step(enc, X, rows, nullptr, 0, 0, 0, B, tp->margin, tp->precision, b, loss_dev, tp, enc->t + 1, st);
         if (r != KNN_OK) return r;
-        if ((r = adam_apply(enc, grad, *tp, enc->t + 1, st)) != KNN_OK) return r;
         enc->t += 1;
         if (loss_out) KNN_HIP(hipMemcpyAsync(loss_out, loss_dev, 4, hipMemcpyDeviceToHost, st));
         KNN_HIP(hipStreamSynchronize(st));

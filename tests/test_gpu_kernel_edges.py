@@ -71,3 +71,37 @@ def test_fallback_one_row_many_parts(orc, nq):
     O, O2 = orc.exact_query(X, Q, k, q_self=self_rows.astype(np.int64))
     assert np.array_equal(idx.cpu().numpy()[0], O[0])
     assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("d,B", [(1, 1), (31, 33), (33, 32), (97, 85), (784, 171)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_gradients_at_tile_edges(orc, d, B, precision):
+    """Encoder gradients where the batch is not a whole number of 32-triplet
+    workgroups or 256-row chunks (3B = 3 .. 513 rows) and the inputs not one
+    of 16 / 32 columns.  Bounds: FP32 sums of at most 784 + 256 terms stay
+    within 1e-5 of the norm; the BF16 mode's hidden values may round the
+    other way at a boundary, 1e-3 of the norm."""
+    from paper_2603_04035_amd import Encoder
+    X = datagen.gmm_isotropic(n=400, d=d, seed=d)
+    rng = np.random.default_rng(B)
+    rows = rng.integers(0, 400, size=3 * B)
+    enc = Encoder(d, seed=4)
+    W1, _, W2, _ = enc.get_weights()
+    b1 = rng.normal(0, 0.1, size=64).astype(np.float32)
+    b2 = rng.normal(0, 0.1, size=32).astype(np.float32)
+    enc.set_weights(W1, b1, W2, b2)
+    loss, g = enc.grads(torch.from_numpy(X).cuda(), torch.from_numpy(rows), B, precision=precision)
+    g = g.cpu().numpy().astype(np.float64)
+    bf = precision == "bf16"
+    Zo = (orc.mlp_forward_bf16 if bf else orc.mlp_forward)(X[rows], W1, b1, W2, b2)
+    lo, dZ = orc.triplet_loss(Zo, B, 1.0)
+    refs = (orc.mlp_backward_bf16 if bf else orc.mlp_backward)(X[rows], W1, b1, W2, dZ)
+    tol = 1e-3 if bf else 1e-5
+    assert abs(loss - lo) <= (1e-4 if bf else 1e-5) * max(abs(lo), 1e-6)
+    ref = np.concatenate([np.asarray(r, np.float64).ravel() for r in refs])
+    scale = np.linalg.norm(ref)
+    at = 0
+    for r in refs:
+        part = g[at:at + r.size]
+        assert np.linalg.norm(part - np.asarray(r, np.float64).ravel()) <= tol * scale, (d, B, at)
+        at += r.size
