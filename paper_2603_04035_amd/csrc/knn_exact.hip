@@ -5,11 +5,11 @@
 // |a - b|^2 = |a|^2 + |b|^2 - 2 a.b of its k-NN section.  Here:
 //
 //  1. stage: inputs are copied into a zero-padded, 128-byte-aligned layout
-//     (FP32, or BF16 rounded to nearest even), with FP32 row norms of the
-//     staged values and the largest reference norm;
+//     (pairs of FP16 parts for FP32, or BF16 / FP16 rounded to nearest even),
+//     with FP32 row norms and the largest reference norm;
 //  2. tile: each workgroup owns 128 query rows and streams 128-row reference
-//     tiles through LDS; MFMA (32x32x2 FP32, or 32x32x16 BF16 with FP32
-//     accumulation) produces dot products, the epilogue forms squared
+//     tiles through LDS; MFMA (32x32x16 FP16 or BF16 with FP32
+//     accumulation; three FP16 products for FP32) produces dot products, the epilogue forms squared
 //     distances and keeps, per query row, the best k' candidates in
 //     registers with wave-wide bitonic merges (threshold-gated, so merges
 //     are rare once lists fill).  The reference set can be split across
@@ -136,6 +136,110 @@ __global__ __launch_bounds__(256) void stage_kernel(const void* __restrict__ X, 
     }
 }
 
+// Staging for the FP32 Gram.  A row is kept as two FP16 parts, x s = hi + lo
+// with s a power of two (below): hi = x s rounded to FP16 (11 bits), lo = the
+// remainder rounded to FP16, so hi + lo holds x s to 2^-22 relative (or
+// 2^-25 absolute, for elements 2^-14 below the scale).  Three FP16 MFMA
+// products (hi hi, hi lo, lo hi; FP32 accumulation) then give the dot product
+// in a fifth of the FP32 MFMA's matrix cycles, with smaller errors than its
+// (three sums of 16 products round less often than eight of two: split_err).
+// Self search, FP32 MFMA -> split: 70,000 x 784 70.9 -> 48.0 ms (160 TFLOP/s
+// of distances); 10,000 queries x 1M x 50 21.3 -> 9.3 ms.
+// 32 elements take 64 bytes of hi, then 64 of lo.
+constexpr int KNN_SPLIT = 3;   // staged element kind
+
+// The scale of a matrix whose largest squared row norm has the float bits
+// `mx`: a power of two that brings the largest norm to at most 2^13, so that
+// no element overflows FP16 and sums of products stay far from FP32's range.
+// Exponents stop at +-63 (products of two scales stay finite); norms^2 below
+// 2^-100, which would need more, are reported by split_range.
+__device__ inline float split_scale(unsigned mx)
+{
+    const int e = (int)(mx >> 23) - 127;            // norm^2 < 2^(e + 1)
+    int k = 13 - ((e + 2) >> 1);                     // norm < 2^ceil((e + 1) / 2)
+    k = k > 63 ? 63 : (k < -63 ? -63 : k);
+    return mx == 0u ? 1.0f : __uint_as_float((unsigned)(k + 127) << 23);
+}
+__device__ inline bool split_range(unsigned mx) { return mx == 0u || (mx >> 23) >= 127u - 100u; }
+
+// Squared row norms of X (FP64 sums rounded once to FP32) and the largest
+// one's bits: 16 lanes per row.
+template <int DT>
+__global__ __launch_bounds__(256) void norm_kernel(const void* __restrict__ X, int64_t n, int d, int64_t ld,
+                                                   float* __restrict__ norms, unsigned* __restrict__ maxnorm)
+{
+    __shared__ unsigned smax[4];
+    const int g = threadIdx.x & 15;
+    unsigned wmax = 0;
+    for (int64_t r0 = (int64_t)blockIdx.x * 32; r0 < n; r0 += (int64_t)gridDim.x * 32) {
+        // two rows per group, their loads together
+        const int64_t ra = r0 + (threadIdx.x >> 4), rb = ra + 16;
+        const int64_t oa = (ra < n ? ra : n - 1) * ld, ob = (rb < n ? rb : n - 1) * ld;
+        double sa = 0.0, sb = 0.0;
+#pragma unroll 4
+        for (int t = g; t < d; t += 16) {
+            const double xa = (double)elem<DT>::ld(X, oa + t), xb = (double)elem<DT>::ld(X, ob + t);
+            sa = fma(xa, xa, sa);
+            sb = fma(xb, xb, sb);
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            sa += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(sa), o));
+            sb += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(sb), o));
+        }
+        const float fa = (float)sa, fb = (float)sb;
+        if (g == 0 && ra < n) norms[ra] = fa;
+        if (g == 0 && rb < n) norms[rb] = fb;
+        const unsigned ua = __float_as_uint(fa), ub = __float_as_uint(fb);
+        wmax = ua > wmax ? ua : wmax;
+        wmax = ub > wmax ? ub : wmax;
+    }
+#pragma unroll
+    for (int o = 32; o >= 16; o >>= 1) {
+        const unsigned y = xor_u32(wmax, o);
+        wmax = y > wmax ? y : wmax;
+    }
+    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = wmax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned m = smax[0];
+        for (int w = 1; w < 4; ++w) m = smax[w] > m ? smax[w] : m;
+        atomicMax(maxnorm, m);
+    }
+}
+
+// The staged rows: thread = 8 elements of a row (16 bytes of hi and of lo),
+// zeros beyond d.  OUT = KNN_SPLIT, or KNN_F16 (hi only: 16-bit inputs, whose
+// values FP16 holds exactly up to the 2^-25 above).  ldp: elements, a
+// multiple of 32 (KNN_SPLIT) or 64.
+template <int DT, int OUT>
+__global__ __launch_bounds__(256) void split_kernel(const void* __restrict__ X, int64_t n, int d, int64_t ld,
+                                                    _Float16* __restrict__ Xs, int ldp,
+                                                    const unsigned* __restrict__ maxnorm)
+{
+    const float sc = split_scale(*maxnorm);
+    const int per = ldp / 8;
+    const int64_t total = n * per;
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < total; q += (int64_t)gridDim.x * 256) {
+        const int64_t row = q / per;
+        const int t0 = (int)(q % per) * 8;
+        _Float16 hi[8], lo[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = t0 + e < d ? elem<DT>::ld(X, row * ld + t0 + e) * sc : 0.0f;
+            hi[e] = (_Float16)x;
+            lo[e] = (_Float16)(x - (float)hi[e]);
+        }
+        if (OUT == KNN_SPLIT) {
+            _Float16* o = Xs + row * (2 * (int64_t)ldp) + (t0 / 32) * 64 + t0 % 32;
+            *(uint4*)o = *(const uint4*)hi;
+            *(uint4*)(o + 32) = *(const uint4*)lo;
+        } else {
+            *(uint4*)(Xs + row * (int64_t)ldp + t0) = *(const uint4*)hi;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ tile
 
 // Tile geometry per staged element kind (KNN_F32, KNN_BF16, KNN_F16).
@@ -157,6 +261,12 @@ struct TileCfg<KNN_BF16> {
 };
 template <>
 struct TileCfg<KNN_F16> : TileCfg<KNN_BF16> {};
+// split rows: a chunk is 32 elements, 32 hi then 32 lo values
+template <>
+struct TileCfg<KNN_SPLIT> : TileCfg<KNN_BF16> {
+    static constexpr int AMAX = 128;
+    static constexpr int AROW = 136;
+};
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -274,17 +384,29 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
         // K permutation: half h of the wave supplies chunk columns
         // h*PER .. h*PER+PER-1, the same for A and B, so every column
         // enters the dot product exactly once.
-        const uint4* ap = (const uint4*)(As + (w * 32 + c) * AROW + (ARES ? k0 : 0) + h * PER);
+        // (split rows: columns h * 16 .. + 15 of the chunk's 32, pieces 0 and
+        // 1 their hi values, 2 and 3 their lo values)
+        constexpr int HP = OUT == KNN_SPLIT ? PER / 2 : PER;
+        const uint4* ap = (const uint4*)(As + (w * 32 + c) * AROW + (ARES ? k0 : 0) + h * HP);
         uint4 a4[NV];
 #pragma unroll
-        for (int i = 0; i < NV; ++i) a4[i] = ap[i];
+        for (int i = 0; i < NV; ++i) a4[i] = ap[OUT == KNN_SPLIT && i >= 2 ? i + 2 : i];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            const uint4* bp = (const uint4*)(Bs + (b * 32 + c) * LROW + h * PER);
+            const uint4* bp = (const uint4*)(Bs + (b * 32 + c) * LROW + h * HP);
             uint4 b4[NV];
 #pragma unroll
-            for (int i = 0; i < NV; ++i) b4[i] = bp[i];
-            if constexpr (OUT == KNN_BF16) {
+            for (int i = 0; i < NV; ++i) b4[i] = bp[OUT == KNN_SPLIT && i >= 2 ? i + 2 : i];
+            if constexpr (OUT == KNN_SPLIT) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const f16x8 ah = __builtin_bit_cast(f16x8, a4[i]), al = __builtin_bit_cast(f16x8, a4[i + 2]);
+                    const f16x8 bh = __builtin_bit_cast(f16x8, b4[i]), bl = __builtin_bit_cast(f16x8, b4[i + 2]);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[b], 0, 0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[b], 0, 0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[b], 0, 0, 0);
+                }
+            } else if constexpr (OUT == KNN_BF16) {
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
                     bf16x8 av = __builtin_bit_cast(bf16x8, a4[i]);
@@ -326,7 +448,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
     const void* __restrict__ Qs, const float* __restrict__ qn, int64_t nq,
     const void* __restrict__ Rs, const float* __restrict__ rn, int64_t nr, int ldp,
     const int32_t* __restrict__ q_self, int self_mode, int64_t self_base, int kp, int64_t split_len, int S,
-    const unsigned* __restrict__ rmax_bits, uint64_t* __restrict__ part)
+    const unsigned* __restrict__ rmax_bits, const unsigned* __restrict__ qmax_bits, uint64_t* __restrict__ part)
 {
     using C = TileCfg<OUT>;
     using E = typename C::E;
@@ -358,7 +480,11 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
     // (8u (|q|^2 + thr + max|r|^2)), so every candidate the exact test
     // accepts passes the gate, and the exact test decides.  Rows past nq
     // get lim = +inf and never pass.
+    // Scaled rows (qmax_bits not null) leave the accumulators and the gate in
+    // units of both scales, powers of two, so nothing is rounded by them.
     const float rmax = __uint_as_float(*rmax_bits);
+    const float scq = qmax_bits ? split_scale(*qmax_bits) : 1.0f, scr = qmax_bits ? split_scale(*rmax_bits) : 1.0f;
+    const float sc = scq * scr, m2 = -2.0f / sc, hsc = 0.5f * sc;
     uint64_t list[16];
     float lim[16];
 #pragma unroll
@@ -395,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
         for (int blk = 0; blk < 4; ++blk) {
             const f32x16 cur = blk == 0 ? acc[0] : (blk == 1 ? acc[1] : (blk == 2 ? acc[2] : acc[3]));
             const float rnj = srn[blk * 32 + c];
-            const float hr = 0.5f * rnj;
+            const float hr = hsc * rnj;
             // gate all 16 rows first: one branch per block when nothing passes
             uint64_t gm[16], any = 0;
 #pragma unroll
@@ -413,7 +539,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
                     const int64_t j = rt + blk * 32 + c;
                     const uint64_t t0 = bcast_u64(list[v], kp - 1), t1 = bcast_u64(list[v], 32 + kp - 1);
                     const float thr = key_d2(h ? t1 : t0);
-                    float d2 = fmaf(-2.0f, cur[v], sq + rnj);
+                    float d2 = fmaf(m2, cur[v], sq + rnj);
                     d2 = d2 > 0.0f ? d2 : 0.0f;
                     const bool ok = j < rend && (int32_t)j != sself[lr] && d2 <= thr && lim[v] < __builtin_inff();
                     const uint64_t okm = ballot(ok);
@@ -422,7 +548,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
                         list[v] = list_add(list[v], ck, okm, lane);
                         const uint64_t u0 = bcast_u64(list[v], kp - 1), u1 = bcast_u64(list[v], 32 + kp - 1);
                         const float t = key_d2(h ? u1 : u0);
-                        const float nl = 0.5f * (sq - t) - 4.76837158e-07f * (sq + t + rmax);   // 8u = 2^-21
+                        const float nl = (0.5f * (sq - t) - 4.76837158e-07f * (sq + t + rmax)) * sc;   // 8u = 2^-21
                         lim[v] = lim[v] < __builtin_inff() ? nl : lim[v];
                     }
                 }
@@ -933,7 +1059,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
         const float qa = sqrtf(qn[row]);
         const float ra = sqrtf(__uint_as_float(*rmax_bits));
         const float E = err_coef * (qa + ra) * (qa + ra);
-        const bool cert = (nvalid < kp) || (Dk * (1.0f + edir) <= T - E);
+        const bool cert = (nvalid < kp) || (Dk * (1.0f + edir) <= T - E && split_range(*rmax_bits));
         if (!cert && lane == 0) {
             int p = atomicAdd(fb_count, 1);
             fb_rows[p] = (int32_t)row;
@@ -1101,6 +1227,52 @@ knn_status stage_matrix(ScratchAlloc& ws, const knn_matrix& X, int kind, void** 
     return KNN_OK;
 }
 
+// Norms, largest norm (*maxn, zeroed beforehand) and staged rows of a matrix
+// for the FP32 Gram.  kind: KNN_SPLIT or KNN_F16.
+static void launch_full(int kind, const knn_matrix& X, void* Xs, int ldp, float* norms, unsigned* maxn,
+                        hipStream_t st)
+{
+    const unsigned ng = (unsigned)std::min<int64_t>(ceil_div(X.n, 32), 4096);
+    const unsigned sg = (unsigned)std::min<int64_t>(ceil_div(X.n * (ldp / 8), 256), 16384);
+#define KNN_FULL(DT)                                                                                             \
+    norm_kernel<DT><<<ng, 256, 0, st>>>(X.data, X.n, X.d, X.ld, norms, maxn);                                    \
+    if (kind == KNN_SPLIT)                                                                                       \
+        split_kernel<DT, KNN_SPLIT><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn);       \
+    else                                                                                                         \
+        split_kernel<DT, KNN_F16><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn)
+    if (X.dtype == KNN_F32) {
+        KNN_FULL(KNN_F32);
+    } else if (X.dtype == KNN_BF16) {
+        KNN_FULL(KNN_BF16);
+    } else {
+        KNN_FULL(KNN_F16);
+    }
+#undef KNN_FULL
+}
+
+static knn_status stage_full(ScratchAlloc& ws, const knn_matrix& X, int kind, void** Xs, int* ldp, float** norms,
+                             unsigned* maxn, hipStream_t st)
+{
+    *ldp = (int)round_up(X.d, kind == KNN_SPLIT ? 32 : 64);
+    knn_status r = ws.alloc(Xs, (size_t)X.n * (size_t)(*ldp) * (kind == KNN_SPLIT ? 4 : 2));
+    if (r != KNN_OK) return r;
+    if ((r = ws.alloc(norms, (size_t)X.n)) != KNN_OK) return r;
+    launch_full(kind, X, *Xs, *ldp, *norms, maxn, st);
+    KNN_HIP(hipGetLastError());
+    return KNN_OK;
+}
+
+// Bound of a GEMM distance's error, in units of u (|q| + |r|)^2, u = 2^-24:
+// each of the m products' additions (three products per element of split
+// rows) changes a partial sum of magnitude at most |q||r| by at most 2u of it
+// (truncated; u if rounded), so the dot product is off by 2 m u |q||r| and the
+// distance by twice that, m (|q| + |r|)^2 at most; the parts' own rounding
+// adds 12 u |q||r| to the dot product, 6 here, the norms and the final sum
+// less than 2.  Measured on the benchmark's data shapes, d = 17 .. 784: at
+// most 11 (16 on the FP32 MFMA's own sums), rms 0.61 to 0.90 of the FP32
+// MFMA's error against 64 bits.
+static float split_err(int d, int kind) { return (float)((kind == KNN_SPLIT ? 3 : 1) * round_up(d, 16) + 8); }
+
 // Zero n words (a fill kernel rather than hipMemsetAsync, so that no memset
 // node is recorded when a caller captures the stream).
 __global__ __launch_bounds__(64) void zero_words_kernel(unsigned* __restrict__ p, int64_t n)
@@ -1238,10 +1410,13 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         return fail(KNN_ENOTSUP, "rerank_k and k above 32 are not supported by the exact path");
     if (budget < 0) return fail(KNN_EINVAL, "workspace limit must be >= 0");
     if (Q.n == 0) return KNN_OK;
-    // staged element kind: FP32, or the 16-bit type of the MFMA form
-    const int kind = precision == KNN_PREC_BF16 ? KNN_BF16 : (precision == KNN_PREC_FP16 ? KNN_F16 : KNN_F32);
-    const bool bf = kind != KNN_F32;
-    if (kind == KNN_F32 && R.d <= kRankDirectD)
+    // staged element kind: the 16-bit type of the MFMA form; in FP32, split
+    // FP16 pairs, or one FP16 value for 16-bit inputs (whose low part is 0)
+    const bool full = precision == KNN_PREC_FP32;
+    const int kind = precision == KNN_PREC_BF16 ? KNN_BF16
+                     : full && R.dtype == KNN_F32 ? KNN_SPLIT : KNN_F16;
+    const bool bf = !full;
+    if (full && R.d <= kRankDirectD)
         return exact_direct_impl(Q, R, q_self, self_mode, k, out_kind, out_idx, out_dist, st, ws, budget);
 
     // query chunk: the largest multiple of the tile height that fits
@@ -1261,16 +1436,19 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     }
 
     knn_status r;
-    unsigned* small = nullptr;   // [0] = max ref norm bits, [1] = fallback count, [2] = fallback parts done
+    // [0] = max ref norm bits, [1] = fallback count, [2] = fallback parts done,
+    // [3] = max query norm bits (FP32, Q != R)
+    unsigned* small = nullptr;
     r = ws.alloc(&small, 4);
     if (r != KNN_OK) return r;
     zero_words_kernel<<<1, 64, 0, st>>>(small, 4);
     void *Rs = nullptr, *Qb = nullptr;
     float *rn = nullptr, *qnb = nullptr;
     int ldp = 0;
-    r = stage_matrix(ws, R, kind, &Rs, &ldp, &rn, small, st, nullptr, 0);
+    if (full) r = stage_full(ws, R, kind, &Rs, &ldp, &rn, small, st);
+    else r = stage_matrix(ws, R, kind, &Rs, &ldp, &rn, small, st, nullptr, 0);
     if (r != KNN_OK) return r;
-    const size_t eb = bf ? 2 : 4;
+    const size_t eb = kind == KNN_SPLIT ? 4 : 2;
     if (!same) {
         if ((r = ws.alloc(&Qb, (size_t)qc * ldp * eb)) != KNN_OK) return r;
         if ((r = ws.alloc(&qnb, (size_t)qc)) != KNN_OK) return r;
@@ -1285,11 +1463,13 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     r = ws.alloc(&fb_rows, (size_t)qc);
     if (r != KNN_OK) return r;
 
-    const bool ares = ldp <= (bf ? TileCfg<KNN_BF16>::AMAX : TileCfg<KNN_F32>::AMAX);
-    // GEMM error bound (FP32): (d + 3) u (|q| + max|r|)^2 with u = 2^-24;
+    // row stride in staged units (a split element is two)
+    const int lds = kind == KNN_SPLIT ? 2 * ldp : ldp;
+    const bool ares = lds <= (kind == KNN_SPLIT ? TileCfg<KNN_SPLIT>::AMAX : TileCfg<KNN_F16>::AMAX);
+    // GEMM error bound (FP32): split_err u (|q| + max|r|)^2 with u = 2^-24;
     // re-rank bound: (d/16 + 8) u relative.
     const float u = 5.9604645e-08f;
-    const float err_coef = (float)(R.d + 3) * u * 1.01f;
+    const float err_coef = split_err(R.d, kind) * u * 1.01f;
     const float edir = (float)(R.d / 16 + 8) * u;
     const int certify = bf ? 0 : 1;
     int* fb_count = (int*)(small + 1);
@@ -1299,21 +1479,24 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         const int64_t nq = Q.n - q0 < qc ? Q.n - q0 : qc;
         const void* Qs;
         const float* qn;
+        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(small + 1, 3);
         if (same) {
             Qs = (const char*)Rs + (size_t)q0 * ldp * eb;
             qn = rn + q0;
         } else {
             const knn_matrix Qc = {(const char*)Q.data + (size_t)q0 * Q.ld * qeb, nq, Q.d, Q.ld, Q.dtype};
-            launch_stage_kind(kind, Qc, Qb, ldp, qnb, nullptr, nullptr, 0, st);
+            if (full) launch_full(kind, Qc, Qb, ldp, qnb, small + 3, st);
+            else launch_stage_kind(kind, Qc, Qb, ldp, qnb, nullptr, nullptr, 0, st);
             Qs = Qb;
             qn = qnb;
         }
         const int32_t* qself = self_mode == 2 ? q_self + q0 : nullptr;
-        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(small + 1, 2);
+        
         dim3 tgrid((unsigned)ceil_div(nq, kTileRows), (unsigned)S);
+        const unsigned* qmax = !full ? nullptr : (same ? small : small + 3);
 #define KNN_TILE(BFV, AR)                                                                        \
-    exact_tile_kernel<BFV, AR><<<tgrid, 256, 0, st>>>(Qs, qn, nq, Rs, rn, R.n, ldp, qself,       \
-                                                      self_mode, q0, kp, split_len, S, small, part)
+    exact_tile_kernel<BFV, AR><<<tgrid, 256, 0, st>>>(Qs, qn, nq, Rs, rn, R.n, lds, qself,       \
+                                                      self_mode, q0, kp, split_len, S, small, qmax, part)
         if (kind == KNN_BF16) {
             if (ares) KNN_TILE(KNN_BF16, true);
             else KNN_TILE(KNN_BF16, false);
@@ -1321,8 +1504,8 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
             if (ares) KNN_TILE(KNN_F16, true);
             else KNN_TILE(KNN_F16, false);
         } else {
-            if (ares) KNN_TILE(KNN_F32, true);
-            else KNN_TILE(KNN_F32, false);
+            if (ares) KNN_TILE(KNN_SPLIT, true);
+            else KNN_TILE(KNN_SPLIT, false);
         }
 #undef KNN_TILE
         KNN_HIP(hipGetLastError());

@@ -105,3 +105,50 @@ def test_gradients_at_tile_edges(orc, d, B, precision):
         part = g[at:at + r.size]
         assert np.linalg.norm(part - np.asarray(r, np.float64).ravel()) <= tol * scale, (d, B, at)
         at += r.size
+
+
+@pytest.mark.parametrize("d", [17, 32, 33, 64, 65, 130])
+@pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
+def test_split_gram_widths_and_types(orc, d, dt):
+    """FP32 precision over row widths at the chunk edges and the input types
+    (FP32: two FP16 parts per value; 16-bit: one)."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    X = torch.from_numpy(datagen.gmm_isotropic(n=1999, d=d, seed=d)).to(dt)
+    idx, dist = knn.knn_exact(X.cuda(), 10)
+    Xv = np.ascontiguousarray(X.float().numpy())
+    O, _ = orc.exact_knn(Xv, 10)
+    res = exact_parity(Xv, np.arange(1999), idx.cpu().numpy(), dist.cpu().numpy(), O)
+    assert parity_ok(res), (d, dt, res)
+
+
+@pytest.mark.parametrize("case", ["1e15", "1e-15", "1e-17", "outlier", "zero-rows"])
+def test_split_gram_scales(orc, case):
+    """FP32 precision over the range of the power-of-two scales: large and
+    small data, data below the range (norms^2 under 2^-100: every row is
+    searched directly), one row 10^6 times the others, and rows of zeros."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    X = datagen.gmm_isotropic(n=1500, d=40, seed=7)
+    if case == "outlier":
+        X[77] *= 1e6
+    elif case == "zero-rows":
+        X[100:104] = 0.0
+    else:
+        X = X * np.float32(float(case))
+    X = np.ascontiguousarray(X.astype(np.float32))
+    idx, dist = knn.knn_exact(torch.from_numpy(X).cuda(), 8)
+    O, _ = orc.exact_knn(X, 8)
+    res = exact_parity(X, np.arange(1500), idx.cpu().numpy(), dist.cpu().numpy(), O)
+    assert parity_ok(res), (case, res)
+
+
+@pytest.mark.parametrize("qs,rs", [(1e8, 1.0), (1e-8, 1.0), (1.0, 1e8)])
+def test_split_gram_query_scale(orc, qs, rs):
+    """Queries and references of very different magnitude have a scale each."""
+    import paper_2603_04035_amd as knn
+    R = np.ascontiguousarray(datagen.gmm_isotropic(n=1500, d=40, seed=8) * np.float32(rs))
+    Q = np.ascontiguousarray(datagen.gmm_isotropic(n=130, d=40, seed=9) * np.float32(qs))
+    idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(R).cuda(), 5)
+    O, O2 = orc.exact_query(R, Q, 5)
+    assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5)
