@@ -9,17 +9,20 @@
 //     with FP32 row norms and the largest reference norm;
 //  2. tile: each workgroup owns 128 query rows and streams 128-row reference
 //     tiles through LDS; MFMA (32x32x16 FP16 or BF16 with FP32
-//     accumulation; three FP16 products for FP32) produces dot products, the epilogue forms squared
-//     distances and keeps, per query row, the best k' candidates in
-//     registers with wave-wide bitonic merges (threshold-gated, so merges
-//     are rare once lists fill).  The reference set can be split across
-//     workgroups to fill the chip; each split keeps its own lists;
-//  3. merge + re-rank: the splits' lists are merged, the best k' by GEMM
+//     accumulation; three FP16 products for FP32) produces dot products.  A
+//     first pass over a sample of the references gives every query a gate,
+//     the second appends the candidates that reach it; under a workspace
+//     limit one pass keeps, per query row, the best k' candidates in
+//     registers.  The reference set can be split across workgroups to fill
+//     the chip; each split keeps its own candidates;
+//  3. merge + re-rank: the splits' candidates are merged, the best k' by GEMM
 //     distance are re-ranked with FP32 direct differences on the original
 //     input values, and the best k kept.  In FP32 precision a row is
 //     certified when its k-th re-ranked distance is below the k'-th GEMM
 //     distance minus the worst-case GEMM error bound; other rows are
 //  4. recomputed exhaustively with direct differences.
+#include <math.h>
+
 #include <algorithm>
 #include <mutex>
 
@@ -274,6 +277,14 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // 8*(v/4) + 4*(l/32) + v%4 and column l%32 of the 32x32 block.
 __device__ inline int mfma_row(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
 
+// Value of lane - 1 (lane 0: 0): a DPP wave shift, no LDS round trip.
+__device__ __attribute__((always_inline)) inline uint64_t shift_up_u64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x138, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Adds the keys of the lanes in `m` (lanes 0..31 for the list held by lanes
 // 0..31, lanes 32..63 for the one held by lanes 32..63) to the two sorted
 // 32-key lists, keeping each list's 32 smallest.  A few keys are inserted one
@@ -287,18 +298,16 @@ __device__ inline uint64_t list_add(uint64_t list, uint64_t key, uint64_t m, int
         const uint64_t ck = seg_sort<32>(key);
         return seg_merge_sorted<32>(list, ck);
     }
-    const bool hi = lane >= 32;
-    const int from = (lane & 31) == 0 ? lane : lane - 1;
+    const bool hi = lane >= 32, first = (lane & 31) == 0;
     while (m0 | m1) {
         const uint64_t x0 = m0 ? bcast_u64(key, __builtin_ctz(m0)) : kEmptyCand;
         const uint64_t x1 = m1 ? bcast_u64(key, 32 + __builtin_ctz(m1)) : kEmptyCand;
         const uint64_t x = hi ? x1 : x0;
-        const bool gt = list > x;
-        const uint64_t gm = ballot(gt);
-        // the lane below (inside the same half) also moves up
-        const bool pgt = (lane & 31) != 0 && ((gm >> ((lane - 1) & 63)) & 1ull);
-        const uint64_t prev = shfl_u64(list, from);
-        list = gt ? (pgt ? prev : x) : list;
+        // entries above x move up one place and the first of them takes x:
+        // with the list ascending that is min(entry, max(entry below, x))
+        const uint64_t up = shift_up_u64(list);   // by every lane: a masked lane's value would not arrive
+        const uint64_t below = first ? 0ull : up;
+        list = umin64(list, umax64(below, x));
         m0 &= m0 - 1u;
         m1 &= m1 - 1u;
     }
@@ -306,44 +315,73 @@ __device__ inline uint64_t list_add(uint64_t list, uint64_t key, uint64_t m, int
 }
 
 // Rows of one pipeline step, loaded into registers: this thread's four
-// 16-byte pieces of reference row r (and of query row r when the query rows
-// stream) for chunk k0, and the reference norm of tile row tid at a tile's
-// first chunk.
+// 16-byte pieces of the 128 reference rows' chunk k0 (and of the query rows'
+// when they stream), and the reference norm of tile row tid % 128.  Piece i is bytes 16 (tid % 8) of row 32 i + tid / 8, so the 64 lanes
+// of a load read eight whole 128-byte lines.  Rows past the end, and a tile
+// past it (the step after the last), read the last row.
+struct StepRegs {
+    uint4 b0, b1, b2, b3, a0, a1, a2, a3;   // named, not arrays: arrays were left in scratch memory
+    float rn;
+};
+
 template <typename E, bool ARES>
-__device__ inline void load_step(const E* Qe, const E* Re, int64_t qrow, int64_t rt, int64_t rend, int r,
-                                 int col, int k0, int ldp, const float* rn, int tid, uint4& b0, uint4& b1,
-                                 uint4& b2, uint4& b3, uint4& a0, uint4& a1, uint4& a2, uint4& a3, float& rnv)
+__device__ inline void load_step(StepRegs& x, const E* Qb, int qlast, const E* Re, int64_t rt, int64_t rend,
+                                 int k0, int ldp, const float* rn, int tid)
 {
-    const int64_t rr = rt + r < rend ? rt + r : rend - 1;
-    const uint4* rsrc = (const uint4*)(Re + rr * ldp + k0 + col);
-    b0 = rsrc[0];
-    b1 = rsrc[1];
-    b2 = rsrc[2];
-    b3 = rsrc[3];
+    const int r0 = tid >> 3, col = (tid & 7) * 16;
+    rt = rt < rend ? rt : rend - 1;
+    const uint32_t rowb = (uint32_t)ldp * (uint32_t)sizeof(E);
+    const char* rb = (const char*)(Re + rt * ldp + k0);
+    const int rlast = rend - rt > kTileRows ? kTileRows - 1 : (int)(rend - rt) - 1;
+    auto at = [&](const char* base, int r, int last) {
+        return *(const uint4*)(base + ((uint32_t)(r < last ? r : last) * rowb + (uint32_t)col));
+    };
+    x.b0 = at(rb, r0, rlast);
+    x.b1 = at(rb, r0 + 32, rlast);
+    x.b2 = at(rb, r0 + 64, rlast);
+    x.b3 = at(rb, r0 + 96, rlast);
     if (!ARES) {
-        const uint4* qsrc = (const uint4*)(Qe + qrow * ldp + k0 + col);
-        a0 = qsrc[0];
-        a1 = qsrc[1];
-        a2 = qsrc[2];
-        a3 = qsrc[3];
+        const char* qb = (const char*)(Qb + k0);
+        x.a0 = at(qb, r0, qlast);
+        x.a1 = at(qb, r0 + 32, qlast);
+        x.a2 = at(qb, r0 + 64, qlast);
+        x.a3 = at(qb, r0 + 96, qlast);
     }
-    rnv = 0.0f;
-    if (k0 == 0 && tid < kTileRows && rt + tid < rend) rnv = rn[rt + tid];
+    // without a branch: one would hold copies of the pieces, and waits for them
+    const int nr = (tid & (kTileRows - 1)) < rlast ? (tid & (kTileRows - 1)) : rlast;
+    x.rn = rn[rt + nr];
+}
+
+// The query rows' whole length (at most AMAX elements) into LDS once.
+template <typename E, int AROW>
+__device__ inline void load_queries(E* As, const E* Qb, int qlast, int ldp, int tid)
+{
+    const int per = ldp * (int)sizeof(E) / 16;   // 16-byte pieces per row
+    for (int e = tid; e < kTileRows * per; e += 256) {
+        const int r = e / per, col = e % per;
+        const int q = r < qlast ? r : qlast;
+        *(uint4*)((char*)(As + r * AROW) + 16 * col) = *(const uint4*)((const char*)(Qb + (int64_t)q * ldp) + 16 * col);
+    }
 }
 
 // All K chunks of reference tile rt (rows rt .. rt + 127, clamped to rend)
 // against the workgroup's 128 query rows: wave w's four 32x32 accumulators
 // (query rows 32w + .., reference columns 32b + ..) are returned in acc.
 // Each step stores the registers loaded by the previous one into LDS and
-// issues the loads of the next step (the next tile's first chunk after the
-// last chunk), so the loads of a step overlap the MFMAs of the one before.
+// issues the loads of the next step (the next tile's first chunk, at rnext or
+// rt + 128, after the last chunk), so the loads of a step overlap the MFMAs of the one before.
 // With ARES the query rows are already in As (row stride AROW).
-template <int OUT, bool ARES>
+// INIT: what the sums start from.  kFromZero; kByColumn: minus half the
+// column's squared norm times the scales (hsc), so that a sum is the score
+// q.r - |r|^2 / 2 the gate tests; kTransposed: the same with the operands
+// swapped (rows = references, columns = queries: a lane's 16 sums belong to
+// one query).  Scores of references past rend are -inf.
+enum { kFromZero = 0, kByColumn = 1, kTransposed = 2 };
+
+template <int OUT, bool ARES, int INIT = kFromZero>
 __device__ __attribute__((always_inline)) inline void tile_gemm(
-    uint4& nb0, uint4& nb1, uint4& nb2, uint4& nb3, uint4& na0, uint4& na1, uint4& na2, uint4& na3, float& nrn,
-    f32x16 (&acc)[4], typename TileCfg<OUT>::E* As, typename TileCfg<OUT>::E* Bs, float* srn,
-    const typename TileCfg<OUT>::E* Qe, const typename TileCfg<OUT>::E* Re, int64_t qrow, int64_t rt,
-    int64_t rend, int ldp, const float* rn, int tid, int w, int h, int c)
+    StepRegs& nx, f32x16 (&acc)[4], typename TileCfg<OUT>::E* As, typename TileCfg<OUT>::E* Bs, float* srn,
+    const typename TileCfg<OUT>::E* Qb, int qlast, const typename TileCfg<OUT>::E* Re, int64_t rt, int64_t rend, int ldp, const float* rn, int tid, int w, int h, int c, float hsc = 0.5f, int64_t rnext = -1)
 {
     using C = TileCfg<OUT>;
     using E = typename C::E;
@@ -351,35 +389,57 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
     constexpr int AROW = ARES ? C::AROW : LROW;
     constexpr int NV = PER * (int)sizeof(E) / 16;   // 16-byte loads per thread and chunk
     static_assert(NV == 4, "four 16-byte pieces per thread and chunk");
-    const int r = tid >> 1, ph = tid & 1;              // staging: row r, half ph of the chunk
+    const int sr = tid >> 3, scol = (tid & 7) * 16;   // staging: see load_step
+    if (INIT == kFromZero) {
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
+    }
 
     for (int k0 = 0; k0 < ldp; k0 += KC) {
         __syncthreads();   // the previous step's LDS reads are done
         {
-            uint4* bdst = (uint4*)(Bs + r * LROW + ph * PER);
-            bdst[0] = nb0;
-            bdst[1] = nb1;
-            bdst[2] = nb2;
-            bdst[3] = nb3;
+            char* bd = (char*)(Bs + sr * LROW) + scol;
+            constexpr int RS = 32 * LROW * (int)sizeof(E);
+            *(uint4*)bd = nx.b0;
+            *(uint4*)(bd + RS) = nx.b1;
+            *(uint4*)(bd + 2 * RS) = nx.b2;
+            *(uint4*)(bd + 3 * RS) = nx.b3;
             if (!ARES) {
-                uint4* adst = (uint4*)(As + r * LROW + ph * PER);
-                adst[0] = na0;
-                adst[1] = na1;
-                adst[2] = na2;
-                adst[3] = na3;
+                char* ad = (char*)(As + sr * LROW) + scol;
+                *(uint4*)ad = nx.a0;
+                *(uint4*)(ad + RS) = nx.a1;
+                *(uint4*)(ad + 2 * RS) = nx.a2;
+                *(uint4*)(ad + 3 * RS) = nx.a3;
             }
-            if (k0 == 0 && tid < kTileRows) srn[tid] = nrn;
+            if (k0 == 0 && tid < kTileRows)
+                srn[tid] = rt + tid < rend ? nx.rn : (INIT == kFromZero ? 0.0f : __builtin_inff());
         }
         __syncthreads();
+        if (INIT == kByColumn && k0 == 0) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float i0 = -hsc * srn[b * 32 + c];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[b][v] = i0;
+            }
+        }
+        if (INIT == kTransposed && k0 == 0) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4) {
+                    const f32x4 x = *(const f32x4*)&srn[b * 32 + 8 * v4 + 4 * h];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[b][4 * v4 + e] = -hsc * x[e];
+                }
+        }
         // the next step's rows are in flight during this step's arithmetic
         {
             const bool last = k0 + KC >= ldp;
-            load_step<E, ARES>(Qe, Re, qrow, last ? rt + kTileRows : rt, rend, r, ph * PER, last ? 0 : k0 + KC,
-                               ldp, rn, tid, nb0, nb1, nb2, nb3, na0, na1, na2, na3, nrn);
+            load_step<E, ARES>(nx, Qb, qlast, Re, last ? (rnext >= 0 ? rnext : rt + kTileRows) : rt, rend, last ? 0 : k0 + KC, ldp, rn, tid);
+            __builtin_amdgcn_sched_barrier(0);   // or the scheduler sinks the loads below the arithmetic
         }
         // K permutation: half h of the wave supplies chunk columns
         // h*PER .. h*PER+PER-1, the same for A and B, so every column
@@ -402,22 +462,28 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
                 for (int i = 0; i < 2; ++i) {
                     const f16x8 ah = __builtin_bit_cast(f16x8, a4[i]), al = __builtin_bit_cast(f16x8, a4[i + 2]);
                     const f16x8 bh = __builtin_bit_cast(f16x8, b4[i]), bl = __builtin_bit_cast(f16x8, b4[i + 2]);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[b], 0, 0, 0);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[b], 0, 0, 0);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[b], 0, 0, 0);
+                    if constexpr (INIT == kTransposed) {
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl, ah, acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, al, acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, ah, acc[b], 0, 0, 0);
+                    } else {
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[b], 0, 0, 0);
+                    }
                 }
             } else if constexpr (OUT == KNN_BF16) {
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
-                    bf16x8 av = __builtin_bit_cast(bf16x8, a4[i]);
-                    bf16x8 bv = __builtin_bit_cast(bf16x8, b4[i]);
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, INIT == kTransposed ? b4[i] : a4[i]);
+                    const bf16x8 bv = __builtin_bit_cast(bf16x8, INIT == kTransposed ? a4[i] : b4[i]);
                     acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[b], 0, 0, 0);
                 }
             } else if constexpr (OUT == KNN_F16) {
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
-                    f16x8 av = __builtin_bit_cast(f16x8, a4[i]);
-                    f16x8 bv = __builtin_bit_cast(f16x8, b4[i]);
+                    const f16x8 av = __builtin_bit_cast(f16x8, INIT == kTransposed ? b4[i] : a4[i]);
+                    const f16x8 bv = __builtin_bit_cast(f16x8, INIT == kTransposed ? a4[i] : b4[i]);
                     acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc[b], 0, 0, 0);
                 }
             } else {
@@ -450,6 +516,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
     const int32_t* __restrict__ q_self, int self_mode, int64_t self_base, int kp, int64_t split_len, int S,
     const unsigned* __restrict__ rmax_bits, const unsigned* __restrict__ qmax_bits, uint64_t* __restrict__ part)
 {
+    constexpr int INIT = ARES ? kByColumn : kFromZero;
     using C = TileCfg<OUT>;
     using E = typename C::E;
     constexpr int KC = C::KC, LROW = C::LROW, PER = KC / 2;
@@ -490,58 +557,48 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         list[v] = kEmptyList;
-        lim[v] = q0 + w * 32 + mfma_row(v, h) < nq ? -__builtin_inff() : __builtin_inff();
+        const int64_t row = q0 + w * 32 + mfma_row(v, h);
+        lim[v] = row >= nq ? __builtin_inff() : -__builtin_inff();
     }
 
-    const E* Qe = (const E*)Qs;
+    const E* Qb = (const E*)Qs + q0 * ldp;
     const E* Re = (const E*)Rs;
-    const int r = tid >> 1, ph = tid & 1;              // staging: row r, half ph of the chunk
-    const int64_t qrow = q0 + r < nq ? q0 + r : nq - 1;
-    if (ARES) {
-        // whole query rows (ldp <= AMAX elements) into LDS once
-        const uint4* src = (const uint4*)(Qe + qrow * ldp + ph * (ldp / 2));
-        uint4* dst = (uint4*)(As + r * AROW + ph * (ldp / 2));
-        const int nv = ldp / 2 * (int)sizeof(E) / 16;
-        for (int i = 0; i < nv; ++i) dst[i] = src[i];
-    }
+    const int qlast = nq - q0 > kTileRows ? kTileRows - 1 : (int)(nq - q0) - 1;
+    if (ARES) load_queries<E, AROW>(As, Qb, qlast, ldp, tid);
 
     // prologue: the first step's rows (addresses are clamped to valid rows,
     // so a load past the split's end is harmless)
-    static_assert(NV == 4, "four 16-byte pieces per thread and chunk");
-    uint4 nb0, nb1, nb2, nb3, na0 = {}, na1 = {}, na2 = {}, na3 = {};
-    float nrn;
-    load_step<E, ARES>(Qe, Re, qrow, rbeg, rend, r, ph * PER, 0, ldp, rn, tid, nb0, nb1, nb2, nb3, na0, na1,
-                       na2, na3, nrn);
+    StepRegs nx;
+    load_step<E, ARES>(nx, Qb, qlast, Re, rbeg, rend, 0, ldp, rn, tid);
     for (int64_t rt = rbeg; rt < rend; rt += kTileRows) {
         f32x16 acc[4];
-        tile_gemm<OUT, ARES>(nb0, nb1, nb2, nb3, na0, na1, na2, na3, nrn, acc, As, Bs, srn, Qe, Re, qrow, rt, rend,
-                            ldp, rn, tid, w, h, c);
+        tile_gemm<OUT, ARES, INIT>(nx, acc, As, Bs, srn, Qb, qlast, Re, rt, rend, ldp, rn, tid, w, h, c, hsc);
 
         // epilogue: distances, threshold gate, list updates
         for (int blk = 0; blk < 4; ++blk) {
             const f32x16 cur = blk == 0 ? acc[0] : (blk == 1 ? acc[1] : (blk == 2 ? acc[2] : acc[3]));
             const float rnj = srn[blk * 32 + c];
-            const float hr = hsc * rnj;
+            const float hr = INIT == kByColumn ? 0.0f : hsc * rnj;
             // gate all 16 rows first: one branch per block when nothing passes
             uint64_t gm[16], any = 0;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                gm[v] = ballot(cur[v] - hr >= lim[v]);
+                gm[v] = ballot((INIT == kByColumn ? cur[v] : cur[v] - hr) >= lim[v]);
                 any |= gm[v];
             }
             if (!any) continue;
+            const int32_t j = (int32_t)rt + blk * 32 + c;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 if (gm[v]) {
                     // exact test; the list's current k'-th distance is the threshold
                     const int lr = w * 32 + mfma_row(v, h);
                     const float sq = sqn[lr];
-                    const int64_t j = rt + blk * 32 + c;
                     const uint64_t t0 = bcast_u64(list[v], kp - 1), t1 = bcast_u64(list[v], 32 + kp - 1);
                     const float thr = key_d2(h ? t1 : t0);
-                    float d2 = fmaf(m2, cur[v], sq + rnj);
+                    float d2 = fmaf(m2, cur[v], INIT == kByColumn ? sq : sq + rnj);
                     d2 = d2 > 0.0f ? d2 : 0.0f;
-                    const bool ok = j < rend && (int32_t)j != sself[lr] && d2 <= thr && lim[v] < __builtin_inff();
+                    const bool ok = j < (int32_t)rend && j != sself[lr] && d2 <= thr && lim[v] < __builtin_inff();
                     const uint64_t okm = ballot(ok);
                     if (okm) {
                         const uint64_t ck = ok ? make_key(d2, (uint32_t)j) : kEmptyCand;
@@ -561,6 +618,269 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
         const int64_t row = q0 + w * 32 + mfma_row(v, h);
         if (row < nq) part[(row * S + s) * kListW + c] = list[v];
     }
+}
+
+// Descending list of 32 values in registers; x enters through one max and 31
+// medians (entry q becomes the median of entries q - 1, q and x).
+__device__ inline void top_insert(float (&t)[kListW], float x)
+{
+    float up = t[0];
+    t[0] = fmaxf(up, x);
+#pragma unroll
+    for (int q = 1; q < kListW; ++q) {
+        const float old = t[q];
+        t[q] = __builtin_amdgcn_fmed3f(up, old, x);
+        up = old;
+    }
+}
+
+// Without a workspace limit the search takes the gated route: a gate per
+// query first, then one pass that only appends what reaches it.  Keeping sorted
+// lists in the tile pass (exact_tile_kernel) costs kp (1 + ln(len / kp))
+// insertions per row and split, and the 16 unrolled copies of the insertion
+// are more code than the instruction cache holds, so each waits for its code:
+// 20,011 x 50 in FP16 took 1,101 us, the same products without insertions 122.
+// The gated route takes 100 to 130 us for each of its two passes there.
+// Whole calls, lists -> gated (MI355X): 5,000 x 50 FP32 420 -> 138 us;
+// 20,011 x 50 FP16 1,200 -> 363 us; 100,000 x 50 FP32 12.4 -> 6.5 ms; 10,000
+// queries x 1M x 50 FP32 7.2 -> 5.1 ms; 20,000 x 128 FP32 1,210 -> 660 us;
+// 70,000 x 784 BF16 17.4 -> 13.8 ms, FP32 28.1 -> 27.8 ms.
+//
+// Gate.  The pass forms the scores s = q.r - |r|^2 / 2 for ntiles tiles spread
+// evenly over the references (tile i at row 128 floor(i all / ntiles); workgroup
+// (query block, p) takes tiles p, p + P, ...) with the operands swapped, so
+// that a lane holds 16 references of one query per block: the best score of
+// each group of 64 references is a max over registers, and the lane keeps the
+// best 32 group scores.  The kp-th best of a query's groups is reached by kp
+// different references, so a gate at that score, lowered by twice the
+// scores' error bound, lets the kp nearest pass.  With g groups it lies near
+// the sample's x-th score, g (1 - exp(-x / g)) = kp; groups are 16 references
+// up to 48 tiles and four up to 4, so that there are at least 32 of them.
+// gtop[(row * P + p) * 32 ..]: the workgroup's best group scores, descending.
+template <int OUT, bool ARES>
+__global__ __launch_bounds__(256, 2) void exact_gate_kernel(
+    const void* __restrict__ Qs, int64_t nq, const void* __restrict__ Rs, const float* __restrict__ rn, int64_t nr,
+    int ldp, const int32_t* __restrict__ q_self, int self_mode, int64_t self_base, int ntiles,
+    const unsigned* __restrict__ rmax_bits, const unsigned* __restrict__ qmax_bits, float* __restrict__ gtop)
+{
+    using C = TileCfg<OUT>;
+    using E = typename C::E;
+    constexpr int LROW = C::LROW, AROW = ARES ? C::AROW : LROW;
+    __shared__ __attribute__((aligned(16))) E As[kTileRows * AROW];
+    __shared__ __attribute__((aligned(16))) E Bs[kTileRows * LROW];
+    __shared__ __attribute__((aligned(16))) float srn[kTileRows];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
+    const int64_t q0 = (int64_t)blockIdx.x * kTileRows;
+    const int p = blockIdx.y, P = gridDim.y;
+    const float hsc = 0.5f * (qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f);
+    const int64_t qr = q0 + w * 32 + c;   // this lane's query
+    const int64_t self = qr >= nq ? -1 : (self_mode == 1 ? self_base + qr : (self_mode == 2 ? (int64_t)q_self[qr] : -1));
+    const E* Qb = (const E*)Qs + q0 * ldp;
+    const E* Re = (const E*)Rs;
+    const int qlast = nq - q0 > kTileRows ? kTileRows - 1 : (int)(nq - q0) - 1;
+    if (ARES) load_queries<E, AROW>(As, Qb, qlast, ldp, tid);
+    float top[kListW];
+#pragma unroll
+    for (int q = 0; q < kListW; ++q) top[q] = -__builtin_inff();
+    const int64_t all = ceil_div(nr, kTileRows);
+    StepRegs nx;
+    load_step<E, ARES>(nx, Qb, qlast, Re, (int64_t)p * all / ntiles * kTileRows, nr, 0, ldp, rn, tid);
+    for (int i = p; i < ntiles; i += P) {
+        const int64_t rt = (int64_t)i * all / ntiles * kTileRows, rnext = (int64_t)(i + P) * all / ntiles * kTileRows;
+        f32x16 acc[4];
+        tile_gemm<OUT, ARES, kTransposed>(nx, acc, As, Bs, srn, Qb, qlast, Re, rt, nr, ldp, rn, tid, w, h, c, hsc, rnext);
+        if (ballot(self >= rt && self < rt + kTileRows)) {
+            const int sr = self >= rt && self < rt + kTileRows ? (int)(self - rt) : -1;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    acc[b][v] = b * 32 + mfma_row(v, h) == sr ? -__builtin_inff() : acc[b][v];
+        }
+        if (ntiles <= 4) {
+            // few references: groups of four
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; v += 4)
+                    top_insert(top, fmaxf(fmaxf(acc[b][v], acc[b][v + 1]), fmaxf(acc[b][v + 2], acc[b][v + 3])));
+            continue;
+        }
+        float m[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            m[b] = acc[b][0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) m[b] = fmaxf(m[b], acc[b][v]);
+        }
+        if (ntiles <= 48) {   // groups of 16
+#pragma unroll
+            for (int b = 0; b < 4; ++b) top_insert(top, m[b]);
+        } else {
+            top_insert(top, fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
+        }
+    }
+    // the best 32 of both halves' groups, sorted descending
+    float z[kListW];
+#pragma unroll
+    for (int q = 0; q < kListW; ++q) z[q] = fmaxf(top[q], xor_f32(top[kListW - 1 - q], 32));
+#pragma unroll
+    for (int j = kListW / 2; j > 0; j >>= 1)
+#pragma unroll
+        for (int q = 0; q < kListW; ++q)
+            if ((q & j) == 0) {
+                const float a = z[q], b = z[q + j];
+                z[q] = fmaxf(a, b);
+                z[q + j] = fminf(a, b);
+            }
+    if (qr < nq && h == 0) {
+        f32x4* out = (f32x4*)(gtop + (qr * P + p) * kListW);
+#pragma unroll
+        for (int q = 0; q < kListW; q += 4) out[q / 4] = f32x4{z[q], z[q + 1], z[q + 2], z[q + 3]};
+    }
+}
+
+// lims[row] = the kp-th best of the row's P lists of group scores, lowered by
+// err (|q| + max|r|)^2 in scaled units.  Half a wave per row.
+__global__ __launch_bounds__(256) void gate_select_kernel(const float* __restrict__ gtop, int64_t nq, int P, int kp,
+                                                          const float* __restrict__ qn,
+                                                          const unsigned* __restrict__ rmax_bits,
+                                                          const unsigned* __restrict__ qmax_bits, float err,
+                                                          float* __restrict__ lims)
+{
+    const int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+    const int lane = threadIdx.x & 63, c = lane & 31;
+    if (row - (lane >> 5) >= nq) return;   // the whole wave
+    const int64_t r = row < nq ? row : nq - 1;
+    float a = gtop[r * P * kListW + c];
+    for (int p = 1; p < P; ++p) {
+        // two descending lists: the larger of entry i and entry 31 - i are
+        // the best 32, a bitonic sequence
+        a = fmaxf(a, gtop[(r * P + p) * kListW + (kListW - 1 - c)]);
+#pragma unroll
+        for (int j = 16; j > 0; j >>= 1) {
+            const float o = xor_f32(a, j);
+            a = (c & j) == 0 ? fmaxf(a, o) : fminf(a, o);
+        }
+    }
+    if (c == kp - 1 && row < nq) {
+        const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+        const float nrm = sqrtf(qn[row]) + sqrtf(__uint_as_float(*rmax_bits));
+        lims[row] = a - err * nrm * nrm * sc;
+    }
+}
+
+// The gated pass: the tiles and pipeline of exact_tile_kernel; a score that
+// reaches its row's gate is appended, as (score, index), to the row's buffer
+// of kCandCap entries for this split (part[(row * S + s) * kCandCap ..], counts
+// in LDS, then cnt[row * S + s]).  A row belongs to one wave, so appending
+// needs no other wave.  When a buffer has no room for another tile's 128, its
+// wave keeps the row's best 32 by (distance, index) and raises the gate to
+// the kp-th of them: rare behind a gate, and the same keys the sorted
+// lists of exact_tile_kernel would keep.
+constexpr int kCandCap = 256;
+
+template <int OUT, bool ARES>
+__global__ __launch_bounds__(256, 2) void exact_append_kernel(
+    const void* __restrict__ Qs, const float* __restrict__ qn, int64_t nq, const void* __restrict__ Rs,
+    const float* __restrict__ rn, int64_t nr, int ldp, int kp, int64_t split_len, int S,
+    const unsigned* __restrict__ rmax_bits, const unsigned* __restrict__ qmax_bits, const float* __restrict__ lims,
+    uint64_t* part, uint32_t* __restrict__ cnt)
+{
+    using C = TileCfg<OUT>;
+    using E = typename C::E;
+    constexpr int LROW = C::LROW, AROW = ARES ? C::AROW : LROW;
+    __shared__ __attribute__((aligned(16))) E As[kTileRows * AROW];
+    __shared__ __attribute__((aligned(16))) E Bs[kTileRows * LROW];
+    __shared__ float srn[kTileRows];
+    __shared__ uint32_t scnt[kTileRows];
+    __shared__ float slim[kTileRows];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
+    const int64_t q0 = (int64_t)blockIdx.x * kTileRows;
+    const int s = blockIdx.y;
+    const int64_t rbeg = (int64_t)s * split_len;
+    const int64_t rend = rbeg + split_len < nr ? rbeg + split_len : nr;
+    const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+    const float rmax = __uint_as_float(*rmax_bits);
+    const float m2 = -2.0f / sc, hsc = 0.5f * sc;
+    if (tid < kTileRows) {
+        scnt[tid] = 0u;
+        slim[tid] = q0 + tid < nq ? lims[q0 + tid] : __builtin_inff();   // rows past nq take nothing
+    }
+    const E* Qb = (const E*)Qs + q0 * ldp;
+    const E* Re = (const E*)Rs;
+    const int qlast = nq - q0 > kTileRows ? kTileRows - 1 : (int)(nq - q0) - 1;
+    if (ARES) load_queries<E, AROW>(As, Qb, qlast, ldp, tid);
+    StepRegs nx;
+    load_step<E, ARES>(nx, Qb, qlast, Re, rbeg, rend, 0, ldp, rn, tid);
+    __syncthreads();
+    float lim[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) lim[v] = slim[w * 32 + mfma_row(v, h)];
+    uint64_t* buf = part + (q0 * S + s) * kCandCap;   // row lr at buf + lr * S * kCandCap
+    const uint32_t rstride = (uint32_t)S * kCandCap;
+    for (int64_t rt = rbeg; rt < rend; rt += kTileRows) {
+        f32x16 acc[4];
+        tile_gemm<OUT, ARES, kByColumn>(nx, acc, As, Bs, srn, Qb, qlast, Re, rt, rend, ldp, rn, tid, w, h, c, hsc);
+        bool full = false;
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) {
+            uint64_t any = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) any |= ballot(acc[blk][v] >= lim[v]);
+            if (!any) continue;
+            const uint32_t j = (uint32_t)rt + blk * 32 + c;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if (acc[blk][v] >= lim[v]) {
+                    const int lr = w * 32 + mfma_row(v, h);
+                    const uint32_t pos = atomicAdd(&scnt[lr], 1u);   // below kCandCap: see `full`
+                    buf[(uint32_t)lr * rstride + pos] = ((uint64_t)__float_as_uint(acc[blk][v]) << 32) | j;
+                    full = full || pos >= kCandCap - kTileRows;
+                }
+            }
+        }
+        if (ballot(full)) {
+            // rows without room for another tile: the best 32 stay
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            const uint32_t n = lane < 32 ? scnt[w * 32 + lane] : 0u;
+            for (uint64_t m = ballot(n > kCandCap - kTileRows); m; m &= m - 1) {
+                const int r = __builtin_ctzll(m), lr = w * 32 + r;
+                const uint32_t nc = bcast_u32(n, r);
+                const float sq = qn[q0 + lr];
+                uint64_t* b = buf + (uint32_t)lr * rstride;
+                uint64_t best = kEmptyCand;
+                for (uint32_t e = 0; e < nc; e += 64) {
+                    uint64_t key = kEmptyCand;
+                    if (e + lane < nc) {
+                        const uint64_t x = b[e + lane];
+                        key = make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq), (uint32_t)x);
+                    }
+                    best = seg_merge_sorted<64>(best, seg_sort<64>(key));
+                }
+                const float t = key_d2(bcast_u64(best, kp - 1));
+                // the kept keys' scores are found again by index
+                for (uint32_t e = 0, kept = 0; e < nc; e += 64) {
+                    const uint64_t x = e + lane < nc ? b[e + lane] : 0ull;
+                    const uint64_t key = e + lane < nc ? make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq),
+                                                                  (uint32_t)x) : kEmptyCand;
+                    const bool keep = key <= bcast_u64(best, kListW - 1) && key != kEmptyCand;
+                    const uint64_t km = ballot(keep);
+                    if (keep) b[kept + rank_below(km)] = x;
+                    kept += (uint32_t)popc64(km);
+                }
+                if (lane == 0) {
+                    scnt[lr] = kListW;
+                    slim[lr] = fmaxf(slim[lr], (0.5f * (sq - t) - 4.76837158e-07f * (sq + t + rmax)) * sc);   // 8u
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lim[v] = slim[w * 32 + mfma_row(v, h)];
+        }
+    }
+    __syncthreads();
+    if (tid < kTileRows && q0 + tid < nq) cnt[(q0 + tid) * S + s] = scnt[tid];
 }
 
 // ------------------------------------------------------------ rank counts
@@ -660,18 +980,13 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
             lthr[v] = q0 + w * 32 + mfma_row(v, h) < nq ? __builtin_inff() : -__builtin_inff();
         }
     }
-    const float* Qe = Qs;
-    const float* Re = Rs;
-    const int r = tid >> 1, ph = tid & 1;
-    const int64_t qrow = q0 + r < nq ? q0 + r : nq - 1;
-    uint4 nb0, nb1, nb2, nb3, na0 = {}, na1 = {}, na2 = {}, na3 = {};
-    float nrn;
-    load_step<float, false>(Qe, Re, qrow, rbeg, rend, r, ph * PER, 0, ldp, rn, tid, nb0, nb1, nb2, nb3, na0, na1,
-                            na2, na3, nrn);
+    const float* Qb = Qs + q0 * ldp;
+    const int qlast = nq - q0 > kTileRows ? kTileRows - 1 : (int)(nq - q0) - 1;
+    StepRegs nx;
+    load_step<float, false>(nx, Qb, qlast, Rs, rbeg, rend, 0, ldp, rn, tid);
     for (int64_t rt = rbeg; rt < rend; rt += kTileRows) {
         f32x16 acc[4];
-        tile_gemm<KNN_F32, false>(nb0, nb1, nb2, nb3, na0, na1, na2, na3, nrn, acc, As, Bs, srn, Qe, Re, qrow, rt,
-                                rend, ldp, rn, tid, w, h, c);
+        tile_gemm<KNN_F32, false>(nx, acc, As, Bs, srn, Qb, qlast, Rs, rt, rend, ldp, rn, tid, w, h, c);
         // row and column bases, opaque to the compiler here so that the 64
         // (block, row) offsets derived from them are formed where they are
         // used instead of being held in registers across the whole loop
@@ -1010,12 +1325,16 @@ __global__ __launch_bounds__(256) void exact_direct_kernel(
 // One wave per query row.  Merges the S split lists (S x 32 keys), keeps
 // the best kp by GEMM distance, re-ranks them with the canonical FP32
 // direct-difference distance on the original inputs and writes the best k.
+// With cnt (nullable) the splits hold cnt[row * S + s] unsorted (score, index)
+// pairs of the gated pass instead, kCandCap apart, among them the row's own
+// index; a score becomes the distance |q|^2 - 2 s / scale.
 template <int DT>
 __global__ __launch_bounds__(256) void merge_rerank_kernel(
-    const uint64_t* __restrict__ part, int S, int64_t nq, int kp, int k,
+    const uint64_t* __restrict__ part, const uint32_t* __restrict__ cnt, const int32_t* __restrict__ q_self,
+    int self_mode, int64_t self_base, const unsigned* __restrict__ qmax_bits, int S, int64_t nq, int kp, int k,
     const void* __restrict__ Q, int64_t ldq, const void* __restrict__ R, int64_t ldr, int d,
     const float* __restrict__ qn, const unsigned* __restrict__ rmax_bits, float err_coef,
-    float edir, int certify, int out_kind, int32_t* __restrict__ out_idx,
+    float edir, int certify, int64_t avail, int out_kind, int32_t* __restrict__ out_idx,
     float* __restrict__ out_dist, int32_t* __restrict__ fb_rows, int* __restrict__ fb_count)
 {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1024,14 +1343,33 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
     // split lists (each sorted, 32 keys): even splits merge in lanes 0..31,
     // odd ones in lanes 32..63, keeping each half's 32 smallest; the two
     // halves then form one ascending 64-key sequence
-    const int sp = lane >> 5;
-    uint64_t acc = sp < S ? part[(row * S + sp) * kListW + (lane & 31)] : kEmptyCand;
-    for (int b = 2; b < S; b += 2) {
-        const uint64_t nk = b + sp < S ? part[(row * S + b + sp) * kListW + (lane & 31)] : kEmptyCand;
-        acc = seg_merge_sorted<32>(acc, nk);
+    uint64_t k0;
+    if (cnt) {
+        const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+        const float m2 = -2.0f / sc, sq = qn[row];
+        const int64_t self = self_mode == 1 ? self_base + row : (self_mode == 2 ? (int64_t)q_self[row] : -1);
+        k0 = kEmptyCand;
+        for (int s = 0; s < S; ++s) {
+            const uint32_t n = cnt[row * S + s];
+            const uint64_t* b = part + (row * S + s) * kCandCap;
+            for (uint32_t e = 0; e < n; e += 64) {
+                const uint64_t x = e + lane < n ? b[e + lane] : 0ull;
+                uint64_t key = make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq), (uint32_t)x);
+                if (e + lane >= n || (int64_t)(uint32_t)x == self) key = kEmptyCand;
+                // nothing below the 32nd so far: skip the sort
+                if (ballot(key < bcast_u64(k0, kListW - 1))) k0 = seg_merge_sorted<64>(k0, seg_sort<64>(key));
+            }
+        }
+    } else {
+        const int sp = lane >> 5;
+        uint64_t acc = sp < S ? part[(row * S + sp) * kListW + (lane & 31)] : kEmptyCand;
+        for (int b = 2; b < S; b += 2) {
+            const uint64_t nk = b + sp < S ? part[(row * S + b + sp) * kListW + (lane & 31)] : kEmptyCand;
+            acc = seg_merge_sorted<32>(acc, nk);
+        }
+        const uint64_t rv = shfl_xor_u64(acc, 31);
+        k0 = seg_bitonic_merge<64>(sp ? rv : acc);
     }
-    const uint64_t rv = shfl_xor_u64(acc, 31);
-    const uint64_t k0 = seg_bitonic_merge<64>(sp ? rv : acc);
     const uint64_t ck = lane < kp ? k0 : kEmptyCand;
     const bool cvalid = lane < kp && key_valid(ck);
     const int nvalid = popc64(ballot(cvalid));
@@ -1059,7 +1397,8 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
         const float qa = sqrtf(qn[row]);
         const float ra = sqrtf(__uint_as_float(*rmax_bits));
         const float E = err_coef * (qa + ra) * (qa + ra);
-        const bool cert = (nvalid < kp) || (Dk * (1.0f + edir) <= T - E && split_range(*rmax_bits));
+        // fewer than kp keys: certain when there are no more candidates
+        const bool cert = nvalid < kp ? (int64_t)nvalid >= avail : (Dk * (1.0f + edir) <= T - E && split_range(*rmax_bits));
         if (!cert && lane == 0) {
             int p = atomicAdd(fb_count, 1);
             fb_rows[p] = (int32_t)row;
@@ -1262,16 +1601,24 @@ static knn_status stage_full(ScratchAlloc& ws, const knn_matrix& X, int kind, vo
     return KNN_OK;
 }
 
-// Bound of a GEMM distance's error, in units of u (|q| + |r|)^2, u = 2^-24:
-// each of the m products' additions (three products per element of split
-// rows) changes a partial sum of magnitude at most |q||r| by at most 2u of it
-// (truncated; u if rounded), so the dot product is off by 2 m u |q||r| and the
-// distance by twice that, m (|q| + |r|)^2 at most; the parts' own rounding
-// adds 12 u |q||r| to the dot product, 6 here, the norms and the final sum
-// less than 2.  Measured on the benchmark's data shapes, d = 17 .. 784: at
-// most 11 (16 on the FP32 MFMA's own sums), rms 0.61 to 0.90 of the FP32
-// MFMA's error against 64 bits.
-static float split_err(int d, int kind) { return (float)((kind == KNN_SPLIT ? 3 : 1) * round_up(d, 16) + 8); }
+// Bound of a GEMM distance's error, in units of u (|q| + |r|)^2, u = 2^-24.
+// One 32x32x16 FP16 MFMA adds 16 exact products to the incoming sum c; on
+// gfx950 its result was measured within u (9 sum |products| + 2 |c|) of the
+// exact value over products and sums of every relative magnitude (addends are
+// aligned to the largest of their group and truncated, so a group of eight
+// loses up to 7u of its largest; largest error 1.005 of that expression), taken as
+// 9 and 3.  A dot product of n instructions (three per 16 elements of split
+// rows) whose sums stay below |q||r| is off by u (9 + 3 n) |q||r|, its parts'
+// own rounding adds 12 u |q||r|, and the distance by twice the total,
+// (1.5 n + 10.5) of (|q| + |r|)^2; scores sum from -|r|^2 / 2, with sums
+// below |q||r| + |r|^2 / 2: 3 n.  Norms and the final sum: less than 3.
+// Measured on the benchmark's data shapes, d = 17 .. 784: at most 11 (16 on
+// the FP32 MFMA's own sums), rms 0.61 to 0.90 of the FP32 MFMA's error.
+static float split_err(int d, int kind)
+{
+    const int64_t n = (kind == KNN_SPLIT ? 3 : 1) * ceil_div(d, 16);
+    return 3.0f * (float)n + 16.0f;
+}
 
 // Zero n words (a fill kernel rather than hipMemsetAsync, so that no memset
 // node is recorded when a caller captures the stream).
@@ -1288,6 +1635,27 @@ static int exact_splits(int64_t qn)
     const int64_t nblk = ceil_div(qn, kTileRows);
     const int64_t S = ceil_div(2048, nblk);
     return (int)(S < 1 ? 1 : (S > 4 ? 4 : S));
+}
+
+// Splits of the gated route, where a split costs no insertions: whole waves
+// of the chip's resident slots (two workgroups on each of 256 CUs) to 90%, at
+// least two tiles per split (2,000 x 300 FP32: 278 us at 2 splits, 149 at 8).
+static int filling_splits(int64_t qn, int64_t nr)
+{
+    const int64_t nblk = ceil_div(qn, kTileRows), slots = 512;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(16, ceil_div(nr, kTileRows) / 2));
+    int best = 1;
+    double fill = 0.0;
+    for (int S = 1; S <= most; ++S) {
+        const int64_t b = nblk * S;
+        const double f = (double)b / (double)(ceil_div(b, slots) * slots);
+        if (f > fill + 0.02) {
+            fill = f;
+            best = S;
+        }
+        if (fill >= 0.9) break;
+    }
+    return best;
 }
 
 static size_t elem_bytes(int dtype) { return dtype == KNN_F32 ? 4 : 2; }
@@ -1380,8 +1748,9 @@ static knn_status exact_direct_impl(const knn_matrix& Q, const knn_matrix& R, co
         float* od = out_dist + q0 * k;
         const dim3 mgrid((unsigned)ceil_div(nq, 4));
 #define KNN_MR(DT)                                                                                       \
-    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, S, nq, k, k, Qd, Q.ld, R.data, R.ld, R.d, nullptr, \
-                                                   nullptr, 0.0f, 0.0f, 0, out_kind, oi, od, nullptr, nullptr)
+    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, nullptr, nullptr, 0, 0, nullptr, S, nq, k, k, Qd, Q.ld, \
+                                                   R.data, R.ld, R.d, nullptr,                                  \
+                                                   nullptr, 0.0f, 0.0f, 0, 0, out_kind, oi, od, nullptr, nullptr)
         if (Q.dtype == KNN_F32) KNN_MR(KNN_F32);
         else if (Q.dtype == KNN_BF16) KNN_MR(KNN_BF16);
         else KNN_MR(KNN_F16);
@@ -1389,6 +1758,58 @@ static knn_status exact_direct_impl(const knn_matrix& Q, const knn_matrix& R, co
         KNN_HIP(hipGetLastError());
     }
     return KNN_OK;
+}
+
+// The tile pass of one query chunk, or (gated) the gate and the gated pass.
+struct TileArgs {
+    const void* Qs;
+    const float* qn;
+    int64_t nq;
+    const void* Rs;
+    const float* rn;
+    int64_t nr;
+    int ld;
+    const int32_t* qself;
+    int self_mode;
+    int64_t q0;
+    int kp;
+    int64_t split_len;
+    int S;
+    const unsigned *rmax, *qmax;
+    uint64_t* part;
+    bool gated;
+    int ntiles;       // the gate's sample
+    float gate_err;
+    float* lims;
+    uint32_t* cnt;
+};
+
+template <int OUT, bool ARES>
+static void launch_tiles_a(const TileArgs& a, hipStream_t st)
+{
+    const dim3 grid((unsigned)ceil_div(a.nq, kTileRows), (unsigned)a.S);
+    if (!a.gated) {
+        exact_tile_kernel<OUT, ARES><<<grid, 256, 0, st>>>(a.Qs, a.qn, a.nq, a.Rs, a.rn, a.nr, a.ld, a.qself,
+                                                           a.self_mode, a.q0, a.kp, a.split_len, a.S, a.rmax, a.qmax,
+                                                           a.part);
+        return;
+    }
+    // the group scores fit in the buffers they precede (32 floats per split)
+    float* gtop = (float*)a.part;
+    const dim3 ggrid(grid.x, (unsigned)std::min(a.S, a.ntiles));
+    exact_gate_kernel<OUT, ARES><<<ggrid, 256, 0, st>>>(a.Qs, a.nq, a.Rs, a.rn, a.nr, a.ld, a.qself, a.self_mode, a.q0,
+                                                        a.ntiles, a.rmax, a.qmax, gtop);
+    gate_select_kernel<<<(unsigned)ceil_div(a.nq, 8), 256, 0, st>>>(gtop, a.nq, (int)ggrid.y, a.kp, a.qn, a.rmax,
+                                                                    a.qmax, a.gate_err, a.lims);
+    exact_append_kernel<OUT, ARES><<<grid, 256, 0, st>>>(a.Qs, a.qn, a.nq, a.Rs, a.rn, a.nr, a.ld, a.kp, a.split_len,
+                                                         a.S, a.rmax, a.qmax, a.lims, a.part, a.cnt);
+}
+
+template <int OUT>
+static void launch_tiles(bool ares, const TileArgs& a, hipStream_t st)
+{
+    if (ares) launch_tiles_a<OUT, true>(a, st);
+    else launch_tiles_a<OUT, false>(a, st);
 }
 
 static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same,
@@ -1401,7 +1822,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     if (out_kind != KNN_OUT_L2 && out_kind != KNN_OUT_SQL2)
         return fail(KNN_EINVAL, "out_kind must be KNN_OUT_L2 or KNN_OUT_SQL2");
     if (!out_idx || !out_dist) return fail(KNN_EINVAL, "null output pointer");
-    const int64_t avail = R.n - (self_mode ? 1 : 0);
+    const int64_t avail = R.n - (self_mode ? 1 : 0);   // candidates per query
     if (k < 1 || (int64_t)k > avail) return fail(KNN_EINVAL, "k must satisfy 1 <= k <= number of candidates");
     int kp = rerank_k;
     if (kp == 0) kp = 2 * k < kListW ? 2 * k : kListW;
@@ -1434,6 +1855,8 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
                                         " bytes the staged reference set and one 128-query chunk need");
         qc = lo * kTileRows;
     }
+    // the gated route's buffers (below): at most 1 GiB per query chunk
+    if (budget == 0) qc = std::min<int64_t>(qc, 4096 * kTileRows);
 
     knn_status r;
     // [0] = max ref norm bits, [1] = fallback count, [2] = fallback parts done,
@@ -1453,19 +1876,36 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         if ((r = ws.alloc(&Qb, (size_t)qc * ldp * eb)) != KNN_OK) return r;
         if ((r = ws.alloc(&qnb, (size_t)qc)) != KNN_OK) return r;
     }
-    const int S0 = exact_splits(qc);
+    // row stride in staged units (a split element is two)
+    const int lds = kind == KNN_SPLIT ? 2 * ldp : ldp;
+    const bool ares = lds <= (kind == KNN_SPLIT ? TileCfg<KNN_SPLIT>::AMAX : TileCfg<KNN_F16>::AMAX);
+    // the gated route needs 2 KiB of scratch per row and split: not under a
+    // limit; with at most four tiles of long rows its second pass over the
+    // products costs more than the insertions (500 x 784 BF16: 207 against 154 us)
+    const bool gated = budget == 0 && (ares || R.n > 4 * kTileRows);
+    const int S0 = gated ? filling_splits(qc, R.n) : exact_splits(qc);
     const int64_t split_len = round_up(ceil_div(R.n, S0), kTileRows);
     const int S = (int)ceil_div(R.n, split_len);
     uint64_t* part = nullptr;
-    r = ws.alloc(&part, (size_t)qc * S * kListW);
+    r = ws.alloc(&part, (size_t)qc * S * (gated ? kCandCap : kListW));
     if (r != KNN_OK) return r;
     int32_t* fb_rows = nullptr;
     r = ws.alloc(&fb_rows, (size_t)qc);
     if (r != KNN_OK) return r;
+    float* lims = nullptr;
+    uint32_t* cnt = nullptr;
+    int ntiles = 0;
+    if (gated) {
+        if ((r = ws.alloc(&lims, (size_t)qc)) != KNN_OK) return r;
+        if ((r = ws.alloc(&cnt, (size_t)qc * S)) != KNN_OK) return r;
+        // The gate's sample of m references costs m scores per row and leaves
+        // about 41 R.n / m keys to append, each as much as some 320 / steps
+        // scores (steps: 128-byte chunks of a row): least in all at m =
+        // sqrt(13,200 R.n / steps)
+        const double m = sqrt(13200.0 * (double)R.n * 64.0 / (double)lds);
+        ntiles = (int)std::min<int64_t>(ceil_div(R.n, kTileRows), std::max<int64_t>(32, (int64_t)(m / kTileRows)));
+    }
 
-    // row stride in staged units (a split element is two)
-    const int lds = kind == KNN_SPLIT ? 2 * ldp : ldp;
-    const bool ares = lds <= (kind == KNN_SPLIT ? TileCfg<KNN_SPLIT>::AMAX : TileCfg<KNN_F16>::AMAX);
     // GEMM error bound (FP32): split_err u (|q| + max|r|)^2 with u = 2^-24;
     // re-rank bound: (d/16 + 8) u relative.
     const float u = 5.9604645e-08f;
@@ -1492,22 +1932,12 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         }
         const int32_t* qself = self_mode == 2 ? q_self + q0 : nullptr;
         
-        dim3 tgrid((unsigned)ceil_div(nq, kTileRows), (unsigned)S);
         const unsigned* qmax = !full ? nullptr : (same ? small : small + 3);
-#define KNN_TILE(BFV, AR)                                                                        \
-    exact_tile_kernel<BFV, AR><<<tgrid, 256, 0, st>>>(Qs, qn, nq, Rs, rn, R.n, lds, qself,       \
-                                                      self_mode, q0, kp, split_len, S, small, qmax, part)
-        if (kind == KNN_BF16) {
-            if (ares) KNN_TILE(KNN_BF16, true);
-            else KNN_TILE(KNN_BF16, false);
-        } else if (kind == KNN_F16) {
-            if (ares) KNN_TILE(KNN_F16, true);
-            else KNN_TILE(KNN_F16, false);
-        } else {
-            if (ares) KNN_TILE(KNN_SPLIT, true);
-            else KNN_TILE(KNN_SPLIT, false);
-        }
-#undef KNN_TILE
+        const TileArgs ta = {Qs, qn, nq, Rs, rn, R.n, lds, qself, self_mode, q0, kp, split_len, S, small, qmax, part,
+                             gated, ntiles, 2.0f * split_err(R.d, kind) * u, lims, cnt};
+        if (kind == KNN_BF16) launch_tiles<KNN_BF16>(ares, ta, st);
+        else if (kind == KNN_F16) launch_tiles<KNN_F16>(ares, ta, st);
+        else launch_tiles<KNN_SPLIT>(ares, ta, st);
         KNN_HIP(hipGetLastError());
 
         const void* Qd = (const char*)Q.data + (size_t)q0 * Q.ld * qeb;
@@ -1515,9 +1945,9 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         float* od = out_dist + q0 * k;
         dim3 mgrid((unsigned)ceil_div(nq, 4));
 #define KNN_MR(DT)                                                                              \
-    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, S, nq, kp, k, Qd, Q.ld, R.data, R.ld,  \
+    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, cnt, qself, self_mode, q0, qmax, S, nq, kp, k, Qd, Q.ld, R.data, R.ld,  \
                                                    R.d, qn, small, err_coef, edir, certify,     \
-                                                   out_kind, oi, od, fb_rows, fb_count)
+                                                   avail, out_kind, oi, od, fb_rows, fb_count)
         if (Q.dtype == KNN_F32) KNN_MR(KNN_F32);
         else if (Q.dtype == KNN_BF16) KNN_MR(KNN_BF16);
         else KNN_MR(KNN_F16);
@@ -1751,8 +2181,9 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
         const float err_coef = (float)(X.d + 3) * u * 1.01f, edir = (float)(X.d / 16 + 8) * u;
         const dim3 mgrid((unsigned)ceil_div(n, 4));
 #define KNN_QMR(DT)                                                                                            \
-    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, S, n, kp, k, X.data, X.ld, X.data, X.ld, X.d, xn, small, \
-                                                   err_coef, edir, 1, KNN_OUT_SQL2, Hn, Hd, fb_rows, fb_count);    \
+    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, nullptr, nullptr, 1, 0, nullptr, S, n, kp, k, X.data, X.ld, \
+                                                   X.data, X.ld, X.d, xn, small,                                 \
+                                                   err_coef, edir, 1, n - 1, KNN_OUT_SQL2, Hn, Hd, fb_rows, fb_count); \
     exact_fallback_kernel<DT><<<1024, 256, 0, st>>>(fb_rows, fb_count, X.data, X.ld, X.data, X.ld, n, X.d, nullptr,  \
                                                     1, 0, k, KNN_OUT_SQL2, Hn, Hd, part, n * S,                    \
                                                     (unsigned*)fb_count + 1)

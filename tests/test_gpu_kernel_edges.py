@@ -152,3 +152,42 @@ def test_split_gram_query_scale(orc, qs, rs):
     idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(R).cuda(), 5)
     O, O2 = orc.exact_query(R, Q, 5)
     assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5)
+
+
+@pytest.mark.parametrize("n", [400, 513, 6200, 20_001])
+@pytest.mark.parametrize("precision,d", [("fp32", 40), ("fp32", 100), ("bf16", 40), ("fp16", 100)])
+def test_gated_route_equals_list_route(n, precision, d):
+    """The gated route (no scratch limit) against the sorted-list route (a
+    limit that fits everything) over the gate's group sizes (up to 4, up to 48
+    and more tiles) and a last tile of one row: the same neighbours and
+    distances, rows sorted by cluster so that a row's candidates crowd one
+    split."""
+    import paper_2603_04035_amd as knn
+    X = datagen.gmm_isotropic(n=n, d=d, comps=12, seed=n)
+    X = np.ascontiguousarray(X[np.argsort(X[:, 0] + 100 * (X @ X[:12].T).argmax(1), kind="stable")])
+    Xd = torch.from_numpy(X).cuda()
+    rows = torch.arange(n, dtype=torch.int32)
+    a = knn.knn_exact(Xd, 14, precision=precision)
+    b = knn.knn_exact_query(Xd, Xd, 14, q_self=rows, precision=precision, workspace_limit=4 << 30)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+def test_gated_route_full_buffers(orc):
+    """Buffers that overflow their 256 entries: every reference of the gate's
+    sample (tiles 0, 2, 4, ... of the order below) is far from the queries and
+    the near ones sit together between them, so a loose gate lets thousands
+    pass and the rows' best 32 are kept again and again."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    rng = np.random.default_rng(3)
+    n, d = 40_000, 24
+    X = (rng.normal(size=(n, d)) + 30.0).astype(np.float32)
+    near = rng.normal(size=(6000, d)).astype(np.float32)
+    X[17_000:23_000] = near                       # 47 tiles in a row hold the queries' neighbours
+    Q = np.ascontiguousarray(near[:257])
+    idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda(), 10,
+                                    q_self=torch.arange(17_000, 17_257, dtype=torch.int32))
+    rows = np.arange(17_000, 17_257)
+    O, _ = orc.exact_knn(X, 10, rows=rows)
+    res = exact_parity(X, rows, idx.cpu().numpy(), dist.cpu().numpy(), O)
+    assert parity_ok(res), res
