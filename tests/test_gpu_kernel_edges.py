@@ -191,3 +191,21 @@ def test_gated_route_full_buffers(orc):
     O, _ = orc.exact_knn(X, 10, rows=rows)
     res = exact_parity(X, rows, idx.cpu().numpy(), dist.cpu().numpy(), O)
     assert parity_ok(res), res
+
+
+@pytest.mark.parametrize("n,d", [(2, 3), (63, 50), (65, 31), (300, 33), (500, 784), (1000, 64)])
+def test_small_search(orc, n, d):
+    """The one-launch search at its edges: fewer references than a batch of
+    64, one more, chunks of 32 coordinates and their remainders."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    X = datagen.gmm_isotropic(n=n, d=d, comps=3, seed=n + d)
+    k = min(n - 1, 32)
+    idx, dist = knn.knn_exact(torch.from_numpy(X).cuda(), k)
+    O, _ = orc.exact_knn(X, k)
+    res = exact_parity(X, np.arange(n), idx.cpu().numpy(), dist.cpu().numpy(), O)
+    assert parity_ok(res), res
+    Q = np.ascontiguousarray(X[:min(n, 5)] + np.float32(0.25))
+    idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda(), k)
+    O, O2 = orc.exact_query(X, Q, k)
+    assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5)
