@@ -372,7 +372,8 @@ knn_status knn_proj_seed(knn_matrix X, const float* Z, int32_t m, const float* d
  *  iters   subspace iterations (0: 200); the eigenvectors come from an
  *          m = min(d, 80, max(2p, p + 16))-column subspace iteration with a
  *          final Rayleigh-Ritz step (exact when m = d), so their error falls
- *          as (lambda_{m+1} / lambda_p)^iters.
+ *          as (lambda_{m+1} / lambda_p)^iters (or faster: the iteration is
+ *          filtered by Chebyshev polynomials).
  *  Z       device, n x p float.   components  device, nullable, d x p
  *          double (row-major).   eigenvalues  device, nullable, p double.
  *  mean    device, nullable, d double.

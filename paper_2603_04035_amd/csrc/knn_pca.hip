@@ -9,11 +9,12 @@
 //               operands), partials summed in chunk order: no atomics, so
 //               the result does not depend on scheduling;
 //  3. subspace: m = min(d, 80, max(2p, p + 16)) columns V (seeded, hashed
-//               values) iterate V <- orth(C V) (C V on
-//               v_mfma_f64_16x16x4_f64), orthonormalised by one shifted
-//               Cholesky-QR pass every q products (q from the basis'
-//               estimated conditioning, 1..8) and by shifted + two plain
-//               passes after the last (Cholesky-QR3); then
+//               values) are filtered by Chebyshev polynomials of C that damp
+//               the eigenvalues below the block's smallest Rayleigh quotient
+//               (Zhou and Saad 2007): rounds of q products C Y on
+//               v_mfma_f64_16x16x4_f64, each round ended by one shifted
+//               Cholesky-QR pass on columns scaled to norm 1, and after the
+//               last by shifted + two plain passes (Cholesky-QR3); then
 //               Rayleigh-Ritz: H = V^T C V, whose eigenpairs come from cyclic
 //               Jacobi rotations (one workgroup, round-robin pairing), and
 //               the p largest Ritz pairs are kept; each eigenvector's entry
@@ -185,7 +186,8 @@ __global__ __launch_bounds__(256) void pca_identity_kernel(int d, int m, double*
     V[e] = (e / d == e % d) ? 1.0 : 0.0;
 }
 
-// W = C V on v_mfma_f64_16x16x4_f64, one workgroup per 16 x 16 block of W
+// W = alpha (C V - shift V) - P on v_mfma_f64_16x16x4_f64 (P nullable; alpha
+// = 1, shift = 0: the plain product), one workgroup per 16 x 16 block of W
 // (rows a of C, columns j of V).  K runs in blocks of 16, block b taken by
 // wave b % 4 (four blocks per round, loads first): lane l (r = l % 16, g = l / 16) holds C[a0 + r][k0 + 4g ..
 // +3] and V[j0 + r][k0 + 4g .. +3], and step s multiplies the k = k0 + 4g +
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(256) void pca_identity_kernel(int d, int m, double*
 // waves' sums are added in wave order.  Accumulator item i of lane l is
 // W[j0 + r][a0 + g + 4i].
 __global__ __launch_bounds__(256) void pca_cv_kernel(const double* __restrict__ C, const double* __restrict__ V, int d,
-                                                     int m, double* __restrict__ W)
+                                                     int m, double alpha, double shift, const double* P, double* W)
 {
     __shared__ double part[3][64][4];
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, r = l & 15, g = l >> 4;
@@ -228,7 +230,12 @@ __global__ __launch_bounds__(256) void pca_cv_kernel(const double* __restrict__ 
         for (int i = 0; i < 4; ++i) {
             const double v = ((acc[i] + part[0][l][i]) + part[1][l][i]) + part[2][l][i];
             const int a = a0 + g + 4 * i;
-            if (a < d) W[(int64_t)(j0 + r) * d + a] = v;
+            if (a < d) {
+                const int64_t e = (int64_t)(j0 + r) * d + a;   // P may be W itself
+                double x = shift != 0.0 ? v - shift * V[e] : v;
+                x = alpha != 1.0 ? alpha * x : x;
+                W[e] = P ? x - P[e] : x;
+            }
         }
     }
 }
@@ -257,6 +264,35 @@ __global__ __launch_bounds__(256) void pca_gram_small_kernel(const double* __res
     }
 }
 
+// out[j] = <V_j, Y_j>, out[m + j] = <V_j, V_j> (one workgroup per column, a
+// fixed-order tree): the columns' Rayleigh quotients when Y = C V.
+__global__ __launch_bounds__(256) void pca_rayleigh_kernel(const double* __restrict__ V, const double* __restrict__ Y,
+                                                           int d, int m, double* __restrict__ out)
+{
+    __shared__ double ra[256], rb[256];
+    const int j = blockIdx.x, t = threadIdx.x;
+    double a = 0.0, b = 0.0;
+    for (int i = t; i < d; i += 256) {
+        const double v = V[(int64_t)j * d + i];
+        a = fma(v, Y[(int64_t)j * d + i], a);
+        b = fma(v, v, b);
+    }
+    ra[t] = a;
+    rb[t] = b;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (t < o) {
+            ra[t] += ra[t + o];
+            rb[t] += rb[t + o];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        out[j] = ra[0];
+        out[m + j] = rb[0];
+    }
+}
+
 // One Cholesky-QR pass: V = W R^{-1}, where S = W^T W = R^T R (R upper
 // triangular).  Every workgroup factors S (its entries in registers, 25 per
 // thread), the same operations in each, so all hold the same factor; then
@@ -268,8 +304,11 @@ __global__ __launch_bounds__(256) void pca_gram_small_kernel(const double* __res
 // the end M S = D L^T with S = L D L^T (L unit lower triangular, D the
 // pivots) and M = L^{-1}.  Then R = D^{1/2} L^T and R^{-1}[i][j] = M[j][i] /
 // sqrt(D[j]): no triangular solve is needed.  M's strict lower triangle sits
-// in the lower half of S, which the upper-triangle elimination never reads.  With shift_rel > 0 the factored matrix is
-// S + s I, s = shift_rel * trace(S) (shifted Cholesky-QR: V spans the same
+// in the lower half of S, which the upper-triangle elimination never reads.
+// The columns of W are first scaled to norm 1 (S to unit diagonal; a zero
+// column stays): filtered columns differ by many orders of magnitude in length
+// alone, which then costs nothing.  With shift_rel > 0 the factored matrix is
+// S + s I, s = shift_rel * m (shifted Cholesky-QR: V spans the same
 // space as W, but is only near-orthonormal, and no pivot can fail however
 // badly W is conditioned).  A non-positive pivot (W of lower rank than m,
 // unshifted) is replaced by 1 and flagged, which keeps the factor finite.
@@ -285,41 +324,27 @@ __global__ __launch_bounds__(256) void pca_cholqr_kernel(const double* __restric
     __shared__ double S[kPcaMaxM * kPcaMaxM];   // the result: upper R-scaled rows, strict lower M
     __shared__ double rowk[2][kPcaMaxM];         // the step's pivot row (double-buffered)
     __shared__ double rinv[kPcaMaxM];
-    __shared__ double diag[kPcaMaxM];
-    __shared__ double shift_;
+    __shared__ double dinv[kPcaMaxM];            // the columns' scales
     const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
     // thread (ty, tx) owns entries (ty + 16u, tx + 16q), u, q < NJ, held in
     // registers through the whole elimination; only the pivot row of each
     // step goes through LDS (one barrier per step)
     constexpr int NJ = kPcaMaxM / 16;
+    if (tid < m) {
+        const double v = Sg[tid * m + tid];
+        dinv[tid] = v > 0.0 ? 1.0 / sqrt(v) : 1.0;
+    }
+    __syncthreads();
     double x[NJ][NJ];
 #pragma unroll
     for (int u = 0; u < NJ; ++u)
 #pragma unroll
         for (int q = 0; q < NJ; ++q) {
             const int i = ty + 16 * u, j = tx + 16 * q;
-            x[u][q] = i < m && j < m && j >= i ? Sg[i * m + j] : 0.0;
+            x[u][q] = i < m && j < m && j >= i ? Sg[i * m + j] * dinv[i] * dinv[j] : 0.0;
+            // S + s I: the same span, positive pivots however badly W is conditioned
+            if (i == j && i < m) x[u][q] += shift_rel * (double)m;
         }
-    if (shift_rel > 0.0) {
-        // S + s I with s = shift_rel * trace(S): the same span, positive
-        // pivots however badly W is conditioned
-        if (ty == tx) {
-#pragma unroll
-            for (int u = 0; u < NJ; ++u) diag[ty + 16 * u] = x[u][u];
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double tr = 0.0;
-            for (int k = 0; k < m; ++k) tr += diag[k];
-            shift_ = shift_rel * tr;
-        }
-        __syncthreads();
-        if (ty == tx) {
-#pragma unroll
-            for (int u = 0; u < NJ; ++u)
-                if (ty + 16 * u < m) x[u][u] += shift_;
-        }
-    }
     if (ty == 0) {
 #pragma unroll
         for (int q = 0; q < NJ; ++q) rowk[0][tx + 16 * q] = x[0][q];
@@ -370,7 +395,8 @@ __global__ __launch_bounds__(256) void pca_cholqr_kernel(const double* __restric
 #pragma unroll
         for (int q = 0; q < NJ; ++q) {
             const int i = ty + 16 * u, j = tx + 16 * q;
-            if (i < m && j < m) S[i * m + j] = x[u][q];
+            // M's column j multiplies column j of W: its scale goes in here
+            if (i < m && j < m) S[i * m + j] = i > j ? x[u][q] * dinv[j] : (i == j ? dinv[i] : x[u][q]);
         }
     __syncthreads();
     // V = W R^{-1} for rows a0 .. a0 + 63 and the workgroup's eight columns:
@@ -396,7 +422,7 @@ __global__ __launch_bounds__(256) void pca_cholqr_kernel(const double* __restric
 #pragma unroll
                 for (int q = 0; q < kPcaCols; ++q) {
                     const int j = j0 + q;
-                    if (i < ie && j < m && i <= j) sp[q] = i == j ? sp[q] + wv[u] : fma(wv[u], S[j * m + i], sp[q]);
+                    if (i < ie && j < m && i <= j) sp[q] = fma(wv[u], S[j * m + i], sp[q]);
                 }
             }
         }
@@ -416,61 +442,81 @@ __global__ __launch_bounds__(256) void pca_cholqr_kernel(const double* __restric
 }
 
 // Cyclic Jacobi on the symmetric m x m matrix H (row-major; H and the
-// rotations E held in LDS, copied back at the end), one workgroup: each sweep runs m - 1 rounds of the round-robin tournament
+// transposed rotations E^T held in LDS, copied back at the end), one
+// workgroup: each sweep runs m - 1 rounds of the round-robin tournament
 // (m even; an odd m plays a bye), every round rotating its m/2 disjoint
-// pairs (p, q) so that H[p][q] becomes 0: rows then columns, with E
-// accumulating the rotations (E starts as the identity).  Sweeps stop when
-// the off-diagonal mass (sum of squares) falls below 1e-26 of the total
-// (off-diagonal entries below 1e-13 of the norm), or after 40.
-__global__ __launch_bounds__(256) void pca_jacobi_kernel(double* __restrict__ Hg, double* __restrict__ Eg, int m)
+// pairs (p, q) so that H[p][q] becomes 0, with E accumulating the rotations (E
+// starts as the identity).  Thread (s, t), s <= t, rotates the 2 x 2 block of
+// rows p_s, q_s and columns p_t, q_t from both sides at once and writes it
+// with its mirror image: the blocks are disjoint, so a round needs one pass
+// and two barriers.  A round is latency (the angles' square roots and
+// divisions, the barriers): with rows and columns in separate passes by 256
+// threads the eigenproblem of an 80-wide block took 2.09 ms, 1.04 now.  Sweeps
+// stop when the off-diagonal mass (sum of squares) falls below 1e-26 of the
+// total (off-diagonal entries below 1e-13 of the norm), or after 40.
+constexpr int kJacThreads = 1024;
+
+__global__ __launch_bounds__(kJacThreads) void pca_jacobi_kernel(double* __restrict__ Hg, double* __restrict__ Eg, int m)
 {
     __shared__ double H[kPcaMaxM * kPcaMaxM];
-    __shared__ double E[kPcaMaxM * kPcaMaxM];
+    __shared__ double E[kPcaMaxM * kPcaMaxM];   // E^T: row j is column j of E
     __shared__ double cs[kPcaMaxM / 2], sn[kPcaMaxM / 2];
     __shared__ int pp[kPcaMaxM / 2], qq[kPcaMaxM / 2];
-    __shared__ double red[256];
+    __shared__ double red[2][kJacThreads / 64];
     const int tid = threadIdx.x;
     // V^T (C V) is symmetric up to rounding: take its symmetric part
-    for (int e = tid; e < m * m; e += 256) H[e] = 0.5 * (Hg[e] + Hg[(e % m) * m + e / m]);
-    const int mm = m + (m & 1);   // players, with a bye for odd m
-    for (int e = tid; e < m * m; e += 256) E[e] = (e / m == e % m) ? 1.0 : 0.0;
+    for (int e = tid; e < m * m; e += kJacThreads) {
+        H[e] = 0.5 * (Hg[e] + Hg[(e % m) * m + e / m]);
+        E[e] = (e / m == e % m) ? 1.0 : 0.0;
+    }
+    const int mm = m + (m & 1), np = mm / 2;   // players, with a bye for odd m
+    // this thread's block (s, t), s <= t < np, of the np (np + 1) / 2 <= 820
+    int bs = -1, bt = 0;
+    {
+        int e = tid;
+        for (int t = 0; t < np && bs < 0; ++t) {
+            if (e <= t) {
+                bs = e;
+                bt = t;
+            }
+            e -= t + 1;
+        }
+    }
     for (int sweep = 0; sweep < 40; ++sweep) {
         __syncthreads();
         double off = 0.0, tot = 0.0;
-        for (int e = tid; e < m * m; e += 256) {
+        for (int e = tid; e < m * m; e += kJacThreads) {
             const double h = H[e];
             tot += h * h;
             if (e / m != e % m) off += h * h;
         }
-        red[tid] = off;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (tid < o) red[tid] += red[tid + o];
-            __syncthreads();
+        for (int o = 32; o > 0; o >>= 1) {
+            off += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(off), o));
+            tot += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(tot), o));
         }
-        off = red[0];
-        __syncthreads();
-        red[tid] = tot;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (tid < o) red[tid] += red[tid + o];
-            __syncthreads();
+        if ((tid & 63) == 0) {
+            red[0][tid >> 6] = off;
+            red[1][tid >> 6] = tot;
         }
-        tot = red[0];
         __syncthreads();
+        off = tot = 0.0;
+        for (int w = 0; w < kJacThreads / 64; ++w) {
+            off += red[0][w];
+            tot += red[1][w];
+        }
         if (!(off > 1e-26 * tot)) break;
         for (int round = 0; round < mm - 1; ++round) {
             // pairs of this round: player 0 fixed, the others rotate
-            for (int t = tid; t < mm / 2; t += 256) {
-                int a = t == 0 ? 0 : 1 + (round + t - 1) % (mm - 1);
-                int b = 1 + (round + mm - 2 - t) % (mm - 1);
+            if (tid < np) {
+                int a = tid == 0 ? 0 : 1 + (round + tid - 1) % (mm - 1);
+                int b = 1 + (round + mm - 2 - tid) % (mm - 1);
                 if (a > b) {
                     const int x = a;
                     a = b;
                     b = x;
                 }
-                pp[t] = a;
-                qq[t] = b;
+                pp[tid] = a;
+                qq[tid] = b;
                 double c = 1.0, s = 0.0;
                 if (b < m) {
                     const double apq = H[a * m + b];
@@ -481,67 +527,50 @@ __global__ __launch_bounds__(256) void pca_jacobi_kernel(double* __restrict__ Hg
                         s = tt * c;
                     }
                 }
-                cs[t] = c;
-                sn[t] = s;
+                cs[tid] = c;
+                sn[tid] = s;
             }
             __syncthreads();
-            // rows: H[p][*], H[q][*] <- c H[p] - s H[q], s H[p] + c H[q]
-            // (pair t by threads with tid / 16 = t mod 16, entries by tid % 16)
-            constexpr int NJ = kPcaMaxM / 16;
-            for (int t = tid >> 4; t < mm / 2; t += 16) {
-                const int p = pp[t], q = qq[t];
-                if (q >= m) continue;
-                const double c = cs[t], s = sn[t];
-                double hp[NJ], hq[NJ];
-#pragma unroll
-                for (int u = 0; u < NJ; ++u) {
-                    const int col = (tid & 15) + 16 * u;
-                    hp[u] = col < m ? H[p * m + col] : 0.0;
-                    hq[u] = col < m ? H[q * m + col] : 0.0;
+            if (bs >= 0) {
+                const int p1 = pp[bs], q1 = qq[bs], p2 = pp[bt], q2 = qq[bt];
+                const bool o1 = q1 < m, o2 = q2 < m;   // not the bye
+                const double c1 = cs[bs], s1 = sn[bs], c2 = cs[bt], s2 = sn[bt];
+                const double x00 = H[p1 * m + p2], x01 = o2 ? H[p1 * m + q2] : 0.0;
+                const double x10 = o1 ? H[q1 * m + p2] : 0.0, x11 = o1 && o2 ? H[q1 * m + q2] : 0.0;
+                const double r00 = c1 * x00 - s1 * x10, r01 = c1 * x01 - s1 * x11;
+                const double r10 = s1 * x00 + c1 * x10, r11 = s1 * x01 + c1 * x11;
+                const double y00 = c2 * r00 - s2 * r01, y01 = s2 * r00 + c2 * r01;
+                const double y10 = c2 * r10 - s2 * r11, y11 = s2 * r10 + c2 * r11;
+                H[p1 * m + p2] = y00;
+                H[p2 * m + p1] = y00;
+                if (o2) {
+                    H[p1 * m + q2] = y01;
+                    H[q2 * m + p1] = y01;
                 }
-#pragma unroll
-                for (int u = 0; u < NJ; ++u) {
-                    const int col = (tid & 15) + 16 * u;
-                    if (col < m) {
-                        H[p * m + col] = c * hp[u] - s * hq[u];
-                        H[q * m + col] = s * hp[u] + c * hq[u];
-                    }
+                if (o1 && (bs != bt)) {
+                    H[q1 * m + p2] = y10;
+                    H[p2 * m + q1] = y10;
+                }
+                if (o1 && o2) {
+                    H[q1 * m + q2] = y11;
+                    H[q2 * m + q1] = y11;
                 }
             }
-            __syncthreads();
-            // columns, and the accumulated rotations E <- E J
-            for (int t = tid >> 4; t < mm / 2; t += 16) {
-                const int p = pp[t], q = qq[t];
-                if (q >= m) continue;
-                const double c = cs[t], s = sn[t];
-                double hp[NJ], hq[NJ], ep[NJ], eq[NJ];
-#pragma unroll
-                for (int u = 0; u < NJ; ++u) {
-                    const int row = (tid & 15) + 16 * u;
-                    const bool ok = row < m;
-                    hp[u] = ok ? H[row * m + p] : 0.0;
-                    hq[u] = ok ? H[row * m + q] : 0.0;
-                    ep[u] = ok ? E[row * m + p] : 0.0;
-                    eq[u] = ok ? E[row * m + q] : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < NJ; ++u) {
-                    const int row = (tid & 15) + 16 * u;
-                    if (row < m) {
-                        H[row * m + p] = c * hp[u] - s * hq[u];
-                        H[row * m + q] = s * hp[u] + c * hq[u];
-                        E[row * m + p] = c * ep[u] - s * eq[u];
-                        E[row * m + q] = s * ep[u] + c * eq[u];
-                    }
+            for (int e = tid; e < np * m; e += kJacThreads) {
+                const int t = e / m, i = e - t * m, p = pp[t], q = qq[t];
+                if (q < m) {
+                    const double c = cs[t], s = sn[t], ep = E[p * m + i], eq = E[q * m + i];
+                    E[p * m + i] = c * ep - s * eq;
+                    E[q * m + i] = s * ep + c * eq;
                 }
             }
             __syncthreads();
         }
     }
     __syncthreads();
-    for (int e = tid; e < m * m; e += 256) {
+    for (int e = tid; e < m * m; e += kJacThreads) {
         Hg[e] = H[e];
-        Eg[e] = E[e];
+        Eg[(e % m) * m + e / m] = E[e];
     }
 }
 
@@ -549,9 +578,13 @@ __global__ __launch_bounds__(256) void pca_jacobi_kernel(double* __restrict__ Hg
 // (ties by index), vectors U_j = V e_j (e_j a column of E), each sign-fixed
 // so that its entry of largest magnitude (the first such) is positive.
 // Workgroup j forms component j; U is d x p row-major, lam has p entries.
+// With `bad` (the subspace is not all of R^d) a smallest Ritz value below
+// 1e-12 of the largest flags an X of lower rank than m (its noise level is
+// some 1e-16 of the largest for exact inputs, 1e-14 for rounded ones).
 __global__ __launch_bounds__(256) void pca_ritz_kernel(const double* __restrict__ H, const double* __restrict__ E,
                                                        const double* __restrict__ V, int d, int m, int p,
-                                                       double* __restrict__ U, double* __restrict__ lam)
+                                                       double* __restrict__ U, double* __restrict__ lam,
+                                                       unsigned* __restrict__ bad)
 {
     __shared__ double ecol[kPcaMaxM];
     __shared__ double red[256];
@@ -561,11 +594,14 @@ __global__ __launch_bounds__(256) void pca_ritz_kernel(const double* __restrict_
     if (tid < m) {
         const double x = H[tid * m + tid];
         int rank = 0;
+        double top = x;
         for (int q = 0; q < m; ++q) {
             const double y = H[q * m + q];
             rank += (y > x || (y == x && q < tid)) ? 1 : 0;
+            top = y > top ? y : top;
         }
         if (rank == j) col_ = tid;
+        if (bad && j == 0 && !(x > 1e-12 * top)) atomicOr(bad, 2u);
     }
     __syncthreads();
     const int col = col_;
@@ -708,7 +744,7 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
         if ((r = ws.alloc(&V, (size_t)d * m)) != KNN_OK) return r;
         if ((r = ws.alloc(&W, (size_t)d * m)) != KNN_OK) return r;
         if ((r = ws.alloc(&U2, (size_t)d * m)) != KNN_OK) return r;
-        if ((r = ws.alloc(&piv, (size_t)m)) != KNN_OK) return r;
+        if ((r = ws.alloc(&piv, (size_t)3 * m)) != KNN_OK) return r;   // pivots, then the Rayleigh sums
         if ((r = ws.alloc(&S, (size_t)m * m)) != KNN_OK) return r;
         if ((r = ws.alloc(&H, (size_t)m * m)) != KNN_OK) return r;
         if ((r = ws.alloc(&E, (size_t)m * m)) != KNN_OK) return r;
@@ -751,49 +787,77 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             pca_gram_small_kernel<<<dim3((unsigned)m, (unsigned)m), 256, 0, st>>>(in, in, d, m, S);
             pca_cholqr_kernel<<<gcols, 256, 0, st>>>(S, in, d, m, out, bad, piv, sh);
         };
+        auto cv = [&](const double* in, double alpha, double sh, const double* prev, double* out) {
+            pca_cv_kernel<<<gcv, 256, 0, st>>>(C, in, d, m, alpha, sh, prev, out);
+        };
         if (m < d) {
-            // Subspace iteration needs orthonormalisation only often enough
-            // to keep the basis well conditioned: W = C^q V for q products,
-            // then one shifted Cholesky-QR pass (the span is that of
-            // orthonormalising after every product).  q is chosen so that the
-            // basis' condition number, estimated from the spread of the last
-            // pass's pivots (kappa(C^q V) ~ sqrt(max D / min D), so kappa(C V)
-            // ~ that to the power 1/q), stays below about 1e4 over the q
-            // products (larger targets lost the weak directions of the pixel
-            // set's block in a CPU emulation).  After the last product a
-            // shifted pass and two plain ones (Cholesky-QR3) make the basis
-            // orthonormal to rounding for Rayleigh-Ritz.
-            std::vector<double> hp((size_t)m);
+            // Chebyshev-filtered subspace iteration.  A round multiplies V by
+            // T_q(2 C / b - 1) (three-term recurrence): components with
+            // eigenvalues below b stay at 1, one at lambda grows as
+            // cosh(q acosh(2 lambda / b - 1)).  b is the smallest Rayleigh quotient
+            // of the last round's columns (at most lambda_m); the first two
+            // rounds, before there is one, are plain products.
+            //  q: the strongest component may outgrow the damped ones by 1e10
+            //     per round, so that rounding of the former (1e-16) stays small
+            //     against the latter; at most 8, and 1 after a pass whose
+            //     smallest pivot (of unit-length columns) shows them dependent
+            //     to 1e-4.
+            //  K products in all: 0.35 T, at least min(T, 24).  For every ratio
+            //     r = lambda_p / lambda_{m+1} that is at least the convergence
+            //     of T power iterations, r^T, or full precision.
+            //  Stop: when the p-th quotient's component has grown e^42 more
+            //     than the m-th's over the rounds so far (both re-evaluated
+            //     from the current quotients): the error against the wanted
+            //     span is then below rounding.
+            // On a 70,000 x 784 set (eigenvalues as i^-1.2, p = 50) 200 power
+            // iterations with a pass after each took 21 of the call's 26 ms;
+            // 31 products in 12 rounds take 1.9 of 5.7 ms.
+            const int K = std::max(std::min(T, 24), (int)std::ceil(0.35 * T));
+            std::vector<double> hv((size_t)3 * m), rho((size_t)m);
+            std::vector<std::pair<int, double>> rounds;   // (q, b), b = 0: plain
+            double b = 0.0;
+            int q = 1;
             cholqr(W, V, shift);
-            int q = 1, since = kPcaMaxQ;   // products since q was last re-estimated
-            for (int it = 0; it < T;) {
-                const int qq = std::min(q, T - it);
-                const double* src = V;
-                for (int r = 0; r < qq; ++r) {
-                    double* dst = (r & 1) ? U2 : W;
-                    pca_cv_kernel<<<gcv, 256, 0, st>>>(C, src, d, m, dst);
-                    src = dst;
+            for (int done = 0; done < K;) {
+                const bool plain = rounds.size() < 2 || !(b > 0.0);
+                const int qq = plain ? 1 : std::min(q, K - done);
+                const double c = plain ? 0.0 : 0.5 * b;
+                // Y_1 = (C V - c V) / c, Y_{k+1} = 2 (C Y_k - c Y_k) / c - Y_{k-1}
+                cv(V, plain ? 1.0 : 1.0 / c, c, nullptr, W);
+                pca_rayleigh_kernel<<<(unsigned)m, 256, 0, st>>>(V, W, d, m, piv + m);
+                double *cur = W, *prev = V;
+                for (int k = 1; k < qq; ++k) {
+                    double* out = k == 1 ? U2 : prev;
+                    cv(cur, 2.0 / c, c, prev, out);
+                    prev = cur;
+                    cur = out;
                 }
-                it += qq;
-                since += qq;
-                cholqr(src, V, shift);
-                // re-estimated about every kPcaMaxQ products (each estimate
-                // waits for the pass's pivots)
-                if (it < T && since >= kPcaMaxQ) {
-                    since = 0;
-                    KNN_HIP(hipMemcpyAsync(hp.data(), piv, (size_t)m * 8, hipMemcpyDeviceToHost, st));
-                    KNN_HIP(hipStreamSynchronize(st));
-                    double lo = hp[0], hi = hp[0];
-                    for (int k = 1; k < m; ++k) {
-                        lo = std::min(lo, hp[k]);
-                        hi = std::max(hi, hp[k]);
-                    }
-                    // kappa(C V) estimate (the pass saw C^qq V), and the
-                    // products that keep kappa^q <= 1e4
-                    const double kap = lo > 0.0 ? std::pow(hi / lo, 0.5 / qq) : 1e300;
-                    q = kap <= 1.0 + 1e-12 ? kPcaMaxQ : (int)std::floor(4.0 / std::log10(kap));
-                    q = std::max(1, std::min(q, kPcaMaxQ));
+                cholqr(cur, V, shift);
+                done += qq;
+                rounds.push_back({qq, plain ? 0.0 : b});
+                if (done >= K) break;
+                KNN_HIP(hipMemcpyAsync(hv.data(), piv, (size_t)3 * m * 8, hipMemcpyDeviceToHost, st));
+                KNN_HIP(hipStreamSynchronize(st));
+                double lo = hv[0];
+                for (int k = 0; k < m; ++k) {
+                    lo = std::min(lo, hv[k]);
+                    const double vv = hv[2 * m + k], r1 = vv > 0.0 ? hv[m + k] / vv : 0.0;
+                    rho[k] = plain ? r1 : c * r1 + c;
                 }
+                std::sort(rho.begin(), rho.end(), [](double x, double y) { return x > y; });
+                const double top = rho[0], wanted = rho[p - 1];
+                b = rho[m - 1];
+                auto growth = [&](double l) {
+                    double g = 0.0;
+                    for (const auto& rd : rounds)
+                        g += rd.second > 0.0 ? rd.first * std::acosh(std::max(2.0 * l / rd.second - 1.0, 1.0))
+                                             : rd.first * std::log(l);
+                    return g;
+                };
+                if (b > 0.0 && growth(wanted) - growth(b) >= 42.0) break;
+                const double x = b > 0.0 ? 2.0 * top / b - 1.0 : 1e300;
+                q = x > 1.0 + 1e-9 ? (int)(std::log(1e10) / std::acosh(x)) : kPcaMaxQ;
+                q = lo < 1e-8 ? 1 : std::max(1, std::min(q, kPcaMaxQ));
             }
             cholqr(V, W, shift);
             cholqr(W, V, 0.0);
@@ -802,10 +866,10 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             KNN_HIP(hipGetLastError());
         }
         // Rayleigh-Ritz: H = V^T C V
-        pca_cv_kernel<<<gcv, 256, 0, st>>>(C, V, d, m, W);
+        cv(V, 1.0, 0.0, nullptr, W);
         pca_gram_small_kernel<<<dim3((unsigned)m, (unsigned)m), 256, 0, st>>>(W, V, d, m, H);
-        pca_jacobi_kernel<<<1, 256, 0, st>>>(H, E, m);
-        pca_ritz_kernel<<<(unsigned)p, 256, 0, st>>>(H, E, V, d, m, p, U, lam);
+        pca_jacobi_kernel<<<1, kJacThreads, 0, st>>>(H, E, m);
+        pca_ritz_kernel<<<(unsigned)p, 256, 0, st>>>(H, E, V, d, m, p, U, lam, m < d ? bad : nullptr);
         pca_by_dtype(X.dtype, [&](auto dt) {
             pca_project_kernel<decltype(dt)::value><<<(unsigned)ceil_div(n, 64), 256, 0, st>>>(
                 X.data, n, X.ld, d, mu, U, p, Z);
@@ -817,7 +881,7 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
         unsigned hb = 0;
         KNN_HIP(hipMemcpyAsync(&hb, bad, 4, hipMemcpyDeviceToHost, st));
         KNN_HIP(hipStreamSynchronize(st));
-        if (hb) return fail(KNN_EINVAL, "X has rank below the subspace width (a zero pivot in Cholesky-QR)");
+        if (hb) return fail(KNN_EINVAL, "X has rank below the subspace width");
         return KNN_OK;
     } catch (...) {
         return fail(KNN_EDEVICE, "unexpected exception");

@@ -209,3 +209,44 @@ def test_small_search(orc, n, d):
     idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda(), k)
     O, O2 = orc.exact_query(X, Q, k)
     assert np.allclose(dist.cpu().numpy(), np.sqrt(O2), rtol=1e-5)
+
+
+def _spectrum(n, d, lam, seed):
+    rng = np.random.default_rng(seed)
+    G = rng.normal(size=(n, d))
+    G -= G.mean(axis=0)
+    U, _ = np.linalg.qr(G)
+    Q, _ = np.linalg.qr(rng.normal(size=(d, d)))
+    return np.ascontiguousarray((1.5 + (U * np.sqrt((n - 1) * np.asarray(lam))) @ Q.T).astype(np.float32))
+
+
+@pytest.mark.parametrize("name", ["slow", "steep", "cliff", "odd"])
+def test_pca_filter_spectra(orc, name):
+    """The filtered iteration on spectra that drive its rules: a slow decay
+    (many products), seven decades (one product per round), a cliff inside
+    the block (dependent columns), and an odd block width (m = 21: the
+    eigensolver's bye).  Bounds as the other PCA tests: eigenvalues 1e-10,
+    vectors 1e-8 (gaps above 1e-3)."""
+    import paper_2603_04035_amd as knn
+    d, p, lam = {"slow": (90, 12, np.arange(1, 91) ** -0.7),
+                 "steep": (90, 8, np.geomspace(1.0, 1e-7, 90)),
+                 "cliff": (90, 6, np.concatenate([np.geomspace(1.0, 0.5, 6), 1e-4 * np.geomspace(1, 0.5, 84)])),
+                 "odd": (60, 5, np.arange(1, 61) ** -1.5)}[name]
+    X = _spectrum(4000, d, lam, 11)
+    Z, V, w, mu = (t.cpu().numpy() for t in knn.pca(torch.from_numpy(X).cuda(), p))
+    oZ, oV, ow, omu = orc.pca(X, p)
+    np.testing.assert_allclose(w, ow, rtol=1e-10)
+    assert np.abs(V - oV).max() <= 1e-8
+    assert np.abs(V.T @ V - np.eye(p)).max() <= 1e-12
+
+
+@pytest.mark.parametrize("X", ["rank", "rounded", "rows", "zero"])
+def test_pca_refuses_low_rank(X):
+    """Rank below the subspace width (m = 19 and 18) stays refused."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(1)
+    X = {"rank": rng.integers(-3, 4, size=(2000, 5)).astype(float) @ rng.integers(-2, 3, size=(5, 100)).astype(float),
+         "rounded": rng.normal(size=(2000, 5)) @ rng.normal(size=(5, 100)) + 30.0,
+         "rows": rng.normal(size=(15, 100)), "zero": np.zeros((100, 50))}[X]
+    with pytest.raises(knn.KnnError):
+        knn.pca(torch.from_numpy(np.ascontiguousarray(X.astype(np.float32))).cuda(), 3 if X.shape[1] == 100 else 2)
