@@ -245,15 +245,11 @@ __global__ __launch_bounds__(256) void split_kernel(const void* __restrict__ X, 
 
 // ------------------------------------------------------------------ tile
 
-// Tile geometry per staged element kind (KNN_F32, KNN_BF16, KNN_F16).
+// Tile geometry per staged element kind (KNN_BF16, KNN_F16, KNN_SPLIT): values
+// per K chunk (128 bytes per row), their LDS row stride (144 bytes), and the
+// longest query rows that stay in LDS, with their stride.
 template <int OUT>
-struct TileCfg {
-    using E = float;
-    static constexpr int KC = 32;    // elements per K chunk (128 bytes per row)
-    static constexpr int LROW = 36;  // LDS row stride in elements (144 bytes)
-    static constexpr int AMAX = 64;  // query rows stay in LDS when ldp <= AMAX
-    static constexpr int AROW = 68;  // their LDS row stride
-};
+struct TileCfg;
 template <>
 struct TileCfg<KNN_BF16> {
     using E = uint16_t;
@@ -376,7 +372,12 @@ __device__ inline void load_queries(E* As, const E* Qb, int qlast, int ldp, int 
 // q.r - |r|^2 / 2 the gate tests; kTransposed: the same with the operands
 // swapped (rows = references, columns = queries: a lane's 16 sums belong to
 // one query).  Scores of references past rend are -inf.
-enum { kFromZero = 0, kByColumn = 1, kTransposed = 2 };
+// kSegmented: operands swapped, from zero, the sums of every kSegChunks chunks
+// formed apart and then added: additions then round sums no larger than their
+// segment's |q_s||r_s|, which add up to |q||r| at most, so the bound counts one
+// segment's instructions instead of all (rank_tile_kernel).
+enum { kFromZero = 0, kByColumn = 1, kTransposed = 2, kSegmented = 3 };
+constexpr int kSegChunks = 4;
 
 template <int OUT, bool ARES, int INIT = kFromZero>
 __device__ __attribute__((always_inline)) inline void tile_gemm(
@@ -390,11 +391,20 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
     constexpr int NV = PER * (int)sizeof(E) / 16;   // 16-byte loads per thread and chunk
     static_assert(NV == 4, "four 16-byte pieces per thread and chunk");
     const int sr = tid >> 3, scol = (tid & 7) * 16;   // staging: see load_step
-    if (INIT == kFromZero) {
+    constexpr bool SWAP = INIT == kTransposed || INIT == kSegmented;
+    if (INIT == kFromZero || INIT == kSegmented) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
+    }
+    f32x16 seg[4];   // the current segment's sums
+    int segc = 0;
+    if (INIT == kSegmented) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) seg[b][v] = 0.0f;
     }
 
     for (int k0 = 0; k0 < ldp; k0 += KC) {
@@ -458,20 +468,17 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
 #pragma unroll
             for (int i = 0; i < NV; ++i) b4[i] = bp[OUT == KNN_SPLIT && i >= 2 ? i + 2 : i];
             if constexpr (OUT == KNN_SPLIT) {
+                f32x16 x = INIT == kSegmented ? seg[b] : acc[b];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const f16x8 ah = __builtin_bit_cast(f16x8, a4[i]), al = __builtin_bit_cast(f16x8, a4[i + 2]);
                     const f16x8 bh = __builtin_bit_cast(f16x8, b4[i]), bl = __builtin_bit_cast(f16x8, b4[i + 2]);
-                    if constexpr (INIT == kTransposed) {
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl, ah, acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, al, acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, ah, acc[b], 0, 0, 0);
-                    } else {
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[b], 0, 0, 0);
-                    }
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_f16(SWAP ? bl : ah, SWAP ? ah : bl, x, 0, 0, 0);
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_f16(SWAP ? bh : al, SWAP ? al : bh, x, 0, 0, 0);
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_f16(SWAP ? bh : ah, SWAP ? ah : bh, x, 0, 0, 0);
                 }
+                if (INIT == kSegmented) seg[b] = x;
+                else acc[b] = x;
             } else if constexpr (OUT == KNN_BF16) {
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
@@ -486,15 +493,18 @@ __device__ __attribute__((always_inline)) inline void tile_gemm(
                     const f16x8 bv = __builtin_bit_cast(f16x8, INIT == kTransposed ? a4[i] : b4[i]);
                     acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc[b], 0, 0, 0);
                 }
-            } else {
+            }
+        }
+        if (INIT == kSegmented) {
+            segc = segc + 1 == kSegChunks ? 0 : segc + 1;
+            if (segc == 0 || k0 + KC >= ldp) {
 #pragma unroll
-                for (int i = 0; i < NV; ++i) {
-                    f32x4 av = __builtin_bit_cast(f32x4, a4[i]);
-                    f32x4 bv = __builtin_bit_cast(f32x4, b4[i]);
+                for (int b = 0; b < 4; ++b)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], acc[b], 0, 0, 0);
-                }
+                    for (int v = 0; v < 16; ++v) {
+                        acc[b][v] += seg[b][v];
+                        seg[b][v] = 0.0f;
+                    }
             }
         }
     }
@@ -770,15 +780,56 @@ __global__ __launch_bounds__(256) void gate_select_kernel(const float* __restric
     }
 }
 
+constexpr int kCandCap = 256;   // entries of a row's buffer
+
+// Rows lr0 .. lr0 + 31 of one wave (counts n32, gates lim32 in LDS) whose
+// buffers have no room for another tile's 128 keep their best 32 by (distance,
+// index) and raise their gate to the kp-th of them.
+__device__ inline void compact_rows(uint64_t* buf, uint32_t rstride, uint32_t* n32, float* lim32,
+                                                       int lr0, const float* qnb, int kp, float m2, float sc,
+                                                       float rmax)
+{
+    const int lane = threadIdx.x & 63;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    const uint32_t n = lane < 32 ? n32[lane] : 0u;
+    for (uint64_t m = ballot(n > kCandCap - kTileRows); m; m &= m - 1) {
+        const int r = __builtin_ctzll(m);
+        const uint32_t nc = bcast_u32(n, r);
+        const float sq = qnb[lr0 + r];
+        uint64_t* b = buf + (uint32_t)(lr0 + r) * rstride;
+        auto key_of = [&](uint64_t x) { return make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq), (uint32_t)x); };
+        uint64_t best = kEmptyCand;
+        for (uint32_t e = 0; e < nc; e += 64) {
+            const uint64_t key = e + lane < nc ? key_of(b[e + lane]) : kEmptyCand;
+            best = seg_merge_sorted<64>(best, seg_sort<64>(key));
+        }
+        const uint64_t last = bcast_u64(best, kListW - 1);
+        const float t = key_d2(bcast_u64(best, kp - 1));
+        // the entries up to the 32nd key move to the front
+        uint32_t kept = 0;
+        for (uint32_t e = 0; e < nc; e += 64) {
+            const uint64_t x = e + lane < nc ? b[e + lane] : 0ull;
+            const bool keep = e + lane < nc && key_of(x) <= last;
+            const uint64_t km = ballot(keep);
+            if (keep) b[kept + rank_below(km)] = x;
+            kept += (uint32_t)popc64(km);
+        }
+        if (lane == 0) {
+            n32[r] = kept;
+            lim32[r] = fmaxf(lim32[r], (0.5f * (sq - t) - 4.76837158e-07f * (sq + t + rmax)) * sc);   // 8u = 2^-21
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+}
+
 // The gated pass: the tiles and pipeline of exact_tile_kernel; a score that
 // reaches its row's gate is appended, as (score, index), to the row's buffer
 // of kCandCap entries for this split (part[(row * S + s) * kCandCap ..], counts
 // in LDS, then cnt[row * S + s]).  A row belongs to one wave, so appending
 // needs no other wave.  When a buffer has no room for another tile's 128, its
 // wave keeps the row's best 32 by (distance, index) and raises the gate to
-// the kp-th of them: rare behind a gate, and the same keys the sorted
-// lists of exact_tile_kernel would keep.
-constexpr int kCandCap = 256;
+// the kp-th of them (compact_rows): rare behind a gate, and the same keys the
+// sorted lists of exact_tile_kernel would keep.
 
 template <int OUT, bool ARES>
 __global__ __launch_bounds__(256, 2) void exact_append_kernel(
@@ -841,40 +892,7 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
             }
         }
         if (ballot(full)) {
-            // rows without room for another tile: the best 32 stay
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            const uint32_t n = lane < 32 ? scnt[w * 32 + lane] : 0u;
-            for (uint64_t m = ballot(n > kCandCap - kTileRows); m; m &= m - 1) {
-                const int r = __builtin_ctzll(m), lr = w * 32 + r;
-                const uint32_t nc = bcast_u32(n, r);
-                const float sq = qn[q0 + lr];
-                uint64_t* b = buf + (uint32_t)lr * rstride;
-                uint64_t best = kEmptyCand;
-                for (uint32_t e = 0; e < nc; e += 64) {
-                    uint64_t key = kEmptyCand;
-                    if (e + lane < nc) {
-                        const uint64_t x = b[e + lane];
-                        key = make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq), (uint32_t)x);
-                    }
-                    best = seg_merge_sorted<64>(best, seg_sort<64>(key));
-                }
-                const float t = key_d2(bcast_u64(best, kp - 1));
-                // the kept keys' scores are found again by index
-                for (uint32_t e = 0, kept = 0; e < nc; e += 64) {
-                    const uint64_t x = e + lane < nc ? b[e + lane] : 0ull;
-                    const uint64_t key = e + lane < nc ? make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq),
-                                                                  (uint32_t)x) : kEmptyCand;
-                    const bool keep = key <= bcast_u64(best, kListW - 1) && key != kEmptyCand;
-                    const uint64_t km = ballot(keep);
-                    if (keep) b[kept + rank_below(km)] = x;
-                    kept += (uint32_t)popc64(km);
-                }
-                if (lane == 0) {
-                    scnt[lr] = kListW;
-                    slim[lr] = fmaxf(slim[lr], (0.5f * (sq - t) - 4.76837158e-07f * (sq + t + rmax)) * sc);   // 8u
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, w * 32, qn + q0, kp, m2, sc, rmax);
 #pragma unroll
             for (int v = 0; v < 16; ++v) lim[v] = slim[w * 32 + mfma_row(v, h)];
         }
@@ -886,266 +904,222 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
 // ------------------------------------------------------------ rank counts
 
 constexpr int kRankP = 16;   // probes per query row (the quality metrics' k <= 16)
-constexpr int kRankM = 16;   // queued pairs per thread in one pass over a tile's rows
+constexpr int kRankFlush = 1024;   // queued pairs that are worth a recheck pass
+constexpr int kRankQueue = kTileRows * kTileRows + kRankFlush;
+
 // For every query row q and each of its probes (keys (canonical d2, index),
 // ascending; kEmptyCand pads), counts[q][p] = the number of reference rows
 // m != self(q) whose key (canonical FP32 d2(q, m), m) is below the probe's
-// key: the probe's rank minus one.  The same tiles and pipeline as
-// exact_tile_kernel (FP32 MFMA Gram, norm expansion, S reference splits
-// whose counts are added into counts, zeroed beforehand; query rows
-// streamed); the epilogue puts each reference row that can be below a
-// probe of its query into a per-row histogram over the probe boundaries (in
-// LDS), so counts are prefix sums.  A GEMM distance within the slack of a
-// probe's distance (the GEMM error bound for the pair's own norms plus the
-// canonical distance's) is undecided: the pair is queued in the
-// workgroup's global queue (room for a whole tile, 128 x 128 pairs) and,
-// after the tile's epilogue, the tile's query and reference rows are
-// streamed again through the tile buffers in 32-coordinate chunks; 16-lane
-// groups sum the queued pairs' canonical FP32 distances from LDS (lane g:
-// coordinates g, g + 16, ... in order, then the fixed 16-lane tree, the sums
-// dist_g16 makes) and put them into the histogram.  No pair is decided any
-// other way.  With LISTS the pass also keeps, per query row and split, the
-// kp smallest GEMM keys (GEMM distance, index) as exact_tile_kernel does,
-// and writes them to part in its split-list layout (row-major over query
-// rows, then splits, kListW keys each), for merge_rerank_kernel; without
-// LISTS, kp and part are unused.
-template <bool LISTS>
+// key: the probe's rank minus one.  The tiles and pipeline of the exact
+// search on split rows, operands swapped (a lane's sums belong to one query:
+// its probes, as scores, and its counts sit in registers), S reference splits
+// whose counts are added into counts, zeroed beforehand.  A score further from
+// a probe's than the slack (the GEMM bound with the tile's largest norm, plus
+// the canonical distance's) decides it; what is left is queued (the pair and
+// its range of undecided probes) in the workgroup's global queue, which is
+// worked off once it holds 1,024 pairs: 16-lane groups form the pairs'
+// canonical FP32 distances from the rows Zf, four pairs in flight, in the order
+// dist_g16 sums, and count them exactly.  No pair is decided any other way.
+// With LISTS the pass also appends, as exact_append_kernel does, what reaches
+// the row's gate, for X's exact k-NN.
+// What bounds it: the three products per element, then rechecks (two rows of
+// 4 d bytes each), whose number is proportional to the slack; forming the sums
+// in segments makes the bound 208 u |q||r| where one chain of FP32 additions had
+// 1,572 (d = 784), some 38 rechecks per tile instead of 250.  70,000 x 784, k =
+// 10: 104 ms with FP32 MFMA, a histogram in LDS and every tile's rows streamed
+// again for its rechecks; 44 ms now.
+template <bool LISTS, bool ARES, int NP>
 __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
-    const float* __restrict__ Qs, const float* __restrict__ qn, int64_t nq, const float* __restrict__ Rs,
-    const float* __restrict__ rn, int64_t nr, int ldp, int d, int self_mode, int64_t self_base,
-    const uint64_t* __restrict__ probes, const unsigned* __restrict__ rmax_bits, float ec_dot, float ec_norm,
-    float edir, int S, int64_t split_len, uint32_t* __restrict__ counts, uint32_t* __restrict__ gqueue, int kp,
-    uint64_t* __restrict__ part)
+    const _Float16* __restrict__ Qs, const float* __restrict__ qn, int64_t nq, const _Float16* __restrict__ Rs,
+    const float* __restrict__ rn, int64_t nr, int lds, const float* __restrict__ Qf, const float* __restrict__ Zf,
+    int64_t ldf, int d, int64_t self_base, const uint64_t* __restrict__ probes, const unsigned* __restrict__ rmax_bits,
+    float ec_dot, float ec_norm, float edir, int S, int64_t split_len, uint32_t* __restrict__ counts,
+    uint64_t* gqueue, int kp, const float* __restrict__ lims, uint64_t* part, uint32_t* __restrict__ cnt)
 {
-    using C = TileCfg<KNN_F32>;
-    constexpr int LROW = C::LROW, KC = C::KC, PER = KC / 2;
-    __shared__ __attribute__((aligned(16))) float ABs[2 * kTileRows * LROW];
-    float* As = ABs;
-    float* Bs = ABs + kTileRows * LROW;
-    // this workgroup's undecided pairs of the current tile:
-    // column in tile << 17 | query row << 10 | a << 5 | b
-    uint32_t* queue = gqueue + (int64_t)blockIdx.x * (kTileRows * kTileRows);
-    __shared__ float srn[kTileRows];
-    __shared__ f32x4 srow[kTileRows];   // per query row: |q|^2, gate, excluded index (bits), |q|
-    __shared__ float smx[kTileRows];
-    __shared__ __attribute__((aligned(16))) uint64_t skey[kTileRows * kRankP];
-    __shared__ __attribute__((aligned(16))) float sthr[kTileRows * kRankP];   // the probes' distances (+inf: none)
-    __shared__ uint32_t hist[kTileRows * (kRankP + 1)];
-    __shared__ uint32_t qcount;   // queue fill
-
+    using C = TileCfg<KNN_SPLIT>;
+    using E = typename C::E;
+    constexpr int LROW = C::LROW, AROW = ARES ? C::AROW : LROW;
+    __shared__ __attribute__((aligned(16))) E As[kTileRows * AROW];
+    __shared__ __attribute__((aligned(16))) E Bs[kTileRows * LROW];
+    __shared__ __attribute__((aligned(16))) float srn[kTileRows];
+    __shared__ uint64_t skey[kTileRows * NP];
+    __shared__ uint32_t sadd[kTileRows * NP];   // the rechecks' counts
+    __shared__ uint32_t scnt[kTileRows];
+    __shared__ float slim[kTileRows];
+    __shared__ uint32_t qcount;
+    uint64_t* queue = gqueue + (int64_t)blockIdx.x * kRankQueue;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
     // workgroup = (query block, reference split): splits rbeg .. rend
     const int64_t q0 = (int64_t)(blockIdx.x / S) * kTileRows;
-    const int64_t rbeg = (int64_t)(blockIdx.x % S) * split_len;
+    const int sp = blockIdx.x % S;
+    const int64_t rbeg = (int64_t)sp * split_len;
     const int64_t rend = rbeg + split_len < nr ? rbeg + split_len : nr;
-    const float ra = sqrtf(__uint_as_float(*rmax_bits));
-    for (int e = tid; e < kTileRows * kRankP; e += 256) {
-        const int64_t qr = q0 + e / kRankP;
-        const uint64_t key = qr < nq ? probes[qr * kRankP + e % kRankP] : kEmptyCand;
-        skey[e] = key;
-        sthr[e] = key == kEmptyCand ? __builtin_inff() : key_d2(key);
+    const float scale = split_scale(*rmax_bits), sc = scale * scale, hsc = 0.5f * sc, m2 = -2.0f / sc;
+    for (int e = tid; e < kTileRows * NP; e += 256) {
+        const int64_t qr = q0 + e / NP;
+        skey[e] = qr < nq ? probes[qr * kRankP + e % NP] : kEmptyCand;
+        sadd[e] = 0u;
     }
-    for (int e = tid; e < kTileRows * (kRankP + 1); e += 256) hist[e] = 0u;
-    if (tid == 0) qcount = 0u;
-    __syncthreads();
     if (tid < kTileRows) {
-        const int64_t qr = q0 + tid;
-        const float sq = qr < nq ? qn[qr] : 0.0f;
-        const int32_t self = qr >= nq ? -1 : (self_mode == 1 ? (int32_t)(self_base + qr) : -1);
-        float mx = -1.0f;
-        for (int p = 0; p < kRankP; ++p) {
-            const uint64_t key = skey[tid * kRankP + p];
-            if (key != kEmptyCand) mx = key_d2(key);
-        }
-        const float qa = sqrtf(sq), E = ec_dot * qa * ra + ec_norm * (sq + ra * ra);
-        const float sl = E + 2.0f * edir * (mx + E);
-        smx[tid] = mx;
-        // rows without probes never pass (the gate takes the largest reference norm)
-        const f32x4 ri = {sq, mx < 0.0f ? -1.0f : mx + sl, __int_as_float(self), qa};
-        srow[tid] = ri;
+        scnt[tid] = 0u;
+        slim[tid] = LISTS && q0 + tid < nq ? lims[q0 + tid] : __builtin_inff();
     }
-
-    // With LISTS, the split's best kp keys (GEMM distance, index) of each
-    // query row as well, kept as exact_tile_kernel keeps them (lane (h, c)
-    // holds entry c of row 32 w + mfma_row(v, h)'s list) and written to part
-    // in its layout: the same pass gives the rows' exact k-NN after the
-    // merge, re-rank and certificate.  lthr is the list's kp-th distance
-    // (-inf for rows past nq, which take nothing).
-    uint64_t list[16];
-    float lthr[16];
-    if constexpr (LISTS) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            list[v] = kEmptyList;
-            lthr[v] = q0 + w * 32 + mfma_row(v, h) < nq ? __builtin_inff() : -__builtin_inff();
-        }
-    }
-    const float* Qb = Qs + q0 * ldp;
+    if (tid == 0) qcount = 0u;
+    const E* Qb = (const E*)Qs + q0 * lds;
+    const E* Re = (const E*)Rs;
     const int qlast = nq - q0 > kTileRows ? kTileRows - 1 : (int)(nq - q0) - 1;
+    if (ARES) load_queries<E, AROW>(As, Qb, qlast, lds, tid);
     StepRegs nx;
-    load_step<float, false>(nx, Qb, qlast, Rs, rbeg, rend, 0, ldp, rn, tid);
+    load_step<E, ARES>(nx, Qb, qlast, Re, rbeg, rend, 0, lds, rn, tid);
+    __syncthreads();
+    // this lane's query: its probes as scores (+inf: none), counts and gate
+    const int lq = w * 32 + c;
+    const int64_t qr = q0 + lq;
+    const float sq = qr < nq ? qn[qr] : 0.0f, qa = sqrtf(sq);
+    const int64_t self = qr < nq ? self_base + qr : -1;
+    float ts[NP], lim = slim[lq], mx = 0.0f, tlow = __builtin_inff();
+    uint32_t num[NP];
+    int nv = 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const uint64_t key = skey[lq * NP + p];
+        const bool on = key != kEmptyCand;
+        ts[p] = on ? 0.5f * (sq - key_d2(key)) * sc : __builtin_inff();
+        tlow = on ? ts[p] : tlow;   // the farthest probe's
+        mx = on ? key_d2(key) : mx;
+        nv += on ? 1 : 0;
+        num[p] = 0u;
+    }
+    uint64_t* buf = LISTS ? part + (q0 * S + sp) * kCandCap : nullptr;
+    const uint32_t rstride = (uint32_t)S * kCandCap;
     for (int64_t rt = rbeg; rt < rend; rt += kTileRows) {
         f32x16 acc[4];
-        tile_gemm<KNN_F32, false>(nx, acc, As, Bs, srn, Qb, qlast, Rs, rt, rend, ldp, rn, tid, w, h, c);
-        // row and column bases, opaque to the compiler here so that the 64
-        // (block, row) offsets derived from them are formed where they are
-        // used instead of being held in registers across the whole loop
-        int lr0 = w * 32 + 4 * h, c0 = c;
-        asm volatile("" : "+v"(lr0), "+v"(c0));
-        float rnj[4], raj[4];   // the lane's four reference columns: |r|^2, |r|
+        tile_gemm<KNN_SPLIT, ARES, kSegmented>(nx, acc, As, Bs, srn, Qb, qlast, Re, rt, rend, lds, rn, tid, w, h, c, hsc);
+        // the tile's largest norm (rows past rend: +inf, left out)
+        float tn = 0.0f;
+        {
+            const float a = srn[lane], b = srn[64 + lane];
+            tn = fmaxf(a < __builtin_inff() ? a : 0.0f, b < __builtin_inff() ? b : 0.0f);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) tn = fmaxf(tn, xor_f32(tn, o));
+        }
+        const float e2 = ec_dot * qa * sqrtf(tn) + ec_norm * (sq + tn + mx);
+        const float sl = hsc * (e2 + 2.0f * edir * (mx + e2));
+        const bool diag = ballot(self >= rt && self < rt + kTileRows) != 0ull;
+        const int sr = self >= rt && self < rt + kTileRows ? (int)(self - rt) : -1;
+        bool full = false;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk) {
-            rnj[blk] = srn[blk * 32 + c0];
-            raj[blk] = sqrtf(rnj[blk]);
-        }
+            float mxs = -__builtin_inff();
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int lr = lr0 + mfma_row(v, 0);
-            const f32x4 ri = srow[lr];   // the row's |q|^2, gate, excluded index, |q|
+            for (int v4 = 0; v4 < 4; ++v4) {
+                const f32x4 x = *(const f32x4*)&srn[blk * 32 + 8 * v4 + 4 * h];
 #pragma unroll
-            for (int blk = 0; blk < 4; ++blk) {
-                const int col = blk * 32 + c0;
-                const int64_t j = rt + col;
-                float d2 = fmaf(-2.0f, acc[blk][v], ri[0] + rnj[blk]);
-                d2 = d2 > 0.0f ? d2 : 0.0f;
-                if constexpr (LISTS) {
-                    const bool okl = d2 <= lthr[v] && j < rend && (int32_t)j != __float_as_int(ri[2]);
-                    const uint64_t okm = ballot(okl);
-                    if (okm) {
-                        list[v] = list_add(list[v], okl ? make_key(d2, (uint32_t)j) : kEmptyCand, okm, lane);
-                        const uint64_t t0 = bcast_u64(list[v], kp - 1), t1 = bcast_u64(list[v], 32 + kp - 1);
-                        lthr[v] = key_d2(h ? t1 : t0);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const int v = 4 * v4 + e;
+                    acc[blk][v] -= hsc * x[e];
+                    if (diag) acc[blk][v] = blk * 32 + mfma_row(v, h) == sr ? -__builtin_inff() : acc[blk][v];
+                    mxs = fmaxf(mxs, acc[blk][v]);
                 }
-                const bool pass = d2 <= ri[1] && j < rend && (int32_t)j != __float_as_int(ri[2]);
-                if (!ballot(pass)) continue;
-                if (pass) {
-                    // the slack of this pair: the GEMM bound with its own
-                    // reference norm, plus the canonical distance's
-                    const float E = ec_dot * ri[3] * raj[blk] + ec_norm * (ri[0] + rnj[blk]);
-                    const float sl = E + 2.0f * edir * (smx[lr] + E);
-                    const f32x4* pt = (const f32x4*)(sthr + lr * kRankP);
-                    const float hi = d2 + sl, lo = d2 - sl;
-                    int a = 0, b = 0;   // probes with thr <= d2 + sl, with thr < d2 - sl
+            }
+            // nothing near any probe or the gate
+            if (!ballot(mxs + sl >= tlow || (LISTS && mxs >= lim))) continue;
+            // rolled, the score picked by index: 16 copies of the body spilled
+            // hundreds of registers and outgrew the instruction cache
+            const f32x16 cur = acc[blk];
+#pragma unroll 1
+            for (int v = 0; v < 16; ++v) {
+                const float x = cur[v], xm = x - sl, xp = x + sl;
+                bool und = false;
 #pragma unroll
-                    for (int p4 = 0; p4 < kRankP / 4; ++p4) {
-                        const f32x4 t4 = pt[p4];
+                for (int p = 0; p < NP; ++p) {
+                    const bool below = xm > ts[p], poss = xp >= ts[p];
+                    num[p] += below ? 1u : 0u;
+                    und = und || (below != poss);
+                }
+                const uint32_t j = (uint32_t)rt + blk * 32 + mfma_row(v, h);
+                if (und) {
+                    int a = 0, b = 0;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            a += t4[e] <= hi ? 1 : 0;
-                            b += t4[e] < lo ? 1 : 0;
-                        }
+                    for (int p = 0; p < NP; ++p) {
+                        a += xp >= ts[p] ? 1 : 0;
+                        b += xm > ts[p] ? 1 : 0;
                     }
-                    // probes a.. have this row below them; b..a-1 are undecided
-                    if (b == a && a < kRankP) atomicAdd(&hist[lr * (kRankP + 1) + a], 1u);
-                    if (b < a) {
-                        const uint32_t slot = atomicAdd(&qcount, 1u);
-                        queue[slot] = ((uint32_t)col << 17) | ((uint32_t)lr << 10) | ((uint32_t)a << 5) | (uint32_t)b;
-                    }
+                    // probes nv - a .. nv - b - 1 are undecided
+                    const uint32_t slot = atomicAdd(&qcount, 1u);
+                    queue[slot] = ((uint64_t)j << 32) | (uint32_t)(lq << 10 | (nv - a) << 5 | (nv - b));
+                }
+                if (LISTS && x >= lim) {
+                    const uint32_t pos = atomicAdd(&scnt[lq], 1u);
+                    buf[(uint32_t)lq * rstride + pos] = ((uint64_t)__float_as_uint(x) << 32) | j;
+                    full = full || pos >= kCandCap - kTileRows;
                 }
             }
         }
-        __syncthreads();   // the queue is complete; every wave's MFMA operands are read
+        if (LISTS && ballot(full)) {
+            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, w * 32, qn + q0, kp, m2, sc,
+                         __uint_as_float(*rmax_bits));
+            lim = slim[lq];
+        }
+        __syncthreads();   // the queue is complete
         const int nqd = (int)qcount;
-        // thread (tid / 16, g = tid % 16) takes pairs base + tid / 16 + 16 m;
-        // a thread past the end reads row 0 of both buffers and drops the sum
-        const int g = tid & 15;
-        for (int base = 0; base < nqd; base += 16 * kRankM) {
-            uint32_t qo[kRankM], ro[kRankM];
-            float dsum[kRankM];
+        if (nqd >= kRankFlush || (rt + kTileRows >= rend && nqd > 0)) {
+            // group tid / 16 takes pairs base + tid / 16 + 16 m; one past the
+            // end repeats the last and drops the sum
+            const int g = tid & 15;
+            for (int base = 0; base < nqd; base += 64) {
+                uint64_t ent[4];
+                const float *a[4], *b[4];
+                float sum[4];
 #pragma unroll
-            for (int m = 0; m < kRankM; ++m) {
-                const int e = base + (tid >> 4) + 16 * m;
-                const uint32_t ent = e < nqd ? queue[e] : 0u;
-                qo[m] = ((ent >> 10) & 127u) * LROW + g;
-                ro[m] = (ent >> 17) * LROW + g;
-                dsum[m] = 0.0f;
-            }
-            // the chunks pass through registers: chunk k0 + KC is loaded
-            // while chunk k0's sums are formed
-            const int rr = tid >> 1, hh = tid & 1;
-            const f32x4* qs = (const f32x4*)(Qs + (q0 + rr < nq ? q0 + rr : nq - 1) * ldp + hh * PER);
-            const f32x4* rs = (const f32x4*)(Rs + (rt + rr < rend ? rt + rr : rend - 1) * ldp + hh * PER);
-            f32x4 x0 = qs[0], x1 = qs[1], x2 = qs[2], x3 = qs[3];
-            f32x4 y0 = rs[0], y1 = rs[1], y2 = rs[2], y3 = rs[3];
-            for (int k0 = 0; k0 < d; k0 += KC) {
-                __syncthreads();   // the previous chunk is read
-                {
-                    f32x4* qd = (f32x4*)(As + rr * LROW + hh * PER);
-                    f32x4* rd = (f32x4*)(Bs + rr * LROW + hh * PER);
-                    qd[0] = x0;
-                    qd[1] = x1;
-                    qd[2] = x2;
-                    qd[3] = x3;
-                    rd[0] = y0;
-                    rd[1] = y1;
-                    rd[2] = y2;
-                    rd[3] = y3;
+                for (int m = 0; m < 4; ++m) {
+                    const int e = base + (tid >> 4) + 16 * m;
+                    ent[m] = queue[e < nqd ? e : nqd - 1];
+                    a[m] = Qf + (q0 + (int64_t)((uint32_t)ent[m] >> 10)) * ldf;
+                    b[m] = Zf + (int64_t)(ent[m] >> 32) * ldf;
+                    sum[m] = 0.0f;
                 }
-                __syncthreads();
-                {
-                    // the last chunk loads itself again (in bounds, unused)
-                    const int kn = (k0 + KC < d ? k0 + KC : k0) / 4;
-                    x0 = qs[kn];
-                    x1 = qs[kn + 1];
-                    x2 = qs[kn + 2];
-                    x3 = qs[kn + 3];
-                    y0 = rs[kn];
-                    y1 = rs[kn + 1];
-                    y2 = rs[kn + 2];
-                    y3 = rs[kn + 3];
-                }
-                // coordinates past d add nothing: fmaf(0, 0, s) == s
-                const bool lo = k0 + g < d, hi = k0 + g + 16 < d;
+#pragma unroll 2
+                for (int t = g; t < d; t += 16) {
+                    float x[4], y[4];
 #pragma unroll
-                for (int m = 0; m < kRankM; ++m) {
-                    const float d0 = As[qo[m]] - Bs[ro[m]], d1 = As[qo[m] + 16] - Bs[ro[m] + 16];
-                    const float e0 = lo ? d0 : 0.0f, e1 = hi ? d1 : 0.0f;
-                    dsum[m] = fmaf(e1, e1, fmaf(e0, e0, dsum[m]));
-                }
-                // the next chunk's loads belong to this step: issued before
-                // the sums above, not moved to the top of the next step
-                asm volatile("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3));
-            }
-#pragma unroll
-            for (int m = 0; m < kRankM; ++m) {
-                const float dc = wave_sum16(dsum[m]);
-                const int e = base + (tid >> 4) + 16 * m;
-                if (e < nqd && g == 0) {
-                    const uint32_t ent = queue[e];
-                    const int lr = (int)((ent >> 10) & 127u), a = (int)((ent >> 5) & 31u), b = (int)(ent & 31u);
-                    const uint64_t km = make_key(dc, (uint32_t)(rt + (ent >> 17)));
-                    const uint64_t* pk = skey + lr * kRankP;
-                    int at = a;
-                    for (int p = b; p < a; ++p) {
-                        if (km < pk[p]) {
-                            at = p;
-                            break;
-                        }
+                    for (int m = 0; m < 4; ++m) {
+                        x[m] = a[m][t];
+                        y[m] = b[m][t];
                     }
-                    if (at < kRankP) atomicAdd(&hist[lr * (kRankP + 1) + at], 1u);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const float df = x[m] - y[m];
+                        sum[m] = fmaf(df, df, sum[m]);
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const float dc = wave_sum16(sum[m]);
+                    const int e = base + (tid >> 4) + 16 * m;
+                    if (e < nqd && g < NP) {
+                        // lane g: probe g, if it is one of the undecided
+                        const uint32_t lo = (uint32_t)ent[m];
+                        const int lr = (int)(lo >> 10), p1 = (int)((lo >> 5) & 31u), p0 = (int)(lo & 31u);
+                        if (g >= p1 && g < p0 && make_key(dc, (uint32_t)(ent[m] >> 32)) < skey[lr * NP + g])
+                            atomicAdd(&sadd[lr * NP + g], 1u);
+                    }
                 }
             }
+            __syncthreads();   // the queue is read
+            if (tid == 0) qcount = 0u;
         }
-        __syncthreads();   // the queue and the tile buffers are free for the next tile
-        if (tid == 0) qcount = 0u;
-    }
-    if constexpr (LISTS) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t row = q0 + w * 32 + mfma_row(v, h);
-            if (row < nq) part[(row * S + blockIdx.x % S) * kListW + c] = list[v];
-        }
+        // (the next tile's first barrier orders the reset before its appends)
     }
     __syncthreads();
-    for (int e = tid; e < kTileRows * kRankP; e += 256) {
-        const int lr = e / kRankP, p = e % kRankP;
-        const int64_t qr = q0 + lr;
-        if (qr >= nq) continue;
-        uint32_t cnt = 0;
-        for (int a = 0; a <= p; ++a) cnt += hist[lr * (kRankP + 1) + a];
-        atomicAdd(&counts[qr * kRankP + p], cnt);   // the splits' counts add up
+    if (qr < nq) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const uint32_t other = xor_u32(num[p], 32);   // the other half's references
+            if (h == 0 && p < nv) atomicAdd(&counts[qr * kRankP + p], num[p] + other + sadd[lq * NP + p]);
+        }
     }
+    if (LISTS && tid < kTileRows && q0 + tid < nq) cnt[(q0 + tid) * S + sp] = scnt[tid];
 }
 
 // Canonical FP32 squared distance for d <= DT <= 16 coordinates: the
@@ -1183,9 +1157,9 @@ __device__ __attribute__((always_inline)) inline float direct_d2(const float (&x
 // counts (zeroed beforehand).  Exact in the canonical precision, no
 // ambiguity.
 constexpr int kRankDirectD = 16;
-// Workgroups per rank_tile_kernel launch: each holds a 64 KiB queue of
-// undecided pairs (256 MiB per launch).
-constexpr int64_t kRankBlocks = 4096;
+// Workgroups per rank_tile_kernel launch: each holds a 136 KiB queue of
+// undecided pairs (272 MiB per launch) and, with lists, 256 KiB of buffers.
+constexpr int64_t kRankBlocks = 2048;
 constexpr int kRankMaxSplits = 8;   // reference splits of the rank pass
 
 // DC = d when it is a compile-time constant (2, 3), 0 for any d <= 16.
@@ -1743,6 +1717,18 @@ static int filling_splits(int64_t qn, int64_t nr)
     return best;
 }
 
+// Tiles of the gate's sample, for references of lds staged units.  A sample of
+// m references costs m scores per row and leaves about 41 nr / m keys to
+// append, each as much as some 320 / steps scores (steps: 128-byte chunks of a
+// row): least in all at m = sqrt(13,200 nr / steps).  20,000 x 128 FP32 at 0.25,
+// 0.5, 1, 2 times that: 671 / 640 / 670 / 794 us; 70,000 x 784 BF16 14.8 / 14.8 /
+// 13.8 / 14.5 ms; 10,000 queries x 1M x 50 FP32 6.0 / 5.6 / 5.1 / 5.2 ms.
+static int gate_tiles(int64_t nr, int lds)
+{
+    const double m = sqrt(13200.0 * (double)nr * 64.0 / (double)lds);
+    return (int)std::min<int64_t>(ceil_div(nr, kTileRows), std::max<int64_t>(32, (int64_t)(m / kTileRows)));
+}
+
 static size_t elem_bytes(int dtype) { return dtype == KNN_F32 ? 4 : 2; }
 
 // Scratch bytes of one exact call with query chunks of qc rows (every
@@ -1996,12 +1982,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     if (gated) {
         if ((r = ws.alloc(&lims, (size_t)qc)) != KNN_OK) return r;
         if ((r = ws.alloc(&cnt, (size_t)qc * S)) != KNN_OK) return r;
-        // The gate's sample of m references costs m scores per row and leaves
-        // about 41 R.n / m keys to append, each as much as some 320 / steps
-        // scores (steps: 128-byte chunks of a row): least in all at m =
-        // sqrt(13,200 R.n / steps)
-        const double m = sqrt(13200.0 * (double)R.n * 64.0 / (double)lds);
-        ntiles = (int)std::min<int64_t>(ceil_div(R.n, kTileRows), std::max<int64_t>(32, (int64_t)(m / kTileRows)));
+        ntiles = gate_tiles(R.n, lds);
     }
 
     // GEMM error bound (FP32): split_err u (|q| + max|r|)^2 with u = 2^-24;
@@ -2217,35 +2198,107 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
     const int64_t split_len = ceil_div(ntile, S) * kTileRows;
     S = (int)ceil_div(n, split_len);   // no empty split
     const int64_t per_launch = kRankBlocks / S;   // query blocks per launch
-    uint32_t* rq = nullptr;
-    if ((X.d > kRankDirectD || Y.d > kRankDirectD) &&
-        (r = ws.alloc(&rq, (size_t)std::min<int64_t>(nblk, per_launch) * S * kTileRows * kTileRows)) != KNN_OK)
-        return r;
     const int kp = 2 * k < kListW ? 2 * k : kListW;   // the lists' re-rank width, as knn_exact's default
-    uint64_t* part = nullptr;
-    if (fused && (r = ws.alloc(&part, (size_t)n * S * kListW)) != KNN_OK) return r;
-    auto rank_tile = [&](const float* Zs, const float* zn, int ldz, int dz, const uint64_t* pz, const unsigned* mx,
-                         uint32_t* cz, uint64_t* lists) {
-        // GEMM distance error: 2 gamma_d |q| |r| for the FP32 dot product
-        // plus 2u (|q|^2 + |r|^2) for the norms (FP64 sums rounded once)
-        // and their sum; the canonical distance's own error (edir) carries
-        // the margin for the final rounding
-        const float ecd = 2.0f * (float)(dz + 2) * u * 1.01f, ecn = 2.02f * u;
+    // scratch of one launch of query blocks: queues, and with lists the gates,
+    // buffers, counts and the rows without a certificate
+    const int64_t lrows = std::min<int64_t>(nblk, per_launch) * kTileRows;
+    uint64_t *rq = nullptr, *part = nullptr;
+    float* lims = nullptr;
+    uint32_t* cnt = nullptr;
+    int32_t* fb_rows = nullptr;
+    unsigned* fb_count = nullptr;   // [1]: fallback parts done
+    if ((X.d > kRankDirectD || Y.d > kRankDirectD) &&
+        (r = ws.alloc(&rq, (size_t)(lrows / kTileRows) * S * kRankQueue)) != KNN_OK)
+        return r;
+    if (fused) {
+        if ((r = ws.alloc(&part, (size_t)lrows * S * kCandCap)) != KNN_OK) return r;
+        if ((r = ws.alloc(&lims, (size_t)lrows)) != KNN_OK) return r;
+        if ((r = ws.alloc(&cnt, (size_t)lrows * S)) != KNN_OK) return r;
+        if ((r = ws.alloc(&fb_rows, (size_t)lrows)) != KNN_OK) return r;
+        if ((r = ws.alloc(&fb_count, 2)) != KNN_OK) return r;
+    }
+    // ranks of the probes pz of Z's rows (FP32 rows Zf, norms zn, largest norm
+    // mx) among Z's rows into cz; with lists also X's exact neighbours into Hn
+    auto rank_tile = [&](const float* Zf, const float* zn, int ldf, int dz, const uint64_t* pz, const unsigned* mx,
+                         uint32_t* cz, bool lists) -> knn_status {
+        const int lds = 2 * (int)round_up(dz, 32);   // split rows, in FP16 values
+        _Float16* Zs = nullptr;
+        if ((r = ws.alloc((void**)&Zs, (size_t)n * lds * 2)) != KNN_OK) return r;
+        split_kernel<KNN_F32, KNN_SPLIT><<<(unsigned)std::min<int64_t>(ceil_div(n * (lds / 16), 256), 16384), 256, 0, st>>>(
+            Zf, n, dz, ldf, Zs, lds / 2, mx);
+        // Error of a GEMM distance: 2 |q||r| (9 + 3 i + s + 12 + 4) u with i
+        // instructions per segment and s segments (see split_err: products and
+        // running sums of a segment; the segments' additions; the parts' rounding;
+        // the score's subtraction and slack), plus 4u (|q|^2 + |r|^2 + the
+        // probe's distance) for the norms (FP64 sums rounded once) and the
+        // probes' scores; the canonical distance's own error is edir
+        const int chunks = lds / 64;
+        const float inst = 6.0f * (float)std::min(chunks, kSegChunks), segs = (float)ceil_div(chunks, kSegChunks);
+        const float ecd = 2.0f * (25.0f + 3.0f * inst + segs) * u * 1.01f, ecn = 4.04f * u;
         const float ed = (float)(dz / 16 + 8) * u;
+        const bool ares = lds <= TileCfg<KNN_SPLIT>::AMAX;
         zero_words_kernel<<<(unsigned)std::min<int64_t>(ceil_div(n * kRankP, 64), 4096), 64, 0, st>>>(cz,
                                                                                                  n * kRankP);
+        const int ntiles = gate_tiles(n, lds);
         for (int64_t q0 = 0; q0 < n; q0 += per_launch * kTileRows) {
             const int64_t nq = std::min<int64_t>(n - q0, per_launch * kTileRows);
-            const unsigned g = (unsigned)(ceil_div(nq, kTileRows) * S);
-            if (lists)
-                rank_tile_kernel<true><<<g, 256, 0, st>>>(Zs + q0 * ldz, zn + q0, nq, Zs, zn, n, ldz, dz, 1, q0,
-                                                          pz + q0 * kRankP, mx, ecd, ecn, ed, S, split_len,
-                                                          cz + q0 * kRankP, rq, kp, lists + q0 * S * kListW);
-            else
-                rank_tile_kernel<false><<<g, 256, 0, st>>>(Zs + q0 * ldz, zn + q0, nq, Zs, zn, n, ldz, dz, 1, q0,
-                                                           pz + q0 * kRankP, mx, ecd, ecn, ed, S, split_len,
-                                                           cz + q0 * kRankP, rq, kp, nullptr);
+            const unsigned nb = (unsigned)ceil_div(nq, kTileRows);
+            if (lists) {
+                const dim3 gg(nb, (unsigned)std::min(S, ntiles));
+                float* gtop = (float*)part;
+                if (ares)
+                    exact_gate_kernel<KNN_SPLIT, true><<<gg, 256, 0, st>>>(Zs + q0 * lds, nq, Zs, zn, n, lds, nullptr, 1,
+                                                                           q0, ntiles, mx, mx, gtop);
+                else
+                    exact_gate_kernel<KNN_SPLIT, false><<<gg, 256, 0, st>>>(Zs + q0 * lds, nq, Zs, zn, n, lds, nullptr, 1,
+                                                                            q0, ntiles, mx, mx, gtop);
+                gate_select_kernel<<<(unsigned)ceil_div(nq, 8), 256, 0, st>>>(
+                    gtop, nq, (int)gg.y, kp, zn + q0, mx, mx, 2.0f * split_err(dz, KNN_SPLIT) * u, lims);
+            }
+#define KNN_RANK(L, A, NP)                                                                                        \
+    rank_tile_kernel<L, A, NP><<<nb * (unsigned)S, 256, 0, st>>>(                                                  \
+        Zs + q0 * lds, zn + q0, nq, Zs, zn, n, lds, Zf + q0 * ldf, Zf, ldf, dz, q0, pz + q0 * kRankP, mx, ecd, ecn, \
+        ed, S, split_len, cz + q0 * kRankP, rq, kp, lims, part, cnt)
+#define KNN_RANK_NP(L, A)                                                                                         \
+    if (k <= 8) KNN_RANK(L, A, 8);                                                                                \
+    else if (k <= 12) KNN_RANK(L, A, 12);                                                                         \
+    else KNN_RANK(L, A, 16)
+            if (lists && ares) {
+                KNN_RANK_NP(true, true);
+            } else if (lists) {
+                KNN_RANK_NP(true, false);
+            } else if (ares) {
+                KNN_RANK_NP(false, true);
+            } else {
+                KNN_RANK_NP(false, false);
+            }
+#undef KNN_RANK_NP
+#undef KNN_RANK
+            KNN_HIP(hipGetLastError());
+            if (!lists) continue;
+            // X's exact lists: merge, canonical re-rank, certificate, and the
+            // exhaustive search for rows not certified
+            zero_words_kernel<<<1, 64, 0, st>>>(fb_count, 2);
+            const float err_coef = split_err(X.d, KNN_SPLIT) * u * 1.01f;
+            const void* Xq = (const char*)X.data + (size_t)q0 * X.ld * elem_bytes(X.dtype);
+#define KNN_QMR(DT)                                                                                              \
+    merge_rerank_kernel<DT><<<(unsigned)ceil_div(nq, 4), 256, 0, st>>>(                                             \
+        part, cnt, nullptr, 1, q0, mx, S, nq, kp, k, Xq, X.ld, X.data, X.ld, X.d, zn + q0, mx, err_coef, ed, 1, n - 1, \
+        KNN_OUT_SQL2, Hn + q0 * k, Hd + q0 * k, fb_rows, (int*)fb_count);                                            \
+    exact_fallback_kernel<DT><<<1024, 256, 0, st>>>(fb_rows, (int*)fb_count, Xq, X.ld, X.data, X.ld, n, X.d, nullptr, \
+                                                    1, q0, k, KNN_OUT_SQL2, Hn + q0 * k, Hd + q0 * k, part, nq * S,  \
+                                                    fb_count + 1)
+            if (X.dtype == KNN_F32) {
+                KNN_QMR(KNN_F32);
+            } else if (X.dtype == KNN_BF16) {
+                KNN_QMR(KNN_BF16);
+            } else {
+                KNN_QMR(KNN_F16);
+            }
+#undef KNN_QMR
+            KNN_HIP(hipGetLastError());
         }
+        return KNN_OK;
     };
     auto rank_direct = [&](const float* Zs, int ldz, int dz, const uint64_t* pz, uint32_t* cz) {
         // reference splits (counts added) so that enough waves hide the tile reads
@@ -2267,41 +2320,15 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
     if (!fused) {
         rank_direct((const float*)Xs, ldx, X.d, pu, cu);
     } else {
-        rank_tile((const float*)Xs, xn, ldx, X.d, pu, small, cu, part);
-        KNN_HIP(hipGetLastError());
-        // X's exact lists from the split lists: merge, canonical re-rank,
-        // certificate, and the exhaustive search for rows not certified
-        int32_t* fb_rows = nullptr;
-        int* fb_count = nullptr;
-        if ((r = ws.alloc(&fb_rows, (size_t)n)) != KNN_OK) return r;
-        if ((r = ws.alloc(&fb_count, 2)) != KNN_OK) return r;   // [1]: fallback parts done
-        zero_words_kernel<<<1, 64, 0, st>>>((unsigned*)fb_count, 2);
-        const float err_coef = (float)(X.d + 3) * u * 1.01f, edir = (float)(X.d / 16 + 8) * u;
-        const dim3 mgrid((unsigned)ceil_div(n, 4));
-#define KNN_QMR(DT)                                                                                            \
-    merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, nullptr, nullptr, 1, 0, nullptr, S, n, kp, k, X.data, X.ld, \
-                                                   X.data, X.ld, X.d, xn, small,                                 \
-                                                   err_coef, edir, 1, n - 1, KNN_OUT_SQL2, Hn, Hd, fb_rows, fb_count); \
-    exact_fallback_kernel<DT><<<1024, 256, 0, st>>>(fb_rows, fb_count, X.data, X.ld, X.data, X.ld, n, X.d, nullptr,  \
-                                                    1, 0, k, KNN_OUT_SQL2, Hn, Hd, part, n * S,                    \
-                                                    (unsigned*)fb_count + 1)
-        if (X.dtype == KNN_F32) {
-            KNN_QMR(KNN_F32);
-        } else if (X.dtype == KNN_BF16) {
-            KNN_QMR(KNN_BF16);
-        } else {
-            KNN_QMR(KNN_F16);
-        }
-#undef KNN_QMR
-        KNN_HIP(hipGetLastError());
+        if ((r = rank_tile((const float*)Xs, xn, ldx, X.d, pu, small, cu, true)) != KNN_OK) return r;
         quality_probes_kernel<<<(unsigned)ceil_div(n, 4), 256, 0, st>>>(n, k, Hn, Ln, (const float*)Xs, ldx, X.d,
                                                                         (const float*)Ys, ldy, Y.d, nullptr, pv,
                                                                         hits, 0);
     }
     if (Y.d <= kRankDirectD)
         rank_direct((const float*)Ys, ldy, Y.d, pv, cv);
-    else
-        rank_tile((const float*)Ys, yn, ldy, Y.d, pv, small + 1, cv, nullptr);
+    else if ((r = rank_tile((const float*)Ys, yn, ldy, Y.d, pv, small + 1, cv, false)) != KNN_OK)
+        return r;
     KNN_HIP(hipGetLastError());
     unsigned long long* tot = (unsigned long long*)(small + 2);
     quality_reduce_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(n, k, pu, cu, pv, cv, hits, trust_out,

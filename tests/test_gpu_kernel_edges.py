@@ -250,3 +250,20 @@ def test_pca_refuses_low_rank(X):
          "rows": rng.normal(size=(15, 100)), "zero": np.zeros((100, 50))}[X]
     with pytest.raises(knn.KnnError):
         knn.pca(torch.from_numpy(np.ascontiguousarray(X.astype(np.float32))).cuda(), 3 if X.shape[1] == 100 else 2)
+
+
+@pytest.mark.parametrize("d,e", [(17, 2), (33, 17), (64, 40), (65, 3), (130, 129)])
+@pytest.mark.parametrize("k", [8, 9, 16])
+def test_rank_pass_widths(orc, d, e, k):
+    """The rank pass over its probe widths (8, 12, 16) and row widths (one
+    to five chunks of 32, with and without resident query rows), with (X) and
+    without (Y above 16 dimensions) the neighbour lists; one tile and a row
+    past four."""
+    X = datagen.gmm_isotropic(n=513, d=d, comps=4, seed=d)
+    rng = np.random.default_rng(e)
+    Y = (X @ rng.normal(size=(d, e)) + rng.normal(scale=0.5, size=(513, e))).astype(np.float32)
+    import paper_2603_04035_amd as knn
+    _, (h, t, c) = knn.quality(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k, per_row=True)
+    oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
+    assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
+    assert np.array_equal(c.cpu().numpy(), oc)
