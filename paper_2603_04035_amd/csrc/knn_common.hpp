@@ -133,6 +133,13 @@ __device__ __attribute__((always_inline)) inline uint64_t bcast_u64(uint64_t v, 
     uint32_t lo = bcast_u32((uint32_t)v, l), hi = bcast_u32((uint32_t)(v >> 32), l);
     return ((uint64_t)hi << 32) | lo;
 }
+// Value of lane - 1 (lane 0: 0): a DPP wave shift, no LDS round trip.
+__device__ __attribute__((always_inline)) inline uint64_t shift_up_u64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x138, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
+}
 __device__ inline uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
 __device__ inline uint64_t umax64(uint64_t a, uint64_t b) { return a < b ? b : a; }
 
@@ -291,6 +298,32 @@ __device__ inline float dist_batch16(const void* X, int64_t ld, int64_t a, uint3
     return mine;
 }
 
+// Canonical FP32 squared distance for d <= DT <= 16 coordinates: the
+// squares of coordinates t < d (t mod 16 = t), then the fixed tree at
+// strides 8, 4, 2, 1 (terms known to be zero left out); every square and
+// sum rounded, as dist_g16 rounds them.
+template <int DT>
+__device__ __attribute__((always_inline)) inline float direct_d2(const float (&xq)[DT], const float* xr, int d)
+{
+#pragma clang fp contract(off)
+    float sq[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        if (t < DT) {
+            const float e = xq[t] - xr[t];
+            sq[t] = t < d ? e * e : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int j = 8; j > 0; j >>= 1) {
+#pragma unroll
+        for (int g = 0; g < j; ++g) {
+            if (g + j < DT) sq[g] = sq[g] + sq[g + j];
+        }
+    }
+    return sq[0];
+}
+
 // ------------------------------------------------------------------ host
 
 void set_error(const std::string& msg);
@@ -361,6 +394,11 @@ __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + 
 __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
 knn_status check_matrix(const knn_matrix& X, const char* name);
+
+// Exact k-NN by direct canonical distances for d <= kLowdimD (knn_lowdim.hip).
+constexpr int kLowdimD = 3;
+knn_status lowdim_knn(const knn_matrix& Q, const knn_matrix& R, bool same, const int32_t* q_self, int self_mode,
+                      int k, int out_kind, int32_t* out_idx, float* out_dist, hipStream_t st, ScratchAlloc& ws);
 
 // Counters that many workgroups add to are kept in kCounterBanks banks of
 // kCounterWords words (one 64-byte line each): workgroup b adds to bank

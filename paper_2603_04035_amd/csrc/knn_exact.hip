@@ -273,14 +273,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // 8*(v/4) + 4*(l/32) + v%4 and column l%32 of the 32x32 block.
 __device__ inline int mfma_row(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
 
-// Value of lane - 1 (lane 0: 0): a DPP wave shift, no LDS round trip.
-__device__ __attribute__((always_inline)) inline uint64_t shift_up_u64(uint64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x138, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, false);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 // Adds the keys of the lanes in `m` (lanes 0..31 for the list held by lanes
 // 0..31, lanes 32..63 for the one held by lanes 32..63) to the two sorted
 // 32-key lists, keeping each list's 32 smallest.  A few keys are inserted one
@@ -1122,32 +1114,6 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
     if (LISTS && tid < kTileRows && q0 + tid < nq) cnt[(q0 + tid) * S + sp] = scnt[tid];
 }
 
-// Canonical FP32 squared distance for d <= DT <= 16 coordinates: the
-// squares of coordinates t < d (t mod 16 = t), then the fixed tree at
-// strides 8, 4, 2, 1 (terms known to be zero left out); every square and
-// sum rounded, as dist_g16 rounds them.
-template <int DT>
-__device__ __attribute__((always_inline)) inline float direct_d2(const float (&xq)[DT], const float* xr, int d)
-{
-#pragma clang fp contract(off)
-    float sq[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        if (t < DT) {
-            const float e = xq[t] - xr[t];
-            sq[t] = t < d ? e * e : 0.0f;
-        }
-    }
-#pragma unroll
-    for (int j = 8; j > 0; j >>= 1) {
-#pragma unroll
-        for (int g = 0; g < j; ++g) {
-            if (g + j < DT) sq[g] = sq[g] + sq[g + j];
-        }
-    }
-    return sq[0];
-}
-
 // The same counts for a low-dimensional space (d <= kRankDirectD, e.g. a 2-D
 // embedding), by direct canonical FP32 distances: there the norm
 // expansion's error bound is wider than neighbour distances, so a GEMM pass
@@ -1908,8 +1874,19 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     const int kind = precision == KNN_PREC_BF16 ? KNN_BF16
                      : full && R.dtype == KNN_F32 ? KNN_SPLIT : KNN_F16;
     const bool bf = !full;
-    if (full && R.d <= kRankDirectD)
+    // a few coordinates: exact_direct_kernel's launches are cheaper sooner (1500 x 2
+    // 61 us against 78, 2000 x 2 73 against 75, 3000 x 2 108 against 77; 2000 x 8 72
+    // against 115, 3000 x 8 109 against 119)
+    const int64_t small_refs = R.d > kRankDirectD ? kSmallRefs : (R.d > kLowdimD ? 2560 : 1536);
+    const bool small = full && R.n <= small_refs && (double)Q.n * (double)R.n * (6.0 * R.d + 150.0) <= kSmallWork;
+    if (full && R.d <= kRankDirectD && !(small && budget == 0)) {
+        // the pruned search needs eleven launches (3000 x 3 88 us against 76,
+        // 5000 x 3 96 against 115; one query in 4000 x 2 73 against 64, in 20,000 x 2
+        // 79 against 160); under a workspace limit the other one, which can be cut up
+        if (R.d <= kLowdimD && budget == 0 && R.n >= 6144)
+            return lowdim_knn(Q, R, same, q_self, self_mode, k, out_kind, out_idx, out_dist, st, ws);
         return exact_direct_impl(Q, R, q_self, self_mode, k, out_kind, out_idx, out_dist, st, ws, budget);
+    }
 
     // query chunk: the largest multiple of the tile height that fits
     int64_t qc = Q.n;
@@ -1926,7 +1903,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
                                         " bytes the staged reference set and one 128-query chunk need");
         qc = lo * kTileRows;
     }
-    if (full && R.n <= kSmallRefs && (double)Q.n * (double)R.n * (6.0 * R.d + 150.0) <= kSmallWork) {
+    if (small) {
         const unsigned g = (unsigned)ceil_div(Q.n, 4);
 #define KNN_SM(DT)                                                                                               \
     exact_small_kernel<DT><<<g, 256, 0, st>>>(Q.data, Q.ld, (int)Q.n, R.data, R.ld, (int)R.n, R.d, q_self,         \
@@ -1945,15 +1922,15 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     knn_status r;
     // [0] = max ref norm bits, [1] = fallback count, [2] = fallback parts done,
     // [3] = max query norm bits (FP32, Q != R)
-    unsigned* small = nullptr;
-    r = ws.alloc(&small, 4);
+    unsigned* words = nullptr;
+    r = ws.alloc(&words, 4);
     if (r != KNN_OK) return r;
-    zero_words_kernel<<<1, 64, 0, st>>>(small, 4);
+    zero_words_kernel<<<1, 64, 0, st>>>(words, 4);
     void *Rs = nullptr, *Qb = nullptr;
     float *rn = nullptr, *qnb = nullptr;
     int ldp = 0;
-    if (full) r = stage_full(ws, R, kind, &Rs, &ldp, &rn, small, st);
-    else r = stage_matrix(ws, R, kind, &Rs, &ldp, &rn, small, st, nullptr, 0);
+    if (full) r = stage_full(ws, R, kind, &Rs, &ldp, &rn, words, st);
+    else r = stage_matrix(ws, R, kind, &Rs, &ldp, &rn, words, st, nullptr, 0);
     if (r != KNN_OK) return r;
     const size_t eb = kind == KNN_SPLIT ? 4 : 2;
     if (!same) {
@@ -1991,28 +1968,28 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     const float err_coef = split_err(R.d, kind) * u * 1.01f;
     const float edir = (float)(R.d / 16 + 8) * u;
     const int certify = bf ? 0 : 1;
-    int* fb_count = (int*)(small + 1);
+    int* fb_count = (int*)(words + 1);
     const size_t qeb = elem_bytes(Q.dtype);
 
     for (int64_t q0 = 0; q0 < Q.n; q0 += qc) {
         const int64_t nq = Q.n - q0 < qc ? Q.n - q0 : qc;
         const void* Qs;
         const float* qn;
-        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(small + 1, 3);
+        if (q0 > 0) zero_words_kernel<<<1, 64, 0, st>>>(words + 1, 3);
         if (same) {
             Qs = (const char*)Rs + (size_t)q0 * ldp * eb;
             qn = rn + q0;
         } else {
             const knn_matrix Qc = {(const char*)Q.data + (size_t)q0 * Q.ld * qeb, nq, Q.d, Q.ld, Q.dtype};
-            if (full) launch_full(kind, Qc, Qb, ldp, qnb, small + 3, st);
+            if (full) launch_full(kind, Qc, Qb, ldp, qnb, words + 3, st);
             else launch_stage_kind(kind, Qc, Qb, ldp, qnb, nullptr, nullptr, 0, st);
             Qs = Qb;
             qn = qnb;
         }
         const int32_t* qself = self_mode == 2 ? q_self + q0 : nullptr;
         
-        const unsigned* qmax = !full ? nullptr : (same ? small : small + 3);
-        const TileArgs ta = {Qs, qn, nq, Rs, rn, R.n, lds, qself, self_mode, q0, kp, split_len, S, small, qmax, part,
+        const unsigned* qmax = !full ? nullptr : (same ? words : words + 3);
+        const TileArgs ta = {Qs, qn, nq, Rs, rn, R.n, lds, qself, self_mode, q0, kp, split_len, S, words, qmax, part,
                              gated, ntiles, 2.0f * split_err(R.d, kind) * u, lims, cnt};
         if (kind == KNN_BF16) launch_tiles<KNN_BF16>(ares, ta, st);
         else if (kind == KNN_F16) launch_tiles<KNN_F16>(ares, ta, st);
@@ -2025,7 +2002,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         dim3 mgrid((unsigned)ceil_div(nq, 4));
 #define KNN_MR(DT)                                                                              \
     merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, cnt, qself, self_mode, q0, qmax, S, nq, kp, k, Qd, Q.ld, R.data, R.ld,  \
-                                                   R.d, qn, small, err_coef, edir, certify,     \
+                                                   R.d, qn, words, err_coef, edir, certify,     \
                                                    avail, out_kind, oi, od, fb_rows, fb_count)
         if (Q.dtype == KNN_F32) KNN_MR(KNN_F32);
         else if (Q.dtype == KNN_BF16) KNN_MR(KNN_BF16);
@@ -2037,7 +2014,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
 #define KNN_FB(DT)                                                                              \
     exact_fallback_kernel<DT><<<fgrid, 256, 0, st>>>(fb_rows, fb_count, Qd, Q.ld, R.data, R.ld, \
                                                      R.n, R.d, qself, self_mode, q0, k,         \
-                                                     out_kind, oi, od, part, nq * S, small + 2)
+                                                     out_kind, oi, od, part, nq * S, words + 2)
             if (Q.dtype == KNN_F32) KNN_FB(KNN_F32);
             else if (Q.dtype == KNN_BF16) KNN_FB(KNN_BF16);
             else KNN_FB(KNN_F16);

@@ -267,3 +267,52 @@ def test_rank_pass_widths(orc, d, e, k):
     oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
     assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
     assert np.array_equal(c.cpu().numpy(), oc)
+
+
+@pytest.mark.parametrize("n", [1536, 1537, 6143, 6144, 8192, 8193, 262_144, 262_145])
+@pytest.mark.parametrize("d", [1, 2, 3])
+@pytest.mark.parametrize("kind", ["normal", "copies", "line", "inf-nan", "huge", "half"])
+def test_pruned_search_equals_all_pairs(n, d, kind):
+    """One to three coordinates: the search pruned by boxes gives the bits of
+    the one over all pairs (taken under a workspace limit), as a self search
+    and for queries; last tiles and groups whole and in part, both grid
+    resolutions, ties, copies, distances that overflow or are NaN."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    if kind == "copies":
+        X = np.round(X)
+        X[:200] = X[0]
+    if kind == "line":
+        X[:, 0] = 1e4
+    if kind == "inf-nan":
+        X[[3, n // 2], 0] = np.inf, np.nan
+        X[n - 1, d - 1] = -np.inf
+    if kind == "huge":
+        X *= 1.5e19
+    X = torch.from_numpy(X).cuda()
+    X = X.half() if kind == "half" else X
+    rows = torch.unique(torch.cat([torch.arange(0, n, max(1, n // 300)), torch.tensor([1, 3, n // 2, n - 1])])).cuda()
+    Q, own = X[rows].contiguous(), rows.to(torch.int32)
+    for k in (1, 32):
+        ref_i, ref_d = knn.knn_exact_query(Q, X, k, q_self=own, workspace_limit=1 << 30)[:2]
+        for i, dist in (knn.knn_exact(X, k)[:2], knn.knn_exact_query(Q, X, k, q_self=own)[:2]):
+            if len(i) == n:
+                i, dist = i[rows], dist[rows]
+            assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
+    ref_i, ref_d = knn.knn_exact_query(Q + 0.25, X, 10, workspace_limit=1 << 30)[:2]
+    i, dist = knn.knn_exact_query(Q + 0.25, X, 10)[:2]
+    assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
+
+
+@pytest.mark.parametrize("n,d", [(2, 1), (64, 2), (1536, 3), (1537, 4), (2560, 16), (2561, 8)])
+def test_small_search_few_coordinates(n, d):
+    """Up to 1536 (d <= 3) and 2560 references the one-launch search gives the
+    bits of the direct one."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(np.random.default_rng(n).integers(-5, 6, (n, d)).astype(np.float32) / 3).cuda()
+    k = min(n - 1, 12)
+    own = torch.arange(n, dtype=torch.int32).cuda()
+    ref_i, ref_d = knn.knn_exact_query(X, X, k, q_self=own, workspace_limit=1 << 30)[:2]
+    i, dist = knn.knn_exact(X, k)[:2]
+    assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
