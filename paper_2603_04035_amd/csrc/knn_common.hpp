@@ -395,6 +395,14 @@ __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return ceil_
 
 knn_status check_matrix(const knn_matrix& X, const char* name);
 
+// Stable radix sort of S independent arrays of n (key, value) pairs each, by
+// keys below 2^bits (knn_encoder.hip): sorted in (k0, v0) on return, the pointers
+// swapped with (k1, v1) as the passes need.  counts: S radix_counts_words(n)
+// words.  iota: the values are 0..n-1 (v0 need not hold them).
+knn_status radix_sort_bits(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n,
+                           uint32_t* counts, hipStream_t st, int bits, int S, bool iota = false);
+size_t radix_counts_words(int64_t n);
+
 // Exact k-NN by direct canonical distances for d <= kLowdimD (knn_lowdim.hip).
 constexpr int kLowdimD = 3;
 knn_status lowdim_knn(const knn_matrix& Q, const knn_matrix& R, bool same, const int32_t* q_self, int self_mode,

@@ -586,15 +586,22 @@ __global__ __launch_bounds__(256) void grad_reduce_adam_kernel(const float* __re
 
 // ------------------------------------------------------------ radix sort
 
-constexpr int kRsThreads = 256, kRsItems = 16, kRsTile = kRsThreads * kRsItems;
-
-__host__ __device__ inline size_t rs_counts(int64_t n)
+// Elements per thread of a workgroup's tile (16 or 4): small arrays are cut finer,
+// for they leave the chip idle (a scatter of 5,000 or 70,000: 7 us against 12; of 1,000,000:
+// 19 us with 16 elements, 22 with 4).
+constexpr int kRsThreads = 256;
+constexpr int64_t kRsFine = 1 << 17;
+__host__ __device__ inline int rs_items(int64_t n) { return n <= kRsFine ? 4 : 16; }
+__host__ __device__ inline int64_t rs_tiles(int64_t n)
 {
-    return (size_t)256 * ((n + kRsTile - 1) / kRsTile) + 256;
+    const int64_t t = (int64_t)kRsThreads * rs_items(n);
+    return (n + t - 1) / t;
 }
+__host__ __device__ inline size_t rs_counts(int64_t n) { return (size_t)256 * rs_tiles(n) + 256; }
 
 // Sorts run on blockIdx.y independent arrays of n elements at once: array
 // y's elements (and outputs) start at y * n, its counts at y * rs_counts(n).
+template <int ITEMS>
 __global__ __launch_bounds__(256) void rs_hist_kernel(const uint32_t* __restrict__ keys, int64_t n, int shift,
                                                       uint32_t* __restrict__ counts, int nblk)
 {
@@ -603,8 +610,9 @@ __global__ __launch_bounds__(256) void rs_hist_kernel(const uint32_t* __restrict
     counts += (int64_t)blockIdx.y * rs_counts(n);
     hist[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int it = 0; it < kRsItems; ++it) {
+    const int64_t base = (int64_t)blockIdx.x * kRsThreads * ITEMS;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t e = base + it * kRsThreads + threadIdx.x;
         if (e < n) atomicAdd(&hist[(keys[e] >> shift) & 255u], 1u);
     }
@@ -652,38 +660,52 @@ __global__ __launch_bounds__(256) void rs_scan_kernel(uint32_t* __restrict__ c, 
     if (threadIdx.x == 0) tot[blockIdx.x] = carry;
 }
 
-// Stable scatter of one 8-bit digit: elements of a tile are visited in index
-// order (item-major, then thread); within a wave, lanes with equal digits are
-// ranked by a ballot match over the 8 digit bits; across waves by per-wave
-// counts in LDS; across tiles by the scanned histogram.
+// Stable scatter of one 8-bit digit.  A wave takes 64 * ITEMS consecutive
+// elements and ranks them by itself: lanes with equal digits by a ballot match
+// over the 8 digit bits, its elements in turn by its own row of counts in
+// LDS.  Then one barrier, the counts' prefix over digits and waves, and the
+// tile goes through LDS in sorted order, so that the stores of a digit are
+// consecutive.  Bound by the matches (VALU) and the stores' runs of 16 elements.
+// vin null: the values are 0..n-1.
+// A pass over 15,000,000 pairs: 78 us (240 MB; 205 us with four barriers per 256
+// elements and stores in input order), over 5,000: 6.8 us (17.2).
+template <int ITEMS>
 __global__ __launch_bounds__(256) void rs_scatter_kernel(const uint32_t* __restrict__ kin,
                                                          const uint32_t* __restrict__ vin,
                                                          uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                          int64_t n, int shift,
                                                          const uint32_t* __restrict__ offs, int nblk)
 {
-    __shared__ uint32_t run[256];
-    __shared__ uint32_t wcnt[4][256];
+    constexpr int TILE = kRsThreads * ITEMS;
+    __shared__ uint32_t wcnt[4][256];   // per wave and digit: elements, then those of earlier waves
+    __shared__ uint32_t lofs[256];      // a digit's first place in the tile
+    __shared__ uint32_t gofs[256];      // its first place in the output less lofs
     __shared__ uint32_t sc[256];
+    __shared__ uint32_t sk[TILE], sv[TILE];
     const int64_t so = (int64_t)blockIdx.y * n;
     kin += so;
-    vin += so;
+    if (vin) vin += so;
     kout += so;
     vout += so;
     offs += (int64_t)blockIdx.y * rs_counts(n);
     const uint32_t* tot = offs + (int64_t)256 * nblk;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t all;
-    const uint32_t dbase = block_exscan256(tot[tid], sc, &all);
-    run[tid] = dbase + offs[(int64_t)tid * nblk + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int it = 0; it < kRsItems; ++it) {
-        const int64_t e = base + it * kRsThreads + tid;
-        const bool valid = e < n;
-        const uint32_t key = valid ? kin[e] : 0u;
-        const uint32_t val = valid ? vin[e] : 0u;
-        const uint32_t dig = (key >> shift) & 255u;
+    const int64_t base = (int64_t)blockIdx.x * TILE, wbase = base + wv * 64 * ITEMS + lane;
+    const int cnt = (int)(n - base < TILE ? n - base : TILE);
+    uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t e = wbase + it * 64;
+        key[it] = e < n ? kin[e] : 0u;
+        val[it] = e < n ? (vin ? vin[e] : (uint32_t)e) : 0u;
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const bool valid = wbase + it * 64 < n;
+        const uint32_t dig = (key[it] >> shift) & 255u;
         uint64_t peers = ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -691,29 +713,47 @@ __global__ __launch_bounds__(256) void rs_scatter_kernel(const uint32_t* __restr
             const uint64_t bal = ballot(valid && bit);
             peers &= bit ? bal : ~bal;
         }
-        const int rank = __popcll(peers & lt);
-        const int cnt = __popcll(peers);
-        wcnt[0][tid] = 0;
-        wcnt[1][tid] = 0;
-        wcnt[2][tid] = 0;
-        wcnt[3][tid] = 0;
-        __syncthreads();
-        if (valid && rank == 0) wcnt[wv][dig] = (uint32_t)cnt;
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = run[dig] + (uint32_t)rank;
-            for (int w = 0; w < wv; ++w) pos += wcnt[w][dig];
-            kout[pos] = key;
-            vout[pos] = val;
+        const uint32_t below = (uint32_t)rank_below(peers), before = wcnt[wv][dig];
+        rank[it] = before + below;
+        // the wave's LDS accesses keep their order: every lane has read before
+        // the first lane of a digit writes
+        if (valid && below == 0u) wcnt[wv][dig] = before + (uint32_t)popc64(peers);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t c = wcnt[w][tid];
+        wcnt[w][tid] = t;
+        t += c;
+    }
+    uint32_t all;
+    const uint32_t lo = block_exscan256(t, sc, &all);
+    const uint32_t dbase = block_exscan256(tot[tid], sc, &all);
+    lofs[tid] = lo;
+    gofs[tid] = dbase + offs[(int64_t)tid * nblk + blockIdx.x] - lo;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (wbase + it * 64 < n) {
+            const uint32_t dig = (key[it] >> shift) & 255u, p = lofs[dig] + wcnt[wv][dig] + rank[it];
+            sk[p] = key[it];
+            sv[p] = val[it];
         }
-        __syncthreads();
-        run[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int p = it * kRsThreads + tid;
+        if (p < cnt) {
+            const uint32_t k = sk[p];
+            const int64_t o = gofs[(k >> shift) & 255u] + (uint32_t)p;
+            kout[o] = k;
+            vout[o] = sv[p];
+        }
     }
 }
-
-knn_status radix_sort_bits(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n,
-                           uint32_t* counts, hipStream_t st, int bits, int S);
 
 // Sort S independent arrays of (key, value) pairs, n each and contiguous
 // (k0 + y n, ...), by key, stable; results in (k0, v0).  k1 / v1 hold S n
@@ -726,20 +766,26 @@ static knn_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uin
 
 size_t radix_counts_words(int64_t n) { return rs_counts(n); }
 
-// As radix_sort_pairs, on keys below 2^bits: ceil(bits / 8) passes (bits in
-// 1..32).  An odd pass count leaves the result in (k1, v1): the pointers are
-// swapped so that (k0, v0) name the sorted arrays on return.
+// ceil(bits / 8) passes (bits in 1..32); an odd count leaves the result in what
+// were k1 and v1.
 knn_status radix_sort_bits(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n,
-                           uint32_t* counts, hipStream_t st, int bits, int S)
+                           uint32_t* counts, hipStream_t st, int bits, int S, bool iota)
 {
-    const int nblk = (int)ceil_div(n, kRsTile);
+    const int nblk = (int)rs_tiles(n);
     const int npass = (bits + 7) / 8;
+    const dim3 g((unsigned)nblk, (unsigned)S);
     for (int pass = 0; pass < npass; ++pass) {
         const int shift = 8 * pass;
-        rs_hist_kernel<<<dim3((unsigned)nblk, (unsigned)S), kRsThreads, 0, st>>>(k0, n, shift, counts, nblk);
-        rs_scan_kernel<<<dim3(256, (unsigned)S), 256, 0, st>>>(counts, n, nblk);
-        rs_scatter_kernel<<<dim3((unsigned)nblk, (unsigned)S), kRsThreads, 0, st>>>(k0, v0, k1, v1, n, shift,
-                                                                                   counts, nblk);
+        const uint32_t* vin = pass == 0 && iota ? nullptr : v0;
+        if (rs_items(n) == 4) {
+            rs_hist_kernel<4><<<g, kRsThreads, 0, st>>>(k0, n, shift, counts, nblk);
+            rs_scan_kernel<<<dim3(256, (unsigned)S), 256, 0, st>>>(counts, n, nblk);
+            rs_scatter_kernel<4><<<g, kRsThreads, 0, st>>>(k0, vin, k1, v1, n, shift, counts, nblk);
+        } else {
+            rs_hist_kernel<16><<<g, kRsThreads, 0, st>>>(k0, n, shift, counts, nblk);
+            rs_scan_kernel<<<dim3(256, (unsigned)S), 256, 0, st>>>(counts, n, nblk);
+            rs_scatter_kernel<16><<<g, kRsThreads, 0, st>>>(k0, vin, k1, v1, n, shift, counts, nblk);
+        }
         KNN_HIP(hipGetLastError());
         std::swap(k0, k1);
         std::swap(v0, v1);

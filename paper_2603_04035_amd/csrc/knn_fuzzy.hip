@@ -37,10 +37,6 @@
 
 namespace knn {
 
-knn_status radix_sort_bits(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n,
-                           uint32_t* counts, hipStream_t st, int bits, int S);
-size_t radix_counts_words(int64_t n);
-
 constexpr int kFzMaxK = KNN_MAX_K;
 
 // ------------------------------------------------------------------ rows

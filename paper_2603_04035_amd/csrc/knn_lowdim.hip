@@ -13,7 +13,7 @@
 // of a search over all pairs.
 //
 // Over all pairs the 70,000 x 2 search (k = 10) is 4.9e9 distances and gates, VALU
-// work of 2.49 ms; it takes 0.17 ms here, 0.11 of them the search (a wave visits
+// work of 2.49 ms; it takes 0.14 ms here, 0.11 of them the search (a wave visits
 // a few tiles; bound by VALU work of the list), the rest the sort.  From 4
 // coordinates on boxes no longer prune, a tile's neighbourhood is most of the
 // set (70,000 x 8: 12 ms here, 7.3 over all pairs).
@@ -22,10 +22,6 @@
 #include "knn_common.hpp"
 
 namespace knn {
-
-knn_status radix_sort_bits(uint32_t*& k0, uint32_t*& v0, uint32_t*& k1, uint32_t*& v1, int64_t n,
-                           uint32_t* counts, hipStream_t st, int bits, int S);
-size_t radix_counts_words(int64_t n);
 
 constexpr int kLdTile = 64;      // references per tile, tiles per group
 constexpr int kLdCells = 256;    // cells per coordinate

@@ -316,3 +316,23 @@ def test_small_search_few_coordinates(n, d):
     ref_i, ref_d = knn.knn_exact_query(X, X, k, q_self=own, workspace_limit=1 << 30)[:2]
     i, dist = knn.knn_exact(X, k)[:2]
     assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
+
+
+@pytest.mark.parametrize("m", [1, 5, 64, 1023, 1024, 1025, 131_072, 131_073, 135_168, 135_169])
+def test_union_order_at_sort_tiles(m):
+    """Edges sorted by target at the edges of the sort's tiles (1,024 pairs up
+    to 131,072, 4,096 above), sources in order within a target: with one
+    neighbour per row, every row of the union holds its neighbour and the
+    rows that point at it, ascending."""
+    import paper_2603_04035_amd as knn
+    n = max(2, m)
+    rng = np.random.default_rng(n)
+    to = (np.arange(n) + rng.integers(1, n, n)) % n   # never the row itself
+    to[: n // 3] = np.where(np.arange(n // 3) == n // 2, to[: n // 3], n // 2)   # a hub
+    idx = torch.from_numpy(to.astype(np.int32)[:, None]).cuda()
+    dist = torch.ones((n, 1), device="cuda")
+    _, _, _, ptr, col, _ = knn.fuzzy_graph(idx, dist)
+    i = np.arange(n, dtype=np.int64)
+    want = np.unique(np.concatenate([i * n + to, to * n + i]))
+    got = np.repeat(i, np.diff(ptr.cpu().numpy())) * n + col.cpu().numpy()[: int(ptr[-1])]
+    assert np.array_equal(got, want)
