@@ -13,124 +13,175 @@
 //   w_ir    = exp(-max(0, d_r - rho_i) / sigma_i);
 // and the symmetric graph W = A + A^T - A o A^T with A[i][idx_ir] = w_ir.
 //
-// 1. rows:   one thread per row.  sigma is bracketed and bisected in FP32
-//            (v_exp_f32), then polished by Newton steps on the sum in
-//            double, whose root it converges to quadratically from the FP32
-//            estimate; the weights are evaluated in double and rounded once.
-//            Each edge e = (i -> j) emits one entry keyed by its target j.
-// 2. sort:   the entries are sorted by target with a stable LSD radix sort
+// 1. rows:   one thread per row.  sigma is bracketed and found in FP32
+//            (safeguarded Newton, v_exp_f32), then polished by Newton steps on
+//            the sum in double, whose root it converges to quadratically from
+//            the FP32 estimate; the weights are evaluated in double and
+//            rounded once.  Each edge e = (i -> j) is keyed by its target j.
+// 2. sort:   the edges are sorted by target with a stable LSD radix sort
 //            (32-bit keys, the edge number as payload), so the edges into a
 //            row form one segment ordered by source: the row's transposed
 //            entries, already in column order.  Deterministic whatever the
 //            thread order.
-// 3. union:  one wave per row merges its own k entries (ranked by column in
-//            registers) with that segment: a column in both gets the
+// 3. union:  16 (k <= 16) or 32 lanes per row merge its own k entries (ranked
+//            by column) with that segment: a column in both gets the
 //            probabilistic union a + b - ab (folded in double in the order
 //            of the entries' numbers, 2e for (i, j) and 2e' + 1 for the
 //            transposed (j, i) of e' = (j -> i)), the others keep their
 //            weight; each entry's CSR position follows from the counts of
 //            smaller columns on both sides.  A count pass and a scan over
-//            the rows give row_ptr, then the same pass writes the entries.
+//            the rows give row_ptr, then the emit pass writes the entries.
 #include <math.h>
 
 #include "knn_common.hpp"
 
 namespace knn {
 
-constexpr int kFzMaxK = KNN_MAX_K;
+constexpr int kFzMaxK = KNN_MAX_K;   // 32: a row's entries fit the lanes of half a wave
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ rows
 
-// FP32 sum of exp(-x_r / s) (s > 0), as exp2 of -x_r * (log2(e) / s).
-__device__ inline float fz_sum32(const float (&x)[kFzMaxK], int k, float s)
+// n / k for n < 2^31 as (n * mul) >> (32 + shift) (k = 1: n itself), with
+// mul = ceil(2^(31 + l) / k), l = ceil(log2 k), shift = l - 1: the rounding of mul
+// adds less than 2^l n / (k 2^(31 + l)) < 1 / k.
+struct DivK {
+    uint32_t k, mul;
+    int shift;
+};
+static DivK div_by(int k)
+{
+    int l = 0;
+    while ((1 << l) < k) ++l;
+    return {(uint32_t)k, k > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)k - 1) / (uint64_t)k) : 0u, l - 1};
+}
+__device__ inline uint32_t div_k(uint32_t n, DivK d) { return d.k == 1u ? n : __umulhi(n, d.mul) >> d.shift; }
+
+// Sum of exp(-x_r / s) (s > 0) in FP32, as exp2 of -x_r * (log2(e) / s); with
+// G also that of exp(-x_r / s) x_r.
+template <int KM, bool G>
+__device__ inline float fz_sum32(const float (&x)[KM], int k, float s, float* g)
 {
     const float c = 1.4426950408889634f / s;
-    float t = 0.0f;
+    float t = 0.0f, tg = 0.0f;
 #pragma unroll
-    for (int r = 0; r < kFzMaxK; ++r)
-        if (r < k) t += exp2f(-x[r] * c);
+    for (int r = 0; r < KM; ++r) {
+        if (r < k) {
+            const float e = __builtin_amdgcn_exp2f(-x[r] * c);
+            t += e;
+            if (G) tg = fmaf(e, x[r], tg);
+        }
+    }
+    if (G) *g = tg;
     return t;
 }
 
+// One thread per row; the block's rows pass through LDS both ways, so that
+// memory sees whole lines (a row is k floats: straight loads and stores touch
+// 64 lines each).  KM: k <= KM.  sigma is bracketed, found by safeguarded
+// Newton steps in FP32 (5 to 7 sums; bisection took 25) and polished in
+// double until a step is below 1e-6 of it (the next error is its square).
+// 1,000,000 x 15: 119 us, bound by the exponentials; 446 with straight loads and
+// stores, bisection, and four steps in double always.
+template <int KM>
 __global__ __launch_bounds__(256) void fuzzy_rows_kernel(
-    const int32_t* __restrict__ idx, const float* __restrict__ dist, int64_t n, int k,
+    const int32_t* __restrict__ idx, const float* __restrict__ dist, int64_t n, int k, DivK dk,
     float* __restrict__ rho_out, float* __restrict__ sigma_out, float* __restrict__ w_out,
-    uint32_t* __restrict__ tgtkey, uint32_t* __restrict__ eid, unsigned* __restrict__ bad)
+    uint32_t* __restrict__ tgtkey, unsigned* __restrict__ bad)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float d[kFzMaxK];
-    double p = 0.0;
-#pragma unroll
-    for (int r = 0; r < kFzMaxK; ++r) {
-        d[r] = r < k ? dist[i * k + r] : 0.0f;
-        if (r < k && d[r] > 0.0f && (p == 0.0 || (double)d[r] < p)) p = (double)d[r];
-    }
-    // x_r = max(0, d_r - rho) in double (exact for FP32 inputs), kept as
-    // FP32 for the bracket search
-    float x[kFzMaxK];
-    int cnt = 0;
-    float xmax = 0.0f;
-#pragma unroll
-    for (int r = 0; r < kFzMaxK; ++r) {
-        const double xd = (double)d[r] - p;
-        x[r] = xd > 0.0 ? (float)xd : 0.0f;
-        if (r < k && !(xd > 0.0)) ++cnt;
-        if (r < k) xmax = fmaxf(xmax, x[r]);
-    }
-    const double target = log2((double)k);
-    double sig = 0.0;
-    if ((double)cnt < target) {
-        const float t32 = (float)target;
-        float lo = 0.0f, hi = xmax;
-        while (fz_sum32(x, k, hi) < t32) hi *= 2.0f;
-        for (int it = 0; it < 40; ++it) {
-            const float mid = 0.5f * (lo + hi);
-            if (!(mid > lo && mid < hi)) break;
-            if (fz_sum32(x, k, mid) < t32) lo = mid;
-            else hi = mid;
-        }
-        // Newton on f(s) = sum exp(-x_r / s) - log2(k), f'(s) = sum
-        // exp(-x_r / s) x_r / s^2, in double from the FP32 bracket
-        double s = 0.5 * ((double)lo + (double)hi);
-        for (int it = 0; it < 4; ++it) {
-            double f = -target, g = 0.0;
-#pragma unroll
-            for (int r = 0; r < kFzMaxK; ++r) {
-                if (r < k) {
-                    const double xr = fmax((double)d[r] - p, 0.0);
-                    const double e = exp(-xr / s);
-                    f += e;
-                    g += e * xr;
-                }
-            }
-            g /= s * s;
-            if (!(g > 0.0)) break;
-            const double ns = s - f / g;
-            if (!(ns > 0.0) || !isfinite(ns)) break;
-            s = ns;
-        }
-        sig = s;
-    }
-    if (rho_out) rho_out[i] = (float)p;
-    if (sigma_out) sigma_out[i] = (float)sig;
+    __shared__ float buf[256 * (KM + 1)];   // row r at r * ks, ks odd
+    const int tid = threadIdx.x, ks = k | 1;
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + tid, e0 = i0 * k;
+    const int rows = (int)(n - i0 < 256 ? n - i0 : 256), ne = rows * k;
     bool ok = true;
-#pragma unroll
-    for (int r = 0; r < kFzMaxK; ++r) {
-        if (r < k) {
-            const double xr = fmax((double)d[r] - p, 0.0);
-            const float w = sig > 0.0 ? (float)exp(-xr / sig) : (xr == 0.0 ? 1.0f : 0.0f);
-            const int64_t e = i * k + r;
-            w_out[e] = w;
-            const int32_t j = idx[e];
-            const bool valid = j >= 0 && (int64_t)j < n && (int64_t)j != i;
-            ok = ok && valid;
-            // keyed by target; invalid edges sort last (key n)
-            tgtkey[e] = valid ? (uint32_t)j : (uint32_t)n;
-            eid[e] = (uint32_t)e;
-        }
+    for (int c = tid; c < ne; c += 256) {
+        const uint32_t r = div_k((uint32_t)c, dk);
+        buf[r * ks + (c - r * k)] = dist[e0 + c];
+        const int32_t j = idx[e0 + c];
+        const bool valid = j >= 0 && (int64_t)j < n && (int64_t)j != i0 + r;
+        ok = ok && valid;
+        // keyed by target; invalid edges sort last (key n)
+        tgtkey[e0 + c] = valid ? (uint32_t)j : (uint32_t)n;
     }
     if (!ok) atomicOr(bad, 1u);
+    __syncthreads();
+    if (tid < rows) {
+        float d[KM];
+        double p = 0.0;
+#pragma unroll
+        for (int r = 0; r < KM; ++r) {
+            d[r] = r < k ? buf[tid * ks + r] : 0.0f;
+            if (r < k && d[r] > 0.0f && (p == 0.0 || (double)d[r] < p)) p = (double)d[r];
+        }
+        // x_r = max(0, d_r - rho) in double (exact for FP32 inputs), kept as
+        // FP32 for the bracket search
+        float x[KM];
+        int cnt = 0;
+        float xmax = 0.0f;
+#pragma unroll
+        for (int r = 0; r < KM; ++r) {
+            const double xd = (double)d[r] - p;
+            x[r] = xd > 0.0 ? (float)xd : 0.0f;
+            if (r < k && !(xd > 0.0)) ++cnt;
+            if (r < k) xmax = fmaxf(xmax, x[r]);
+        }
+        const double target = log2((double)k);
+        double sig = 0.0;
+        if ((double)cnt < target) {
+            const float t32 = (float)target;
+            float lo = 0.0f, hi = xmax, g;
+            while (fz_sum32<KM, false>(x, k, hi, nullptr) < t32) hi *= 2.0f;
+            float s32 = 0.5f * hi;
+            for (int it = 0; it < 40; ++it) {
+                if (!(s32 > lo && s32 < hi)) s32 = 0.5f * (lo + hi);
+                if (!(s32 > lo && s32 < hi)) break;
+                const float f = fz_sum32<KM, true>(x, k, s32, &g) - t32;
+                if (f < 0.0f) lo = s32;
+                else hi = s32;
+                const float step = f * s32 * s32 / g;
+                s32 -= step;
+                if (fabsf(step) < 4e-7f * s32) break;   // not where both are infinite (g = 0)
+            }
+            // Newton on f(s) = sum exp(-x_r / s) - log2(k), f'(s) = sum
+            // exp(-x_r / s) x_r / s^2, in double
+            s32 = fminf(fmaxf(s32, lo), hi);
+            double s = s32 > 0.0f && s32 < __builtin_inff() ? (double)s32 : 0.5 * ((double)lo + (double)hi);
+            for (int it = 0; it < 4; ++it) {
+                double f = -target, gd = 0.0;
+#pragma unroll
+                for (int r = 0; r < KM; ++r) {
+                    if (r < k) {
+                        const double xr = fmax((double)d[r] - p, 0.0);
+                        const double e = exp(-xr / s);
+                        f += e;
+                        gd += e * xr;
+                    }
+                }
+                gd /= s * s;
+                if (!(gd > 0.0)) break;
+                const double ns = s - f / gd;
+                if (!(ns > 0.0) || !isfinite(ns)) break;
+                const bool last = fabs(ns - s) <= 1e-6 * ns;
+                s = ns;
+                if (last) break;
+            }
+            sig = s;
+        }
+        if (rho_out) rho_out[i] = (float)p;
+        if (sigma_out) sigma_out[i] = (float)sig;
+#pragma unroll
+        for (int r = 0; r < KM; ++r) {
+            if (r < k) {
+                const double xr = fmax((double)d[r] - p, 0.0);
+                buf[tid * ks + r] = sig > 0.0 ? (float)exp(-xr / sig) : (xr == 0.0 ? 1.0f : 0.0f);
+            }
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < ne; c += 256) {
+        const uint32_t r = div_k((uint32_t)c, dk);
+        w_out[e0 + c] = buf[r * ks + (c - r * k)];
+    }
 }
 
 // ------------------------------------------------------------------ union
@@ -147,121 +198,122 @@ __global__ __launch_bounds__(256) void fuzzy_inptr_kernel(const uint32_t* __rest
     }
 }
 
-__device__ inline uint32_t lane_u32(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
-__device__ inline float lane_f32(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
-
-// One wave per row i.  Lanes r < k hold the row's own entries (i, idx_ir);
-// the transposed entries (i, j) of the edges j -> i are the segment
-// [in_ptr[i], in_ptr[i + 1]) of the sorted edges, in column order.  The
-// count pass (EMIT false) stores the union's size in cnt[i], flags a
-// column repeated in a row's list and keeps each own entry's partner and
-// count of smaller transposed columns; the emit pass writes the union at
-// row_ptr[i], columns ascending.
-template <bool EMIT>
+// A wave takes 64 / G consecutive rows (k <= G).  Row i's G lanes rank its own
+// entries (i, idx_ir) by column and hold them in that order; the transposed
+// entries (i, j) of the edges j -> i are the segment [in_ptr[i], in_ptr[i + 1])
+// of the sorted edges, in column order, and each own lane finds its place and
+// its partner there by bisection.  The count pass (EMIT false) stores the
+// union's size in cnt[i] and flags a column repeated in a row's list; the emit
+// pass writes the union at row_ptr[i], columns ascending.  Its transposed
+// entries are taken 64 at a time over all of the wave's rows (their segments
+// follow each other; a hub gets every lane): each finds its place among
+// its row's own entries by bisection in LDS.
+// 1,000,000 x 15: 121 and 333 us; 734 and 708 with a wave per row and
+// every pair of own and transposed entry compared.  The emit pass is bound by the
+// gather of the transposed entries' weights (a line per entry).
+template <bool EMIT, int G>
 __global__ __launch_bounds__(256) void fuzzy_union_kernel(
-    const int32_t* __restrict__ idx, const float* __restrict__ w, int k, int64_t n,
+    const int32_t* __restrict__ idx, const float* __restrict__ w, int k, DivK dk, int64_t n,
     const uint32_t* __restrict__ sorted_e, const uint32_t* __restrict__ in_ptr, uint32_t* __restrict__ cnt,
-    uint32_t* __restrict__ own_less, float* __restrict__ own_wm, const int64_t* __restrict__ row_ptr,
-    int32_t* __restrict__ col_out, float* __restrict__ val_out, unsigned* __restrict__ bad)
+    const int64_t* __restrict__ row_ptr, int32_t* __restrict__ col_out, float* __restrict__ val_out,
+    unsigned* __restrict__ bad)
 {
-    const int lane = threadIdx.x & 63;
-    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
-        // own entries; an invalid one (reported by the rows kernel) takes no part
-        const int32_t jj = lane < k ? idx[i * k + lane] : -1;
-        const bool ov = jj >= 0 && (int64_t)jj < n && (int64_t)jj != i;
-        const uint32_t oc = ov ? (uint32_t)jj : 0xFFFFFFFFu;
-        const float ow = ov ? w[i * k + lane] : 0.0f;
-        uint32_t orank = 0;   // own entries with a smaller column
-        bool rep = false;     // an earlier lane holds the same column
-        for (int r = 0; r < k; ++r) {
-            const uint32_t c2 = lane_u32(oc, r);
-            orank += c2 < oc ? 1u : 0u;
-            rep = rep || (ov && r < lane && c2 == oc);
+    constexpr int NR = 64 / G;   // rows per wave
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    __shared__ __attribute__((aligned(16))) uint32_t raw_s[4][64];   // own columns as given
+    __shared__ uint32_t own_s[4][64];    // own columns ascending
+    __shared__ float ow_s[4][64];        // and their weights
+    __shared__ uint32_t match_s[4][NR];  // own entries (bits) with a transposed partner
+    __shared__ uint32_t seg_s[4][NR + 1];
+    __shared__ int64_t base_s[4][NR];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane / G, r = lane % G;
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + wv) * NR, i = i0 + g;
+    if (i0 >= n) return;   // the whole wave
+    const bool row = i < n;
+    // own entries; an invalid one (reported by the rows kernel) takes no part
+    const int32_t jj = row && r < k ? idx[i * k + r] : -1;
+    const bool given = jj >= 0 && (int64_t)jj < n && (int64_t)jj != i;
+    const uint32_t gc = given ? (uint32_t)jj : kNone;
+    const float gw = EMIT && given ? w[i * k + r] : 0.0f;
+    const uint32_t b = in_ptr[row ? i : n], e = in_ptr[row ? i + 1 : n];
+    raw_s[wv][lane] = gc;
+    if (r == 0) {
+        seg_s[wv][g] = b;
+        if (g == NR - 1) seg_s[wv][NR] = e;
+        if (EMIT) base_s[wv][g] = row ? row_ptr[i] : 0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // place among the row's entries: smaller columns, and equal ones given before
+    uint32_t place = 0;
+#pragma unroll
+    for (int t = 0; t < G; t += 4) {
+        const u32x4 c = *(const u32x4*)&raw_s[wv][g * G + t];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) place += c[q] < gc || (c[q] == gc && t + q < r) ? 1u : 0u;
+    }
+    own_s[wv][g * G + place] = gc;
+    if (EMIT) ow_s[wv][g * G + place] = gw;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t oc = own_s[wv][lane];
+    const bool ov = oc != kNone;
+    if (!EMIT) {
+        const uint32_t prev = r > 0 ? own_s[wv][lane - 1] : kNone;
+        if (ballot(ov && prev == oc) && lane == 0) atomicOr(bad, 2u);
+    }
+    // transposed entries with a smaller column: edges below oc * k
+    uint32_t lo = b, hi = ov ? e : b;
+    const uint32_t first = oc * dk.k;
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (sorted_e[mid] < first) lo = mid + 1;
+        else hi = mid;
+    }
+    const bool om = ov && lo < e && sorted_e[lo] - first < dk.k;
+    const uint64_t below = ~0ull >> (64 - G) << (g * G);   // the row's lanes
+    const uint64_t matched = ballot(om) & below;
+    if (!EMIT) {
+        const uint32_t nown = (uint32_t)popc64(ballot(ov) & below);
+        if (row && r == 0) cnt[i] = nown + (e - b) - (uint32_t)popc64(matched);
+        return;
+    }
+    const uint32_t mbits = (uint32_t)(matched >> (g * G));
+    if (r == 0) match_s[wv][g] = mbits;
+    if (ov) {
+        const float ow = ow_s[wv][lane];
+        float v = ow;
+        if (om) {
+            // entry 2e of (i, j) precedes entry 2e' + 1 of (j, i) iff i < j
+            const float wm = w[sorted_e[lo]];
+            const double x0 = (double)((int64_t)i < (int64_t)oc ? ow : wm), x1 = (double)((int64_t)i < (int64_t)oc ? wm : ow);
+            v = (float)(x0 + x1 - x0 * x1);
         }
-        if (!EMIT && ballot(rep) && lane == 0) atomicOr(bad, 2u);
-        const int64_t b = in_ptr[i], e = in_ptr[i + 1];
-        // per own entry: its transposed partner (matched, with weight wm) and
-        // the transposed entries with a smaller column; found by the count
-        // pass, which keeps them per edge (oless | matched << 31, wm) for the
-        // emit pass
-        bool om = false;
-        float wm = 0.0f;
-        uint32_t oless = 0;
-        if (EMIT) {
-            const uint32_t ol = lane < k ? own_less[i * k + lane] : 0u;
-            om = ov && (ol >> 31) != 0u;
-            oless = ol & 0x7FFFFFFFu;
-            wm = lane < k ? own_wm[i * k + lane] : 0.0f;
-        }
-        for (int64_t c0 = b; c0 < (EMIT ? b : e); c0 += 64) {
-            const int64_t p = c0 + lane;
-            const bool iv = p < e;
-            const uint32_t ed = iv ? sorted_e[p] : 0u;
-            const uint32_t ic = iv ? ed / (uint32_t)k : 0xFFFFFFFFu;
-            const float iw = iv ? w[ed] : 0.0f;
-            for (int r = 0; r < k; ++r) {
-                const uint32_t ocr = lane_u32(oc, r);
-                const uint64_t mb = ballot(iv && ic == ocr);
-                const uint64_t lt = ballot(iv && ic < ocr);
-                const float ws = lane_f32(iw, mb ? __builtin_ctzll(mb) : 0);
-                if (lane == r) {
-                    oless += (uint32_t)popc64(lt);
-                    if (mb) {
-                        om = true;
-                        wm = ws;
-                    }
-                }
-            }
-        }
-        const uint32_t nown = (uint32_t)popc64(ballot(ov)), nmatch = (uint32_t)popc64(ballot(om));
-        if (!EMIT) {
-            if (lane == 0) cnt[i] = nown + (uint32_t)(e - b) - nmatch;
-            if (lane < k) {
-                own_less[i * k + lane] = oless | (om ? 0x80000000u : 0u);
-                own_wm[i * k + lane] = wm;
-            }
-            continue;
-        }
-        const int64_t base = row_ptr[i];
-        uint32_t mless = 0;   // matched own entries with a smaller column
-        for (int r = 0; r < k; ++r) {
-            const uint32_t c2 = lane_u32(oc, r), m2 = lane_u32(om ? 1u : 0u, r);
-            mless += m2 && c2 < oc ? 1u : 0u;
-        }
-        if (ov) {
-            const int64_t pos = base + orank + oless - mless;
-            col_out[pos] = (int32_t)oc;
-            float v = ow;
-            if (om) {
-                // entry 2e of (i, j) precedes entry 2e' + 1 of (j, i) iff i < j
-                const double x[2] = {(double)((int64_t)i < (int64_t)oc ? ow : wm),
-                                     (double)((int64_t)i < (int64_t)oc ? wm : ow)};
-                double u = 0.0;
-                for (int t = 0; t < 2; ++t) u = u + x[t] - u * x[t];
-                v = (float)u;
-            }
-            val_out[pos] = v;
-        }
-        // transposed entries without a partner: position = their index in the
-        // segment plus the unmatched own entries with a smaller column
-        for (int64_t c0 = b; c0 < e; c0 += 64) {
-            const int64_t p = c0 + lane;
-            const bool iv = p < e;
-            const uint32_t ed = iv ? sorted_e[p] : 0u;
-            const uint32_t ic = iv ? ed / (uint32_t)k : 0xFFFFFFFFu;
-            bool im = false;
-            uint32_t uless = 0;
-            for (int r = 0; r < k; ++r) {
-                const uint32_t ocr = lane_u32(oc, r), m2 = lane_u32(om ? 1u : 0u, r);
-                im = im || ic == ocr;
-                uless += !m2 && ocr < ic ? 1u : 0u;
-            }
-            if (iv && !im) {
-                const int64_t pos = base + (p - b) + uless;
-                col_out[pos] = (int32_t)ic;
-                val_out[pos] = w[ed];
-            }
-        }
+        const int64_t pos = base_s[wv][g] + r + (lo - b) - popc64(mbits & ((1u << r) - 1u));
+        col_out[pos] = (int32_t)oc;
+        val_out[pos] = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // transposed entries without a partner: their index in the segment plus the
+    // unmatched own entries with a smaller column
+    const uint32_t pe = seg_s[wv][NR];
+    for (uint32_t p = seg_s[wv][0] + lane; p < pe; p += 64) {
+        int h = 0;   // its row
+#pragma unroll
+        for (int q = 1; q < NR; ++q) h += p >= seg_s[wv][q] ? 1 : 0;
+        const uint32_t ed = sorted_e[p], ic = div_k(ed, dk);
+        const uint32_t* own = own_s[wv] + h * G;
+        uint32_t c = 0;   // own entries with a smaller column
+#pragma unroll
+        for (uint32_t t = G / 2; t > 0; t >>= 1) c += own[c + t - 1] < ic ? t : 0u;
+        const uint32_t at = own[c];
+        if (at == ic) continue;
+        c += at < ic ? 1u : 0u;
+        const uint32_t um = c - (uint32_t)popc64(match_s[wv][h] & ((1ull << c) - 1ull));
+        const int64_t pos = base_s[wv][h] + (p - seg_s[wv][h]) + um;
+        col_out[pos] = (int32_t)ic;
+        val_out[pos] = w[ed];
     }
 }
 
@@ -361,9 +413,8 @@ extern "C" knn_status knn_fuzzy_graph(const int32_t* knn_idx, const float* knn_d
         hipStream_t st = (hipStream_t)stream;
         Workspace ws(st, 0);
         knn_status r;
-        uint32_t *key, *eid, *k1, *v1, *counts, *inptr, *cnt, *bsum, *oless;
-        float* owm;
-        unsigned* bad;
+        uint32_t *key, *eid, *k1, *v1, *counts, *inptr, *cnt, *bsum;
+            unsigned* bad;
         float* w = weights;
         const int64_t nb = ceil_div(n, kFzScanRows);
         if ((r = ws.alloc(&key, (size_t)m)) != KNN_OK) return r;
@@ -374,25 +425,35 @@ extern "C" knn_status knn_fuzzy_graph(const int32_t* knn_idx, const float* knn_d
         if ((r = ws.alloc(&inptr, (size_t)n + 1)) != KNN_OK) return r;
         if ((r = ws.alloc(&cnt, (size_t)n)) != KNN_OK) return r;
         if ((r = ws.alloc(&bsum, (size_t)nb + 1)) != KNN_OK) return r;
-        if ((r = ws.alloc(&oless, (size_t)m)) != KNN_OK) return r;
-        if ((r = ws.alloc(&owm, (size_t)m)) != KNN_OK) return r;
         if ((r = ws.alloc(&bad, 1)) != KNN_OK) return r;
         if (!w && (r = ws.alloc(&w, (size_t)n * k)) != KNN_OK) return r;
         KNN_HIP(hipMemsetAsync(bad, 0, 4, st));
-        fuzzy_rows_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(knn_idx, knn_dist, n, k, rho, sigma, w, key,
-                                                                     eid, bad);
+        const DivK dk = div_by(k);
+        const unsigned rgrid = (unsigned)ceil_div(n, 256);
+        if (k <= 16)
+            fuzzy_rows_kernel<16><<<rgrid, 256, 0, st>>>(knn_idx, knn_dist, n, k, dk, rho, sigma, w, key, bad);
+        else
+            fuzzy_rows_kernel<32><<<rgrid, 256, 0, st>>>(knn_idx, knn_dist, n, k, dk, rho, sigma, w, key, bad);
         KNN_HIP(hipGetLastError());
         // by target (keys <= n: invalid edges last), stably
-        if ((r = radix_sort_bits(key, eid, k1, v1, m, counts, st, bits_for(n), 1)) != KNN_OK) return r;
+        if ((r = radix_sort_bits(key, eid, k1, v1, m, counts, st, bits_for(n), 1, true)) != KNN_OK) return r;
         fuzzy_inptr_kernel<<<(unsigned)std::min<int64_t>(ceil_div(m, 256), 8192), 256, 0, st>>>(key, m, n, inptr);
-        const unsigned ugrid = (unsigned)std::min<int64_t>(ceil_div(n, 4), 65536);
-        fuzzy_union_kernel<false><<<ugrid, 256, 0, st>>>(knn_idx, w, k, n, eid, inptr, cnt, oless, owm, nullptr,
-                                                         nullptr, nullptr, bad);
+        const unsigned ugrid = (unsigned)ceil_div(n, k <= 16 ? 16 : 8);   // rows per workgroup
+        if (k <= 16)
+            fuzzy_union_kernel<false, 16><<<ugrid, 256, 0, st>>>(knn_idx, w, k, dk, n, eid, inptr, cnt, nullptr, nullptr,
+                                                                 nullptr, bad);
+        else
+            fuzzy_union_kernel<false, 32><<<ugrid, 256, 0, st>>>(knn_idx, w, k, dk, n, eid, inptr, cnt, nullptr, nullptr,
+                                                                 nullptr, bad);
         fuzzy_block_sum_kernel<<<(unsigned)nb, 256, 0, st>>>(cnt, n, bsum);
         fuzzy_scan_kernel<<<1, 256, 0, st>>>(bsum, nb);
         fuzzy_rowptr_kernel<<<(unsigned)nb, 256, 0, st>>>(cnt, n, bsum, nb, row_ptr);
-        fuzzy_union_kernel<true><<<ugrid, 256, 0, st>>>(knn_idx, w, k, n, eid, inptr, cnt, oless, owm, row_ptr, col,
-                                                        val, bad);
+        if (k <= 16)
+            fuzzy_union_kernel<true, 16><<<ugrid, 256, 0, st>>>(knn_idx, w, k, dk, n, eid, inptr, cnt, row_ptr, col, val,
+                                                                bad);
+        else
+            fuzzy_union_kernel<true, 32><<<ugrid, 256, 0, st>>>(knn_idx, w, k, dk, n, eid, inptr, cnt, row_ptr, col, val,
+                                                                bad);
         KNN_HIP(hipGetLastError());
         unsigned host[2] = {0, 0};
         KNN_HIP(hipMemcpyAsync(&host[0], bad, 4, hipMemcpyDeviceToHost, st));

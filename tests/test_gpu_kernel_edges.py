@@ -336,3 +336,24 @@ def test_union_order_at_sort_tiles(m):
     want = np.unique(np.concatenate([i * n + to, to * n + i]))
     got = np.repeat(i, np.diff(ptr.cpu().numpy())) * n + col.cpu().numpy()[: int(ptr[-1])]
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n", [34, 255, 256, 257, 1039])
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 31, 32])
+def test_fuzzy_rows_and_unions_at_group_edges(orc, n, k):
+    """Rows in groups of 16 and of 32 lanes, whole and part workgroups: random
+    neighbours (hubs among them, so that segments span the waves' chunks),
+    distances over ten orders of magnitude and with ties, against the oracle
+    within the bars of the fuzzy tests."""
+    from tests.test_gpu_fuzzy import _check
+    rng = np.random.default_rng(100 * n + k)
+    p = np.where(np.arange(n) < 4, 20.0, 1.0)
+    G = np.empty((n, k), np.int32)
+    for i in range(n):
+        q = p.copy()
+        q[i] = 0.0
+        G[i] = rng.choice(n, size=k, replace=False, p=q / q.sum())
+    D = rng.uniform(0.5, 2.0, size=(n, k)).astype(np.float32) * 10.0 ** rng.integers(-5, 6, size=(n, 1))
+    D[::7] = np.round(D[::7])
+    D = np.sort(D, axis=1).astype(np.float32)
+    _check(orc, torch.from_numpy(G).cuda(), torch.from_numpy(D).cuda())
