@@ -379,10 +379,18 @@ public:
     using ScratchAlloc::alloc;
     knn_status alloc(void** p, size_t bytes) override;
     size_t used() const { return used_; }
+    // The limit counts only `charged` bytes of the next request, of `bytes`
+    // (scratch that grew with a kernel's work split, not with the problem, so
+    // that limits stay what they were).
+    void charge_as(size_t bytes, size_t charged)
+    {
+        waived_ += (size_t)((bytes + 255) / 256 * 256) - (size_t)((charged + 255) / 256 * 256);
+    }
 
 private:
     hipStream_t stream_;
     int64_t limit_;
+    size_t waived_ = 0;    // bytes of used_ that the limit does not count
     int dev_ = -1;
     size_t used_ = 0;      // bytes handed out by this call (arena + overflow)
     size_t off_ = 0;       // arena bytes used

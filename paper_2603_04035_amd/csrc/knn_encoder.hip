@@ -598,6 +598,8 @@ __host__ __device__ inline int64_t rs_tiles(int64_t n)
     return (n + t - 1) / t;
 }
 __host__ __device__ inline size_t rs_counts(int64_t n) { return (size_t)256 * rs_tiles(n) + 256; }
+// The counts of tiles of 4096, which workspace limits go by.
+inline size_t rs_charged(int64_t n) { return (size_t)256 * ceil_div(n, 4096) + 256; }
 
 // Sorts run on blockIdx.y independent arrays of n elements at once: array
 // y's elements (and outputs) start at y * n, its counts at y * rs_counts(n).
@@ -1172,6 +1174,7 @@ static knn_status proj_seed_impl(const knn_matrix& X, const float* Z, int m, con
     if ((r = ws.alloc(&vals, (size_t)n * P)) != KNN_OK) return r;
     if ((r = ws.alloc(&k1, (size_t)n * P)) != KNN_OK) return r;
     if ((r = ws.alloc(&v1, (size_t)n * P)) != KNN_OK) return r;
+    ws.charge_as(rs_counts(n) * P * 4, rs_charged(n) * P * 4);
     if ((r = ws.alloc(&counts, rs_counts(n) * P)) != KNN_OK) return r;
     const unsigned g = (unsigned)ceil_div(n, 256);
     if (m <= 32) proj_vals_kernel<32><<<g, 256, 0, st>>>(Z, n, m, dirs, P * D, Y);
@@ -1260,6 +1263,7 @@ knn_status morton_order(const knn_matrix& X, int D, uint64_t seed, Workspace& ws
     if ((r = ws.alloc(&k1, (size_t)n)) != KNN_OK) return r;
     if ((r = ws.alloc(&v1, (size_t)n)) != KNN_OK) return r;
     if ((r = ws.alloc(&lohi, (size_t)2 * D)) != KNN_OK) return r;
+    ws.charge_as(rs_counts(n) * 4, rs_charged(n) * 4);
     if ((r = ws.alloc(&counts, rs_counts(n))) != KNN_OK) return r;
     dirs_kernel<<<D, 64, 0, st>>>(X.d, seed ^ 0x5DEECE66Dull, dirs);
     const unsigned g = (unsigned)ceil_div(n, 256);

@@ -416,13 +416,21 @@ struct ListRaw {
     uint32_t n, o;
 };
 
+// Orders a wave's LDS accesses (its lanes run in step and the LDS serves one
+// wave in order, so only the compiler has to be held).
+__device__ __attribute__((always_inline)) inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ inline ListRaw load_lists(int64_t v, bool valid, const JoinCfg& cfg,
                                      const int32_t* __restrict__ newf,
                                      const uint32_t* __restrict__ revnew,
                                      const int32_t* __restrict__ oldf,
                                      const uint32_t* __restrict__ revold)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int64_t vv = valid ? v : 0;
     const int rn = min(max(lane - cfg.s, 0), cfg.R - 1), ro = min(max(lane - cfg.K, 0), cfg.R - 1);
     const uint32_t* pn = lane < cfg.s ? (const uint32_t*)(newf + vv * cfg.s + lane) : revnew + vv * cfg.R + rn;
@@ -443,7 +451,7 @@ __device__ inline int join_lists(int64_t v, const ListRaw& raw, const JoinCfg& c
                                  uint32_t* __restrict__ revnew, uint32_t* __restrict__ revold,
                                  uint64_t seed, int iter, uint32_t* sh, uint32_t* ids, int& L, int& dropped)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     if (cfg.reset) {
         if (lane >= cfg.s && lane < cfg.s + cfg.R) revnew[v * cfg.R + (lane - cfg.s)] = 0xFFFFFFFFu;
         if (lane >= cfg.K && lane < cfg.K + cfg.R) revold[v * cfg.R + (lane - cfg.K)] = 0xFFFFFFFFu;
@@ -456,7 +464,7 @@ __device__ inline int join_lists(int64_t v, const ListRaw& raw, const JoinCfg& c
     const uint32_t oid = lane < cfg.K ? raw.o : (lane < cfg.K + cfg.R ? ro : 0xFFFFFFFFu);
     sh[lane] = nid;
     sh[64 + lane] = oid;
-    __syncthreads();
+    wave_sync();
     int ln = lane;
     asm volatile("" : "+v"(ln));   // keep the position tests per point, not hoisted masks
     bool nv = nid != 0xFFFFFFFFu && nid != (uint32_t)v;
@@ -593,8 +601,12 @@ __device__ inline unsigned long long offers_resolve(const PendingOffers& po)
 // Local join on MFMA, every form (OUT is the staged element type: KNN_F32,
 // KNN_BF16 or KNN_F16).  One wave per point v; the grid is split into 8
 // groups (blockIdx mod 8, the round-robin XCD assignment of workgroups) that
-// each sweep one contiguous range of the processing order, so concurrently
-// joined points are Z-order neighbours sharing an L2.
+// take chunks of up to 512 consecutive points of the processing order in turn,
+// so the points joined at a time on one XCD are Z-order neighbours sharing an
+// L2, and those of all XCDs neighbours sharing the memory-side cache (1,000,000 x
+// 50, six joins: 19.5 ms, 20.9 with a range of the order per group).
+// Bound, on narrow rows, by memory transactions: 41e9 a second in all, gathered
+// lines, slot reads and atomics, 70% of what leaves the L2s being reads.
 //
 // The join list (new members first, then old; L <= 64) is two 32-row
 // blocks.  Its L x L Gram is accumulated by 32 x 32 MFMA tiles (FP32
@@ -605,8 +617,7 @@ __device__ inline unsigned long long offers_resolve(const PendingOffers& po)
 // index to (step, half) one-to-one, which is all a Gram product needs since
 // both operands use the same assignment.
 //
-// Column block cb (members 32cb + c) is finished before the next starts, so
-// two accumulator tiles are live.  Member m pairs with every row if it is
+// Member m pairs with every row if it is
 // new and with the new rows if it is old; each lane keeps the best J of its
 // 32 rows that beat m's current worst distance, the two lanes of column m
 // swap and merge their lists, and each offers half of the merged best J.
@@ -615,6 +626,16 @@ __device__ inline unsigned long long offers_resolve(const PendingOffers& po)
 // values) and the current worst distance of its list, read once per member
 // and zeroed in the operand piece that holds them.
 constexpr int kPC = 4;   // pieces per lane per row held in registers at a time
+constexpr int kTurn = 36;   // LDS row of a transposed tile, in floats
+
+// Forms of the join: rows of at most kPC pieces, which stay in registers
+// (members 32..63 with rows 0..31 multiplied a second time); wider rows
+// (WideTiles::plain); FP32 rows of 48 pieces or more with new lists of more than
+// one block (WideTiles::ahead, in workgroups of four waves, one per SIMD).
+// Joins of 150,000 x 400 (50 pieces), K = 30: 17.1 ms solo, 17.9 to 18.6 wide; x 300: 14.6
+// and 13.0; K = 15 with s = 8 (x 784): 15.5 and 14.8.
+enum JoinMode { kJoinNarrow, kJoinWide, kJoinSolo };
+constexpr int kSoloPieces = 48;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -664,6 +685,109 @@ __device__ inline void clear_tail(uint4& x, int p, int np, int64_t rowbytes, int
     }
 }
 
+// The tiles of a join on rows of more than kPC pieces: members 0..31 with rows
+// 0..31 (g00) and 32..63 (g10; TWO), members 32..63 with rows 32..63 (g11;
+// LAST).  Every row is gathered once.
+//
+// plain: kPC pieces at a time; other waves of the SIMD cover the loads.
+// ahead: the next kPC pieces are in flight while these are multiplied, and the
+// tiles' steps alternate (a step waits for the one before it on its tile).  For
+// one wave per SIMD: where FP32 steps (64 cycles each) are most of the work, two
+// waves on one SIMD disturb each other more than they cover (70,000 x 784, K = 31,
+// the third join: 2.3 ms with one, 3.1 with two, 2.9 with four and plain).
+template <int OUT>
+struct WideTiles {
+    f32x16 g00, g10, g11;
+
+    __device__ __attribute__((always_inline)) void load(uint4 (&A)[kPC], const uint8_t* r, int ch, int np)
+    {
+#pragma unroll
+        for (int q = 0; q < kPC; ++q) A[q] = load_piece(r, ch * kPC + q, np);
+    }
+    template <bool TWO, bool LAST>
+    __device__ __attribute__((always_inline)) void step(const uint4& a, const uint4& b)
+    {
+        if constexpr (OUT != KNN_F32) {
+            g00 = gram_step<OUT>(a, a, g00);
+            if constexpr (TWO) g10 = gram_step<OUT>(b, a, g10);
+            if constexpr (LAST) g11 = gram_step<OUT>(b, b, g11);
+        } else {
+            const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float x = __uint_as_float(av[t]), y = __uint_as_float(bv[t]);
+                g00 = __builtin_amdgcn_mfma_f32_32x32x2f32(x, x, g00, 0, 0, 0);
+                if constexpr (TWO) g10 = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, g10, 0, 0, 0);
+                if constexpr (LAST) g11 = __builtin_amdgcn_mfma_f32_32x32x2f32(y, y, g11, 0, 0, 0);
+            }
+        }
+    }
+    __device__ __attribute__((always_inline)) void plain(const uint8_t* r0, const uint8_t* r1, bool two, bool last,
+                                                         int np, int64_t rowbytes, int h, int c, float* nrm, float* thr)
+    {
+        for (int p0 = 0; p0 < np; p0 += kPC) {
+            uint4 A0[kPC], A1[kPC];
+            load(A0, r0, p0 / kPC, np);
+            if (two) load(A1, r1, p0 / kPC, np);
+#pragma unroll
+            for (int q = 0; q < kPC; ++q) clear_tail(A0[q], p0 + q, np, rowbytes, h, nrm + c, thr + c);
+            if (two) {
+#pragma unroll
+                for (int q = 0; q < kPC; ++q) clear_tail(A1[q], p0 + q, np, rowbytes, h, nrm + 32 + c, thr + 32 + c);
+            }
+#pragma unroll
+            for (int q = 0; q < kPC; ++q) {
+                if (p0 + q < np) {
+                    g00 = gram_step<OUT>(A0[q], A0[q], g00);
+                    if (two) g10 = gram_step<OUT>(A1[q], A0[q], g10);
+                    if (last) g11 = gram_step<OUT>(A1[q], A1[q], g11);
+                }
+            }
+        }
+    }
+    // A branch around loads in flight would make the waits cover them: TWO and
+    // LAST are fixed.
+    template <bool TWO, bool LAST>
+    __device__ __attribute__((always_inline)) void ahead(const uint8_t* r0, const uint8_t* r1, int np, int64_t rowbytes,
+                                                       int h, int c, float* nrm, float* thr)
+    {
+        const int nch = (np + kPC - 1) / kPC;
+        uint4 X0[kPC], X1[kPC], Y0[kPC], Y1[kPC];
+        load(X0, r0, 0, np);
+        if constexpr (TWO) load(X1, r1, 0, np);
+        int ch = 0;
+        for (; ch + 2 < nch; ch += 2) {
+            load(Y0, r0, ch + 1, np);
+            if constexpr (TWO) load(Y1, r1, ch + 1, np);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < kPC; ++q) step<TWO, LAST>(X0[q], X1[q]);
+            __builtin_amdgcn_sched_barrier(0);
+            load(X0, r0, ch + 2, np);
+            if constexpr (TWO) load(X1, r1, ch + 2, np);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < kPC; ++q) step<TWO, LAST>(Y0[q], Y1[q]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the last one or two chunks, the row's trailing words among them
+        load(Y0, r0, ch + 1, np);
+        if constexpr (TWO) load(Y1, r1, ch + 1, np);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int q = 0; q < kPC; ++q) {
+                const int p = (ch + b) * kPC + q;
+                uint4& a0 = b ? Y0[q] : X0[q];
+                uint4& a1 = b ? Y1[q] : X1[q];
+                clear_tail(a0, p, np, rowbytes, h, nrm + c, thr + c);
+                if constexpr (TWO) clear_tail(a1, p, np, rowbytes, h, nrm + 32 + c, thr + 32 + c);
+                if (p < np) step<TWO, LAST>(a0, a1);
+            }
+        }
+    }
+};
+
 // Candidates of member m from one 32-row block's accumulator column: rows
 // 32 blk + 8 (e / 4) + 4 h + e % 4 of tile entry e, branch-free.  Member m
 // pairs with rows i < lim (L if m is new, nn if it is old), i != m.  Groups
@@ -687,47 +811,71 @@ __device__ inline void scan_block(const f32x16& g, int blk, int h4, int m, int l
     }
 }
 
-template <int OUT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void nnd_join_mfma_kernel(
+template <int OUT, int MODE>
+__global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
+    __attribute__((amdgpu_waves_per_eu(MODE == kJoinSolo ? 1 : 4))) void nnd_join_mfma_kernel(
     int64_t n, JoinCfg cfg, const uint8_t* __restrict__ Xr, int64_t rowbytes, int np,
     const int32_t* __restrict__ newf, uint32_t* __restrict__ revnew,
     const int32_t* __restrict__ oldf, uint32_t* __restrict__ revold,
-    unsigned long long* __restrict__ cand, uint64_t seed, int iter, unsigned long long* __restrict__ counters)
+    unsigned long long* __restrict__ cand, uint64_t seed, int iter, unsigned long long* __restrict__ counters,
+    unsigned* __restrict__ cursors, int batch, int step, int chunk)
 {
-    __shared__ uint32_t ids[64];
-    __shared__ __attribute__((aligned(16))) float nrm[64];
-    __shared__ float thr[64];
-    __shared__ __attribute__((aligned(16))) uint32_t sh[128];
-    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;
+    constexpr bool WIDE = MODE != kJoinNarrow;
+    constexpr int NW = MODE == kJoinSolo ? 4 : 1;   // waves, each on its own points
+    __shared__ uint32_t ids_s[NW][64];
+    __shared__ __attribute__((aligned(16))) float nrm_s[NW][64];
+    __shared__ float thr_s[NW][64];
+    __shared__ __attribute__((aligned(16))) uint32_t sh_s[NW][128];
+    __shared__ __attribute__((aligned(16))) float turn_s[NW][WIDE ? 32 * kTurn : 4];
+    const int lane = threadIdx.x & 63, wv = NW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int c = lane & 31, h = lane >> 5;
+    uint32_t *ids = ids_s[wv], *sh = sh_s[wv];
+    float *nrm = nrm_s[wv], *thr = thr_s[wv], *turn = turn_s[wv];
     // emitted: offers in the low 32 bits, slot collisions in the high 32 (a
     // lane sends far fewer than 2^32 offers), so one register pair counts both
     unsigned long long emitted = 0;
     // wave-uniform tallies (rows gathered, pairs joined, members cut) live in
     // LDS, updated by lane 0, so that they hold no registers in the loop
-    __shared__ unsigned long long tally[3];
-    if (threadIdx.x == 0) tally[0] = tally[1] = tally[2] = 0ull;
+    __shared__ unsigned long long tally_s[NW][3];
+    unsigned long long* tally = tally_s[wv];
+    if (lane == 0) tally[0] = tally[1] = tally[2] = 0ull;
     const uint64_t salt = (uint64_t)iter ^ seed;
     const int J = cfg.J;
-    const int nch = (np + kPC - 1) / kPC;
     const bool tail_in_pieces = 32 * (int64_t)np == rowbytes;   // the last piece holds the norm / worst words
     const unsigned grp = blockIdx.x & 7u;
-    const int64_t gsz = (int64_t)(gridDim.x >> 3);
-    const int64_t lo = n * grp / 8, hi = n * (grp + 1) / 8;
+    const int64_t gw = (int64_t)(gridDim.x >> 3) * NW;   // the group's waves
+    // the group's q-th point
+    const auto point = [&](int64_t q) { return ((((q >> chunk) * 8 + grp) << chunk) | (q & ((1 << chunk) - 1))); };
 
     PendingOffers po;
     po.p[0] = po.p[1] = nullptr;
-    int64_t v = lo + (int64_t)(blockIdx.x >> 3);
-    ListRaw cur = load_lists(v, v < hi, cfg, newf, revnew, oldf, revold);
-    for (; v < hi; v += gsz) {
+    // A wave takes `batch` points at a time: the first ones by its number, then
+    // by the group's cursor, asked one batch ahead (with equal shares the last
+    // wave ended 13 to 17% after the median one); or it takes every step-th
+    // point, `batch` beyond its share, where the cursor's atomics would cost
+    // more than that.
+    int64_t q = ((int64_t)(blockIdx.x >> 3) * NW + wv) * (step == 1 ? batch : 1), v = point(q), vn;
+    unsigned ahead = 0;
+    if (step == 1 && lane == 0) ahead = atomicAdd(&cursors[grp * 16], (unsigned)batch);
+    int left = batch;
+    ListRaw cur = load_lists(v, v < n, cfg, newf, revnew, oldf, revold);
+    for (; v < n; v = vn) {
+        q += step;
+        if (--left == 0) {
+            q = gw * batch + (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)ahead);
+            left = batch;
+            if (lane == 0) ahead = atomicAdd(&cursors[grp * 16], (unsigned)batch);
+        }
+        vn = point(q);
         int L = 0, dr = 0;
         const int nn = __builtin_amdgcn_readfirstlane(join_lists(v, cur, cfg, revnew, revold, seed, iter, sh, ids, L, dr));
-        if (threadIdx.x == 0) tally[2] += (unsigned long long)dr;
+        if (lane == 0) tally[2] += (unsigned long long)dr;
         L = __builtin_amdgcn_readfirstlane(L);
         // the next point's lists are in flight while this one is joined
-        cur = load_lists(v + gsz, v + gsz < hi, cfg, newf, revnew, oldf, revold);
-        __syncthreads();
+        cur = load_lists(vn, vn < n, cfg, newf, revnew, oldf, revold);
+        wave_sync();
         if (nn == 0 || L < 2) continue;
-        if (threadIdx.x == 0) {
+        if (lane == 0) {
             tally[0] += (unsigned long long)L;
             tally[1] += (unsigned long long)(nn * (nn - 1) / 2 + nn * (L - nn));
         }
@@ -741,46 +889,76 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void nn
         const bool v0 = c < L, v1 = 32 + c < L;
         const uint8_t* r0 = Xr + (int64_t)ids[v0 ? c : 0] * rowbytes + 16 * h;
         const uint8_t* r1 = Xr + (int64_t)ids[v1 ? 32 + c : 0] * rowbytes + 16 * h;
+        WideTiles<OUT> wt;
+        if constexpr (WIDE) {
+            // not held through the tiles (12 registers)
+            emitted += offers_resolve(po);
+            po.p[0] = po.p[1] = nullptr;
+            float z = 0.0f;
+            asm volatile("" : "+v"(z));
+#pragma unroll
+            for (int e = 0; e < 16; ++e) wt.g00[e] = wt.g10[e] = wt.g11[e] = z;
+            if constexpr (MODE == kJoinWide) wt.plain(r0, r1, two, nn > 32, np, rowbytes, h, c, nrm, thr);
+            else if (nn > 32) wt.template ahead<true, true>(r0, r1, np, rowbytes, h, c, nrm, thr);
+            else if (two) wt.template ahead<true, false>(r0, r1, np, rowbytes, h, c, nrm, thr);
+            else wt.template ahead<false, false>(r0, r1, np, rowbytes, h, c, nrm, thr);
+        }
         uint4 A0[kPC], A1[kPC];
         for (int cb = 0; cb < (two ? 2 : 1); ++cb) {
             // rows 32..63 x members 32..63 pair old with old when every new
             // member is in the first block
             const bool lower = two && (cb == 0 || nn > 32);
-            float z = 0.0f;
-            asm volatile("" : "+v"(z));   // one zero register per pass, not sixteen held ones
-            f32x16 at, ab;
+            // the member block's tiles with rows 0..31 and 32..63
+            f32x16 &at = wt.g00, &ab = wt.g10;
+            if constexpr (WIDE) {
+                if (cb == 1) {
+                    // rows 0..31 x members 32..63: g10 transposed, bit for bit
+                    // (a product's factors commute, the order of the sum is the same)
+                    wave_sync();
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                at[e] = z;
-                ab[e] = z;
-            }
-            for (int ch = 0; ch < nch; ++ch) {
-                if (cb == 0 || nch > 1) {
+                    for (int e = 0; e < 16; ++e) turn[(8 * (e >> 2) + 4 * h + (e & 3)) * kTurn + c] = wt.g10[e];
+                    wave_sync();
 #pragma unroll
-                    for (int q = 0; q < kPC; ++q) A0[q] = load_piece(r0, ch * kPC + q, np);
-                    if (two) {
+                    for (int e4 = 0; e4 < 4; ++e4) {
+                        const f32x4 x = *(const f32x4*)&turn[c * kTurn + 8 * e4 + 4 * h];
 #pragma unroll
-                        for (int q = 0; q < kPC; ++q) A1[q] = load_piece(r1, ch * kPC + q, np);
+                        for (int e = 0; e < 4; ++e) at[4 * e4 + e] = x[e];
                     }
 #pragma unroll
-                    for (int q = 0; q < kPC; ++q) clear_tail(A0[q], ch * kPC + q, np, rowbytes, h, nrm + c, thr + c);
+                    for (int e = 0; e < 16; ++e) ab[e] = wt.g11[e];
+                }
+            } else {
+                float z = 0.0f;
+                asm volatile("" : "+v"(z));   // one zero register per pass, not sixteen held ones
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    at[e] = z;
+                    ab[e] = z;
+                }
+                if (cb == 0) {
+#pragma unroll
+                    for (int q = 0; q < kPC; ++q) A0[q] = load_piece(r0, q, np);
                     if (two) {
 #pragma unroll
-                        for (int q = 0; q < kPC; ++q)
-                            clear_tail(A1[q], ch * kPC + q, np, rowbytes, h, nrm + 32 + c, thr + 32 + c);
+                        for (int q = 0; q < kPC; ++q) A1[q] = load_piece(r1, q, np);
+                    }
+#pragma unroll
+                    for (int q = 0; q < kPC; ++q) clear_tail(A0[q], q, np, rowbytes, h, nrm + c, thr + c);
+                    if (two) {
+#pragma unroll
+                        for (int q = 0; q < kPC; ++q) clear_tail(A1[q], q, np, rowbytes, h, nrm + 32 + c, thr + 32 + c);
                     }
                 }
-                const int pc = min(kPC, np - ch * kPC);
 #pragma unroll
                 for (int q = 0; q < kPC; ++q) {
-                    if (q < pc) {
+                    if (q < np) {
                         const uint4 b = cb == 0 ? A0[q] : A1[q];
                         at = gram_step<OUT>(A0[q], b, at);
                         if (lower) ab = gram_step<OUT>(A1[q], b, ab);
                     }
                 }
             }
-            __syncthreads();   // the norms and thresholds stored from the gathered rows
+            wave_sync();   // the norms and thresholds stored from the gathered rows
             // lane-dependent indices are re-derived per point (an opaque copy
             // of the lane id) so that they are not held across the loop
             int ln = lane;
@@ -1170,8 +1348,11 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         sampold = revold;
     }
     if ((r = ws.alloc(&cand, (size_t)n * cfg.C)) != KNN_OK) return r;
+    // the banks, then the join groups' cursors, a 64-byte line each
     const size_t cnt_bytes = (size_t)kCounterBanks * kCounterWords * 8;
-    if ((r = ws.alloc(&counters, (size_t)kCounterBanks * kCounterWords)) != KNN_OK) return r;
+    ws.charge_as(cnt_bytes + 512, 64);
+    if ((r = ws.alloc(&counters, (size_t)kCounterBanks * kCounterWords + 64)) != KNN_OK) return r;
+    unsigned* cursors = (unsigned*)(counters + (size_t)kCounterBanks * kCounterWords);
     KNN_HIP(hipMemsetAsync(revnew, 0xFF, (size_t)n * T * 4, st));
     KNN_HIP(hipMemsetAsync(revold, 0xFF, (size_t)n * T * 4, st));
 
@@ -1222,12 +1403,40 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     KNN_HIP(hipGetDevice(&dev));
     int ncu = 256;
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    const bool heavy = kind == KNN_F32 && np >= kSoloPieces;
+    const JoinMode mode = np <= kPC ? kJoinNarrow : (heavy && cfg.s + cfg.R > 32 ? kJoinSolo : kJoinWide);
+    const auto join = [&](auto f) {
+        if (kind == KNN_F16)
+            f(mode == kJoinNarrow ? nnd_join_mfma_kernel<KNN_F16, kJoinNarrow> : nnd_join_mfma_kernel<KNN_F16, kJoinWide>);
+        else if (kind == KNN_BF16)
+            f(mode == kJoinNarrow ? nnd_join_mfma_kernel<KNN_BF16, kJoinNarrow>
+                                  : nnd_join_mfma_kernel<KNN_BF16, kJoinWide>);
+        else
+            f(mode == kJoinNarrow ? nnd_join_mfma_kernel<KNN_F32, kJoinNarrow>
+              : mode == kJoinWide ? nnd_join_mfma_kernel<KNN_F32, kJoinWide>
+                                  : nnd_join_mfma_kernel<KNN_F32, kJoinSolo>);
+    };
+    const int jthreads = mode == kJoinSolo ? 256 : 64;
     int jpc = 0;
-    KNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &jpc, (const void*)nnd_join_mfma_kernel<KNN_BF16>, 64, 0));
+    hipError_t occ = hipSuccess;
+    join([&](auto kernel) { occ = hipOccupancyMaxActiveBlocksPerMultiprocessor(&jpc, (const void*)kernel, jthreads, 0); });
+    KNN_HIP(occ);
     if (jpc < 1) jpc = 1;
     // a multiple of 8: the join splits its grid into 8 contiguous point ranges
     const unsigned join_grid = (unsigned)round_up((int64_t)ncu * jpc, 8);
+    // Points a join wave takes at a time, where its share is large enough that
+    // the cursors' atomics (12 ns each, one after the other) are a small part:
+    // six joins of 150,000 x 100 in BF16 with shares of 36 take 2.40 ms by twos and
+    // 1.94 with fixed shares, of x 784 in FP32 14.3 and 15.0; of 1,000,000 x 50 in
+    // BF16 (shares of 244) 19.5 ms by eights and 20.9 with fixed ones.
+    const int64_t share = n / ((int64_t)join_grid * (jthreads / 64));
+    const bool shared = share >= (heavy ? 32 : 128);
+    const int batch = !shared ? 0x7FFFFFFF : (heavy ? 2 : 8);
+    // consecutive points a group's XCD takes before the next group's turn: 512, or
+    // fewer so that each group has 16 turns
+    int chunk = 9;
+    while (chunk > 0 && ((int64_t)128 << chunk) > n) --chunk;
+    const int step = shared ? 1 : (int)(join_grid / 8) * (jthreads / 64);
     // grid-stride kernels get exactly the resident block count (a partial
     // second round of blocks would run on an otherwise idle chip), rounded to
     // a multiple of 8: they split their grids into 8 contiguous row ranges
@@ -1242,7 +1451,7 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     Timer tj, tm, ts;
     for (int it = 0; it < p->max_iters; ++it) {
         const int iter = iter_offset + it;
-        KNN_HIP(hipMemsetAsync(counters, 0, cnt_bytes, st));
+        KNN_HIP(hipMemsetAsync(counters, 0, cnt_bytes + 512, st));
         // iteration `iter` was sampled by the init kernel or the previous merge
         (void)hipEventRecord(ts.a, st);
         if (!cfg.reset)
@@ -1250,15 +1459,10 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
                                                                            sampold);
         (void)hipEventRecord(ts.b, st);
         (void)hipEventRecord(tj.a, st);
-        if (kind == KNN_F16)
-            nnd_join_mfma_kernel<KNN_F16><<<join_grid, 64, 0, st>>>(n, cfg, Xr, rowbytes, np, newf, sampnew, oldf,
-                                                                    sampold, cand, p->seed, iter, counters);
-        else if (kind == KNN_BF16)
-            nnd_join_mfma_kernel<KNN_BF16><<<join_grid, 64, 0, st>>>(n, cfg, Xr, rowbytes, np, newf, sampnew, oldf,
-                                                                     sampold, cand, p->seed, iter, counters);
-        else
-            nnd_join_mfma_kernel<KNN_F32><<<join_grid, 64, 0, st>>>(n, cfg, Xr, rowbytes, np, newf, sampnew, oldf,
-                                                                    sampold, cand, p->seed, iter, counters);
+        join([&](auto kernel) {
+            kernel<<<join_grid, jthreads, 0, st>>>(n, cfg, Xr, rowbytes, np, newf, sampnew, oldf, sampold, cand, p->seed,
+                                             iter, counters, cursors, batch, step, chunk);
+        });
         KNN_HIP(hipGetLastError());
         (void)hipEventRecord(tj.b, st);
         // the merge samples the next iteration unless this is the last one

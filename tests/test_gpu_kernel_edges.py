@@ -357,3 +357,32 @@ def test_fuzzy_rows_and_unions_at_group_edges(orc, n, k):
     D[::7] = np.round(D[::7])
     D = np.sort(D, axis=1).astype(np.float32)
     _check(orc, torch.from_numpy(G).cuda(), torch.from_numpy(D).cuda())
+
+
+@pytest.mark.parametrize("precision,limit", [("fp32", 1_468_928), ("bf16", 1_667_072)])
+def test_nnd_workspace_limit_unchanged(precision, limit):
+    """The least accepted limit of a 1,500 x 20 build does not move with the
+    sizes of counters and sort tiles."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(datagen.gmm_isotropic(n=1500, d=20, seed=1)).cuda()
+    knn.nndescent_build(X, 5, build_k=8, max_iters=1, precision=precision, workspace_limit_bytes=limit)
+    with pytest.raises(knn.KnnError) as e:
+        knn.nndescent_build(X, 5, build_k=8, max_iters=1, precision=precision, workspace_limit_bytes=limit - 1)
+    assert e.value.status == -2
+
+
+@pytest.mark.parametrize("n", [40, 600, 5000, 40_001])
+@pytest.mark.parametrize("precision,d,wide", [("fp32", 32, 33), ("fp32", 20, 400), ("fp32", 200, 376), ("fp32", 370, 385),
+                                              ("bf16", 64, 65), ("fp16", 50, 300)])
+@pytest.mark.parametrize("K,rho", [(8, 0.5), (31, 1.0)])
+def test_join_forms_agree(n, precision, d, wide, K, rho):
+    """Rows padded with zero columns to a width of another form of the join (4
+    pieces of 32 bytes and 5, 47 and 48 of them, with new lists within and
+    beyond one block; 40,001 points: shared out in the widest form) give the
+    same lists bit for bit: zeros change no sum."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(datagen.gmm_isotropic(n=n, d=d, seed=d)).cuda()
+    W = torch.cat([X, torch.zeros((n, wide - d), device="cuda")], 1).contiguous()
+    args = dict(build_k=K, sample_rate=rho, max_iters=3, delta=0.0, seed=5, precision=precision)
+    a, b = knn.nndescent_build(X, 7, **args)[:2], knn.nndescent_build(W, 7, **args)[:2]
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
