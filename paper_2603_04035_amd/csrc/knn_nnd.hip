@@ -430,7 +430,8 @@ __device__ inline ListRaw load_lists(int64_t v, bool valid, const JoinCfg& cfg,
                                      const int32_t* __restrict__ oldf,
                                      const uint32_t* __restrict__ revold)
 {
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // the lane's addresses are formed per point, not held (they spilled)
     const int64_t vv = valid ? v : 0;
     const int rn = min(max(lane - cfg.s, 0), cfg.R - 1), ro = min(max(lane - cfg.K, 0), cfg.R - 1);
     const uint32_t* pn = lane < cfg.s ? (const uint32_t*)(newf + vv * cfg.s + lane) : revnew + vv * cfg.R + rn;
@@ -452,9 +453,11 @@ __device__ inline int join_lists(int64_t v, const ListRaw& raw, const JoinCfg& c
                                  uint64_t seed, int iter, uint32_t* sh, uint32_t* ids, int& L, int& dropped)
 {
     const int lane = threadIdx.x & 63;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));   // keep the position tests and addresses per point, not hoisted
     if (cfg.reset) {
-        if (lane >= cfg.s && lane < cfg.s + cfg.R) revnew[v * cfg.R + (lane - cfg.s)] = 0xFFFFFFFFu;
-        if (lane >= cfg.K && lane < cfg.K + cfg.R) revold[v * cfg.R + (lane - cfg.K)] = 0xFFFFFFFFu;
+        if (ln >= cfg.s && ln < cfg.s + cfg.R) revnew[v * cfg.R + (ln - cfg.s)] = 0xFFFFFFFFu;
+        if (ln >= cfg.K && ln < cfg.K + cfg.R) revold[v * cfg.R + (ln - cfg.K)] = 0xFFFFFFFFu;
     }
     // reverse samples hold codes: recover the source ids
     const uint32_t sn = rev_salt(seed, kTagRevNew, iter, v), so = rev_salt(seed, kTagRevOld, iter, v);
@@ -465,28 +468,37 @@ __device__ inline int join_lists(int64_t v, const ListRaw& raw, const JoinCfg& c
     sh[lane] = nid;
     sh[64 + lane] = oid;
     wave_sync();
-    int ln = lane;
-    asm volatile("" : "+v"(ln));   // keep the position tests per point, not hoisted masks
     bool nv = nid != 0xFFFFFFFFu && nid != (uint32_t)v;
     bool ov = oid != 0xFFFFFFFFu && oid != (uint32_t)v;
     // Repeats keep their first position.  A forward list holds distinct
     // indices, and a reverse list holds a source at most once (a source
     // uses one slot index for all its targets), so a new entry can repeat
     // only a forward-new one (lanes < s), and an old entry a new one or,
-    // if it is a reverse-old entry, a forward-old one (lanes < K).
-#pragma unroll 2
-    for (int q = 0; q < 64; q += 4) {
+    // if it is a reverse-old entry, a forward-old one (lanes < K).  So the
+    // forward lanes are left out at the end, and a group of four positions is
+    // compared whole unless it straddles s or K, where a lane may meet itself.
+    bool rn_rep = false, ro_rep = false, both = false;
+    for (int q = 0; q < cfg.s; q += 4) {
         const uint4 x = *(const uint4*)(sh + q);
-        if (q < cfg.s)
-            nv = nv && !(q + 0 < ln && x.x == nid) && !(q + 1 < ln && x.y == nid) &&
-                 !(q + 2 < ln && x.z == nid) && !(q + 3 < ln && x.w == nid);
-        ov = ov && x.x != oid && x.y != oid && x.z != oid && x.w != oid;
+        both = both || x.x == oid || x.y == oid || x.z == oid || x.w == oid;
+        if (q + 4 <= cfg.s)
+            rn_rep = rn_rep || x.x == nid || x.y == nid || x.z == nid || x.w == nid;
+        else
+            rn_rep = rn_rep || x.x == nid || (q + 1 < cfg.s && x.y == nid) || (q + 2 < cfg.s && x.z == nid);
+    }
+    for (int q = (cfg.s + 3) & ~3; q < cfg.s + cfg.R; q += 4) {
+        const uint4 x = *(const uint4*)(sh + q);
+        both = both || x.x == oid || x.y == oid || x.z == oid || x.w == oid;
     }
     for (int q = 0; q < cfg.K; q += 4) {
         const uint4 x = *(const uint4*)(sh + 64 + q);
-        ov = ov && !(q + 0 < ln && x.x == oid) && !(q + 1 < ln && x.y == oid) &&
-             !(q + 2 < ln && x.z == oid) && !(q + 3 < ln && x.w == oid);
+        if (q + 4 <= cfg.K)
+            ro_rep = ro_rep || x.x == oid || x.y == oid || x.z == oid || x.w == oid;
+        else
+            ro_rep = ro_rep || x.x == oid || (q + 1 < cfg.K && x.y == oid) || (q + 2 < cfg.K && x.z == oid);
     }
+    nv = nv && !(rn_rep && ln >= cfg.s);
+    ov = ov && !both && !(ro_rep && ln >= cfg.K);
     const uint64_t nm = ballot(nv), om = ballot(ov);
     int nn = popc64(nm), no = popc64(om);
     const int all = nn + no;
@@ -554,7 +566,7 @@ struct PendingOffers {
 };
 
 __device__ inline void offers_issue(PendingOffers& po, const uint32_t (&best)[kJMax], int J, int h, bool valid,
-                                    float cut, const uint32_t* ids, uint32_t me, int C, uint64_t salt,
+                                    float cut, const uint32_t* ids, uint32_t me, int C, const uint32_t* slots,
                                     unsigned long long* __restrict__ cand)
 {
 #pragma unroll
@@ -567,8 +579,7 @@ __device__ inline void offers_issue(PendingOffers& po, const uint32_t (&best)[kJ
         if (valid && q < J && b != kNoSel && __uint_as_float(b & ~63u) < cut) {
             const uint32_t src = ids[b & 63u];
             po.key[t] = ((uint64_t)(b & ~63u) << 32) | src;
-            const uint32_t slot = bounded(mix64(((uint64_t)src << 20) ^ salt), (uint32_t)C);
-            po.p[t] = &cand[(int64_t)me * C + slot];
+            po.p[t] = &cand[(int64_t)me * C + slots[b & 63u]];
             po.seen[t] = *po.p[t];
         }
     }
@@ -604,9 +615,12 @@ __device__ inline unsigned long long offers_resolve(const PendingOffers& po)
 // take chunks of up to 512 consecutive points of the processing order in turn,
 // so the points joined at a time on one XCD are Z-order neighbours sharing an
 // L2, and those of all XCDs neighbours sharing the memory-side cache (1,000,000 x
-// 50, six joins: 19.5 ms, 20.9 with a range of the order per group).
-// Bound, on narrow rows, by memory transactions: 41e9 a second in all, gathered
-// lines, slot reads and atomics, 70% of what leaves the L2s being reads.
+// 50 in BF16, six joins: 19.5 ms, 20.9 with a range of the order per group).
+// Bound, on narrow rows, by memory transactions (gathered lines, slot reads and
+// atomics: 41e9 a second leave the L2s, 70% of them reads) and by VALU work
+// (half of the issue slots): with the pairing tests as tags from LDS, a member's
+// slot hashed once, repeats tested whole groups at a time and no address held
+// over the points (they spilled) the same six joins take 17.7 ms.
 //
 // The join list (new members first, then old; L <= 64) is two 32-row
 // blocks.  Its L x L Gram is accumulated by 32 x 32 MFMA tiles (FP32
@@ -789,24 +803,31 @@ struct WideTiles {
 };
 
 // Candidates of member m from one 32-row block's accumulator column: rows
-// 32 blk + 8 (e / 4) + 4 h + e % 4 of tile entry e, branch-free.  Member m
-// pairs with rows i < lim (L if m is new, nn if it is old), i != m.  Groups
-// of 8 rows at or past rows_end (the same for the whole wave) are skipped.
-__device__ inline void scan_block(const f32x16& g, int blk, int h4, int m, int lim, int rows_end, float nm,
-                                  const float* nrm, uint32_t (&best)[kJMax])
+// 32 blk + 8 (e / 4) + 4 h + e % 4 of tile entry e, branch-free.  tag[i] is i
+// for the rows the member pairs with (all L if it is new, the nn new ones if it
+// is old) and kNoSel for the others, which makes their keys kNoSel.  DIAG: the
+// block holds m itself.  Groups of 8 rows at or past rows_end (the same for
+// the whole wave) are skipped.
+template <bool DIAG>
+__device__ __attribute__((always_inline)) inline void scan_block(const f32x16& g, int blk, int h4, int m, int rows_end,
+                                                                 float nm, const float* nrm, const uint32_t* tag,
+                                                                 uint32_t (&best)[kJMax])
 {
+    const int own = m - 32 * blk - h4;   // m's row is entry 8 e4 + e = own
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
         if (32 * blk + 8 * e4 >= rows_end) break;
         const int i0 = 32 * blk + 8 * e4 + h4;
         const f32x4 ni = *(const f32x4*)(nrm + i0);
+        const uint4 t4 = *(const uint4*)(tag + i0);
+        const uint32_t ti[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int i = i0 + e;
             float d2 = ni[e] + nm - 2.0f * g[4 * e4 + e];
             d2 = d2 > 0.0f ? d2 : 0.0f;
-            const bool ok = i < lim && i != m;
-            sel_insert(best, ok ? ((__float_as_uint(d2) & ~63u) | (uint32_t)i) : kNoSel);
+            uint32_t key = (__float_as_uint(d2) & ~63u) | ti[e];
+            if (DIAG) key = own == 8 * e4 + e ? kNoSel : key;
+            sel_insert(best, key);
         }
     }
 }
@@ -831,6 +852,10 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
     const int c = lane & 31, h = lane >> 5;
     uint32_t *ids = ids_s[wv], *sh = sh_s[wv];
     float *nrm = nrm_s[wv], *thr = thr_s[wv], *turn = turn_s[wv];
+    // per member: its row tags (see scan_block) and its slot as a candidate
+    __shared__ __attribute__((aligned(16))) uint32_t tag_s[NW][2][64];
+    __shared__ uint32_t slot_s[NW][64];
+    uint32_t *tag_new = tag_s[wv][0], *tag_old = tag_s[wv][1], *slots = slot_s[wv];
     // emitted: offers in the low 32 bits, slot collisions in the high 32 (a
     // lane sends far fewer than 2^32 offers), so one register pair counts both
     unsigned long long emitted = 0;
@@ -855,16 +880,16 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
     // point, `batch` beyond its share, where the cursor's atomics would cost
     // more than that.
     int64_t q = ((int64_t)(blockIdx.x >> 3) * NW + wv) * (step == 1 ? batch : 1), v = point(q), vn;
-    unsigned ahead = 0;
-    if (step == 1 && lane == 0) ahead = atomicAdd(&cursors[grp * 16], (unsigned)batch);
+    __shared__ unsigned ahead_s[NW];
+    if (step == 1 && lane == 0) ahead_s[wv] = atomicAdd(&cursors[grp * 16], (unsigned)batch);
     int left = batch;
     ListRaw cur = load_lists(v, v < n, cfg, newf, revnew, oldf, revold);
     for (; v < n; v = vn) {
         q += step;
         if (--left == 0) {
-            q = gw * batch + (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)ahead);
+            q = gw * batch + (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)ahead_s[wv]);
             left = batch;
-            if (lane == 0) ahead = atomicAdd(&cursors[grp * 16], (unsigned)batch);
+            if (lane == 0) ahead_s[wv] = atomicAdd(&cursors[grp * 16], (unsigned)batch);
         }
         vn = point(q);
         int L = 0, dr = 0;
@@ -879,6 +904,9 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
             tally[0] += (unsigned long long)L;
             tally[1] += (unsigned long long)(nn * (nn - 1) / 2 + nn * (L - nn));
         }
+        tag_new[lane] = lane < L ? (uint32_t)lane : kNoSel;
+        tag_old[lane] = lane < nn ? (uint32_t)lane : kNoSel;
+        if (lane < L) slots[lane] = bounded(mix64(((uint64_t)ids[lane] << 20) ^ salt), (uint32_t)cfg.C);
         if (!tail_in_pieces && lane < L) {
             // rows whose trailing words lie past the gathered pieces
             const float2 a = *(const float2*)(Xr + (int64_t)ids[lane] * rowbytes + rowbytes - 8);
@@ -890,10 +918,10 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
         const uint8_t* r0 = Xr + (int64_t)ids[v0 ? c : 0] * rowbytes + 16 * h;
         const uint8_t* r1 = Xr + (int64_t)ids[v1 ? 32 + c : 0] * rowbytes + 16 * h;
         WideTiles<OUT> wt;
+        // not held through the tiles (12 registers)
+        emitted += offers_resolve(po);
+        po.p[0] = po.p[1] = nullptr;
         if constexpr (WIDE) {
-            // not held through the tiles (12 registers)
-            emitted += offers_resolve(po);
-            po.p[0] = po.p[1] = nullptr;
             float z = 0.0f;
             asm volatile("" : "+v"(z));
 #pragma unroll
@@ -968,17 +996,22 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
 #pragma unroll
             for (int q = 0; q < kJMax; ++q) best[q] = kNoSel;
             const float nm = nrm[m];
-            const int lim = m < nn ? L : nn;
             // a pass whose members are all old needs only the first nn rows
             const int rows_end = 32 * cb >= nn ? nn : L;
-            scan_block(at, 0, h4, m, lim, rows_end, nm, nrm, best);
-            if (lower) scan_block(ab, 1, h4, m, lim, rows_end, nm, nrm, best);
+            const uint32_t* tag = m < nn ? tag_new : tag_old;
+            if (cb == 0) {
+                scan_block<true>(at, 0, h4, m, rows_end, nm, nrm, tag, best);
+                if (lower) scan_block<false>(ab, 1, h4, m, rows_end, nm, nrm, tag, best);
+            } else {
+                scan_block<false>(at, 0, h4, m, rows_end, nm, nrm, tag, best);
+                if (lower) scan_block<true>(ab, 1, h4, m, rows_end, nm, nrm, tag, best);
+            }
             uint32_t recv[kJMax];
 #pragma unroll
             for (int q = 0; q < kJMax; ++q) recv[q] = xor_u32(best[q], 32);
             sel_merge(best, recv);
             emitted += offers_resolve(po);
-            offers_issue(po, best, J, h, m < L, m < L ? thr[m] : 0.0f, ids, ids[m], cfg.C, salt, cand);
+            offers_issue(po, best, J, h, m < L, m < L ? thr[m] : 0.0f, ids, ids[m], cfg.C, slots, cand);
         }
     }
     emitted += offers_resolve(po);
