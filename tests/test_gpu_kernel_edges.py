@@ -386,3 +386,16 @@ def test_join_forms_agree(n, precision, d, wide, K, rho):
     args = dict(build_k=K, sample_rate=rho, max_iters=3, delta=0.0, seed=5, precision=precision)
     a, b = knn.nndescent_build(X, 7, **args)[:2], knn.nndescent_build(W, 7, **args)[:2]
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("p", [1, 15, 16, 17, 24, 32, 39, 40, 64])
+def test_pca_factor_block_edges(orc, p):
+    """Subspaces of 17, 31, 32, 34, 48, 64, 78 and 80 columns: the factor's blocks
+    of 16 whole and in part.  Bounds as the other PCA tests."""
+    import paper_2603_04035_amd as knn
+    X = _spectrum(3000, 100, np.arange(1, 101) ** -0.7, 5)
+    Z, V, w, mu = (t.cpu().numpy() for t in knn.pca(torch.from_numpy(X).cuda(), p))
+    oZ, oV, ow, omu = orc.pca(X, p)
+    np.testing.assert_allclose(w, ow, rtol=1e-10)
+    assert np.abs(V - oV).max() <= 1e-8
+    assert np.abs(V.T @ V - np.eye(p)).max() <= 1e-12
