@@ -1261,7 +1261,8 @@ __global__ __launch_bounds__(256) void exact_direct_kernel(
 }
 
 // Small searches in FP32: every pair's canonical distance, one launch, no
-// staging, no scratch.  A wave owns a query; 64 references at a time pass
+// staging, no scratch.  A wave owns a query (WQ = 4: four waves, a quarter of
+// the references each, their lists merged at the end); 64 references at a time pass
 // through LDS, 32 coordinates each, lane = reference, its distance summed in
 // the 16 partial sums and the tree of dist_g16.  Keys below the list's k-th
 // enter the wave's 64-entry sorted list, a few one by one, more by a sort and a
@@ -1271,26 +1272,28 @@ __global__ __launch_bounds__(256) void exact_direct_kernel(
 constexpr int64_t kSmallRefs = 4096;
 constexpr double kSmallWork = 3e9;   // queries * references * (6 d + 150) instructions
 
-template <int DT>
+template <int DT, int WQ>
 __global__ __launch_bounds__(256) void exact_small_kernel(
     const void* __restrict__ Q, int64_t ldq, int nq, const void* __restrict__ R, int64_t ldr, int nr, int d,
     const int32_t* __restrict__ q_self, int self_mode, int k, int out_kind, int32_t* __restrict__ out_idx,
     float* __restrict__ out_dist)
 {
-    constexpr int CW = 32;   // coordinates per chunk
-    __shared__ float rs[64][CW + 1];
+    constexpr int CW = 32;         // coordinates per chunk
+    constexpr int TR = 64 * WQ;    // references per tile
+    __shared__ __attribute__((aligned(16))) float rs[TR][CW + 1];
     __shared__ __attribute__((aligned(16))) float qs[4][CW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int q0 = blockIdx.x * 4, q = q0 + w;
+    const int q0 = blockIdx.x * (4 / WQ), q = WQ == 4 ? q0 : q0 + w;
+    const int row = WQ == 4 ? tid : lane, qw = WQ == 4 ? 0 : w;   // this lane's row of the tile, its query's of qs
     const int qc = q < nq ? q : nq - 1;
     const int self = self_mode == 1 ? qc : (self_mode == 2 ? q_self[qc] : -1);
     const int cc = tid & 31, rr = tid >> 5;   // staging: column cc of rows rr, rr + 8, ...
     const int qr = q0 + (rr & 3) < nq ? q0 + (rr & 3) : nq - 1;
-    float xr[8], xq;
+    float xr[8 * WQ], xq;
     auto fetch = [&](int base, int c0) {
         const int t = c0 + cc;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 8 * WQ; ++u) {
             const int r = base + rr + 8 * u;
             xr[u] = t < d ? elem<DT>::ld(R, (int64_t)(r < nr ? r : nr - 1) * ldr + t) : 0.0f;
         }
@@ -1298,25 +1301,25 @@ __global__ __launch_bounds__(256) void exact_small_kernel(
     };
     uint64_t list = kEmptyList;
     fetch(0, 0);
-    for (int base = 0; base < nr; base += 64) {
+    for (int base = 0; base < nr; base += TR) {
         float s[16];
 #pragma unroll
         for (int g = 0; g < 16; ++g) s[g] = 0.0f;
         for (int c0 = 0; c0 < d; c0 += CW) {
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < 8; ++u) rs[rr + 8 * u][cc] = xr[u];
+            for (int u = 0; u < 8 * WQ; ++u) rs[rr + 8 * u][cc] = xr[u];
             if (rr < 4) qs[rr][cc] = xq;
             __syncthreads();
             if (c0 + CW < d) fetch(base, c0 + CW);
-            else if (base + 64 < nr) fetch(base + 64, 0);
+            else if (base + TR < nr) fetch(base + TR, 0);
             // coordinates past d are zero on both sides: the sums keep their bits
 #pragma unroll
             for (int t = 0; t < CW; t += 4) {
-                const f32x4 x = *(const f32x4*)&qs[w][t];
+                const f32x4 x = *(const f32x4*)&qs[qw][t];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float df = x[e] - rs[lane][t + e];
+                    const float df = x[e] - rs[row][t + e];
                     s[(t + e) & 15] = fmaf(df, df, s[(t + e) & 15]);
                 }
             }
@@ -1325,7 +1328,7 @@ __global__ __launch_bounds__(256) void exact_small_kernel(
         for (int j = 8; j > 0; j >>= 1)
 #pragma unroll
             for (int g = 0; g < j; ++g) s[g] = s[g] + s[g + j];
-        const int j = base + lane;
+        const int j = base + row;
         const uint64_t key = j < nr && j != self ? make_key(s[0], (uint32_t)j) : kEmptyCand;
         uint64_t m = ballot(key < bcast_u64(list, k - 1));
         if (popc64(m) > 6) {
@@ -1337,6 +1340,16 @@ __global__ __launch_bounds__(256) void exact_small_kernel(
                 list = umin64(list, umax64(up, x));
             }
         }
+    }
+    if constexpr (WQ == 4) {
+        // the four waves' lists
+        uint64_t* all = (uint64_t*)&rs[0][0];
+        __syncthreads();
+        all[tid] = list;
+        __syncthreads();
+        if (w != 0) return;
+        list = seg_merge_sorted<64>(seg_merge_sorted<64>(list, all[64 + lane]),
+                                    seg_merge_sorted<64>(all[128 + lane], all[192 + lane]));
     }
     if (q < nq && lane < k) {
         const float d2 = key_d2(list);
@@ -1904,13 +1917,24 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         qc = lo * kTileRows;
     }
     if (small) {
-        const unsigned g = (unsigned)ceil_div(Q.n, 4);
-#define KNN_SM(DT)                                                                                               \
-    exact_small_kernel<DT><<<g, 256, 0, st>>>(Q.data, Q.ld, (int)Q.n, R.data, R.ld, (int)R.n, R.d, q_self,         \
-                                              self_mode, k, out_kind, out_idx, out_dist)
-        if (Q.dtype == KNN_F32) KNN_SM(KNN_F32);
-        else if (Q.dtype == KNN_BF16) KNN_SM(KNN_BF16);
-        else KNN_SM(KNN_F16);
+        // Few queries leave CUs idle: four waves share one (100 queries in 1,000 /
+        // 4,000 x 50: 45 / 92 us, 57 / 135 with a wave each; 300: 66 / 159 and
+        // 58 / 136, for then two workgroups of 256 registers meet on a CU).
+        const bool wide = Q.n <= 256 && R.n >= 512;
+        const unsigned g = (unsigned)(wide ? Q.n : ceil_div(Q.n, 4));
+#define KNN_SM(DT, WQ)                                                                                           \
+    exact_small_kernel<DT, WQ><<<g, 256, 0, st>>>(Q.data, Q.ld, (int)Q.n, R.data, R.ld, (int)R.n, R.d, q_self,     \
+                                                  self_mode, k, out_kind, out_idx, out_dist)
+        if (Q.dtype == KNN_F32) {
+            if (wide) KNN_SM(KNN_F32, 4);
+            else KNN_SM(KNN_F32, 1);
+        } else if (Q.dtype == KNN_BF16) {
+            if (wide) KNN_SM(KNN_BF16, 4);
+            else KNN_SM(KNN_BF16, 1);
+        } else {
+            if (wide) KNN_SM(KNN_F16, 4);
+            else KNN_SM(KNN_F16, 1);
+        }
 #undef KNN_SM
         KNN_HIP(hipGetLastError());
         KNN_HIP(hipStreamSynchronize(st));

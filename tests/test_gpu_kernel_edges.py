@@ -399,3 +399,20 @@ def test_pca_factor_block_edges(orc, p):
     np.testing.assert_allclose(w, ow, rtol=1e-10)
     assert np.abs(V - oV).max() <= 1e-8
     assert np.abs(V.T @ V - np.eye(p)).max() <= 1e-12
+
+
+@pytest.mark.parametrize("nq", [1, 3, 255, 256, 257])
+@pytest.mark.parametrize("n,d", [(511, 40), (512, 40), (513, 5), (1000, 33), (4096, 64)])
+def test_small_search_few_queries(nq, n, d):
+    """Up to 256 queries in 512 references and more: four waves per query give
+    the bits of the list route (a workspace limit, on a set that is not small: the same
+    references with 5,000 far copies appended)."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(nq + n)
+    X = torch.from_numpy(rng.integers(-9, 10, (n, d)).astype(np.float32) / 4).cuda()
+    Q = torch.from_numpy(rng.integers(-9, 10, (nq, d)).astype(np.float32) / 4).cuda()
+    far = torch.cat([X, X.new_full((5000, d), 100.0)]).contiguous()
+    k = 20
+    i, dist = knn.knn_exact_query(Q, X, k)[:2]
+    ref_i, ref_d = knn.knn_exact_query(Q, far, k, workspace_limit=1 << 30)[:2]
+    assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
