@@ -209,8 +209,9 @@ __global__ __launch_bounds__(256) void fuzzy_inptr_kernel(const uint32_t* __rest
 // follow each other; a hub gets every lane): each finds its place among
 // its row's own entries by bisection in LDS.
 // 1,000,000 x 15: 121 and 333 us; 734 and 708 with a wave per row and
-// every pair of own and transposed entry compared.  The emit pass is bound by the
-// gather of the transposed entries' weights (a line per entry).
+// every pair of own and transposed entry compared.  Bound by the latency of the
+// bisections; the gather of the transposed entries' weights (a line per entry)
+// is 75 us of the emit pass, and carrying them through the sort cost 120 there.
 template <bool EMIT, int G>
 __global__ __launch_bounds__(256) void fuzzy_union_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ w, int k, DivK dk, int64_t n,
