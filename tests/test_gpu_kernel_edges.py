@@ -416,3 +416,20 @@ def test_small_search_few_queries(nq, n, d):
     i, dist = knn.knn_exact_query(Q, X, k)[:2]
     ref_i, ref_d = knn.knn_exact_query(Q, far, k, workspace_limit=1 << 30)[:2]
     assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
+
+
+@pytest.mark.parametrize("n", [60, 255, 256, 257, 1029])
+@pytest.mark.parametrize("e", [1, 2, 3, 7])
+@pytest.mark.parametrize("k", [8, 12, 13])
+def test_direct_ranks_with_ties(orc, n, e, k):
+    """Ranks in a low-dimensional space, probe widths 8, 12 and 16: lattice
+    rows, so that references tie with probes before, in and behind the probes'
+    groups of 8; whole and part tiles of 256; equal to the oracle's terms."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(n + e)
+    X = rng.integers(0, 4, (n, e + 1)).astype(np.float32)
+    Y = rng.integers(0, 4, (n, e)).astype(np.float32)
+    _, (h, t, c) = knn.quality(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k, per_row=True)
+    oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
+    assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
+    assert np.array_equal(c.cpu().numpy(), oc)
