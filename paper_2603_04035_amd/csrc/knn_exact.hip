@@ -1993,9 +1993,11 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     const int lds = kind == KNN_SPLIT ? 2 * ldp : ldp;
     const bool ares = lds <= (kind == KNN_SPLIT ? TileCfg<KNN_SPLIT>::AMAX : TileCfg<KNN_F16>::AMAX);
     // the gated route needs 2 KiB of scratch per row and split: not under a
-    // limit; with at most four tiles of long rows its second pass over the
-    // products costs more than the insertions (500 x 784 BF16: 207 against 154 us)
-    const bool gated = budget == 0 && (ares || R.n > 4 * kTileRows);
+    // limit; with two to four tiles of long rows its second pass over the
+    // products costs more than the insertions (500 x 784 BF16: 187 us against 142;
+    // 500 x 200: 105 and 110, 128 x 784: 105 and 140, 100,000 queries in 500 x 200:
+    // 503 and 881)
+    const bool gated = budget == 0 && (ares || lds <= 256 || R.n <= kTileRows || R.n > 4 * kTileRows);
     const int S0 = gated ? filling_splits(qc, R.n) : exact_splits(qc);
     const int64_t split_len = round_up(ceil_div(R.n, S0), kTileRows);
     const int S = (int)ceil_div(R.n, split_len);

@@ -433,3 +433,18 @@ def test_direct_ranks_with_ties(orc, n, e, k):
     oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
     assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
     assert np.array_equal(c.cpu().numpy(), oc)
+
+
+@pytest.mark.parametrize("n", [40, 128, 129, 400, 512])
+@pytest.mark.parametrize("precision,d", [("bf16", 200), ("fp16", 256), ("bf16", 257), ("fp16", 700)])
+def test_gated_route_few_references(n, precision, d):
+    """Up to four tiles of references, rows where the gate is taken and where it
+    is not: the bits of the list route (a limit that fits everything)."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(datagen.gmm_isotropic(n=n, d=d, comps=3, seed=n)).cuda()
+    Q = torch.from_numpy(datagen.gmm_isotropic(n=1500, d=d, comps=3, seed=n)).cuda()
+    own = torch.arange(n, dtype=torch.int32).cuda()
+    for q, s in ((X, own), (Q, None)):
+        a = knn.knn_exact_query(q, X, 12, q_self=s, precision=precision)
+        b = knn.knn_exact_query(q, X, 12, q_self=s, precision=precision, workspace_limit=4 << 30)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
