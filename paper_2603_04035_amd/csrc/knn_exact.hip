@@ -875,7 +875,9 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
             const uint32_t j = (uint32_t)rt + blk * 32 + c;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                if (acc[blk][v] >= lim[v]) {
+                // columns past the references score -inf, which a gate of -inf
+                // (fewer groups than kp) lets pass: not references
+                if (acc[blk][v] >= lim[v] && j < (uint32_t)rend) {
                     const int lr = w * 32 + mfma_row(v, h);
                     const uint32_t pos = atomicAdd(&scnt[lr], 1u);   // below kCandCap: see `full`
                     buf[(uint32_t)lr * rstride + pos] = ((uint64_t)__float_as_uint(acc[blk][v]) << 32) | j;
@@ -1041,7 +1043,7 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
                     const uint32_t slot = atomicAdd(&qcount, 1u);
                     queue[slot] = ((uint64_t)j << 32) | (uint32_t)(lq << 10 | (nv - a) << 5 | (nv - b));
                 }
-                if (LISTS && x >= lim) {
+                if (LISTS && x >= lim && j < (uint32_t)rend) {   // as exact_append_kernel
                     const uint32_t pos = atomicAdd(&scnt[lq], 1u);
                     buf[(uint32_t)lq * rstride + pos] = ((uint64_t)__float_as_uint(x) << 32) | j;
                     full = full || pos >= kCandCap - kTileRows;

@@ -448,3 +448,61 @@ def test_gated_route_few_references(n, precision, d):
         a = knn.knn_exact_query(q, X, 12, q_self=s, precision=precision)
         b = knn.knn_exact_query(q, X, 12, q_self=s, precision=precision, workspace_limit=4 << 30)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+def _with_room(X):
+    """X's rows at the front of a buffer whose other rows are copies of row 0:
+    a row past the end would be at distance 0 of row 0."""
+    buf = torch.from_numpy(X[:1].repeat(len(X) + 256, 0))
+    buf[: len(X)] = torch.from_numpy(X)
+    return buf.cuda()[: len(X)]
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 12, 16, 20, 31, 32, 33])
+@pytest.mark.parametrize("precision,d", [("fp32", 20), ("bf16", 20), ("fp16", 50), ("bf16", 100), ("fp16", 300)])
+def test_fewer_references_than_rerank_width(orc, n, precision, d):
+    """Every other row is a neighbour or a candidate (k = n - 1, and 15 with a
+    re-rank width of 30): all are found, in the canonical order, and nothing past
+    the end of the references is."""
+    import paper_2603_04035_amd as knn
+    from oracle.compare import exact_parity, parity_ok
+    X = datagen.gmm_isotropic(n=n, d=d, comps=3, seed=n + d)
+    Xd = _with_room(X)
+    own = torch.arange(n, dtype=torch.int32).cuda()
+    for k in {min(n - 1, 32), min(n - 1, 15)}:
+        idx, dist = knn.knn_exact(Xd, k, precision=precision)[:2]
+        ref = knn.knn_exact_query(Xd, Xd, k, q_self=own, precision=precision, workspace_limit=1 << 30)
+        assert int(idx.min()) >= 0 and int(idx.max()) < n
+        assert torch.equal(idx, ref[0]) and torch.equal(dist, ref[1])
+        O, _ = orc.exact_knn(X, k)
+        res = exact_parity(X, np.arange(n), idx.cpu().numpy(), dist.cpu().numpy(), O)
+        assert parity_ok(res), (k, res)
+
+
+@pytest.mark.parametrize("nr", [20, 31])
+def test_many_queries_in_few_references(orc, nr):
+    """FP32 queries past the one-launch search's work, in fewer references
+    than the re-rank width."""
+    import paper_2603_04035_amd as knn
+    nq, d, k = 40_001, 700, 16
+    R = datagen.gmm_isotropic(n=nr, d=d, comps=3, seed=nr)
+    Q = datagen.gmm_isotropic(n=nq, d=d, comps=3, seed=5)
+    assert nq * nr * (6.0 * d + 150.0) > 3e9
+    idx, dist = knn.knn_exact_query(torch.from_numpy(Q).cuda(), _with_room(R), k)[:2]
+    assert int(idx.min()) >= 0 and int(idx.max()) < nr
+    rows = np.arange(0, nq, 397)
+    O, O2 = orc.exact_query(R, np.ascontiguousarray(Q[rows]), k)
+    assert np.allclose(dist.cpu().numpy()[rows], np.sqrt(O2), rtol=1e-5)
+
+
+@pytest.mark.parametrize("n,k", [(4, 2), (12, 7), (20, 12), (26, 16), (32, 16)])
+def test_quality_few_rows(orc, n, k):
+    """The rank pass's neighbour lists where a row has fewer others than the
+    lists' re-rank width, 2 k."""
+    import paper_2603_04035_amd as knn
+    X = datagen.gmm_isotropic(n=n, d=20, comps=3, seed=n)
+    Y = np.ascontiguousarray(np.random.default_rng(n).normal(size=(n, 2)).astype(np.float32))
+    _, (h, t, c) = knn.quality(_with_room(X), torch.from_numpy(Y).cuda(), k, per_row=True)
+    oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
+    assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
+    assert np.array_equal(c.cpu().numpy(), oc)
