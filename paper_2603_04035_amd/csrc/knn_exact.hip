@@ -776,10 +776,12 @@ constexpr int kCandCap = 256;   // entries of a row's buffer
 
 // Rows lr0 .. lr0 + 31 of one wave (counts n32, gates lim32 in LDS) whose
 // buffers have no room for another tile's 128 keep their best 32 by (distance,
-// index) and raise their gate to the kp-th of them.
+// index) and raise their gate to the kp-th of them.  self32 (nullable): the
+// rows' own indices, which are dropped here (counted, one would take the place
+// of the kp-th neighbour).
 __device__ inline void compact_rows(uint64_t* buf, uint32_t rstride, uint32_t* n32, float* lim32,
-                                                       int lr0, const float* qnb, int kp, float m2, float sc,
-                                                       float rmax)
+                                    const int32_t* self32, int lr0, const float* qnb, int kp, float m2, float sc,
+                                    float rmax)
 {
     const int lane = threadIdx.x & 63;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
@@ -788,11 +790,13 @@ __device__ inline void compact_rows(uint64_t* buf, uint32_t rstride, uint32_t* n
         const int r = __builtin_ctzll(m);
         const uint32_t nc = bcast_u32(n, r);
         const float sq = qnb[lr0 + r];
+        const uint32_t self = self32 ? (uint32_t)self32[r] : 0xFFFFFFFFu;
         uint64_t* b = buf + (uint32_t)(lr0 + r) * rstride;
         auto key_of = [&](uint64_t x) { return make_key(fmaf(m2, __uint_as_float((uint32_t)(x >> 32)), sq), (uint32_t)x); };
         uint64_t best = kEmptyCand;
         for (uint32_t e = 0; e < nc; e += 64) {
-            const uint64_t key = e + lane < nc ? key_of(b[e + lane]) : kEmptyCand;
+            const uint64_t x = e + lane < nc ? b[e + lane] : ~0ull;
+            const uint64_t key = e + lane < nc && (uint32_t)x != self ? key_of(x) : kEmptyCand;
             best = seg_merge_sorted<64>(best, seg_sort<64>(key));
         }
         const uint64_t last = bcast_u64(best, kListW - 1);
@@ -801,7 +805,7 @@ __device__ inline void compact_rows(uint64_t* buf, uint32_t rstride, uint32_t* n
         uint32_t kept = 0;
         for (uint32_t e = 0; e < nc; e += 64) {
             const uint64_t x = e + lane < nc ? b[e + lane] : 0ull;
-            const bool keep = e + lane < nc && key_of(x) <= last;
+            const bool keep = e + lane < nc && (uint32_t)x != self && key_of(x) <= last;
             const uint64_t km = ballot(keep);
             if (keep) b[kept + rank_below(km)] = x;
             kept += (uint32_t)popc64(km);
@@ -819,16 +823,19 @@ __device__ inline void compact_rows(uint64_t* buf, uint32_t rstride, uint32_t* n
 // of kCandCap entries for this split (part[(row * S + s) * kCandCap ..], counts
 // in LDS, then cnt[row * S + s]).  A row belongs to one wave, so appending
 // needs no other wave.  When a buffer has no room for another tile's 128, its
-// wave keeps the row's best 32 by (distance, index) and raises the gate to
-// the kp-th of them (compact_rows): rare behind a gate, and the same keys the
-// sorted lists of exact_tile_kernel would keep.
+// wave keeps the row's best 32 by (distance, index), its own index left out, and
+// raises the gate to the kp-th of them (compact_rows): the keys the sorted
+// lists of exact_tile_kernel would keep.  Rare where a row's neighbours are
+// spread over the references; where they follow each other (rows sorted by
+// cluster, position or time) the gate's groups are near-copies and several
+// hundred references pass it.
 
 template <int OUT, bool ARES>
 __global__ __launch_bounds__(256, 2) void exact_append_kernel(
     const void* __restrict__ Qs, const float* __restrict__ qn, int64_t nq, const void* __restrict__ Rs,
-    const float* __restrict__ rn, int64_t nr, int ldp, int kp, int64_t split_len, int S,
-    const unsigned* __restrict__ rmax_bits, const unsigned* __restrict__ qmax_bits, const float* __restrict__ lims,
-    uint64_t* part, uint32_t* __restrict__ cnt)
+    const float* __restrict__ rn, int64_t nr, int ldp, const int32_t* __restrict__ q_self, int self_mode,
+    int64_t self_base, int kp, int64_t split_len, int S, const unsigned* __restrict__ rmax_bits,
+    const unsigned* __restrict__ qmax_bits, const float* __restrict__ lims, uint64_t* part, uint32_t* __restrict__ cnt)
 {
     using C = TileCfg<OUT>;
     using E = typename C::E;
@@ -838,6 +845,7 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
     __shared__ float srn[kTileRows];
     __shared__ uint32_t scnt[kTileRows];
     __shared__ float slim[kTileRows];
+    __shared__ int32_t sself[kTileRows];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
     const int64_t q0 = (int64_t)blockIdx.x * kTileRows;
     const int s = blockIdx.y;
@@ -849,6 +857,8 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
     if (tid < kTileRows) {
         scnt[tid] = 0u;
         slim[tid] = q0 + tid < nq ? lims[q0 + tid] : __builtin_inff();   // rows past nq take nothing
+        const int64_t qr = q0 + tid;
+        sself[tid] = qr >= nq ? -1 : (self_mode == 1 ? (int32_t)(self_base + qr) : (self_mode == 2 ? q_self[qr] : -1));
     }
     const E* Qb = (const E*)Qs + q0 * ldp;
     const E* Re = (const E*)Rs;
@@ -886,7 +896,7 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
             }
         }
         if (ballot(full)) {
-            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, w * 32, qn + q0, kp, m2, sc, rmax);
+            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, sself + w * 32, w * 32, qn + q0, kp, m2, sc, rmax);
 #pragma unroll
             for (int v = 0; v < 16; ++v) lim[v] = slim[w * 32 + mfma_row(v, h)];
         }
@@ -1051,7 +1061,8 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
             }
         }
         if (LISTS && ballot(full)) {
-            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, w * 32, qn + q0, kp, m2, sc,
+            // a row's own score is -inf: never among the best
+            compact_rows(buf, rstride, scnt + w * 32, slim + w * 32, nullptr, w * 32, qn + q0, kp, m2, sc,
                          __uint_as_float(*rmax_bits));
             lim = slim[lq];
         }
@@ -1881,8 +1892,9 @@ static void launch_tiles_a(const TileArgs& a, hipStream_t st)
                                                         a.ntiles, a.rmax, a.qmax, gtop);
     gate_select_kernel<<<(unsigned)ceil_div(a.nq, 8), 256, 0, st>>>(gtop, a.nq, (int)ggrid.y, a.kp, a.qn, a.rmax,
                                                                     a.qmax, a.gate_err, a.lims);
-    exact_append_kernel<OUT, ARES><<<grid, 256, 0, st>>>(a.Qs, a.qn, a.nq, a.Rs, a.rn, a.nr, a.ld, a.kp, a.split_len,
-                                                         a.S, a.rmax, a.qmax, a.lims, a.part, a.cnt);
+    exact_append_kernel<OUT, ARES><<<grid, 256, 0, st>>>(a.Qs, a.qn, a.nq, a.Rs, a.rn, a.nr, a.ld, a.qself,
+                                                         a.self_mode, a.q0, a.kp, a.split_len, a.S, a.rmax, a.qmax,
+                                                         a.lims, a.part, a.cnt);
 }
 
 template <int OUT>

@@ -506,3 +506,24 @@ def test_quality_few_rows(orc, n, k):
     oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
     assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
     assert np.array_equal(c.cpu().numpy(), oc)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("k,rerank", [(16, 0), (31, 0), (32, 0), (20, 20), (19, 20)])
+def test_compacted_buffers_leave_self_out(precision, k, rerank):
+    """Rows along a curve, neighbours next to each other: hundreds of
+    references pass a row's gate and its buffer is cut back again and again.  The
+    row's own index, nearest of all, is not one of those kept: the bits of the
+    list route (a limit that fits everything), as a self search and as queries."""
+    import paper_2603_04035_amd as knn
+    n, d = 5000, 50
+    rng = np.random.default_rng(2)
+    t = np.linspace(0.0, 1.0, n)[:, None]
+    X = np.sin(t * rng.uniform(2.0, 9.0, (1, d)) + rng.uniform(0.0, 6.0, (1, d)))
+    X = torch.from_numpy((20 * X + 0.02 * rng.standard_normal((n, d))).astype(np.float32)).cuda()
+    own = torch.arange(n, dtype=torch.int32).cuda()
+    args = dict(precision=precision, rerank_k=rerank)
+    ref = knn.knn_exact_query(X, X, k, q_self=own, workspace_limit=4 << 30, **args)
+    for got in (knn.knn_exact(X, k, **args), knn.knn_exact_query(X, X, k, q_self=own, **args)):
+        assert int(got[0].min()) >= 0
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
