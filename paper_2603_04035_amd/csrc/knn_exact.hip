@@ -918,8 +918,8 @@ constexpr int kRankQueue = kTileRows * kTileRows + kRankFlush;
 // search on split rows, operands swapped (a lane's sums belong to one query:
 // its probes, as scores, and its counts sit in registers), S reference splits
 // whose counts are added into counts, zeroed beforehand.  A score further from
-// a probe's than the slack (the GEMM bound with the tile's largest norm, plus
-// the canonical distance's) decides it; what is left is queued (the pair and
+// a probe's than the slack (the GEMM bound with the tile's largest norm, the
+// parts' absolute error, plus the canonical distance's) decides it; what is left is queued (the pair and
 // its range of undecided probes) in the workgroup's global queue, which is
 // worked off once it holds 1,024 pairs: 16-lane groups form the pairs'
 // canonical FP32 distances from the rows Zf, four pairs in flight, in the order
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
     const _Float16* __restrict__ Qs, const float* __restrict__ qn, int64_t nq, const _Float16* __restrict__ Rs,
     const float* __restrict__ rn, int64_t nr, int lds, const float* __restrict__ Qf, const float* __restrict__ Zf,
     int64_t ldf, int d, int64_t self_base, const uint64_t* __restrict__ probes, const unsigned* __restrict__ rmax_bits,
-    float ec_dot, float ec_norm, float edir, int S, int64_t split_len, uint32_t* __restrict__ counts,
+    float ec_dot, float ec_norm, float edir, float eabs, float eden, int S, int64_t split_len, uint32_t* __restrict__ counts,
     uint64_t* gqueue, int kp, const float* __restrict__ lims, uint64_t* part, uint32_t* __restrict__ cnt)
 {
     using C = TileCfg<KNN_SPLIT>;
@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
             for (int o = 32; o > 0; o >>= 1) tn = fmaxf(tn, xor_f32(tn, o));
         }
         const float e2 = ec_dot * qa * sqrtf(tn) + ec_norm * (sq + tn + mx);
-        const float sl = hsc * (e2 + 2.0f * edir * (mx + e2));
+        const float sl = hsc * (e2 + 2.0f * edir * (mx + e2)) + eabs * scale * (qa + sqrtf(tn)) + eden;
         const bool diag = ballot(self >= rt && self < rt + kTileRows) != 0ull;
         const int sr = self >= rt && self < rt + kTileRows ? (int)(self - rt) : -1;
         bool full = false;
@@ -2276,11 +2276,18 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
         // running sums of a segment; the segments' additions; the parts' rounding;
         // the score's subtraction and slack), plus 4u (|q|^2 + |r|^2 + the
         // probe's distance) for the norms (FP64 sums rounded once) and the
-        // probes' scores; the canonical distance's own error is edir
+        // probes' scores; the canonical distance's own error is edir.
+        // The parts of elements far below the common scale are off by up to
+        // 2^-25 of a scaled unit each, which no relative term covers: a score by
+        // 2^-25 sqrt(d) (|q| + |r|) + d 2^-50 in scaled units.  Twice the first
+        // is taken (eabs), and d 2^-24 for the second and for norms and
+        // distances among FP32's denormals (eden).  Next to nothing for rows of
+        // like norms; with one row 10^6 times the others the slack is some
+        // 60 times as wide, from 10^8 times on most pairs are rechecked.
         const int chunks = lds / 64;
         const float inst = 6.0f * (float)std::min(chunks, kSegChunks), segs = (float)ceil_div(chunks, kSegChunks);
         const float ecd = 2.0f * (25.0f + 3.0f * inst + segs) * u * 1.01f, ecn = 4.04f * u;
-        const float ed = (float)(dz / 16 + 8) * u;
+        const float ed = (float)(dz / 16 + 8) * u, ea = u * sqrtf((float)dz), en = u * (float)dz;
         const bool ares = lds <= TileCfg<KNN_SPLIT>::AMAX;
         zero_words_kernel<<<(unsigned)std::min<int64_t>(ceil_div(n * kRankP, 64), 4096), 64, 0, st>>>(cz,
                                                                                                  n * kRankP);
@@ -2303,7 +2310,7 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
 #define KNN_RANK(L, A, NP)                                                                                        \
     rank_tile_kernel<L, A, NP><<<nb * (unsigned)S, 256, 0, st>>>(                                                  \
         Zs + q0 * lds, zn + q0, nq, Zs, zn, n, lds, Zf + q0 * ldf, Zf, ldf, dz, q0, pz + q0 * kRankP, mx, ecd, ecn, \
-        ed, S, split_len, cz + q0 * kRankP, rq, kp, lims, part, cnt)
+        ed, ea, en, S, split_len, cz + q0 * kRankP, rq, kp, lims, part, cnt)
 #define KNN_RANK_NP(L, A)                                                                                         \
     if (k <= 8) KNN_RANK(L, A, 8);                                                                                \
     else if (k <= 12) KNN_RANK(L, A, 12);                                                                         \

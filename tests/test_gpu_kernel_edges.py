@@ -527,3 +527,27 @@ def test_compacted_buffers_leave_self_out(precision, k, rerank):
     for got in (knn.knn_exact(X, k, **args), knn.knn_exact_query(X, X, k, q_self=own, **args)):
         assert int(got[0].min()) >= 0
         assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+@pytest.mark.parametrize("case", ["1e4", "1e6", "1e7", "1e9", "spread", "small"])
+@pytest.mark.parametrize("d,e", [(64, 2), (20, 33), (300, 40)])
+def test_ranks_of_rows_of_unlike_norms(orc, case, d, e):
+    """The rank pass where the rows' norms differ widely (one row enlarged;
+    norms over twelve decades; every row below the scales' range), in X and in
+    an embedding above 16 dimensions: equal to the oracle's integers."""
+    import paper_2603_04035_amd as knn
+    n, k = 600, 10
+    rng = np.random.default_rng(d)
+    X = rng.normal(size=(n, d)).astype(np.float32)
+    Y = (X @ rng.normal(size=(d, e)) + rng.normal(scale=0.5, size=(n, e))).astype(np.float32)
+    for A in (X, Y):
+        if case == "spread":
+            A *= (10.0 ** rng.uniform(-6, 6, size=(n, 1))).astype(np.float32)
+        elif case == "small":
+            A *= np.float32(1e-17)
+        else:
+            A[77] *= np.float32(float(case))
+    _, (h, t, c) = knn.quality(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k, per_row=True)
+    oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
+    assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
+    assert np.array_equal(c.cpu().numpy(), oc)
