@@ -165,6 +165,14 @@ __device__ inline float split_scale(unsigned mx)
 }
 __device__ inline bool split_range(unsigned mx) { return mx == 0u || (mx >> 23) >= 127u - 100u; }
 
+// The queries' scale goes by the largest norm up to 2^14 times the references':
+// one query far outside would take the others' parts below FP16's range.
+// Beyond that (split_far) elements are cut off at FP16's largest value and the
+// row is searched directly.
+constexpr unsigned kSplitFar = 28u << 23;   // 2^28 in squared norms
+__device__ inline float query_scale(unsigned qmx, unsigned rmx) { return split_scale(min(qmx, rmx + kSplitFar)); }
+__device__ inline bool split_far(float qn, unsigned rmx) { return __float_as_uint(qn) > rmx + kSplitFar; }
+
 // Squared row norms of X (FP64 sums rounded once to FP32) and the largest
 // one's bits: 16 lanes per row.
 template <int DT>
@@ -214,13 +222,15 @@ __global__ __launch_bounds__(256) void norm_kernel(const void* __restrict__ X, i
 // The staged rows: thread = 8 elements of a row (16 bytes of hi and of lo),
 // zeros beyond d.  OUT = KNN_SPLIT, or KNN_F16 (hi only: 16-bit inputs, whose
 // values FP16 holds exactly up to the 2^-25 above).  ldp: elements, a
-// multiple of 32 (KNN_SPLIT) or 64.
+// multiple of 32 (KNN_SPLIT) or 64.  rmax (nullable): X are queries, of
+// references with this largest norm.
 template <int DT, int OUT>
 __global__ __launch_bounds__(256) void split_kernel(const void* __restrict__ X, int64_t n, int d, int64_t ld,
                                                     _Float16* __restrict__ Xs, int ldp,
-                                                    const unsigned* __restrict__ maxnorm)
+                                                    const unsigned* __restrict__ maxnorm,
+                                                    const unsigned* __restrict__ rmax)
 {
-    const float sc = split_scale(*maxnorm);
+    const float sc = rmax ? query_scale(*maxnorm, *rmax) : split_scale(*maxnorm);
     const int per = ldp / 8;
     const int64_t total = n * per;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < total; q += (int64_t)gridDim.x * 256) {
@@ -229,7 +239,8 @@ __global__ __launch_bounds__(256) void split_kernel(const void* __restrict__ X, 
         _Float16 hi[8], lo[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float x = t0 + e < d ? elem<DT>::ld(X, row * ld + t0 + e) * sc : 0.0f;
+            float x = t0 + e < d ? elem<DT>::ld(X, row * ld + t0 + e) * sc : 0.0f;
+            x = fminf(fmaxf(x, -65504.0f), 65504.0f);
             hi[e] = (_Float16)x;
             lo[e] = (_Float16)(x - (float)hi[e]);
         }
@@ -552,7 +563,7 @@ __global__ __launch_bounds__(256, 2) void exact_tile_kernel(
     // Scaled rows (qmax_bits not null) leave the accumulators and the gate in
     // units of both scales, powers of two, so nothing is rounded by them.
     const float rmax = __uint_as_float(*rmax_bits);
-    const float scq = qmax_bits ? split_scale(*qmax_bits) : 1.0f, scr = qmax_bits ? split_scale(*rmax_bits) : 1.0f;
+    const float scq = qmax_bits ? query_scale(*qmax_bits, *rmax_bits) : 1.0f, scr = qmax_bits ? split_scale(*rmax_bits) : 1.0f;
     const float sc = scq * scr, m2 = -2.0f / sc, hsc = 0.5f * sc;
     uint64_t list[16];
     float lim[16];
@@ -674,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void exact_gate_kernel(
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
     const int64_t q0 = (int64_t)blockIdx.x * kTileRows;
     const int p = blockIdx.y, P = gridDim.y;
-    const float hsc = 0.5f * (qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f);
+    const float hsc = 0.5f * (qmax_bits ? query_scale(*qmax_bits, *rmax_bits) * split_scale(*rmax_bits) : 1.0f);
     const int64_t qr = q0 + w * 32 + c;   // this lane's query
     const int64_t self = qr >= nq ? -1 : (self_mode == 1 ? self_base + qr : (self_mode == 2 ? (int64_t)q_self[qr] : -1));
     const E* Qb = (const E*)Qs + q0 * ldp;
@@ -766,7 +777,7 @@ __global__ __launch_bounds__(256) void gate_select_kernel(const float* __restric
         }
     }
     if (c == kp - 1 && row < nq) {
-        const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+        const float sc = qmax_bits ? query_scale(*qmax_bits, *rmax_bits) * split_scale(*rmax_bits) : 1.0f;
         const float nrm = sqrtf(qn[row]) + sqrtf(__uint_as_float(*rmax_bits));
         lims[row] = a - err * nrm * nrm * sc;
     }
@@ -851,7 +862,7 @@ __global__ __launch_bounds__(256, 2) void exact_append_kernel(
     const int s = blockIdx.y;
     const int64_t rbeg = (int64_t)s * split_len;
     const int64_t rend = rbeg + split_len < nr ? rbeg + split_len : nr;
-    const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+    const float sc = qmax_bits ? query_scale(*qmax_bits, *rmax_bits) * split_scale(*rmax_bits) : 1.0f;
     const float rmax = __uint_as_float(*rmax_bits);
     const float m2 = -2.0f / sc, hsc = 0.5f * sc;
     if (tid < kTileRows) {
@@ -1413,7 +1424,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
     int self_mode, int64_t self_base, const unsigned* __restrict__ qmax_bits, int S, int64_t nq, int kp, int k,
     const void* __restrict__ Q, int64_t ldq, const void* __restrict__ R, int64_t ldr, int d,
     const float* __restrict__ qn, const unsigned* __restrict__ rmax_bits, float err_coef,
-    float edir, int certify, int64_t avail, int out_kind, int32_t* __restrict__ out_idx,
+    float edir, float eabs, int certify, int64_t avail, int out_kind, int32_t* __restrict__ out_idx,
     float* __restrict__ out_dist, int32_t* __restrict__ fb_rows, int* __restrict__ fb_count)
 {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1424,7 +1435,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
     // halves then form one ascending 64-key sequence
     uint64_t k0;
     if (cnt) {
-        const float sc = qmax_bits ? split_scale(*qmax_bits) * split_scale(*rmax_bits) : 1.0f;
+        const float sc = qmax_bits ? query_scale(*qmax_bits, *rmax_bits) * split_scale(*rmax_bits) : 1.0f;
         const float m2 = -2.0f / sc, sq = qn[row];
         const int64_t self = self_mode == 1 ? self_base + row : (self_mode == 2 ? (int64_t)q_self[row] : -1);
         k0 = kEmptyCand;
@@ -1475,9 +1486,12 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(
         const float Dk = key_d2(bcast_u64(nk, k - 1));
         const float qa = sqrtf(qn[row]);
         const float ra = sqrtf(__uint_as_float(*rmax_bits));
-        const float E = err_coef * (qa + ra) * (qa + ra);
+        // the absolute error of the queries' parts (2^-25 of a scaled unit,
+        // taken twice), which (|q| + max|r|)^2 holds only where their norms are
+        // not far above the references'
+        const float E = err_coef * (qa + ra) * (qa + ra) + eabs * ra / query_scale(*qmax_bits, *rmax_bits);
         // fewer than kp keys: certain when there are no more candidates
-        const bool cert = nvalid < kp ? (int64_t)nvalid >= avail : (Dk * (1.0f + edir) <= T - E && split_range(*rmax_bits));
+        const bool cert = nvalid < kp ? (int64_t)nvalid >= avail : (Dk * (1.0f + edir) <= T - E && split_range(*rmax_bits) && !split_far(qn[row], *rmax_bits));
         if (!cert && lane == 0) {
             int p = atomicAdd(fb_count, 1);
             fb_rows[p] = (int32_t)row;
@@ -1646,18 +1660,18 @@ knn_status stage_matrix(ScratchAlloc& ws, const knn_matrix& X, int kind, void** 
 }
 
 // Norms, largest norm (*maxn, zeroed beforehand) and staged rows of a matrix
-// for the FP32 Gram.  kind: KNN_SPLIT or KNN_F16.
+// for the FP32 Gram.  kind: KNN_SPLIT or KNN_F16.  rmax: see split_kernel.
 static void launch_full(int kind, const knn_matrix& X, void* Xs, int ldp, float* norms, unsigned* maxn,
-                        hipStream_t st)
+                        const unsigned* rmax, hipStream_t st)
 {
     const unsigned ng = (unsigned)std::min<int64_t>(ceil_div(X.n, 32), 4096);
     const unsigned sg = (unsigned)std::min<int64_t>(ceil_div(X.n * (ldp / 8), 256), 16384);
 #define KNN_FULL(DT)                                                                                             \
     norm_kernel<DT><<<ng, 256, 0, st>>>(X.data, X.n, X.d, X.ld, norms, maxn);                                    \
     if (kind == KNN_SPLIT)                                                                                       \
-        split_kernel<DT, KNN_SPLIT><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn);       \
+        split_kernel<DT, KNN_SPLIT><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn, rmax); \
     else                                                                                                         \
-        split_kernel<DT, KNN_F16><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn)
+        split_kernel<DT, KNN_F16><<<sg, 256, 0, st>>>(X.data, X.n, X.d, X.ld, (_Float16*)Xs, ldp, maxn, rmax)
     if (X.dtype == KNN_F32) {
         KNN_FULL(KNN_F32);
     } else if (X.dtype == KNN_BF16) {
@@ -1675,7 +1689,7 @@ static knn_status stage_full(ScratchAlloc& ws, const knn_matrix& X, int kind, vo
     knn_status r = ws.alloc(Xs, (size_t)X.n * (size_t)(*ldp) * (kind == KNN_SPLIT ? 4 : 2));
     if (r != KNN_OK) return r;
     if ((r = ws.alloc(norms, (size_t)X.n)) != KNN_OK) return r;
-    launch_full(kind, X, *Xs, *ldp, *norms, maxn, st);
+    launch_full(kind, X, *Xs, *ldp, *norms, maxn, nullptr, st);
     KNN_HIP(hipGetLastError());
     return KNN_OK;
 }
@@ -1841,7 +1855,7 @@ static knn_status exact_direct_impl(const knn_matrix& Q, const knn_matrix& R, co
 #define KNN_MR(DT)                                                                                       \
     merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, nullptr, nullptr, 0, 0, nullptr, S, nq, k, k, Qd, Q.ld, \
                                                    R.data, R.ld, R.d, nullptr,                                  \
-                                                   nullptr, 0.0f, 0.0f, 0, 0, out_kind, oi, od, nullptr, nullptr)
+                                                   nullptr, 0.0f, 0.0f, 0.0f, 0, 0, out_kind, oi, od, nullptr, nullptr)
         if (Q.dtype == KNN_F32) KNN_MR(KNN_F32);
         else if (Q.dtype == KNN_BF16) KNN_MR(KNN_BF16);
         else KNN_MR(KNN_F16);
@@ -2034,7 +2048,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     // re-rank bound: (d/16 + 8) u relative.
     const float u = 5.9604645e-08f;
     const float err_coef = split_err(R.d, kind) * u * 1.01f;
-    const float edir = (float)(R.d / 16 + 8) * u;
+    const float edir = (float)(R.d / 16 + 8) * u, eabs = 2.0f * u * sqrtf((float)R.d);
     const int certify = bf ? 0 : 1;
     int* fb_count = (int*)(words + 1);
     const size_t qeb = elem_bytes(Q.dtype);
@@ -2049,7 +2063,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
             qn = rn + q0;
         } else {
             const knn_matrix Qc = {(const char*)Q.data + (size_t)q0 * Q.ld * qeb, nq, Q.d, Q.ld, Q.dtype};
-            if (full) launch_full(kind, Qc, Qb, ldp, qnb, words + 3, st);
+            if (full) launch_full(kind, Qc, Qb, ldp, qnb, words + 3, words, st);
             else launch_stage_kind(kind, Qc, Qb, ldp, qnb, nullptr, nullptr, 0, st);
             Qs = Qb;
             qn = qnb;
@@ -2070,7 +2084,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         dim3 mgrid((unsigned)ceil_div(nq, 4));
 #define KNN_MR(DT)                                                                              \
     merge_rerank_kernel<DT><<<mgrid, 256, 0, st>>>(part, cnt, qself, self_mode, q0, qmax, S, nq, kp, k, Qd, Q.ld, R.data, R.ld,  \
-                                                   R.d, qn, words, err_coef, edir, certify,     \
+                                                   R.d, qn, words, err_coef, edir, eabs, certify, \
                                                    avail, out_kind, oi, od, fb_rows, fb_count)
         if (Q.dtype == KNN_F32) KNN_MR(KNN_F32);
         else if (Q.dtype == KNN_BF16) KNN_MR(KNN_BF16);
@@ -2270,7 +2284,7 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
         _Float16* Zs = nullptr;
         if ((r = ws.alloc((void**)&Zs, (size_t)n * lds * 2)) != KNN_OK) return r;
         split_kernel<KNN_F32, KNN_SPLIT><<<(unsigned)std::min<int64_t>(ceil_div(n * (lds / 16), 256), 16384), 256, 0, st>>>(
-            Zf, n, dz, ldf, Zs, lds / 2, mx);
+            Zf, n, dz, ldf, Zs, lds / 2, mx, nullptr);
         // Error of a GEMM distance: 2 |q||r| (9 + 3 i + s + 12 + 4) u with i
         // instructions per segment and s segments (see split_err: products and
         // running sums of a segment; the segments' additions; the parts' rounding;
@@ -2335,7 +2349,7 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
             const void* Xq = (const char*)X.data + (size_t)q0 * X.ld * elem_bytes(X.dtype);
 #define KNN_QMR(DT)                                                                                              \
     merge_rerank_kernel<DT><<<(unsigned)ceil_div(nq, 4), 256, 0, st>>>(                                             \
-        part, cnt, nullptr, 1, q0, mx, S, nq, kp, k, Xq, X.ld, X.data, X.ld, X.d, zn + q0, mx, err_coef, ed, 1, n - 1, \
+        part, cnt, nullptr, 1, q0, mx, S, nq, kp, k, Xq, X.ld, X.data, X.ld, X.d, zn + q0, mx, err_coef, ed, 2.0f * ea, 1, n - 1, \
         KNN_OUT_SQL2, Hn + q0 * k, Hd + q0 * k, fb_rows, (int*)fb_count);                                            \
     exact_fallback_kernel<DT><<<1024, 256, 0, st>>>(fb_rows, (int*)fb_count, Xq, X.ld, X.data, X.ld, n, X.d, nullptr, \
                                                     1, q0, k, KNN_OUT_SQL2, Hn + q0 * k, Hd + q0 * k, part, nq * S,  \

@@ -551,3 +551,24 @@ def test_ranks_of_rows_of_unlike_norms(orc, case, d, e):
     oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
     assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
     assert np.array_equal(c.cpu().numpy(), oc)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [40, 200])
+@pytest.mark.parametrize("far", [1e3, 1e5, 1e7, 1e10])
+def test_one_query_far_outside(orc, dt, d, far):
+    """One query of a norm far above the others' and the references': the
+    others' neighbours are found as without it (FP32 precision)."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(d)
+    R = torch.from_numpy(rng.normal(size=(5000, d)).astype(np.float32)).to(dt)
+    Q = torch.from_numpy(rng.normal(size=(300, d)).astype(np.float32))
+    Q[123] *= far
+    Q = Q.to(dt)
+    k = 10
+    idx, dist = knn.knn_exact_query(Q.cuda(), R.cuda(), k)[:2]
+    Qf, Rf = (np.ascontiguousarray(a.float().numpy()) for a in (Q, R))
+    O, O2 = orc.exact_query(Rf, Qf, k)
+    G = idx.cpu().numpy()
+    D = np.sqrt(((Qf.astype(np.float64)[:, None, :] - Rf.astype(np.float64)[G]) ** 2).sum(2))
+    assert np.allclose(D, np.sqrt(O2), rtol=2e-6) and np.allclose(dist.cpu().numpy(), D, rtol=2e-6)
