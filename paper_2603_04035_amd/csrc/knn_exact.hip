@@ -922,6 +922,34 @@ constexpr int kRankP = 16;   // probes per query row (the quality metrics' k <= 
 constexpr int kRankFlush = 1024;   // queued pairs that are worth a recheck pass
 constexpr int kRankQueue = kTileRows * kTileRows + kRankFlush;
 
+// Squared norms from 2^124 on: sums and distances may overflow FP32, and bound
+// nothing.
+__device__ inline bool rank_wide(unsigned mx) { return mx >= (127u + 124u) << 23; }
+
+// The counts of rank_tile_kernel below where rank_wide, every pair decided by
+// its canonical distance; nothing is done otherwise.  A workgroup takes a query,
+// a 16-lane group a reference.  (In the tile pass itself this branch cost
+// 3.6% of a 70,000 x 784 call.)
+__global__ __launch_bounds__(256) void rank_wide_kernel(const float* __restrict__ Zf, int64_t ldf, int d, int64_t q0,
+                                                        int64_t nq, int64_t n, const uint64_t* __restrict__ probes,
+                                                        const unsigned* __restrict__ rmax_bits,
+                                                        uint32_t* __restrict__ counts)
+{
+    if (!rank_wide(*rmax_bits)) return;
+    const int g = threadIdx.x & 15;
+    for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
+        const uint64_t key = probes[q * kRankP + g];
+        uint32_t num = 0;
+        for (int64_t r0 = 0; r0 < n; r0 += 16) {
+            const int64_t r = r0 + (threadIdx.x >> 4);
+            const bool act = r < n && r != q0 + q;
+            const float d2 = dist_g16<KNN_F32>(Zf, (q0 + q) * ldf, Zf, (act ? r : 0) * ldf, d, act);
+            num += act && key != kEmptyCand && make_key(d2, (uint32_t)r) < key ? 1u : 0u;
+        }
+        if (num) atomicAdd(&counts[q * kRankP + g], num);
+    }
+}
+
 // For every query row q and each of its probes (keys (canonical d2, index),
 // ascending; kEmptyCand pads), counts[q][p] = the number of reference rows
 // m != self(q) whose key (canonical FP32 d2(q, m), m) is below the probe's
@@ -969,6 +997,11 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
     const int sp = blockIdx.x % S;
     const int64_t rbeg = (int64_t)sp * split_len;
     const int64_t rend = rbeg + split_len < nr ? rbeg + split_len : nr;
+    if (rank_wide(*rmax_bits)) {
+        // rank_wide_kernel's: empty lists, whose rows are searched exhaustively
+        if (LISTS && tid < kTileRows && q0 + tid < nq) cnt[(q0 + tid) * S + sp] = 0u;
+        return;
+    }
     const float scale = split_scale(*rmax_bits), sc = scale * scale, hsc = 0.5f * sc, m2 = -2.0f / sc;
     for (int e = tid; e < kTileRows * NP; e += 256) {
         const int64_t qr = q0 + e / NP;
@@ -977,7 +1010,9 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
     }
     if (tid < kTileRows) {
         scnt[tid] = 0u;
-        slim[tid] = LISTS && q0 + tid < nq ? lims[q0 + tid] : __builtin_inff();
+        // a gate of -inf (fewer groups than kp) would let the columns past the
+        // references pass, whose scores are -inf
+        slim[tid] = LISTS && q0 + tid < nq ? fmaxf(lims[q0 + tid], -3.402823466e38f) : __builtin_inff();
     }
     if (tid == 0) qcount = 0u;
     const E* Qb = (const E*)Qs + q0 * lds;
@@ -1005,6 +1040,11 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
         nv += on ? 1 : 0;
         num[p] = 0u;
     }
+    // the slack, in score units, with a tile's largest norm |r|^2: hsc (e2 + 2 edir
+    // (mx + e2)) + eabs scale (|q| + |r|) + eden with e2 = ec_dot |q||r| + ec_norm
+    // (|q|^2 + |r|^2 + mx), as slr |r| + slt |r|^2 + sl0
+    const float hx = hsc * (1.0f + 2.0f * edir), slr = hx * ec_dot * qa + eabs * scale, slt = hx * ec_norm;
+    const float sl0 = hx * ec_norm * (sq + mx) + 2.0f * hsc * edir * mx + eabs * scale * qa + eden;
     uint64_t* buf = LISTS ? part + (q0 * S + sp) * kCandCap : nullptr;
     const uint32_t rstride = (uint32_t)S * kCandCap;
     for (int64_t rt = rbeg; rt < rend; rt += kTileRows) {
@@ -1018,8 +1058,7 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) tn = fmaxf(tn, xor_f32(tn, o));
         }
-        const float e2 = ec_dot * qa * sqrtf(tn) + ec_norm * (sq + tn + mx);
-        const float sl = hsc * (e2 + 2.0f * edir * (mx + e2)) + eabs * scale * (qa + sqrtf(tn)) + eden;
+        const float sl = fmaf(slr, sqrtf(tn), fmaf(slt, tn, sl0));
         const bool diag = ballot(self >= rt && self < rt + kTileRows) != 0ull;
         const int sr = self >= rt && self < rt + kTileRows ? (int)(self - rt) : -1;
         bool full = false;
@@ -1064,7 +1103,7 @@ __global__ __launch_bounds__(256, 2) void rank_tile_kernel(
                     const uint32_t slot = atomicAdd(&qcount, 1u);
                     queue[slot] = ((uint64_t)j << 32) | (uint32_t)(lq << 10 | (nv - a) << 5 | (nv - b));
                 }
-                if (LISTS && x >= lim && j < (uint32_t)rend) {   // as exact_append_kernel
+                if (LISTS && x >= lim) {
                     const uint32_t pos = atomicAdd(&scnt[lq], 1u);
                     buf[(uint32_t)lq * rstride + pos] = ((uint64_t)__float_as_uint(x) << 32) | j;
                     full = full || pos >= kCandCap - kTileRows;
@@ -2340,6 +2379,8 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
             }
 #undef KNN_RANK_NP
 #undef KNN_RANK
+            rank_wide_kernel<<<(unsigned)std::min<int64_t>(nq, 4096), 256, 0, st>>>(Zf, ldf, dz, q0, nq, n, pz + q0 * kRankP,
+                                                                                  mx, cz + q0 * kRankP);
             KNN_HIP(hipGetLastError());
             if (!lists) continue;
             // X's exact lists: merge, canonical re-rank, certificate, and the

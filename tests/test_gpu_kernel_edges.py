@@ -572,3 +572,30 @@ def test_one_query_far_outside(orc, dt, d, far):
     G = idx.cpu().numpy()
     D = np.sqrt(((Qf.astype(np.float64)[:, None, :] - Rf.astype(np.float64)[G]) ** 2).sum(2))
     assert np.allclose(D, np.sqrt(O2), rtol=2e-6) and np.allclose(dist.cpu().numpy(), D, rtol=2e-6)
+
+
+@pytest.mark.parametrize("case", ["offset", "spread", "few"])
+@pytest.mark.parametrize("d,e", [(64, 2), (20, 33)])
+def test_ranks_of_rows_whose_norms_overflow(orc, case, d, e):
+    """Finite rows with squared norms past FP32's range: far from the origin
+    with ordinary distances, distances that overflow too, and a few such rows
+    among ordinary ones (more than one and fewer than a tile past the last
+    whole one).  Equal to the oracle's integers."""
+    import paper_2603_04035_amd as knn
+    n, k = 300, 10
+    rng = np.random.default_rng(d)
+    X = rng.normal(size=(n, d)).astype(np.float32)
+    Y = (X @ rng.normal(size=(d, e)) + rng.normal(scale=0.5, size=(n, e))).astype(np.float32)
+    for A in (X, Y):
+        if case == "offset":
+            A *= np.float32(1e16)
+            A += np.float32(1e19)
+        elif case == "spread":
+            A *= np.float32(1.5e19)
+        else:
+            A[::50] *= np.float32(1e20)
+    _, (h, t, c) = knn.quality(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k, per_row=True)
+    with np.errstate(over="ignore"):
+        oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
+    assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
+    assert np.array_equal(c.cpu().numpy(), oc)
