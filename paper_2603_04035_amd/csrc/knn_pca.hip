@@ -468,8 +468,11 @@ __global__ __launch_bounds__(256) void pca_cholqr_kernel(const double* __restric
 // and two barriers.  A round is latency (the angles' square roots and
 // divisions, the barriers): with rows and columns in separate passes by 256
 // threads the eigenproblem of an 80-wide block took 2.09 ms, 1.04 now.  Sweeps
-// stop when the off-diagonal mass (sum of squares) falls below 1e-26 of the
-// total (off-diagonal entries below 1e-13 of the norm), or after 40.
+// stop when the sum of H[i][j]^2 / (H[i][i] H[j][j]) off the diagonal falls
+// below 1e-26 (entries below 1e-13 of the eigenvalues they would mix: against
+// the whole norm, a leading eigenvalue 10^6 times the rest left the rest's
+// vectors off by 10^-7), when the off-diagonal mass is below 1e-33 of the total
+// (rounding), or after 40.
 constexpr int kJacThreads = 1024;
 
 __global__ __launch_bounds__(kJacThreads) void pca_jacobi_kernel(double* __restrict__ Hg, double* __restrict__ Eg, int m)
@@ -478,7 +481,7 @@ __global__ __launch_bounds__(kJacThreads) void pca_jacobi_kernel(double* __restr
     __shared__ double E[kPcaMaxM * kPcaMaxM];   // E^T: row j is column j of E
     __shared__ double cs[kPcaMaxM / 2], sn[kPcaMaxM / 2];
     __shared__ int pp[kPcaMaxM / 2], qq[kPcaMaxM / 2];
-    __shared__ double red[2][kJacThreads / 64];
+    __shared__ double red[3][kJacThreads / 64];
     const int tid = threadIdx.x;
     // V^T (C V) is symmetric up to rounding: take its symmetric part
     for (int e = tid; e < m * m; e += kJacThreads) {
@@ -500,27 +503,34 @@ __global__ __launch_bounds__(kJacThreads) void pca_jacobi_kernel(double* __restr
     }
     for (int sweep = 0; sweep < 40; ++sweep) {
         __syncthreads();
-        double off = 0.0, tot = 0.0;
+        double off = 0.0, tot = 0.0, rel = 0.0;
         for (int e = tid; e < m * m; e += kJacThreads) {
-            const double h = H[e];
-            tot += h * h;
-            if (e / m != e % m) off += h * h;
+            const double h = H[e], h2 = h * h;
+            const int i = e / m, j = e - i * m;
+            tot += h2;
+            if (i != j && h2 > 0.0) {
+                off += h2;
+                rel += h2 / fabs(H[i * m + i] * H[j * m + j]);
+            }
         }
         for (int o = 32; o > 0; o >>= 1) {
             off += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(off), o));
             tot += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(tot), o));
+            rel += __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(rel), o));
         }
         if ((tid & 63) == 0) {
             red[0][tid >> 6] = off;
             red[1][tid >> 6] = tot;
+            red[2][tid >> 6] = rel;
         }
         __syncthreads();
-        off = tot = 0.0;
+        off = tot = rel = 0.0;
         for (int w = 0; w < kJacThreads / 64; ++w) {
             off += red[0][w];
             tot += red[1][w];
+            rel += red[2][w];
         }
-        if (!(off > 1e-26 * tot)) break;
+        if (!(off > 1e-33 * tot) || rel <= 1e-26) break;
         for (int round = 0; round < mm - 1; ++round) {
             // pairs of this round: player 0 fixed, the others rotate
             if (tid < np) {

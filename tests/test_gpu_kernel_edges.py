@@ -599,3 +599,25 @@ def test_ranks_of_rows_whose_norms_overflow(orc, case, d, e):
         oh, ot, oc = orc.quality_rows(X, Y, k, canonical=True)
     assert np.array_equal(h.cpu().numpy(), oh) and np.array_equal(t.cpu().numpy(), ot)
     assert np.array_equal(c.cpu().numpy(), oc)
+
+
+@pytest.mark.parametrize("lead", [2.0, 64.0, 4096.0])
+def test_pca_vectors_beside_a_leading_eigenvalue(lead):
+    """The eigensolver alone (the block is all of R^16) on Hadamard columns, whose
+    sums are exact: two of variance near 1 with a covariance of 2^-22 and one
+    `lead` times as long.  The covariance is nothing against the whole norm, but
+    turns the two vectors by 1.5e-5.  Bound: 100 roundings."""
+    import paper_2603_04035_amd as knn
+    n, d, p = 64, 16, 4
+    H = np.ones((1, 1))
+    while len(H) < n:
+        H = np.block([[H, H], [H, -H]])
+    X = H[:, 1:d + 1] * np.concatenate([[lead, 1.0078125, 1.0], 2.0 ** -np.arange(1, d - 2)])
+    X[:, 2] += 2.0 ** -22 * H[:, 2]
+    assert np.array_equal(X, X.astype(np.float32))
+    B = X[:, 1:3].T @ X[:, 1:3]
+    ref = np.linalg.eigh(B)[1][:, ::-1]
+    ref = ref * np.sign(ref[np.abs(ref).argmax(0), np.arange(2)])
+    V = knn.pca(torch.from_numpy(X.astype(np.float32)).cuda(), p)[1].cpu().numpy()
+    print(lead, np.abs(V[1:3, 1:3] - ref).max(), ref[0, 1])
+    assert np.abs(V[1:3, 1:3] - ref).max() <= 1e-14
