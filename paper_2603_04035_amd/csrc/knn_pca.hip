@@ -828,25 +828,31 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             //     against the latter; at most 8, and 1 after a pass whose
             //     smallest pivot (of unit-length columns) shows them dependent
             //     to 1e-4.
-            //  K products in all: 0.35 T, at least min(T, 24).  For every ratio
-            //     r = lambda_p / lambda_{m+1} that is at least the convergence
-            //     of T power iterations, r^T, or full precision.
-            //  Stop: when the p-th quotient's component has grown e^42 more
+            //  Stop: when the p-th quotient's component has grown e^38 more
             //     than the m-th's over the rounds so far (both re-evaluated
             //     from the current quotients): the error against the wanted
-            //     span is then below rounding.
+            //     span is then below rounding.  Or, from K = 0.35 T products on
+            //     (at least min(T, 24)), when it has grown at least as much more
+            //     than lambda_{m+1}'s as T power iterations would give, (lambda_p /
+            //     lambda_{m+1})^T.  lambda_{m+1} is not known, but lies between the mean
+            //     of the eigenvalues outside the block (from the trace) and
+            //     the m-th quotient: five values are tried, and the next round's
+            //     b is the one with most left to gain.  Above b the logarithm of T_q
+            //     rises by q / sqrt(lambda (lambda - b)), that of lambda^q by q / lambda,
+            //     so such rounds gain on the power iterations at that value
+            //     and above.  T + K products at most.
             // On a 70,000 x 784 set (eigenvalues as i^-1.2, p = 50) 200 power
             // iterations with a pass after each took 21 of the call's 26 ms;
             // 31 products in 12 rounds take 1.5 of 5.2 ms.
             const int K = std::max(std::min(T, 24), (int)std::ceil(0.35 * T));
-            std::vector<double> hv((size_t)3 * m), rho((size_t)m);
+            std::vector<double> hv((size_t)3 * m), rho((size_t)m), diag;
             std::vector<std::pair<int, double>> rounds;   // (q, b), b = 0: plain
             double b = 0.0;
             int q = 1;
             cholqr(W, V, shift);
-            for (int done = 0; done < K;) {
+            for (int done = 0;;) {
                 const bool plain = rounds.size() < 2 || !(b > 0.0);
-                const int qq = plain ? 1 : std::min(q, K - done);
+                const int qq = plain ? 1 : std::min(q, T + K - done);
                 const double c = plain ? 0.0 : 0.5 * b;
                 // Y_1 = (C V - c V) / c, Y_{k+1} = 2 (C Y_k - c Y_k) / c - Y_{k-1}
                 cv(V, plain ? 1.0 : 1.0 / c, c, nullptr, W);
@@ -861,26 +867,56 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
                 cholqr(cur, V, shift);
                 done += qq;
                 rounds.push_back({qq, plain ? 0.0 : b});
-                if (done >= K) break;
+                if (done >= T + K || (T == 1 && done == 1)) break;
                 KNN_HIP(hipMemcpyAsync(hv.data(), piv, (size_t)3 * m * 8, hipMemcpyDeviceToHost, st));
                 KNN_HIP(hipStreamSynchronize(st));
-                double lo = hv[0];
+                double lo = hv[0], sum = 0.0;
                 for (int k = 0; k < m; ++k) {
                     lo = std::min(lo, hv[k]);
                     const double vv = hv[2 * m + k], r1 = vv > 0.0 ? hv[m + k] / vv : 0.0;
                     rho[k] = plain ? r1 : c * r1 + c;
+                    sum += rho[k];
                 }
                 std::sort(rho.begin(), rho.end(), [](double x, double y) { return x > y; });
                 const double top = rho[0], wanted = rho[p - 1];
                 b = rho[m - 1];
-                auto growth = [&](double l) {
+                // how much more a component at `wanted` has grown than one at l, as a
+                // logarithm (T_q(x) = cosh(q acosh x), at most 1 for x <= 1)
+                auto grown = [](double l, int q, double b) {
+                    if (!(b > 0.0)) return q * std::log(l);
+                    const double y = q * std::acosh(std::max(2.0 * l / b - 1.0, 1.0));
+                    return y + std::log1p(std::exp(-2.0 * y)) - std::log(2.0);
+                };
+                auto gain = [&](double l) {
                     double g = 0.0;
                     for (const auto& rd : rounds)
-                        g += rd.second > 0.0 ? rd.first * std::acosh(std::max(2.0 * l / rd.second - 1.0, 1.0))
-                                             : rd.first * std::log(l);
+                        g += grown(wanted, rd.first, rd.second) - grown(l, rd.first, rd.second);
                     return g;
                 };
-                if (b > 0.0 && growth(wanted) - growth(b) >= 42.0) break;
+                if (b > 0.0 && gain(b) >= 38.0) break;
+                if (done >= K) {
+                    if (!(b > 0.0) || !(wanted > 0.0)) break;   // rank below m
+                    if (diag.empty()) {
+                        diag.resize((size_t)d);
+                        KNN_HIP(hipMemcpy2DAsync(diag.data(), 8, C, ((size_t)d + 1) * 8, 8, (size_t)d,
+                                                 hipMemcpyDeviceToHost, st));
+                        KNN_HIP(hipStreamSynchronize(st));
+                    }
+                    double trace = 0.0;
+                    for (double v : diag) trace += v;
+                    const double rest = std::min(std::max((trace - sum) / (d - m), 1e-16 * top), b);
+                    double most = 1e-9, at = 0.0;
+                    for (int i = 0; i < 5; ++i) {
+                        const double l = b * std::pow(rest / b, 0.25 * i);
+                        const double left = std::min(38.0, T * std::log(wanted / l)) - gain(l);
+                        if (left > most) {
+                            most = left;
+                            at = l;
+                        }
+                    }
+                    if (!(at > 0.0)) break;
+                    b = at;
+                }
                 const double x = b > 0.0 ? 2.0 * top / b - 1.0 : 1e300;
                 q = x > 1.0 + 1e-9 ? (int)(std::log(1e10) / std::acosh(x)) : kPcaMaxQ;
                 q = lo < 1e-8 ? 1 : std::max(1, std::min(q, kPcaMaxQ));

@@ -621,3 +621,33 @@ def test_pca_vectors_beside_a_leading_eigenvalue(lead):
     V = knn.pca(torch.from_numpy(X.astype(np.float32)).cuda(), p)[1].cpu().numpy()
     print(lead, np.abs(V[1:3, 1:3] - ref).max(), ref[0, 1])
     assert np.abs(V[1:3, 1:3] - ref).max() <= 1e-14
+
+
+@pytest.mark.parametrize("a,lead,iters", [(0.1, 1e5, 0), (0.2, 1e5, 0), (0.3, 1e5, 0), (0.1, 1.0, 0), (0.2, 1e5, 40),
+                                          (0.1, 1.0, 10), ("drop", 1.0, 6), ("drop", 1e5, 0)])
+def test_pca_at_least_the_power_iterations(a, lead, iters):
+    """Spectra on which the filter is slow: a flat tail, alone and under one
+    eigenvalue 10^5 times as large (one product per round), and a drop right
+    behind the block, below which the filter is flat.  Bound: twice the error
+    of `iters` (0: 200) plain iterations of the same width, or 1e-9
+    (rounding against the leading eigenvalue)."""
+    import paper_2603_04035_amd as knn
+    d, p, m = 300, 50, 80
+    lam = np.concatenate([np.linspace(1.1, 1.0, 80), np.linspace(0.1, 0.05, d - 80)]) if a == "drop" else \
+        np.arange(1, d + 1) ** -a
+    lam[0] *= lead
+    X = _spectrum(3000, d, lam, 3)
+    Xc = X.astype(np.float64)
+    Xc -= Xc.mean(0)
+    C = Xc.T @ Xc / (len(X) - 1)
+
+    def signed(U):
+        return U * np.sign(U[np.abs(U).argmax(0), np.arange(U.shape[1])])
+    ref = signed(np.linalg.eigh(C)[1][:, ::-1][:, :p])
+    V = np.random.default_rng(0).normal(size=(d, m))
+    for _ in range(iters or 200):
+        V = np.linalg.qr(C @ V)[0]
+    plain = signed(V @ np.linalg.eigh(V.T @ C @ V)[1][:, ::-1][:, :p])
+    got = knn.pca(torch.from_numpy(X).cuda(), p, iters=iters)[1].cpu().numpy()
+    print(np.abs(got - ref).max(), np.abs(plain - ref).max())
+    assert np.abs(got - ref).max() <= max(2 * np.abs(plain - ref).max(), 1e-9)
