@@ -102,8 +102,8 @@ knn_status Workspace::alloc(void** p, size_t bytes)
     if (dev_ < 0) return fail(KNN_EDEVICE, "no current device");
     if (bytes == 0) bytes = 256;
     bytes = (size_t)round_up((int64_t)bytes, 256);
-    if (limit_ > 0 && (int64_t)(used_ + bytes - waived_) > limit_)
-        return fail(KNN_ENOMEM, "workspace limit exceeded: need " + std::to_string(used_ + bytes - waived_) +
+    if (limit_ > 0 && (int64_t)(used_ + bytes) > limit_)
+        return fail(KNN_ENOMEM, "workspace limit exceeded: need " + std::to_string(used_ + bytes) +
                                     " bytes, limit " + std::to_string(limit_));
     Arena& a = g_arena[dev_];
     if (nptr_ == 0 && off_ + bytes <= a.cap) {

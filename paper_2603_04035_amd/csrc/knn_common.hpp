@@ -379,18 +379,10 @@ public:
     using ScratchAlloc::alloc;
     knn_status alloc(void** p, size_t bytes) override;
     size_t used() const { return used_; }
-    // The limit counts only `charged` bytes of the next request, of `bytes`
-    // (scratch that grew with a kernel's work split, not with the problem, so
-    // that limits stay what they were).
-    void charge_as(size_t bytes, size_t charged)
-    {
-        waived_ += (size_t)((bytes + 255) / 256 * 256) - (size_t)((charged + 255) / 256 * 256);
-    }
 
 private:
     hipStream_t stream_;
     int64_t limit_;
-    size_t waived_ = 0;    // bytes of used_ that the limit does not count
     int dev_ = -1;
     size_t used_ = 0;      // bytes handed out by this call (arena + overflow)
     size_t off_ = 0;       // arena bytes used
@@ -416,9 +408,9 @@ constexpr int kLowdimD = 3;
 knn_status lowdim_knn(const knn_matrix& Q, const knn_matrix& R, bool same, const int32_t* q_self, int self_mode,
                       int k, int out_kind, int32_t* out_idx, float* out_dist, hipStream_t st, ScratchAlloc& ws);
 
-// Counters that many workgroups add to are kept in kCounterBanks banks of
-// kCounterWords words (one 64-byte line each): workgroup b adds to bank
-// b mod kCounterBanks and the host sums the banks.  A single bank makes every
+// Counters that many workgroups add to are kept in up to kCounterBanks banks (a
+// power of two) of kCounterWords words (one 64-byte line each): workgroup b adds to
+// bank b mod their number and the host sums the banks.  A single bank makes every
 // workgroup queue on one cache line (about 12 ns per atomic): the 4,096
 // waves of a join ended 20,000 atomics, 250 us, after its work.
 constexpr int kCounterBanks = 128, kCounterWords = 8;

@@ -598,8 +598,17 @@ __host__ __device__ inline int64_t rs_tiles(int64_t n)
     return (n + t - 1) / t;
 }
 __host__ __device__ inline size_t rs_counts(int64_t n) { return (size_t)256 * rs_tiles(n) + 256; }
-// The counts of tiles of 4096, which workspace limits go by.
-inline size_t rs_charged(int64_t n) { return (size_t)256 * ceil_div(n, 4096) + 256; }
+// The counts of S sorts after the arrays' projections Y (n words per sort at
+// least) are no longer needed: scratch for tiles of 4096, and Y itself where finer
+// tiles need more (from 1,025 elements on, when n words hold them), so that
+// they do not add to a workspace limit.
+static knn_status rs_alloc_counts(Workspace& ws, int64_t n, int S, float* Y, uint32_t** counts)
+{
+    const size_t coarse = (size_t)256 * ceil_div(n, 4096) + 256;
+    knn_status r = ws.alloc(counts, coarse * S);
+    if (r == KNN_OK && rs_counts(n) > coarse) *counts = (uint32_t*)Y;
+    return r;
+}
 
 // Sorts run on blockIdx.y independent arrays of n elements at once: array
 // y's elements (and outputs) start at y * n, its counts at y * rs_counts(n).
@@ -1174,8 +1183,7 @@ static knn_status proj_seed_impl(const knn_matrix& X, const float* Z, int m, con
     if ((r = ws.alloc(&vals, (size_t)n * P)) != KNN_OK) return r;
     if ((r = ws.alloc(&k1, (size_t)n * P)) != KNN_OK) return r;
     if ((r = ws.alloc(&v1, (size_t)n * P)) != KNN_OK) return r;
-    ws.charge_as(rs_counts(n) * P * 4, rs_charged(n) * P * 4);
-    if ((r = ws.alloc(&counts, rs_counts(n) * P)) != KNN_OK) return r;
+    if ((r = rs_alloc_counts(ws, n, P, Y, &counts)) != KNN_OK) return r;
     const unsigned g = (unsigned)ceil_div(n, 256);
     if (m <= 32) proj_vals_kernel<32><<<g, 256, 0, st>>>(Z, n, m, dirs, P * D, Y);
     else proj_vals_kernel<0><<<g, 256, 0, st>>>(Z, n, m, dirs, P * D, Y);
@@ -1247,9 +1255,10 @@ __global__ __launch_bounds__(64) void dirs_kernel(int m, uint64_t seed, float* _
 // Internal processing order of the points: the Z-order curve of D seeded
 // random projections of X (4-bit codes for D = 8), ties by index.  Points
 // that are close get close positions, so rows and candidate slots touched
-// together share cache lines.  perm[new] = old, inv[old] = new.
+// together share cache lines.  perm[new] = old, inv[old] = new.  spare: n * D
+// words of the call's scratch that are free after the work on st.
 knn_status morton_order(const knn_matrix& X, int D, uint64_t seed, Workspace& ws, uint32_t** perm,
-                        uint32_t** inv, hipStream_t st)
+                        uint32_t** inv, void** spare, hipStream_t st)
 {
     const int64_t n = X.n;
     knn_status r;
@@ -1263,8 +1272,7 @@ knn_status morton_order(const knn_matrix& X, int D, uint64_t seed, Workspace& ws
     if ((r = ws.alloc(&k1, (size_t)n)) != KNN_OK) return r;
     if ((r = ws.alloc(&v1, (size_t)n)) != KNN_OK) return r;
     if ((r = ws.alloc(&lohi, (size_t)2 * D)) != KNN_OK) return r;
-    ws.charge_as(rs_counts(n) * 4, rs_charged(n) * 4);
-    if ((r = ws.alloc(&counts, rs_counts(n))) != KNN_OK) return r;
+    if ((r = rs_alloc_counts(ws, n, 1, Y, &counts)) != KNN_OK) return r;
     dirs_kernel<<<D, 64, 0, st>>>(X.d, seed ^ 0x5DEECE66Dull, dirs);
     const unsigned g = (unsigned)ceil_div(n, 256);
     const bool staged = (size_t)D * X.d * sizeof(float) <= 32768;
@@ -1282,6 +1290,7 @@ knn_status morton_order(const knn_matrix& X, int D, uint64_t seed, Workspace& ws
     if ((r = radix_sort_pairs(keys, *perm, k1, v1, n, counts, st)) != KNN_OK) return r;
     inverse_perm_kernel<<<g, 256, 0, st>>>(*perm, n, *inv);
     KNN_HIP(hipGetLastError());
+    *spare = Y;
     return KNN_OK;
 }
 

@@ -47,7 +47,7 @@ knn_status stage_matrix(ScratchAlloc& ws, const knn_matrix& X, int kind, void** 
                         float** norms, unsigned* maxnorm, hipStream_t st, const uint32_t* rowmap,
                         int aux);
 knn_status morton_order(const knn_matrix& X, int D, uint64_t seed, Workspace& ws, uint32_t** perm,
-                        uint32_t** inv, hipStream_t st);
+                        uint32_t** inv, void** spare, hipStream_t st);
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
     int64_t n, JoinCfg cfg, const uint8_t* __restrict__ Xr, int64_t rowbytes, int np,
     const int32_t* __restrict__ newf, uint32_t* __restrict__ revnew,
     const int32_t* __restrict__ oldf, uint32_t* __restrict__ revold,
-    unsigned long long* __restrict__ cand, uint64_t seed, int iter, unsigned long long* __restrict__ counters,
+    unsigned long long* __restrict__ cand, uint64_t seed, int iter, unsigned long long* __restrict__ counters, unsigned bank_mask,
     unsigned* __restrict__ cursors, int batch, int step, int chunk)
 {
     constexpr bool WIDE = MODE != kJoinNarrow;
@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(MODE == kJoinSolo ? 256 : 64)
         coll += shfl_u64(coll, lane ^ o);
     }
     if (lane == 0) {
-        unsigned long long* bank = counters + (blockIdx.x % kCounterBanks) * kCounterWords;
+        unsigned long long* bank = counters + (blockIdx.x & bank_mask) * kCounterWords;
         if (emitted) atomicAdd(&bank[1], emitted);
         if (tally[0]) atomicAdd(&bank[2], tally[0]);
         if (coll) atomicAdd(&bank[3], coll);
@@ -1055,7 +1055,7 @@ template <bool Smp>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void nnd_merge_kernel(
     int64_t n, int K, int C, int32_t* __restrict__ gidx, float* __restrict__ gd2,
     uint8_t* __restrict__ gflag, unsigned long long* __restrict__ cand,
-    unsigned long long* __restrict__ counters, float* __restrict__ worst, int64_t wstride,
+    unsigned long long* __restrict__ counters, unsigned bank_mask, float* __restrict__ worst, int64_t wstride,
     SampleArgs sa)
 {
     extern __shared__ uint64_t sbuf_all[];
@@ -1195,7 +1195,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void n
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
     }
-    if (lane == 0 && upd) atomicAdd(&counters[(blockIdx.x % kCounterBanks) * kCounterWords], upd);
+    if (lane == 0 && upd) atomicAdd(&counters[(blockIdx.x & bank_mask) * kCounterWords], upd);
 }
 
 // --------------------------------------------------------------- finalize
@@ -1340,7 +1340,8 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     // processing order: Z-order curve of X (see morton_order); every staged
     // copy and every list below is indexed in that order
     uint32_t *perm = nullptr, *inv = nullptr;
-    r = morton_order(X, 8, p->seed, ws, &perm, &inv, st);
+    void* spare = nullptr;   // 8 n words that are free from here on
+    r = morton_order(X, 8, p->seed, ws, &perm, &inv, &spare, st);
     if (r != KNN_OK) return r;
     void* Xs = nullptr;
     float* norms = nullptr;
@@ -1381,11 +1382,17 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         sampold = revold;
     }
     if ((r = ws.alloc(&cand, (size_t)n * cfg.C)) != KNN_OK) return r;
-    // the banks, then the join groups' cursors, a 64-byte line each
-    const size_t cnt_bytes = (size_t)kCounterBanks * kCounterWords * 8;
-    ws.charge_as(cnt_bytes + 512, 64);
-    if ((r = ws.alloc(&counters, (size_t)kCounterBanks * kCounterWords + 64)) != KNN_OK) return r;
-    unsigned* cursors = (unsigned*)(counters + (size_t)kCounterBanks * kCounterWords);
+    // the banks, then the join groups' cursors, a 64-byte line each: in the
+    // order's spare scratch, or one bank of its own where a few rows leave too
+    // little of that (they need no more, and no cursors)
+    if ((r = ws.alloc(&counters, kCounterWords)) != KNN_OK) return r;
+    int banks = 1;
+    if ((size_t)n * 32 >= (size_t)kCounterBanks * kCounterWords * 8 + 512) {
+        banks = kCounterBanks;
+        counters = (unsigned long long*)spare;
+    }
+    const size_t cnt_bytes = (size_t)banks * kCounterWords * 8, cur_bytes = banks > 1 ? 512 : 0;
+    unsigned* cursors = (unsigned*)(counters + (size_t)banks * kCounterWords);
     KNN_HIP(hipMemsetAsync(revnew, 0xFF, (size_t)n * T * 4, st));
     KNN_HIP(hipMemsetAsync(revold, 0xFF, (size_t)n * T * 4, st));
 
@@ -1463,7 +1470,7 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     // 1.94 with fixed shares, of x 784 in FP32 14.3 and 15.0; of 1,000,000 x 50 in
     // BF16 (shares of 244) 19.5 ms by eights and 20.9 with fixed ones.
     const int64_t share = n / ((int64_t)join_grid * (jthreads / 64));
-    const bool shared = share >= (heavy ? 32 : 128);
+    const bool shared = banks > 1 && share >= (heavy ? 32 : 128);
     const int batch = !shared ? 0x7FFFFFFF : (heavy ? 2 : 8);
     // consecutive points a group's XCD takes before the next group's turn: 512, or
     // fewer so that each group has 16 turns
@@ -1484,7 +1491,7 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     Timer tj, tm, ts;
     for (int it = 0; it < p->max_iters; ++it) {
         const int iter = iter_offset + it;
-        KNN_HIP(hipMemsetAsync(counters, 0, cnt_bytes + 512, st));
+        KNN_HIP(hipMemsetAsync(counters, 0, cnt_bytes + cur_bytes, st));
         // iteration `iter` was sampled by the init kernel or the previous merge
         (void)hipEventRecord(ts.a, st);
         if (!cfg.reset)
@@ -1494,7 +1501,7 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         (void)hipEventRecord(tj.a, st);
         join([&](auto kernel) {
             kernel<<<join_grid, jthreads, 0, st>>>(n, cfg, Xr, rowbytes, np, newf, sampnew, oldf, sampold, cand, p->seed,
-                                             iter, counters, cursors, batch, step, chunk);
+                                             iter, counters, (unsigned)banks - 1, cursors, batch, step, chunk);
         });
         KNN_HIP(hipGetLastError());
         (void)hipEventRecord(tj.b, st);
@@ -1506,16 +1513,16 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
         (void)hipEventRecord(tm.a, st);
         if (smp)
             nnd_merge_kernel<true><<<merge_grid, 256, merge_lds, st>>>(n, K, cfg.C, gidx, gd2, gflag, cand,
-                                                                       counters, worst, wstride, sa);
+                                                                       counters, (unsigned)banks - 1, worst, wstride, sa);
         else
             nnd_merge_kernel<false><<<merge_grid, 256, merge_lds, st>>>(n, K, cfg.C, gidx, gd2, gflag, cand,
-                                                                        counters, worst, wstride, sa);
+                                                                        counters, (unsigned)banks - 1, worst, wstride, sa);
         KNN_HIP(hipGetLastError());
         (void)hipEventRecord(tm.b, st);
         KNN_HIP(hipMemcpyAsync(host_cnt, counters, cnt_bytes, hipMemcpyDeviceToHost, st));
         KNN_HIP(hipStreamSynchronize(st));
         unsigned long long cnt[6] = {};   // the banks' sums
-        for (int b = 0; b < kCounterBanks; ++b)
+        for (int b = 0; b < banks; ++b)
             for (int i = 0; i < 6; ++i) cnt[i] += host_cnt[b * kCounterWords + i];
         float ms = 0;
         (void)hipEventElapsedTime(&ms, tj.a, tj.b);

@@ -651,3 +651,29 @@ def test_pca_at_least_the_power_iterations(a, lead, iters):
     got = knn.pca(torch.from_numpy(X).cuda(), p, iters=iters)[1].cpu().numpy()
     print(np.abs(got - ref).max(), np.abs(plain - ref).max())
     assert np.abs(got - ref).max() <= max(2 * np.abs(plain - ref).max(), 1e-9)
+
+
+@pytest.mark.parametrize("n", [12, 271, 272, 1024, 1025, 5000, 131_072, 131_073])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_build_within_its_least_limit(n, precision):
+    """The least workspace limit a build accepts holds all it takes (counters
+    and sort counts lie in scratch that is free by then): the same lists and
+    counts as without a limit, with a bank of counters of their own (fewer than
+    272 rows) and 128 banks, and at the edges of the sort's tiles."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(datagen.gmm_isotropic(n=n, d=12, seed=n)).cuda()
+    args = dict(build_k=8, max_iters=3, delta=0.0, precision=precision, seed=3)
+    lo, hi = 0, 4000 * n + (1 << 20)   # refused, accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        try:
+            knn.nndescent_build(X, 5, workspace_limit_bytes=mid, **args)
+            hi = mid
+        except knn.KnnError as e:
+            assert e.status == -2
+            lo = mid
+    a = knn.nndescent_build(X, 5, workspace_limit_bytes=hi, **args)
+    b = knn.nndescent_build(X, 5, **args)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    for key in ("updates", "pairs_joined", "list_dropped"):   # offers race for slots
+        assert np.array_equal(a[2][key], b[2][key]), key
