@@ -754,12 +754,16 @@ __global__ __launch_bounds__(256, 2) void exact_gate_kernel(
 }
 
 // lims[row] = the kp-th best of the row's P lists of group scores, lowered by
-// err (|q| + max|r|)^2 in scaled units.  Half a wave per row.
+// err (|q| + max|r|)^2 in scaled units.  Half a wave per row.  ecert > 0: rows
+// are certified with the bound ecert (|q| + max|r|)^2; where that is not below
+// the kp-th distance nothing can be, and the gate is +inf: the row goes to the
+// exhaustive search without collecting candidates, all of which would pass (one
+// row 10^6 times the others, 20,000 x 50: 4 of 22.8 ms).
 __global__ __launch_bounds__(256) void gate_select_kernel(const float* __restrict__ gtop, int64_t nq, int P, int kp,
                                                           const float* __restrict__ qn,
                                                           const unsigned* __restrict__ rmax_bits,
                                                           const unsigned* __restrict__ qmax_bits, float err,
-                                                          float* __restrict__ lims)
+                                                          float ecert, float* __restrict__ lims)
 {
     const int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
     const int lane = threadIdx.x & 63, c = lane & 31;
@@ -779,7 +783,8 @@ __global__ __launch_bounds__(256) void gate_select_kernel(const float* __restric
     if (c == kp - 1 && row < nq) {
         const float sc = qmax_bits ? query_scale(*qmax_bits, *rmax_bits) * split_scale(*rmax_bits) : 1.0f;
         const float nrm = sqrtf(qn[row]) + sqrtf(__uint_as_float(*rmax_bits));
-        lims[row] = a - err * nrm * nrm * sc;
+        const bool hopeless = ecert > 0.0f && ecert * nrm * nrm >= qn[row] - 2.0f * a / sc;
+        lims[row] = hopeless ? __builtin_inff() : a - err * nrm * nrm * sc;
     }
 }
 
@@ -1923,7 +1928,7 @@ struct TileArgs {
     uint64_t* part;
     bool gated;
     int ntiles;       // the gate's sample
-    float gate_err;
+    float gate_err, cert_err;   // cert_err 0: no certificate
     float* lims;
     uint32_t* cnt;
 };
@@ -1944,7 +1949,7 @@ static void launch_tiles_a(const TileArgs& a, hipStream_t st)
     exact_gate_kernel<OUT, ARES><<<ggrid, 256, 0, st>>>(a.Qs, a.nq, a.Rs, a.rn, a.nr, a.ld, a.qself, a.self_mode, a.q0,
                                                         a.ntiles, a.rmax, a.qmax, gtop);
     gate_select_kernel<<<(unsigned)ceil_div(a.nq, 8), 256, 0, st>>>(gtop, a.nq, (int)ggrid.y, a.kp, a.qn, a.rmax,
-                                                                    a.qmax, a.gate_err, a.lims);
+                                                                    a.qmax, a.gate_err, a.cert_err, a.lims);
     exact_append_kernel<OUT, ARES><<<grid, 256, 0, st>>>(a.Qs, a.qn, a.nq, a.Rs, a.rn, a.nr, a.ld, a.qself,
                                                          a.self_mode, a.q0, a.kp, a.split_len, a.S, a.rmax, a.qmax,
                                                          a.lims, a.part, a.cnt);
@@ -2111,7 +2116,7 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
         
         const unsigned* qmax = !full ? nullptr : (same ? words : words + 3);
         const TileArgs ta = {Qs, qn, nq, Rs, rn, R.n, lds, qself, self_mode, q0, kp, split_len, S, words, qmax, part,
-                             gated, ntiles, 2.0f * split_err(R.d, kind) * u, lims, cnt};
+                             gated, ntiles, 2.0f * split_err(R.d, kind) * u, certify ? err_coef : 0.0f, lims, cnt};
         if (kind == KNN_BF16) launch_tiles<KNN_BF16>(ares, ta, st);
         else if (kind == KNN_F16) launch_tiles<KNN_F16>(ares, ta, st);
         else launch_tiles<KNN_SPLIT>(ares, ta, st);
@@ -2345,6 +2350,7 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
         zero_words_kernel<<<(unsigned)std::min<int64_t>(ceil_div(n * kRankP, 64), 4096), 64, 0, st>>>(cz,
                                                                                                  n * kRankP);
         const int ntiles = gate_tiles(n, lds);
+        const float err_coef = split_err(dz, KNN_SPLIT) * u * 1.01f;
         for (int64_t q0 = 0; q0 < n; q0 += per_launch * kTileRows) {
             const int64_t nq = std::min<int64_t>(n - q0, per_launch * kTileRows);
             const unsigned nb = (unsigned)ceil_div(nq, kTileRows);
@@ -2358,7 +2364,7 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
                     exact_gate_kernel<KNN_SPLIT, false><<<gg, 256, 0, st>>>(Zs + q0 * lds, nq, Zs, zn, n, lds, nullptr, 1,
                                                                             q0, ntiles, mx, mx, gtop);
                 gate_select_kernel<<<(unsigned)ceil_div(nq, 8), 256, 0, st>>>(
-                    gtop, nq, (int)gg.y, kp, zn + q0, mx, mx, 2.0f * split_err(dz, KNN_SPLIT) * u, lims);
+                    gtop, nq, (int)gg.y, kp, zn + q0, mx, mx, 2.0f * split_err(dz, KNN_SPLIT) * u, err_coef, lims);
             }
 #define KNN_RANK(L, A, NP)                                                                                        \
     rank_tile_kernel<L, A, NP><<<nb * (unsigned)S, 256, 0, st>>>(                                                  \
@@ -2386,7 +2392,6 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
             // X's exact lists: merge, canonical re-rank, certificate, and the
             // exhaustive search for rows not certified
             zero_words_kernel<<<1, 64, 0, st>>>(fb_count, 2);
-            const float err_coef = split_err(X.d, KNN_SPLIT) * u * 1.01f;
             const void* Xq = (const char*)X.data + (size_t)q0 * X.ld * elem_bytes(X.dtype);
 #define KNN_QMR(DT)                                                                                              \
     merge_rerank_kernel<DT><<<(unsigned)ceil_div(nq, 4), 256, 0, st>>>(                                             \
