@@ -1788,7 +1788,8 @@ static int exact_splits(int64_t qn)
 
 // Splits of the gated route, where a split costs no insertions: whole waves
 // of the chip's resident slots (two workgroups on each of 256 CUs) to 90%, at
-// least two tiles per split (2,000 x 300 FP32: 278 us at 2 splits, 149 at 8).
+// least two tiles per split (2,000 x 300 FP32: 278 us at 2 splits, 149 at 8; one
+// query in 2,000 x 784 BF16: 478 us with all 16 tiles in one workgroup, 135 at 8).
 static int filling_splits(int64_t qn, int64_t nr)
 {
     const int64_t nblk = ceil_div(qn, kTileRows), slots = 512;
@@ -1798,7 +1799,7 @@ static int filling_splits(int64_t qn, int64_t nr)
     for (int S = 1; S <= most; ++S) {
         const int64_t b = nblk * S;
         const double f = (double)b / (double)(ceil_div(b, slots) * slots);
-        if (f > fill + 0.02) {
+        if (f > 1.02 * fill) {
             fill = f;
             best = S;
         }
@@ -2080,8 +2081,11 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     // limit; with two to four tiles of long rows its second pass over the
     // products costs more than the insertions (500 x 784 BF16: 187 us against 142;
     // 500 x 200: 105 and 110, 128 x 784: 105 and 140, 100,000 queries in 500 x 200:
-    // 503 and 881)
-    const bool gated = budget == 0 && (ares || lds <= 256 || R.n <= kTileRows || R.n > 4 * kTileRows);
+    // 503 and 881); one to four queries in few references insert little (BF16, one
+    // in 1,000 x 50: 63 us against 53, in 4,000 x 50 80 and 75, in 6,000 x 50 86 and
+    // 87; four in 1,000 x 50 65 and 72, x 784 135 and 123)
+    const bool few = Q.n <= 4 && Q.n * R.n <= 4096;
+    const bool gated = budget == 0 && !few && (ares || lds <= 256 || R.n <= kTileRows || R.n > 4 * kTileRows);
     const int S0 = gated ? filling_splits(qc, R.n) : exact_splits(qc);
     const int64_t split_len = round_up(ceil_div(R.n, S0), kTileRows);
     const int S = (int)ceil_div(R.n, split_len);

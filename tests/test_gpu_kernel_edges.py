@@ -677,3 +677,18 @@ def test_build_within_its_least_limit(n, precision):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     for key in ("updates", "pairs_joined", "list_dropped"):   # offers race for slots
         assert np.array_equal(a[2][key], b[2][key]), key
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp16"])
+@pytest.mark.parametrize("nq", [1, 2, 4, 5, 16])
+@pytest.mark.parametrize("nr,d", [(600, 50), (1024, 200), (2000, 300), (4096, 64), (4097, 64), (9000, 40)])
+def test_few_queries_routes_agree(precision, nq, nr, d):
+    """Few queries on both sides of the rule for lists (at most four, at most
+    4,096 pairs), and the gated route's splits with one block of queries:
+    the bits of the list route."""
+    import paper_2603_04035_amd as knn
+    X = torch.from_numpy(datagen.gmm_isotropic(n=nr, d=d, comps=5, seed=nr)).cuda()
+    Q = torch.from_numpy(datagen.gmm_isotropic(n=nq, d=d, comps=5, seed=nr)).cuda()
+    a = knn.knn_exact_query(Q, X, 12, precision=precision)
+    b = knn.knn_exact_query(Q, X, 12, precision=precision, workspace_limit=4 << 30)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
