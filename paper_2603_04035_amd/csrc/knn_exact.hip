@@ -2002,9 +2002,14 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     const bool bf = !full;
     // a few coordinates: exact_direct_kernel's launches are cheaper sooner (1500 x 2
     // 61 us against 78, 2000 x 2 73 against 75, 3000 x 2 108 against 77; 2000 x 8 72
-    // against 115, 3000 x 8 109 against 119)
+    // against 115, 3000 x 8 109 against 119), and its work per pair is less (queries x
+    // references x coordinates: 4000 x 1000 x 2 67 us against 78, 4000 x 1500 x 2 83
+    // and 79, 16,000 x 600 x 2 122 and 85; 4000 x 2500 x 8 113 and 122, 16,000 x 1000 x
+    // 8 155 and 131, 100,000 x 100 x 8 199 and 164)
     const int64_t small_refs = R.d > kRankDirectD ? kSmallRefs : (R.d > kLowdimD ? 2560 : 1536);
-    const bool small = full && R.n <= small_refs && (double)Q.n * (double)R.n * (6.0 * R.d + 150.0) <= kSmallWork;
+    const double small_pairs = R.d > kRankDirectD ? kSmallWork / (6.0 * R.d + 150.0) : (R.d > kLowdimD ? 1.1e7 : 5e6);
+    const bool small = full && R.n <= small_refs &&
+                       (double)Q.n * (double)(R.n + (R.d > kRankDirectD ? 0 : 64)) <= small_pairs;
     if (full && R.d <= kRankDirectD && !(small && budget == 0)) {
         // the pruned search needs eleven launches (3000 x 3 88 us against 76,
         // 5000 x 3 96 against 115; one query in 4000 x 2 73 against 64, in 20,000 x 2

@@ -692,3 +692,17 @@ def test_few_queries_routes_agree(precision, nq, nr, d):
     a = knn.knn_exact_query(Q, X, 12, precision=precision)
     b = knn.knn_exact_query(Q, X, 12, precision=precision, workspace_limit=4 << 30)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("nq,nr,d", [(32_000, 92, 2), (32_000, 93, 2), (3333, 1436, 3), (3334, 1436, 3), (4000, 2560, 9),
+                                     (4192, 2560, 9), (4193, 2560, 9)])
+def test_many_queries_few_coordinates(nq, nr, d):
+    """Both sides of the one-launch search's bounds on queries x references (up
+    to 3 and up to 16 coordinates): the bits of the direct search."""
+    import paper_2603_04035_amd as knn
+    rng = np.random.default_rng(nq)
+    X = torch.from_numpy(rng.integers(-9, 10, (nr, d)).astype(np.float32) / 4).cuda()
+    Q = torch.from_numpy(rng.integers(-9, 10, (nq, d)).astype(np.float32) / 4).cuda()
+    i, dist = knn.knn_exact_query(Q, X, 10)[:2]
+    ref_i, ref_d = knn.knn_exact_query(Q, X, 10, workspace_limit=1 << 30)[:2]
+    assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
