@@ -85,13 +85,19 @@ const char* knn_last_error(void);
  * section, computed by tiled GEMM with the norm expansion of the paper's
  * k-NN section, then re-ranked by direct differences).
  *
- *  precision  KNN_PREC_FP32: FP32 MFMA distances; KNN_PREC_BF16: BF16 MFMA
- *             distances with FP32 accumulation.  Either way the best
+ *  precision  KNN_PREC_FP32: distances from three FP16 MFMA products of rows
+ *             held as two FP16 parts (22 bits), FP32 accumulation;
+ *             KNN_PREC_BF16 / KNN_PREC_FP16: 16-bit MFMA distances with FP32
+ *             accumulation.  Either way the best
  *             `rerank_k` candidates per row are re-ranked with FP32
  *             direct-difference distances, and FP32 rows whose candidate
  *             set cannot be certified are recomputed exhaustively.  With
  *             KNN_PREC_FP32 and d <= 16 no GEMM is run: every pair's
- *             direct-difference distance is formed (the same lists).
+ *             direct-difference distance is formed (the same lists).  The
+ *             exhaustive search, some ten times as slow, takes all rows whose
+ *             error bound exceeds their neighbour distances: far from the origin,
+ *             beside rows of much larger norm, of queries with norms above 2^14
+ *             times the references', and in sets whose norms stay below 1e-15.
  *  rerank_k   candidates kept per row before the re-rank, k <= rerank_k <=
  *             KNN_MAX_K (0 = min(2k, KNN_MAX_K)).
  *  out_idx    device, n x k int32.   out_dist  device, n x k float.
@@ -372,8 +378,8 @@ knn_status knn_proj_seed(knn_matrix X, const float* Z, int32_t m, const float* d
  *  iters   subspace iterations (0: 200); the eigenvectors come from an
  *          m = min(d, 80, max(2p, p + 16))-column subspace iteration with a
  *          final Rayleigh-Ritz step (exact when m = d), so their error falls
- *          as (lambda_{m+1} / lambda_p)^iters (or faster: the iteration is
- *          filtered by Chebyshev polynomials).
+ *          at least as (lambda_{m+1} / lambda_p)^iters, down to rounding
+ *          (the iteration is filtered by Chebyshev polynomials).
  *  Z       device, n x p float.   components  device, nullable, d x p
  *          double (row-major).   eigenvalues  device, nullable, p double.
  *  mean    device, nullable, d double.
@@ -392,7 +398,7 @@ knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, double* com
  * N(i) / L(i) = the k nearest in X / Y.  Ranks break distance ties by the
  * smaller index and are taken on canonical FP32 direct-difference squared
  * distances (the order knn_exact returns); the X-space distances come from
- * an FP32 MFMA Gram with every comparison inside its error bound re-decided
+ * a Gram of three FP16 MFMA products with every comparison inside its error bound re-decided
  * in the canonical precision.  Above 16 dimensions the same Gram pass also
  * yields X's exact k-NN (knn_exact's merge, re-rank and certificate); the
  * embedding's k-NN and ranks use direct differences when e <= 16.

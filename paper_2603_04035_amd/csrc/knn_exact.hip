@@ -1755,14 +1755,21 @@ static knn_status stage_full(ScratchAlloc& ws, const knn_matrix& X, int kind, vo
 // gfx950 its result was measured within u (9 sum |products| + 2 |c|) of the
 // exact value over products and sums of every relative magnitude (addends are
 // aligned to the largest of their group and truncated, so a group of eight
-// loses up to 7u of its largest; largest error 1.005 of that expression), taken as
-// 9 and 3.  A dot product of n instructions (three per 16 elements of split
+// loses up to 7u of its largest), taken as 9 and 3.  Sampled: 8e8 outputs, products
+// of normal, positive and cancelling factors over up to 2^28 in magnitude, sums from
+// 2^-20 to 2^20 and the negated sum of the products, one dominant product with
+// the rest around its truncation grid; the largest error was 1.005 of that
+// expression, where c = 0.  So the 16 below, which counts the 9, leaves room:
+// 13 in its place would still do.  A dot product of n instructions (three per 16 elements of split
 // rows) whose sums stay below |q||r| is off by u (9 + 3 n) |q||r|, its parts'
 // own rounding adds 12 u |q||r|, and the distance by twice the total,
 // (1.5 n + 10.5) of (|q| + |r|)^2; scores sum from -|r|^2 / 2, with sums
 // below |q||r| + |r|^2 / 2: 3 n.  Norms and the final sum: less than 3.
 // Measured on the benchmark's data shapes, d = 17 .. 784: at most 11 (16 on
-// the FP32 MFMA's own sums), rms 0.61 to 0.90 of the FP32 MFMA's error.
+// the FP32 MFMA's own sums), rms 0.61 to 0.90 of the FP32 MFMA's error.  (Rows
+// far below the common scale have the parts' absolute error besides; against the
+// largest norm it is nothing, and merge_rerank_kernel's eabs and
+// rank_tile_kernel's eabs stand for it where it is not.)
 static float split_err(int d, int kind)
 {
     const int64_t n = (kind == KNN_SPLIT ? 3 : 1) * ceil_div(d, 16);

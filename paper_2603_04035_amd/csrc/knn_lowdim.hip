@@ -58,8 +58,9 @@ __global__ __launch_bounds__(kLdSample) void ld_cells_kernel(const void* __restr
     }
 }
 
-// Position of cell (x, y) on the Hilbert curve over 2^bits x 2^bits cells: one
-// quadrant per level, the lower quadrants' curves transposed (and mirrored).
+// Position of cell (x, y) on the Hilbert curve over 2^bits x 2^bits cells, by the
+// curve's recursive definition (Hilbert 1891): one quadrant per level, the lower
+// quadrants' curves transposed (and mirrored).
 __device__ inline uint32_t hilbert(uint32_t x, uint32_t y, int bits)
 {
     uint32_t pos = 0;

@@ -1462,7 +1462,8 @@ static knn_status nnd_run(const knn_matrix& X, const knn_nnd_params* p, const in
     join([&](auto kernel) { occ = hipOccupancyMaxActiveBlocksPerMultiprocessor(&jpc, (const void*)kernel, jthreads, 0); });
     KNN_HIP(occ);
     if (jpc < 1) jpc = 1;
-    // a multiple of 8: the join splits its grid into 8 contiguous point ranges
+    // a multiple of 8: the join splits its grid into 8 groups, which take chunks of
+    // points in turn
     const unsigned join_grid = (unsigned)round_up((int64_t)ncu * jpc, 8);
     // Points a join wave takes at a time, where its share is large enough that
     // the cursors' atomics (12 ns each, one after the other) are a small part:
