@@ -11,6 +11,7 @@ namespace knn {
 static thread_local std::string g_last_error;
 
 void set_error(const std::string& msg) { g_last_error = msg; }
+std::string last_error() { return g_last_error; }
 
 knn_status fail(knn_status s, const std::string& msg)
 {

@@ -327,6 +327,7 @@ __device__ __attribute__((always_inline)) inline float direct_d2(const float (&x
 // ------------------------------------------------------------------ host
 
 void set_error(const std::string& msg);
+std::string last_error();
 knn_status fail(knn_status s, const std::string& msg);
 
 #define KNN_HIP(call)                                                                  \

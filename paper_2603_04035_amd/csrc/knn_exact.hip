@@ -2097,12 +2097,23 @@ static knn_status exact_impl(const knn_matrix& Q, const knn_matrix& R, bool same
     // in 1,000 x 50: 63 us against 53, in 4,000 x 50 80 and 75, in 6,000 x 50 86 and
     // 87; four in 1,000 x 50 65 and 72, x 784 135 and 123)
     const bool few = Q.n <= 4 && Q.n * R.n <= 4096;
-    const bool gated = budget == 0 && !few && (ares || lds <= 256 || R.n <= kTileRows || R.n > 4 * kTileRows);
-    const int S0 = gated ? filling_splits(qc, R.n) : exact_splits(qc);
-    const int64_t split_len = round_up(ceil_div(R.n, S0), kTileRows);
-    const int S = (int)ceil_div(R.n, split_len);
+    bool gated = budget == 0 && !few && (ares || lds <= 256 || R.n <= kTileRows || R.n > 4 * kTileRows);
+    int64_t split_len = 0;
+    int S = 0;
     uint64_t* part = nullptr;
-    r = ws.alloc(&part, (size_t)qc * S * (gated ? kCandCap : kListW));
+    auto buffers = [&]() {
+        const int S0 = gated ? filling_splits(qc, R.n) : exact_splits(qc);
+        split_len = round_up(ceil_div(R.n, S0), kTileRows);
+        S = (int)ceil_div(R.n, split_len);
+        return ws.alloc(&part, (size_t)qc * S * (gated ? kCandCap : kListW));
+    };
+    const std::string before = last_error();
+    r = buffers();
+    if (r == KNN_ENOMEM && gated) {
+        // a device nearly full: the lists take an eighth and at most four splits
+        gated = false;
+        if ((r = buffers()) == KNN_OK) set_error(before);
+    }
     if (r != KNN_OK) return r;
     int32_t* fb_rows = nullptr;
     r = ws.alloc(&fb_rows, (size_t)qc);
@@ -2328,21 +2339,30 @@ static knn_status quality_impl(const knn_matrix& X, const knn_matrix& Y, int k, 
     if (S > ntile) S = (int)ntile;
     const int64_t split_len = ceil_div(ntile, S) * kTileRows;
     S = (int)ceil_div(n, split_len);   // no empty split
-    const int64_t per_launch = kRankBlocks / S;   // query blocks per launch
     const int kp = 2 * k < kListW ? 2 * k : kListW;   // the lists' re-rank width, as knn_exact's default
     // scratch of one launch of query blocks: queues, and with lists the gates,
     // buffers, counts and the rows without a certificate
-    const int64_t lrows = std::min<int64_t>(nblk, per_launch) * kTileRows;
+    int64_t per_launch = 0, lrows = 0;   // query blocks per launch, and their rows
     uint64_t *rq = nullptr, *part = nullptr;
     float* lims = nullptr;
     uint32_t* cnt = nullptr;
     int32_t* fb_rows = nullptr;
     unsigned* fb_count = nullptr;   // [1]: fallback parts done
-    if ((X.d > kRankDirectD || Y.d > kRankDirectD) &&
-        (r = ws.alloc(&rq, (size_t)(lrows / kTileRows) * S * kRankQueue)) != KNN_OK)
-        return r;
+    const std::string before = last_error();
+    for (int64_t most = kRankBlocks / S;; most /= 2) {
+        per_launch = most;
+        lrows = std::min<int64_t>(nblk, per_launch) * kTileRows;
+        const size_t queue = X.d > kRankDirectD || Y.d > kRankDirectD ? (size_t)(lrows / kTileRows) * S * kRankQueue : 0;
+        const size_t cand = fused ? (size_t)lrows * S * kCandCap : 0;
+        if (queue + cand == 0) break;
+        r = ws.alloc(&rq, queue + cand);
+        if (r == KNN_OK) set_error(before);
+        if (r == KNN_OK || most < 2) break;
+        // a device nearly full: fewer query blocks per launch
+    }
+    if (r != KNN_OK) return r;
     if (fused) {
-        if ((r = ws.alloc(&part, (size_t)lrows * S * kCandCap)) != KNN_OK) return r;
+        part = rq + (size_t)(lrows / kTileRows) * S * kRankQueue;
         if ((r = ws.alloc(&lims, (size_t)lrows)) != KNN_OK) return r;
         if ((r = ws.alloc(&cnt, (size_t)lrows * S)) != KNN_OK) return r;
         if ((r = ws.alloc(&fb_rows, (size_t)lrows)) != KNN_OK) return r;

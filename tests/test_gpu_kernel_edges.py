@@ -706,3 +706,29 @@ def test_many_queries_few_coordinates(nq, nr, d):
     i, dist = knn.knn_exact_query(Q, X, 10)[:2]
     ref_i, ref_d = knn.knn_exact_query(Q, X, 10, workspace_limit=1 << 30)[:2]
     assert torch.equal(i, ref_i) and torch.equal(dist, ref_d)
+
+
+def test_device_nearly_full(orc):
+    """600 MB of device memory left: the gated search's buffers (1.2 GB for
+    65,600 rows) give way to lists, and the rank pass to smaller launches; the
+    results are the usual ones.  In a process of its own, whose scratch arena is
+    empty."""
+    import subprocess
+    import sys
+    code = """
+import numpy as np, torch
+import paper_2603_04035_amd as knn
+from paper_2603_04035_amd import datagen
+X = torch.from_numpy(datagen.gmm_isotropic(n=65_600, d=20, seed=3)).cuda()
+Y = X[:, :2].contiguous()
+hog = torch.empty(torch.cuda.mem_get_info()[0] - (600 << 20), dtype=torch.uint8, device="cuda")
+low = knn.knn_exact(X, 10), knn.quality(X, Y, 10)
+del hog
+torch.cuda.empty_cache()
+full = knn.knn_exact(X, 10), knn.quality(X, Y, 10)
+assert torch.equal(low[0][0], full[0][0]) and torch.equal(low[0][1], full[0][1])
+assert low[1] == full[1], (low[1], full[1])
+print("same")
+"""
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert out.stdout.strip().endswith("same"), out.stderr[-800:]
