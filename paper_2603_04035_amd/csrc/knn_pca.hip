@@ -293,6 +293,13 @@ __global__ __launch_bounds__(256) void pca_rayleigh_kernel(const double* __restr
     }
 }
 
+// out[k] = C[k][k] (a strided copy to the host takes 5 ms for 784 of them).
+__global__ __launch_bounds__(256) void pca_diag_kernel(const double* __restrict__ C, int d, double* __restrict__ out)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < d) out[k] = C[(int64_t)k * d + k];
+}
+
 // One Cholesky-QR pass: V = W R^{-1}, where S = W^T W = R^T R (R upper
 // triangular).  Every workgroup factors S (its entries in registers, 25 per
 // thread), the same operations in each, so all hold the same factor; then
@@ -834,10 +841,16 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             //     span is then below rounding.  Or, from K = 0.35 T products on
             //     (at least min(T, 24)), when it has grown at least as much more
             //     than lambda_{m+1}'s as T power iterations would give, (lambda_p /
-            //     lambda_{m+1})^T.  lambda_{m+1} is not known, but lies between the mean
-            //     of the eigenvalues outside the block (from the trace) and
-            //     the m-th quotient: five values are tried, and the next round's
-            //     b is the one with most left to gain.  Above b the logarithm of T_q
+            //     lambda_{m+1})^T.  lambda_{m+1} is not known, but lies between the
+            //     eigenvalues' sum of squares over their sum outside the block
+            //     (C's Frobenius norm and trace less the block's) and the m-th
+            //     quotient; where the former is at least that of a spectrum that
+            //     goes on with the block's mean spacing, lambda_{m+1} is taken to
+            //     be at most eight spacings below the m-th (noise and
+            //     power laws: within one; a drop right behind the block fails
+            //     the test).
+            //     Five values are tried, and the next round's b is the one with
+            //     most left to gain.  Above b the logarithm of T_q
             //     rises by q / sqrt(lambda (lambda - b)), that of lambda^q by q / lambda,
             //     so such rounds gain on the power iterations at that value
             //     and above.  T + K products at most.
@@ -845,7 +858,8 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             // iterations with a pass after each took 21 of the call's 26 ms;
             // 31 products in 12 rounds take 1.5 of 5.2 ms.
             const int K = std::max(std::min(T, 24), (int)std::ceil(0.35 * T));
-            std::vector<double> hv((size_t)3 * m), rho((size_t)m), diag;
+            std::vector<double> hv((size_t)3 * m), rho((size_t)m);
+            double rest = -1.0;   // lower bound of lambda_{m+1}
             std::vector<std::pair<int, double>> rounds;   // (q, b), b = 0: plain
             double b = 0.0;
             int q = 1;
@@ -870,12 +884,11 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
                 if (done >= T + K || (T == 1 && done == 1)) break;
                 KNN_HIP(hipMemcpyAsync(hv.data(), piv, (size_t)3 * m * 8, hipMemcpyDeviceToHost, st));
                 KNN_HIP(hipStreamSynchronize(st));
-                double lo = hv[0], sum = 0.0;
+                double lo = hv[0];
                 for (int k = 0; k < m; ++k) {
                     lo = std::min(lo, hv[k]);
                     const double vv = hv[2 * m + k], r1 = vv > 0.0 ? hv[m + k] / vv : 0.0;
                     rho[k] = plain ? r1 : c * r1 + c;
-                    sum += rho[k];
                 }
                 std::sort(rho.begin(), rho.end(), [](double x, double y) { return x > y; });
                 const double top = rho[0], wanted = rho[p - 1];
@@ -896,18 +909,39 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
                 if (b > 0.0 && gain(b) >= 38.0) break;
                 if (done >= K) {
                     if (!(b > 0.0) || !(wanted > 0.0)) break;   // rank below m
-                    if (diag.empty()) {
-                        diag.resize((size_t)d);
-                        KNN_HIP(hipMemcpy2DAsync(diag.data(), 8, C, ((size_t)d + 1) * 8, 8, (size_t)d,
-                                                 hipMemcpyDeviceToHost, st));
+                    if (rest < 0.0) {
+                        // squared column norms and diagonal of C, and V^T C V
+                        std::vector<double> cn((size_t)2 * d), hb((size_t)m * m);
+                        pca_rayleigh_kernel<<<(unsigned)d, 256, 0, st>>>(C, C, d, d, U2);
+                        pca_diag_kernel<<<(unsigned)ceil_div(d, 256), 256, 0, st>>>(C, d, U2 + d);
+                        cv(V, 1.0, 0.0, nullptr, W);
+                        pca_gram_small_kernel<<<dim3((unsigned)m, (unsigned)m), 256, 0, st>>>(W, V, d, m, S);
+                        KNN_HIP(hipMemcpyAsync(cn.data(), U2, (size_t)2 * d * 8, hipMemcpyDeviceToHost, st));
+                        KNN_HIP(hipMemcpyAsync(hb.data(), S, (size_t)m * m * 8, hipMemcpyDeviceToHost, st));
                         KNN_HIP(hipStreamSynchronize(st));
+                        double one = 0.0, two = 0.0, all = 0.0;
+                        for (int k = 0; k < d; ++k) {
+                            all += cn[k];
+                            one += cn[d + k];
+                        }
+                        two = all;
+                        for (int k = 0; k < m * m; ++k) two -= hb[k] * hb[k];
+                        for (int k = 0; k < m; ++k) one -= hb[k * m + k];
+                        // the mean where the squares are lost in rounding
+                        rest = two > 1e-12 * all ? two / one : one / (d - m);
+                        rest = one > 0.0 ? std::max(rest, one / (d - m)) : 0.0;
                     }
-                    double trace = 0.0;
-                    for (double v : diag) trace += v;
-                    const double rest = std::min(std::max((trace - sum) / (d - m), 1e-16 * top), b);
+                    const double step = (wanted - b) / (m - p);
+                    double l1 = 0.0, l2 = 0.0;
+                    for (int k = 1; k <= d - m && b - step * k > 0.0; ++k) {
+                        l1 += b - step * k;
+                        l2 += (b - step * k) * (b - step * k);
+                    }
+                    const double goes_on = rest * l1 >= l2 ? b - 8.0 * step : 0.0;
+                    const double least = std::min(std::max({rest, goes_on, 1e-16 * top}), b);
                     double most = 1e-9, at = 0.0;
                     for (int i = 0; i < 5; ++i) {
-                        const double l = b * std::pow(rest / b, 0.25 * i);
+                        const double l = b * std::pow(least / b, 0.25 * i);
                         const double left = std::min(38.0, T * std::log(wanted / l)) - gain(l);
                         if (left > most) {
                             most = left;
