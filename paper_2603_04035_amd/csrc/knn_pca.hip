@@ -856,7 +856,7 @@ extern "C" knn_status knn_pca(knn_matrix X, int32_t p, int32_t iters, float* Z, 
             //     and above.  T + K products at most.
             // On a 70,000 x 784 set (eigenvalues as i^-1.2, p = 50) 200 power
             // iterations with a pass after each took 21 of the call's 26 ms;
-            // 31 products in 12 rounds take 1.5 of 5.2 ms.
+            // 32 products in 12 rounds take 1.5 of 5.2 ms.
             const int K = std::max(std::min(T, 24), (int)std::ceil(0.35 * T));
             std::vector<double> hv((size_t)3 * m), rho((size_t)m);
             double rest = -1.0;   // lower bound of lambda_{m+1}
